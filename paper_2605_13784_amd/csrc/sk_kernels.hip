@@ -267,13 +267,14 @@ __device__ __forceinline__ void sk_merge_row(const sk_launch& P, const size_t pr
 // from registers.  Key row rho of the first product is loaded from key tau(rho) (bits 2 and 3
 // swapped) so that the 8 P values a lane hands to one PV instruction belong to 8 consecutive
 // keys, which are one 16-byte read of V^T.
-// Softmax runs in the log2 domain in fp32; the running maximum is only raised when a tile
-// exceeds it by more than SK_RESCALE_SLACK, which keeps exp2 arguments <= the slack and makes
-// accumulator rescaling rare; the result is the same up to rounding.
+// Softmax runs in the log2 domain in fp32 against a reference maximum that is only raised when a weight
+// may exceed 2^8 (step_softmax), which bounds the weights and makes accumulator rescaling rare; the
+// result is the same up to rounding.
 // ---------------------------------------------------------------------------------------------
 #define SK_TILE 32                 // keys per tile
 #define SK_TILE_BYTES 16384        // K 8 KiB | V^T 8 KiB
-#define SK_RESCALE_SLACK 8.0f
+#define SK_RESCALE_SLACK 8.0f      // log2 of the largest weight before the reference maximum is raised
+#define SK_SUM_LIMIT 256.0f        // 2^slack: no weight of a lane whose sum of weights stays below exceeds it
 
 template <int N> struct sk_int { static constexpr int value = N; };
 typedef __attribute__((address_space(3))) void* sk_lds_ptr;
@@ -286,6 +287,8 @@ typedef const __attribute__((address_space(1))) void* sk_glb_ptr;
 
 // s_waitcnt vmcnt(n) only (gfx9 encoding: vmcnt = simm16[3:0] | simm16[15:14] << 4)
 #define SK_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8))
+
+#define SK_LGKMCNT0 0xc07f       // s_waitcnt lgkmcnt(0) only
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() would also wait for every
 // outstanding global load, i.e. drain the ring of tiles in flight.
@@ -356,20 +359,16 @@ __device__ __forceinline__ sk_tile_blocks sk_lookup_tile(const sk_seg& g, int t0
 // 0-3; one load per wave and tile (wave sub loads rows 8 (sub & 1) .. + 7 of group sub >> 1, `k_group`,
 // into unit sub).  V^T: the same units as with head_dim 128, of which 64 dims fill two per group, so
 // only the waves with sub < 2 load it (`v_wave`).
-template <unsigned US, int J, int D>
+template <unsigned US, int J, int D, bool MAY_STREAM>
 __device__ __forceinline__ void sk_issue_group(const sk_seg& g, int t0, int last_group, uint32_t blk,
                                                unsigned unit_addr, unsigned koff, unsigned voff, int k_group, bool v_wave)
 {
     constexpr int LOG2_TOK_BYTES = D == 128 ? 8 : 7;       // K bytes per token and head = V^T bytes per token
     int tg = t0 + 16 * J;
     tg = tg < last_group ? tg : last_group;
-    const unsigned char* bb = g.base + ((uint64_t)blk << (g.log2B + LOG2_TOK_BYTES + 1));
-    if (g.B > 16) {
-        const unsigned slot0 = (unsigned)tg & (unsigned)(g.B - 1);
-        koff += slot0 << LOG2_TOK_BYTES;          // K: 256 (128) bytes per token
-        voff += slot0 << LOG2_TOK_BYTES;          // V^T: 4 (2) KiB per 16-token group
-    }
-    if (g.once) {       // uniform over the workgroup
+    // the group's place in the block: 256 (128) bytes per token for K, 4 (2) KiB per 16-token group for V^T
+    const unsigned char* bb = g.base + ((uint64_t)blk << (g.log2B + LOG2_TOK_BYTES + 1)) + (((unsigned)tg & (unsigned)(g.B - 1)) << LOG2_TOK_BYTES);
+    if (MAY_STREAM && g.once) {       // uniform over the workgroup
         if (D == 128) sk_dma16<J * 4 * US, true>(bb, koff, unit_addr);
         else if (k_group == J) sk_dma16<0, true>(bb, koff, unit_addr);
         if (D == 128 || v_wave) sk_dma16<(8 + J * 4) * US, true>(bb, voff, unit_addr);
@@ -379,12 +378,12 @@ __device__ __forceinline__ void sk_issue_group(const sk_seg& g, int t0, int last
         if (D == 128 || v_wave) sk_dma16<(8 + J * 4) * US, false>(bb, voff, unit_addr);
     }
 }
-template <unsigned US, int D>
+template <unsigned US, int D, bool MAY_STREAM>
 __device__ __forceinline__ void sk_issue_tile(const sk_seg& g, int t0, int last_group, const sk_tile_blocks& tb,
                                               unsigned unit_addr, unsigned koff, unsigned voff, int k_group, bool v_wave)
 {
-    sk_issue_group<US, 0, D>(g, t0, last_group, tb.blk[0], unit_addr, koff, voff, k_group, v_wave);
-    sk_issue_group<US, 1, D>(g, t0, last_group, tb.blk[1], unit_addr, koff, voff, k_group, v_wave);
+    sk_issue_group<US, 0, D, MAY_STREAM>(g, t0, last_group, tb.blk[0], unit_addr, koff, voff, k_group, v_wave);
+    sk_issue_group<US, 1, D, MAY_STREAM>(g, t0, last_group, tb.blk[1], unit_addr, koff, voff, k_group, v_wave);
 }
 
 template <int NRG, int NPH, int NSS, int D>
@@ -401,6 +400,9 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     // phases per row group running freely (128 rows: half the arithmetic per wave of the four-wave
     // 128-row instance, two waves per SIMD)
     constexpr bool LOCKSTEP = NW == 8 && NPH == 1;
+    // how the reference maximum is kept (step_softmax); the four-wave 128-row instance has no registers to keep
+    // the scores of two tiles beside their V^T operands
+    constexpr bool LAZY_MAX = LOCKSTEP || TPW == 1;
     constexpr int NLG = NW / 4;              // groups of four waves; each loads whole tiles
     static_assert(NW == 4 || (LOCKSTEP && NSS == 4) || (NW == 8 && NPH == 2 && NSS == 2), "four waves, or eight as described");
     static_assert(NSS == 2 || NSS == 4, "ring depth in iterations: 64 KiB (two workgroups per CU) or 128 KiB (one)");
@@ -567,44 +569,25 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 for (int mt = 0; mt < NMT; ++mt)
                     va[t][q][mt] = *(sk_lds_u4ptr)(vptr[mt] + soff + SK_SLOT_OFF(0, t) + q * 4 * US);
         };
-        // mask (only tiles that cross a limit), row maximum, P = exp2(s * scale - m), row sums
-        auto step_softmax = [&](const int it) __attribute__((always_inline)) {
+        // a tile is masked when it crosses a causal or end-of-segment limit, or touches evicted tokens
+        auto needs_mask = [&](const int it) __attribute__((always_inline)) {
             const int pos_first = first_pos(it);
-            // a tile is masked when it crosses a causal or end-of-segment limit, or touches evicted tokens
-            const bool need_mask = pos_first + TPW * SK_TILE - 1 > lim_wave_min ||
-                                   (pos_first < g.hole_lo + g.hole_n && pos_first + TPW * SK_TILE > g.hole_lo);
-            // the maximum is taken on the raw scores; the softmax scale is applied inside the
-            // exponent below (one FMA per score)
-            float mt_ = SK_NEG_INF;
-            if (need_mask) {
+            return pos_first + TPW * SK_TILE - 1 > lim_wave_min ||
+                   (pos_first < g.hole_lo + g.hole_n && pos_first + TPW * SK_TILE > g.hole_lo);
+        };
+        auto mask_scores = [&](const int it) __attribute__((always_inline)) {
+            const int pos_first = first_pos(it);
 #pragma unroll
-                for (int t = 0; t < TPW; ++t)
+            for (int t = 0; t < TPW; ++t)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int pos = pos_first + t * SK_TILE + 16 * (v >> 3) + 8 * kg + (v & 7);
-                        const bool vis = pos <= lim_row && (unsigned)(pos - g.hole_lo) >= (unsigned)g.hole_n;
-                        const float x = vis ? sacc[t][v] : SK_NEG_INF;
-                        sacc[t][v] = x;
-                        mt_ = fmaxf(mt_, x);
-                    }
-            } else {
-#pragma unroll
-                for (int t = 0; t < TPW; ++t)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) mt_ = fmaxf(mt_, sacc[t][v]);
-            }
-            { const sk_halves h = sk_both_halves(mt_); mt_ = fmaxf(h.lo, h.hi) * c_scale; }      // log2 units (c_scale > 0)
-            const bool raise = mt_ > m_ref + SK_RESCALE_SLACK;
-            if (__any(raise)) {
-                const float alpha = raise ? sk_exp2(m_ref - mt_) : 1.0f;
-                l_run *= alpha; lx_run *= alpha;
-#pragma unroll
-                for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) oacc[mt][v] *= alpha;
-                m_ref = raise ? mt_ : m_ref;
-            }
-            const float neg_m = (m_ref == SK_NEG_INF) ? 0.f : -m_ref;
+                for (int v = 0; v < 16; ++v) {
+                    const int pos = pos_first + t * SK_TILE + 16 * (v >> 3) + 8 * kg + (v & 7);
+                    const bool vis = pos <= lim_row && (unsigned)(pos - g.hole_lo) >= (unsigned)g.hole_n;
+                    sacc[t][v] = vis ? sacc[t][v] : SK_NEG_INF;
+                }
+        };
+        // P = exp2(s * scale - m) for the reference maximum m as it stands, and the lane's sum of it (unrounded)
+        auto weights = [&](const float neg_m) __attribute__((always_inline)) -> float {
             float lx0 = 0.f, lx1 = 0.f;
 #pragma unroll
             for (int t = 0; t < TPW; ++t)
@@ -615,7 +598,41 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                     pb[t][1][v] = (__bf16)p1;
                     lx0 += p0; lx1 += p1;
                 }
-            lx_run += lx0 + lx1;
+            return lx0 + lx1;
+        };
+        // Softmax of one iteration.  The row maximum is not looked for in every tile: the weights are formed
+        // against the reference maximum as it stands, and only when their sum says that one of them may
+        // exceed 2^8 (or when there is no reference yet: the sum is then infinite or NaN) does
+        // the wave find the tile's maximum, raise the reference, rescale and form them again.  That leaves
+        // 16 maxima and a cross-lane exchange out of the vector work of nearly every iteration (256-token
+        // append at 32,512 tokens: 128.9 -> 124.4 us; 512 at 130,560: 939 -> 915 us).
+        auto step_softmax = [&]() __attribute__((always_inline)) {
+            float lx = 0.f;
+            bool look = true;
+            if (LAZY_MAX) {
+                lx = weights(-m_ref);
+                look = __any(!(lx <= SK_SUM_LIMIT));
+            }
+            if (look) {
+                float mt_ = SK_NEG_INF;
+#pragma unroll
+                for (int t = 0; t < TPW; ++t)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) mt_ = fmaxf(mt_, sacc[t][v]);
+                { const sk_halves h = sk_both_halves(mt_); mt_ = fmaxf(h.lo, h.hi) * c_scale; }      // log2 units (c_scale > 0)
+                const bool raise = mt_ > m_ref + (LAZY_MAX ? 0.f : SK_RESCALE_SLACK);
+                if (LAZY_MAX || __any(raise)) {
+                    const float alpha = raise ? sk_exp2(m_ref - mt_) : 1.0f;
+                    l_run *= alpha; lx_run *= alpha;
+#pragma unroll
+                    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) oacc[mt][v] *= alpha;
+                    m_ref = raise ? mt_ : m_ref;
+                }
+                lx = weights(m_ref == SK_NEG_INF ? 0.f : -m_ref);      // no key seen yet: all weights 0
+            }
+            lx_run += lx;
             // The row sum that normalises the output is taken over the weights as the matrix pipe sees
             // them (rounded to bf16), two per instruction with fp32 accumulation: numerator and
             // denominator of the output then carry the same weights, so a row that one key dominates
@@ -664,7 +681,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                         if (NLG > 1 && (p % NLG) != lg) continue;
                         const int t0 = g.begin + a * g.step + p * SK_TILE;
                         const sk_tile_blocks tb = sk_lookup_tile(g, t0, last_group);
-                        sk_issue_tile<US, D>(g, t0, last_group, tb, unit_base + SK_SLOT_OFF(a, p), koff, voff, k_group, v_wave);
+                        sk_issue_tile<US, D, true>(g, t0, last_group, tb, unit_base + SK_SLOT_OFF(a, p), koff, voff, k_group, v_wave);
                     }
                 }
             }
@@ -692,7 +709,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
 #pragma unroll
                     for (int p = 0; p < TPI; ++p) {
                         if (NLG > 1 && (p % NLG) != lg) continue;
-                        sk_issue_tile<US, D>(g, g.begin + (it + NSS - 1) * g.step + p * SK_TILE, last_group, nb[p],
+                        sk_issue_tile<US, D, true>(g, g.begin + (it + NSS - 1) * g.step + p * SK_TILE, last_group, nb[p],
                                                        unit_base + SK_SLOT_OFF((slot + NSS - 1) % NSS, p), koff, voff, k_group, v_wave);
                     }
                     if (it + NSS < niter) {
@@ -705,7 +722,8 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 step_scores(slot * 1024);
 #pragma unroll
                 for (int t = 0; t < TPW; ++t) load_v_tile(t, slot * 1024);   // requested now: their LDS latency hides behind the softmax
-                step_softmax(it);
+                if (needs_mask(it)) mask_scores(it);
+                step_softmax();
 #pragma unroll
                 for (int t = 0; t < TPW; ++t) pv_tile(t);
             };
@@ -737,35 +755,29 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // addresses of the current slot are rebuilt from the per-unit bases once per iteration.
             // Every wave does every iteration (rows or keys that do not count are masked): the slots
             // are synchronised, so skipping work would not save time.
+            // Bound: power.  At 32,512 cached tokens an iteration takes 2,900 cycles for 2,048 of matrix
+            // instructions per SIMD, and the chip lowers its clock as they get fewer (3,070 cycles at 1.86 GHz
+            // before the waves feeding the matrix pipe had priority, 2,895 at 1.80 GHz with it): 512 tokens at
+            // 130,560 run at 1.26 PFLOP/s against 1.38 of a large library product.
             constexpr int LPW = 4;               // direct-to-LDS loads per wave per iteration (one tile)
             const int my_tile = 1 - grp;
             const int ahead = 2 + grp;           // iterations loaded before the loop
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                if (a < ahead && a < niter) {
-                    const int t0 = g.begin + a * g.step + my_tile * SK_TILE;
-                    const sk_tile_blocks tb = sk_lookup_tile(g, t0, last_group);
-                    sk_issue_tile<US, D>(g, t0, last_group, tb, unit_base + SK_SLOT_OFF(a, my_tile), koff, voff, k_group, v_wave);
-                }
-            }
-            sk_tile_blocks nb = sk_lookup_tile(g, g.begin + ahead * g.step + my_tile * SK_TILE, last_group);
-            {   // iteration 0 has landed: all but the loads of the later iterations issued above
-                const int issued = niter < ahead ? niter : ahead;
-                if (issued >= 3) SK_WAIT_VMCNT(2 * LPW); else if (issued == 2) SK_WAIT_VMCNT(LPW); else SK_WAIT_VMCNT(0);
-            }
-            if (grp == 1) sk_lds_barrier();      // group 1 stays one barrier behind
-            // wait for this wave's loads of iteration i; those of iteration i + 1 may still be in flight
-            auto wait_iteration = [&](const int i) __attribute__((always_inline)) {
-                if (i + 1 < niter) SK_WAIT_VMCNT(LPW); else SK_WAIT_VMCNT(0);
+            // Loads are issued for `ahead` iterations past the end too (they re-read the segment's last
+            // group and nothing reads them), so that the number of loads in flight at each wait is a constant.
+            int t_next = g.begin + my_tile * SK_TILE;
+            sk_tile_blocks nb = sk_lookup_tile(g, t_next, last_group);
+            auto issue_next = [&](const int slot) __attribute__((always_inline)) {
+                sk_issue_tile<US, D, false>(g, t_next, last_group, nb, unit_base + SK_SLOT_OFF(slot, my_tile), koff, voff, k_group, v_wave);
+                t_next += g.step;
+                nb = sk_lookup_tile(g, t_next, last_group);
             };
-            auto refill = [&](const int j) __attribute__((always_inline)) {
-                const int i = j + ahead;
-                if (i < niter) {
-                    sk_issue_tile<US, D>(g, g.begin + i * g.step + my_tile * SK_TILE, last_group, nb,
-                                                   unit_base + SK_SLOT_OFF(i & 3, my_tile), koff, voff, k_group, v_wave);
-                    if (i + 1 < niter) nb = sk_lookup_tile(g, g.begin + (i + 1) * g.step + my_tile * SK_TILE, last_group);
-                }
-            };
+            issue_next(0);
+            issue_next(1);
+            if (grp == 1) {
+                issue_next(2);
+                SK_WAIT_VMCNT(2 * LPW);          // iteration 0 has landed
+                sk_lds_barrier();                // group 1 stays one barrier behind
+            } else SK_WAIT_VMCNT(LPW);
             // Matrix slot: eight groups of four matrix instructions, P V of the previous iteration
             // (V^T through vp, the pointers of its ring slot) and S of the current one (K through
             // kc).  Operands stream from LDS two groups ahead of their use, into the registers that
@@ -821,12 +833,29 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 }
 #undef SK_SB
             };
+            // Iterations that need a mask: those that reach past what the wave's first row may see, and those
+            // that touch evicted tokens.
+            const int last_0 = g.begin + g.pos_shift + TPI * SK_TILE - 1;       // last position of iteration 0
+            const int n_free = lim_wave_min < last_0 ? 0 : (int)((unsigned)(lim_wave_min - last_0) / (unsigned)g.step) + 1;      // iterations the limit leaves whole
+            int hole_it = 0, hole_its = 0;
+            if (g.hole_n > 0 && g.hole_lo < g.end && g.hole_lo + g.hole_n > g.begin) {
+                hole_it = g.hole_lo > g.begin ? (g.hole_lo - g.begin) / g.step : 0;
+                hole_its = (g.hole_lo + g.hole_n - g.begin) / g.step + 1 - hole_it;
+            }
+            auto mask_iteration = [&](const int j) __attribute__((always_inline)) {
+                if (j >= n_free || (unsigned)(j - hole_it) < (unsigned)hole_its) mask_scores(j);
+            };
             // Vector slot: softmax of iteration j, and the operands of the first group of matrix
             // instructions of the slot that follows (V^T, first 16 keys of the iteration).
             auto vector_slot = [&](const int j, const sk_lds_cptr (&vc)[4]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int mt = 0; mt < 4; ++mt) va0[mt] = *(sk_lds_u4ptr)(vc[mt]);
-                step_softmax(j);
+                __builtin_amdgcn_sched_barrier(0);
+                mask_iteration(j);
+                step_softmax();
+                // (the scalar loads of the block ids have long arrived; said here, so that the matrix slot's
+                // waits for its LDS operands need not allow for them and can count)
+                __builtin_amdgcn_s_waitcnt(SK_LGKMCNT0);
             };
             sk_lds_cptr kc[8];          // K operand addresses in the ring slot of the current iteration
             sk_lds_cptr vc[4];          // V^T operand addresses in it (the next matrix slot reads them as "previous")
@@ -837,9 +866,9 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // slots of iteration 0 (ring slot 0): S only
             sk_lds_barrier();
             matrix_slot(sk_int<0>{}, 0, kc, vc);
-            if (grp == 1 && 1 < niter) wait_iteration(1);
+            if (grp == 1) SK_WAIT_VMCNT(LPW);
             sk_lds_barrier();
-            refill(0);
+            issue_next(ahead);
             vector_slot(0, vc);
 #pragma unroll 1
             for (int j = 1; j < niter; ++j) {
@@ -848,17 +877,22 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 for (int mt = 0; mt < 4; ++mt) { vp[mt] = vc[mt]; vc[mt] = vptr[mt] + (j & 3) * 1024; }
 #pragma unroll
                 for (int ks = 0; ks < 8; ++ks) kc[ks] = kptr[ks] + (j & 3) * 1024;
-                if (grp == 0) wait_iteration(j);
-                    sk_lds_barrier();                                  // barrier 2j (group 0), 2j+1 (group 1)
+                // a wave waits for its own loads of the iteration that is published by its next barrier of
+                // even number; those of one later iteration stay in flight
+                if (grp == 0) SK_WAIT_VMCNT(LPW);
+                sk_lds_barrier();                                  // barrier 2j (group 0), 2j+1 (group 1)
+                __builtin_amdgcn_s_setprio(2);                     // the wave feeding the matrix pipe goes first (1.8 % of the kernel)
                 matrix_slot(sk_int<1>{}, j, kc, vp);
-                if (grp == 1 && j + 1 < niter) wait_iteration(j + 1);
+                __builtin_amdgcn_s_setprio(0);
+                if (grp == 1) SK_WAIT_VMCNT(LPW);
                 sk_lds_barrier();                                  // barrier 2j+1 (group 0), 2j+2 (group 1)
-                refill(j);
+                issue_next((j + ahead) & 3);
                 vector_slot(j, vc);
             }
             // slots after the last iteration: P V only
             sk_lds_barrier();
             matrix_slot(sk_int<2>{}, niter, kc, vc);
+            SK_WAIT_VMCNT(0);                    // nothing is still on its way into the ring
             sk_lds_barrier();
             if (grp == 0) sk_lds_barrier();      // the barrier group 1 took first
         }

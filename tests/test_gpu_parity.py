@@ -200,6 +200,31 @@ def test_large_logits_and_needle():
         assert torch.allclose(got, v[pos, 2].float(), atol=1e-2), "needle at %d not retrieved" % pos
 
 
+@pytest.mark.parametrize("hd", [128, 64])
+@pytest.mark.parametrize("env", [None, LONG_CACHE_PATHS])
+def test_scores_that_grow_along_the_cache(hd, env):
+    """The kernels weigh a tile against the maximum they have and look for a new one only when the sum of
+    the weights says so: keys whose size grows in steps (by a little, so that weights stay just below the
+    limit, and by much, so that they overflow to infinity first), and one that falls again, for every
+    kernel instance, with masked tiles among them."""
+    shape = synth.Shape("bf16", 32, 8, hd)
+    gen = synth.generator(2, stream=400 + hd)
+    n = 900
+    pr = Pair(shape, n_blocks=n // 16 + 30, max_sessions=2, max_batch_tokens=1024, env=env)
+    sid = pr.create()
+    q, k, v = synth.draw_qkv(gen, n, shape)
+    grow = torch.ones(n)
+    for at, f in ((64, 1.5), (130, 1.2), (200, 3.0), (300, 0.2), (500, 12.0), (515, 60.0), (600, 0.5), (700, 2.5)):
+        grow[at:] *= f
+    k = (k.float() * grow[:, None, None]).to(torch.bfloat16)
+    for a, b in ((0, 5), (5, 400), (400, n)):
+        pr.append(sid, q[a:b], k[a:b], v[a:b], name="append %d:%d" % (a, b))
+    for nq in (1, 16, 32, 60):
+        for S in (0, 1, 3):
+            pr.query(sid, q[:nq], n_splits=S, name="query A nq=%d S=%d" % (nq, S))
+            pr.query(sid, q[:nq], k[-nq:], v[-nq:], n_splits=S, name="query B nq=%d S=%d" % (nq, S))
+
+
 @pytest.mark.parametrize("scale", [0.05, 0.2])
 def test_custom_softmax_scale(scale):
     """Eq. 1's 1/sqrt(d_k) is the default, not the only scale: a pool created with softmax_scale set
