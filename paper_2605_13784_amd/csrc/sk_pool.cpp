@@ -610,6 +610,66 @@ void add_tiles(ListGroup& g, const TileReq& base, int32_t q_row0, int32_t T)
     }
 }
 
+int64_t list_parts(const TileReq& t, int64_t chunk) { return std::max<int64_t>(1, (t.kv_vis + chunk - 1) / chunk); }
+int32_t list_bucket(int64_t len, int64_t chunk) { return int32_t(len * 8 / chunk); }
+
+// Length of the pieces a launch's tiles are cut into: the one for which the launch is expected to end first.
+// The workgroups are taken up in order by the CUs that become free (those of a KV head by that head's share of
+// the CUs), so the end is that of a list schedule; more pieces end more evenly, but each costs its start and
+// end and a partial that the combine kernel reads back.  Times in us, measured: an iteration of 64 keys in the
+// 256-row kernel 1.7 (one workgroup per CU); in the smaller ones 1.4 with one workgroup per CU and 2.7 with
+// two (the stream from HBM); start and end of a workgroup 6; a partial of 128 rows 0.018.
+// Measured against pieces of one length for about 2,048 workgroups, in session order: 48-session step 4.58 ->
+// 4.05 ms (append launch 4.25 -> 3.76: no 19,648-key pieces that end in a ragged last round, tiles whole and
+// longest first; combine kernels 0.16 -> 0.02); 64 questions at 64K 1.13 -> 1.04 ms (7 pieces per tile, 3.5
+// rounds of the chip -> 2 pieces, one round).
+int64_t list_chunk(const sk_pool* p, const ListGroup& g)
+{
+    int64_t longest = 0;
+    for (const TileReq& t : g.tiles) longest = std::max<int64_t>(longest, t.kv_vis);
+    if (longest == 0) return 256;
+    const int Hkv = p->d.n_kv_heads;
+    const bool big = g.v.id == SK_KV_MFMA256;
+    double best = 0; int64_t best_chunk = 0, last = 0;
+    std::vector<double> free_at;
+    std::vector<int32_t> rest[9];
+    for (int64_t k = 1; k <= 256; k += std::max<int64_t>(1, k / 4)) {
+        const int64_t chunk = std::max<int64_t>(256, ((longest + k - 1) / k + 63) / 64 * 64);
+        if (chunk == last) break;
+        last = chunk;
+        int64_t whole = 0, parts = 0, n = 0;
+        for (auto& r : rest) r.clear();
+        for (const TileReq& t : g.tiles) {
+            const int64_t np = list_parts(t, chunk);
+            n += np;
+            if (np > 1) parts += np;
+            const int64_t left = t.kv_vis - (np - 1) * chunk;
+            whole += np - 1;
+            rest[list_bucket(left, chunk)].push_back(int32_t((left + 63) / 64));
+        }
+        const bool sparse = big || n * Hkv <= p->n_cus;
+        const double it = big ? 1.7 : (sparse ? 1.4 : 2.7), ends = 6.0;
+        const size_t lanes = (size_t)std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
+        // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
+        const double c = double(chunk / 64) * it + ends;
+        free_at.assign(lanes, c * double(whole / (int64_t)lanes));
+        for (int64_t i = 0; i < whole % (int64_t)lanes; ++i) free_at[(size_t)i] += c;
+        auto later = [](double x, double y) { return x > y; };
+        std::make_heap(free_at.begin(), free_at.end(), later);
+        double end = *std::max_element(free_at.begin(), free_at.end());
+        for (int b = 8; b >= 0; --b)
+            for (int32_t its : rest[b]) {
+                std::pop_heap(free_at.begin(), free_at.end(), later);
+                free_at.back() += double(its) * it + ends;
+                end = std::max(end, free_at.back());
+                std::push_heap(free_at.begin(), free_at.end(), later);
+            }
+        end += double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0;
+        if (best_chunk == 0 || end < 0.995 * best) { best = end; best_chunk = chunk; }
+    }
+    return best_chunk;
+}
+
 constexpr int kMaxGroups = 3;   // one launch per kernel variant in use
 
 // A batched call in two halves.  plan_list cuts the tiles into workgroups, builds the lists and takes
@@ -631,35 +691,12 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
     if (n_groups > kMaxGroups) return SK_E_INVAL;
     if (inject(p, SK_SITE_PLAN)) return SK_E_WORKSPACE;
     const int Hkv = p->d.n_kv_heads;
-    int64_t kv_group[kMaxGroups] = {};
     P.kv_total = 0; P.n_tiles = 0;
     for (int gi = 0; gi < n_groups; ++gi)
-        for (const TileReq& t : groups[gi].tiles) { P.kv_total += t.kv_vis; kv_group[gi] += t.kv_vis; ++P.n_tiles; }
+        for (const TileReq& t : groups[gi].tiles) { P.kv_total += t.kv_vis; ++P.n_tiles; }
     if (P.n_tiles == 0) return SK_OK;
-    // One chunk length per group (= per launch), so that the workgroups of a launch cost about the
-    // same whatever the session length, and every launch has enough of them to fill the chip
-    // several times over (rounds of one 512-thread workgroup per CU, or of two 256-thread ones).
     int64_t chunk_g[kMaxGroups];
-    for (int gi = 0; gi < n_groups; ++gi) {
-        const int64_t per_round = groups[gi].v.id == SK_KV_MFMA256 ? 256 : 512;
-        const int64_t target = 4 * int64_t(p->target_wgs);       // 2,048 by default: 8 rounds of 256, 4 of 512
-        chunk_g[gi] = std::max<int64_t>(256, (kv_group[gi] * Hkv + target - 1) / target);
-        chunk_g[gi] = (chunk_g[gi] + 63) / 64 * 64;
-        // Workgroups of a launch run in rounds of `per_round`; pick, near that length, the one whose
-        // last round is fullest (a launch of 7.1 rounds takes as long as one of 8).
-        auto count_wgs = [&](int64_t c) {
-            int64_t n = 0;
-            for (const TileReq& t : groups[gi].tiles) n += std::max<int64_t>(1, (t.kv_vis + c - 1) / c);
-            return n * Hkv;
-        };
-        double best_eff = -1.0; int64_t best = chunk_g[gi];
-        for (int64_t c = std::max<int64_t>(256, chunk_g[gi] * 3 / 4 / 64 * 64); c <= chunk_g[gi] * 5 / 4; c += 64) {
-            const int64_t n = count_wgs(c);
-            const double eff = double(n) / double((n + per_round - 1) / per_round * per_round);
-            if (eff >= best_eff) { best_eff = eff; best = c; }       // ties: the longer chunk (fewer partials)
-        }
-        chunk_g[gi] = best;
-    }
+    for (int gi = 0; gi < n_groups; ++gi) chunk_g[gi] = list_chunk(p, groups[gi]);
     const int64_t cap_rows = p->L.part_slots * kPartSlotRows;
     size_t bytes = 0;
     for (;;) {
@@ -672,52 +709,61 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
             P.work[gi].clear(); P.comb[gi].clear();
             P.rows_base[gi] = rows_used;
             int64_t slot = 0;       // in units of this group's rows_per_slot, from rows_base
-            // runs of consecutive tiles of one session: split-major order inside a run, so that
-            // workgroups resident at the same time read the same keys (L2 reuse across row tiles)
+            struct Piece { int32_t tile, part, bucket; };
+            std::vector<Piece> pieces;
+            std::vector<int32_t> nparts(g.tiles.size()), slot0(g.tiles.size()), unit0(g.tiles.size());
+            for (size_t i = 0; i < g.tiles.size(); ++i) {
+                const int32_t np = (int32_t)list_parts(g.tiles[i], chunk);
+                nparts[i] = np;
+                slot0[i] = np > 1 ? (int32_t)slot : -1;
+                unit0[i] = np > 1 ? (int32_t)unit : -1;
+                if (np > 1) { slot += int64_t(np) * Hkv; unit += Hkv; }
+            }
+            // In the order the workgroups start in: the longest pieces first (whole chunks, then what is left of
+            // each tile, falling in eighths of a chunk), so that the launch ends evenly; among equals the tiles
+            // of a session side by side, one part after the other, so that what runs at the same time reads
+            // the same keys through the L2.
             size_t i0 = 0;
             while (i0 < g.tiles.size()) {
                 size_t i1 = i0;
                 int32_t max_parts = 1;
-                std::vector<int32_t> nparts, slot0, unit0;
-                while (i1 < g.tiles.size() && g.tiles[i1].tbl_off == g.tiles[i0].tbl_off) {
-                    const int32_t np = std::max<int64_t>(1, (g.tiles[i1].kv_vis + chunk - 1) / chunk);
-                    nparts.push_back(np); max_parts = std::max(max_parts, np);
-                    slot0.push_back(np > 1 ? (int32_t)slot : -1);
-                    unit0.push_back(np > 1 ? (int32_t)unit : -1);
-                    if (np > 1) { slot += int64_t(np) * Hkv; unit += Hkv; }
-                    ++i1;
-                }
+                for (; i1 < g.tiles.size() && g.tiles[i1].tbl_off == g.tiles[i0].tbl_off; ++i1) max_parts = std::max(max_parts, nparts[i1]);
                 for (int32_t part = 0; part < max_parts; ++part)
-                    for (size_t i = i0; i < i1; ++i) {
-                        const TileReq& t = g.tiles[i];
-                        const int32_t np = nparts[i - i0];
-                        if (part >= np) continue;
-                        for (int h = 0; h < Hkv; ++h) {
-                            sk_work w = {};
-                            w.tbl_off = t.tbl_off; w.kv_head = h; w.q_tok0 = t.q_tok0; w.n_tok = t.n_tok; w.pos0 = t.pos0;
-                            w.kv_begin = int32_t(part * chunk);
-                            w.kv_end = int32_t(std::min<int64_t>(t.kv_vis, (part + 1) * chunk));
-                            w.part = np > 1 ? slot0[i - i0] + part * Hkv + h : -1;
-                            w.unit = np > 1 ? unit0[i - i0] + h : -1;
-                            w.part0 = np > 1 ? slot0[i - i0] + h : -1;
-                            w.n_parts = np;
-                            w.hole_lo = t.hole_lo; w.hole_hi = t.hole_hi;
-                            w.tok_period = t.tok_period; w.sub_blocks = t.sub_blocks;
-                            if (part == np - 1)
-                                for (int e = 0; e < 2; ++e) { w.eph_blk[e] = t.eph_blk[e]; w.eph_cnt[e] = t.eph_cnt[e]; w.eph_pos0[e] = t.eph_pos0[e]; }
-                            P.work[gi].push_back(w);
+                    for (size_t i = i0; i < i1; ++i)
+                        if (part < nparts[i]) {
+                            const int64_t len = std::min<int64_t>(g.tiles[i].kv_vis - int64_t(part) * chunk, chunk);
+                            pieces.push_back(Piece{(int32_t)i, part, list_bucket(len, chunk)});
                         }
-                    }
-                for (size_t i = i0; i < i1; ++i) {
-                    if (nparts[i - i0] < 2) continue;
-                    for (int h = 0; h < Hkv; ++h) {
-                        sk_comb c = {};
-                        c.part0 = slot0[i - i0] + h; c.n_parts = nparts[i - i0]; c.part_stride = Hkv;
-                        c.q_tok0 = g.tiles[i].q_tok0; c.n_tok = g.tiles[i].n_tok; c.kv_head = h;
-                        P.comb[gi].push_back(c);
-                    }
-                }
                 i0 = i1;
+            }
+            std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.bucket > y.bucket; });
+            for (const Piece& pc : pieces) {
+                const TileReq& t = g.tiles[(size_t)pc.tile];
+                const int32_t np = nparts[(size_t)pc.tile], part = pc.part, s0 = slot0[(size_t)pc.tile], u0 = unit0[(size_t)pc.tile];
+                for (int h = 0; h < Hkv; ++h) {
+                    sk_work w = {};
+                    w.tbl_off = t.tbl_off; w.kv_head = h; w.q_tok0 = t.q_tok0; w.n_tok = t.n_tok; w.pos0 = t.pos0;
+                    w.kv_begin = int32_t(part * chunk);
+                    w.kv_end = int32_t(std::min<int64_t>(t.kv_vis, (part + 1) * chunk));
+                    w.part = np > 1 ? s0 + part * Hkv + h : -1;
+                    w.unit = np > 1 ? u0 + h : -1;
+                    w.part0 = np > 1 ? s0 + h : -1;
+                    w.n_parts = np;
+                    w.hole_lo = t.hole_lo; w.hole_hi = t.hole_hi;
+                    w.tok_period = t.tok_period; w.sub_blocks = t.sub_blocks;
+                    if (part == np - 1)
+                        for (int e = 0; e < 2; ++e) { w.eph_blk[e] = t.eph_blk[e]; w.eph_cnt[e] = t.eph_cnt[e]; w.eph_pos0[e] = t.eph_pos0[e]; }
+                    P.work[gi].push_back(w);
+                }
+            }
+            for (size_t i = 0; i < g.tiles.size(); ++i) {
+                if (nparts[i] < 2) continue;
+                for (int h = 0; h < Hkv; ++h) {
+                    sk_comb c = {};
+                    c.part0 = slot0[i] + h; c.n_parts = nparts[i]; c.part_stride = Hkv;
+                    c.q_tok0 = g.tiles[i].q_tok0; c.n_tok = g.tiles[i].n_tok; c.kv_head = h;
+                    P.comb[gi].push_back(c);
+                }
             }
             rows_used += slot * g.v.rows_per_slot;
             if (rows_used > cap_rows) ok = false;

@@ -87,6 +87,33 @@ def test_ragged_multi_session_steps(shape, n_sessions, lo, hi):
             assert bool((mem[a:e] == 0xFF).all()), "block %d was written" % b
 
 
+@pytest.mark.parametrize("tokens", [3, 40, 70])
+def test_step_over_sessions_at_the_edges_of_a_piece(tokens):
+    """Cached lengths around the shortest piece a tile is cut into (256 keys), empty sessions and one much
+    longer than the others, so that whole pieces, remainders and single-piece tiles (written directly)
+    meet in one launch; 3 / 40 / 70 tokens take the 64-, 256- and 256-row kernels."""
+    shape = synth.CFG4
+    gen = synth.generator(4, stream=500 + tokens)
+    lengths = [0, 1, 64, 255, 256, 257, 512, 513, 6000, 0]
+    n = len(lengths)
+    pool = sk.Pool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, 16, sum(lengths) // 16 + 120, max_sessions=n,
+                   max_batch_tokens=2048, kv_fill=0xFF)
+    ref = oracle.OraclePool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim)
+    sids = [pool.sk_session_create() for _ in range(n)]
+    for _ in sids:
+        ref.create()
+    _grow(pool, ref, sids, lengths, shape, gen)
+    ops = [sk.SK_OP_QUERY_B] * (n - 2) + [sk.SK_OP_QUERY_A, sk.SK_OP_APPEND]
+    for step in range(2):
+        cu = np.arange(n + 1, dtype=np.int32) * tokens
+        q, k, v = synth.draw_qkv(gen, int(cu[-1]), shape)
+        out, lse = pool.sk_batch_step(sids, ops, cu, dev(q), dev(k), dev(v))
+        ro, rl = ref.batch_step(sids, ops, cu, synth.to_raw(q), synth.to_raw(k), synth.to_raw(v))
+        compare("step %d" % step, out, lse, ro, rl, shape.dtype)
+        ops = [sk.SK_OP_APPEND, sk.SK_OP_QUERY_A] * (n // 2)
+    _check_caches(pool, ref, sids)
+
+
 def test_batch_errors_leave_state_unchanged():
     shape = synth.CFG4
     gen = synth.generator(4, stream=77)
