@@ -113,6 +113,9 @@ size_t sk_pool_workspace_bytes(const sk_pool_desc* desc);
  * changes a result beyond the rounding order of the split merge; they exist for sweeps):
  *   SK_TARGET_WGS=n    workgroups a single-session call is cut into (default: 256 or 512 by shape)
  *   SK_FORCE_SIMPLE=1  always the fp32-FMA attention kernel
+ *   SK_NO_SMALL=1      never the kernel for calls of at most 32 query rows per KV head
+ *   SK_SMALL_DISTRUST=1  in that kernel the last workgroup of a KV head computes the head's rows alone, as if
+ *                      the parts had not run on one XCD (tests)
  *   SK_NO_256=1        never the 256-row eight-wave instance of the bf16 kernel
  *   SK_NO_PACK=1       a question batch gives every question a row tile of its own
  *   SK_NO_INTERLEAVE=1 the splits of a query take contiguous chunks of the cache instead of
@@ -174,7 +177,8 @@ int sk_session_append(sk_pool* pool, int32_t id, const void* q, const void* k, c
  * processed by separate workgroups and merged by log-sum-exp; 0 = chosen by the library.
  * An empty cache with k == NULL gives SK_E_EMPTY.  nq == 0 is a no-op.
  * The call enqueues kernels only (its decomposition travels in the kernel arguments, and so does
- * the list that stages its own k,v while they span at most 80 groups of 16 tokens): it can be
+ * the list that stages its own k,v while they span at most 80 groups of 16 tokens; calls of at most 32
+ * query rows per KV head read them where they are): it can be
  * captured in a HIP graph and replayed, as long as the session is not changed in between (its
  * length is baked into the captured arguments).
  */

@@ -36,7 +36,7 @@ struct sk_geom {
     int32_t d;
     int32_t elem;                 // bytes per element (2 or 4)
     float scale_log2e;            // softmax scale * log2(e)
-    int32_t pad;
+    uint32_t g_magic;             // ceil(2^16 / G): row / G of a tile's row is (row * g_magic) >> 16
 };
 
 #define SK_NO_CAUSAL (1 << 30)    // pos0 at or above this: rows see every key of every segment
@@ -89,10 +89,24 @@ struct sk_scatter {
 #define SK_SCATTER_ARGS_MAX 80
 struct sk_scatter_list { sk_scatter item[SK_SCATTER_ARGS_MAX]; };
 
+// Division of a 31-bit count by a constant of the launch as one multiplication (a hardware-less integer
+// division costs a workgroup's start tens of instructions, one behind the other).
+struct sk_div { uint32_t mul; int32_t shift; };      // n / d == umulhi(n, mul) >> shift for n < 2^30; mul 0: d == 1
+static inline sk_div sk_make_div(uint32_t d)
+{
+    if (d <= 1) return sk_div{0, 0};
+    int l = 0;
+    while ((1u << l) < d) ++l;                        // 2^(l-1) < d <= 2^l
+    // m = ceil(2^(31 + l) / d) <= 2^32 - 1 for l >= 1; exact for n < 2^31 (error of m below 2^l, see Granlund & Montgomery 1994)
+    const uint64_t m = ((uint64_t(1) << (31 + l)) + d - 1) / d;
+    return sk_div{(uint32_t)m, l - 1};
+}
+
 enum { SK_MODE_REGULAR = 0, SK_MODE_LIST = 1 };
 // attention kernel variants: fp32-FMA kernel; bf16 MFMA kernel with 128-, 64- and 256-row tiles; the
 // 128-row tile again with eight waves (two key phases per row group, one workgroup per CU)
-enum { SK_KV_SIMPLE = 0, SK_KV_MFMA128 = 1, SK_KV_MFMA64 = 2, SK_KV_MFMA256 = 3, SK_KV_MFMA128P = 4 };
+enum { SK_KV_SIMPLE = 0, SK_KV_MFMA128 = 1, SK_KV_MFMA64 = 2, SK_KV_MFMA256 = 3, SK_KV_MFMA128P = 4,
+       SK_KV_SMALL = 5 };   // at most 32 rows per KV head
 
 // Kernel argument block of the attention and combine kernels.
 struct sk_launch {
@@ -128,7 +142,25 @@ struct sk_launch {
     int32_t fuse;
     int32_t wait_polls;
     int32_t merge_fences;   // 1: full device-scope fences around the arrival (slow: an L2 walk each); 0: see the kernel
+    sk_div by_heads, by_tiles, by_chunk;      // Hkv, n_tiles, chunk (regular mode)
+    // calls of at most 32 rows per KV head (sk_attn_bf16_small): the call's own tokens where the caller has them
+    // ([own_cnt][Hkv][d], the last keys of the last part), and the launch geometry
+    const void* own_k;
+    const void* own_v;
+    int32_t own_cnt;
+    int32_t head_pad;       // workgroups from one part of a head to the next (KV heads, padded to a multiple of 8)
+    sk_div by_pad;
+    int32_t distrust;       // 1: treat the parts as run on several XCDs (the last one computes the tile alone; tests)
     int32_t kv_once;        // 1: every key is read by exactly one workgroup of the launch (loaded non-temporal)
+};
+
+// The commit of a small append, done by workgroups first_wg, first_wg + 1, .. of its attention launch.
+#define SK_COMMIT_ITEMS 3             // 16-token groups that 32 tokens can touch
+struct sk_commit {
+    int32_t first_wg;       // INT32_MAX: nothing to commit
+    int32_t* tables_rw;
+    unsigned char* kv_rw;
+    sk_scatter item[SK_COMMIT_ITEMS];
 };
 
 // Launchers implemented in sk_kernels.hip (return hipError_t as int).
@@ -139,6 +171,7 @@ int sk_launch_scatter_args(const sk_geom& g, const void* k, const void* v, const
                            int32_t n_items, int32_t* tables_rw, unsigned char* kv_rw,
                            unsigned char* eph_rw, void* stream);
 int sk_launch_attention(const sk_launch& L, int variant, int32_t n_workgroups, void* stream, void* ev_start, void* ev_stop);
+int sk_launch_attention_small(const sk_launch& L, const sk_commit& C, int32_t n_workgroups, void* stream, void* ev_start, void* ev_stop);
 int sk_launch_combine(const sk_launch& L, int32_t n_row_tiles, void* stream, void* ev_start, void* ev_stop);
 int sk_launch_gather(const sk_geom& g, int32_t tbl_off, int64_t first, int64_t count,
                      void* k_out, void* v_out, void* stream);

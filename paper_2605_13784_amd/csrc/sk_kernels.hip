@@ -37,6 +37,29 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f)
     return (uint16_t)(u >> 16);
 }
 
+__device__ __forceinline__ int sk_divide(const int n, const sk_div d)
+{
+    return d.mul ? (int)(__umulhi((uint32_t)n, d.mul) >> d.shift) : n;
+}
+
+// Requests every 64-byte line of a kernel's argument block at once.  The arguments lie in memory that nothing
+// has read yet; left to the compiler they are fetched field by field as the code branches, each first touch of
+// a line a round trip of its own in front of the kernel's first useful load (with the divisions below done by
+// multiplication and the first tiles requested before the query operand is waited for: first tile in LDS at 2.2
+// instead of 3.0 us after a workgroup's start, a 32-token query at 32K 40.2 -> 39.2 us).
+template <unsigned BYTES>
+__device__ __forceinline__ void sk_touch_arguments()
+{
+    typedef const __attribute__((address_space(4))) uint32_t* args_ptr;
+    const args_ptr a = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr unsigned LINES = (BYTES + 63) / 64;
+    uint32_t x[LINES];
+#pragma unroll
+    for (unsigned i = 0; i < LINES; ++i) x[i] = a[i * 16];
+#pragma unroll
+    for (unsigned i = 0; i < LINES; ++i) asm volatile("" : : "s"(x[i]));
+}
+
 // Work item of workgroup b.  Regular mode derives it from the launch parameters: consecutive
 // workgroups differ in KV head first (so with 8 KV heads a head stays on one XCD and its K/V
 // stay in that XCD's L2), then in row tile, then in split.
@@ -48,7 +71,7 @@ __device__ __forceinline__ int sk_tile_parts(const sk_launch& P, int tok0, int n
         kv_vis = last < kv_vis ? last : kv_vis;
     }
     *kv_vis_out = kv_vis;
-    int np = (kv_vis + P.chunk - 1) / P.chunk;
+    int np = sk_divide(kv_vis + P.chunk - 1, P.by_chunk);
     if (P.eph_cnt[0] > 0 || P.eph_cnt[1] > 0) np += 1;      // uncommitted tokens: own part
     return np < 1 ? 1 : np;
 }
@@ -57,8 +80,8 @@ __device__ __forceinline__ bool sk_decode_work(const sk_launch& P, int b, sk_wor
 {
     if (P.mode == SK_MODE_LIST) { w = P.work[b]; return true; }
     const int Hkv = P.g.Hkv;
-    int head = b % Hkv, rest = b / Hkv;
-    int tile = rest % P.n_tiles, split = rest / P.n_tiles;
+    const int rest = sk_divide(b, P.by_heads), head = b - rest * Hkv;
+    const int split = sk_divide(rest, P.by_tiles), tile = rest - split * P.n_tiles;
     int tok0 = tile * P.tok_per_tile;
     int ntok = P.n_tok - tok0; ntok = ntok < P.tok_per_tile ? ntok : P.tok_per_tile;
     int kv_vis;
@@ -417,6 +440,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     constexpr unsigned XCH_BYTES = NPH > 1 ? NRG * 17 * 64 * 16 : 0;
     __shared__ __attribute__((aligned(16))) unsigned char lds[RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES];
 
+    sk_touch_arguments<sizeof(sk_launch)>();
     sk_work w;
     if (!sk_decode_work(P, blockIdx.x, w)) return;
 
@@ -436,7 +460,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     // whole token of a tile are idle).  Rows are below 256, so the division is a multiplication by
     // ceil(2^16 / G) and a shift, exactly.
     const int G = P.g.G;
-    const unsigned g_magic = (65536u + (unsigned)G - 1u) / (unsigned)G;
+    const unsigned g_magic = P.g.g_magic;
     auto div_g = [&](const int row) __attribute__((always_inline)) { return (int)(((unsigned)row * g_magic) >> 16); };
     const int row_in_tile = rg * 32 + r;
     const int tok_local = div_g(row_in_tile);
@@ -463,18 +487,12 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     // Q^T operand: lane (row r, k-group kg) keeps Q[row][16*ks + 8*kg .. +7] for ks = 0..7
     bf16x8 qreg[8];
     {
-        uint4 z = make_uint4(0, 0, 0, 0);
+        // Rows past the tile re-read its first token's head row; what they compute goes nowhere.  Nothing here waits for
+        // the loads: the segment loop issues its own first.
         const uint4* qp = (const uint4*)((const unsigned char*)P.q +
                           ((size_t)(w.q_tok0 + (row_valid ? tok_local : 0)) * P.g.Hq + hq) * (D * 2));
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            uint4 x = z;
-            if (ks < NKS) {
-                x = qp[ks * 2 + kg];                   // rows past the tile re-read row 0, then zeroed
-                if (!row_valid) x = z;
-            }
-            qreg[ks] = __builtin_bit_cast(bf16x8, x);
-        }
+        for (int ks = 0; ks < NKS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[ks * 2 + kg]);
     }
 
     f32x16 oacc[4];
@@ -662,10 +680,13 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
         };
 
         sk_lds_barrier();                      // ring free (previous segment fully consumed)
-        // The query operand must have arrived before the loop (a wait for it placed by the
-        // compiler inside the loop would drain the ring on every iteration).
+        // The query operand must have arrived before the loop (a wait for it placed by the compiler inside
+        // the loop would drain the ring on every iteration), but the first tiles are requested before it is
+        // waited for.
+        auto await_query = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) asm volatile("" : : "v"(qreg[ks]));
+            for (int ks = 0; ks < NKS; ++ks) asm volatile("" : : "v"(qreg[ks]));
+        };
 
         if constexpr (!LOCKSTEP) {
             // ---- free-running waves: every wave walks S, softmax, PV of an iteration in turn; overlap of
@@ -685,6 +706,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                     }
                 }
             }
+            await_query();
             // block ids of the next refill are looked up one iteration ahead of their use
             sk_tile_blocks nb[TPI];
 #pragma unroll
@@ -773,11 +795,10 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             };
             issue_next(0);
             issue_next(1);
-            if (grp == 1) {
-                issue_next(2);
-                SK_WAIT_VMCNT(2 * LPW);          // iteration 0 has landed
-                sk_lds_barrier();                // group 1 stays one barrier behind
-            } else SK_WAIT_VMCNT(LPW);
+            if (grp == 1) issue_next(2);
+            await_query();
+            SK_WAIT_VMCNT(LPW);                  // iteration 0 has landed (group 1: and iteration 1)
+            if (grp == 1) sk_lds_barrier();      // group 1 stays one barrier behind
             // Matrix slot: eight groups of four matrix instructions, P V of the previous iteration
             // (V^T through vp, the pointers of its ring slot) and S of the current one (K through
             // kc).  Operands stream from LDS two groups ahead of their use, into the registers that
@@ -1069,6 +1090,352 @@ __global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 1 : 2) void sk_att
 }
 
 // ---------------------------------------------------------------------------------------------
+// bf16 MFMA attention kernel for calls of at most 32 query rows per KV head (a decoded token, a short
+// question): what such a call takes is latency, not rate, so everything between the launch and the
+// result is kept short.
+//
+// A workgroup is four waves that share nothing until the end: wave w takes the 32-key tiles w, w + 4, .. of
+// the workgroup's keys, straight from memory into the operand registers of the matrix instructions
+// (sixteen 16-byte loads per lane and tile, all in flight at once; no LDS ring, no barrier in the loop),
+// with the arithmetic and register layout of the kernel above.  The four partial results meet in LDS.
+// The call's own K/V (a query's, or a chunk being appended: at most 32 tokens) are read where the caller
+// has them, as one more tile of the last part, so no staging launch stands in front; an append's commit
+// runs in further workgroups of the same launch.
+//
+// The parts of a row tile are merged by the workgroup that finishes last (P.fuse), which reads the others'
+// partials through the L2 it shares with them: the launch maps all parts of a KV head to one XCD, so their
+// ordinary stores are visible there once they have completed.  That they did run on one XCD is checked, not
+// assumed: every workgroup adds its XCD number and its square to the unit's 64-bit arrival word (one
+// device-scope atomic), and the last one merges only if n * sum(x^2) == sum(x)^2, i.e. all x are equal.
+// If not, it computes the whole row tile by itself.  Nobody waits for anybody.
+//
+// Bound: round trips.  One query token with its own K/V at 2,600 cached tokens: one launch of 8.1 us where a staging,
+// an attention and a combine kernel took 16.3 back to back; 1.0 us from a workgroup's start to its first loads
+// (arguments, block table), 2.2 to the end of its keys, 1.1 for the meeting in LDS, 0.4 for the arrival and 2.2 for
+// the merge (three round trips).  10.7 MB of cache at the rate of a plain read would be 1.7 us.
+// ---------------------------------------------------------------------------------------------
+__device__ __forceinline__ unsigned sk_xcd_id() { return (unsigned)__builtin_amdgcn_s_getreg((3 << 11) | 20); }    // HW_REG_XCC_ID, bits 3:0
+
+template <int D>
+__device__ __forceinline__ void sk_commit_group(const sk_geom& g, const void* k, const void* v, const sk_scatter& it, const int head,
+                                                int32_t* tables_rw, unsigned char* kv_rw, uint16_t* vt);
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, const sk_commit C)
+{
+    constexpr int NKS = D / 16, NMT = D / 32, NWV = 4, CPR = D / 4;      // CPR: float4 chunks of an output row
+    constexpr int ROWB = D * 2, LOG2_TOK_BYTES = D == 128 ? 8 : 7;
+    __shared__ float4 tr[NWV][32][CPR];
+    __shared__ float4 stat[NWV][32];
+    __shared__ int decision;
+    sk_touch_arguments<sizeof(sk_launch) + sizeof(sk_commit)>();
+    const int Hkv = P.g.Hkv;
+    if (__builtin_expect((int)blockIdx.x >= C.first_wg, 0)) {                  // the commit of an append
+        const int i = blockIdx.x - C.first_wg, item = sk_divide(i, P.by_heads);
+        sk_commit_group<D>(P.g, P.own_k, P.own_v, C.item[item], i - item * Hkv, C.tables_rw, C.kv_rw, (uint16_t*)&tr[0][0][0]);
+        return;
+    }
+    // workgroup -> (part, KV head); the heads of a part are padded to a multiple of the XCD count
+    const int part = sk_divide(blockIdx.x, P.by_pad), head = blockIdx.x - part * P.head_pad;
+    if (head >= Hkv) return;
+    const int n_parts = P.n_splits;
+    bool whole = n_parts == 1;                            // this workgroup computes the row tile from end to end
+    for (;;) {
+        // (opaque, or everything below that depends on the lane only is computed before the first load is
+        // requested: the loop almost never runs twice)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int r = lane & 31, kg = lane >> 5;
+        const int G = P.g.G, nrows = P.n_tok * G;
+        const unsigned g_magic = P.g.g_magic;
+        auto div_g = [&](const int row) __attribute__((always_inline)) { return (int)(((unsigned)row * g_magic) >> 16); };
+        const int tok = div_g(r < nrows ? r : 0), hq = head * G + (r < nrows ? r - tok * G : 0);
+        const float c_scale = P.g.scale_log2e;
+        const int tau = (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);      // key of S^T row r (bits 2 and 3 swapped)
+        auto put_row = [&](const int row, const int c4, const float4 x, const float inv, const float lse) __attribute__((always_inline)) {
+            const int t2 = div_g(row);
+            const size_t orow = (size_t)t2 * P.g.Hq + head * G + (row - t2 * G);
+            if (P.out_dtype == 0) *(float4*)((float*)P.out + orow * D + c4 * 4) = make_float4(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
+            else {
+                const uint32_t lo = f32_to_bf16_bits(x.x * inv) | ((uint32_t)f32_to_bf16_bits(x.y * inv) << 16);
+                const uint32_t hi = f32_to_bf16_bits(x.z * inv) | ((uint32_t)f32_to_bf16_bits(x.w * inv) << 16);
+                *(uint2*)((uint16_t*)P.out + orow * D + c4 * 4) = make_uint2(lo, hi);
+            }
+            if (P.lse && c4 == 0) P.lse[orow] = lse;
+        };
+
+        bf16x8 qreg[NKS];
+        {
+            const sk_u32x4* qp = (const sk_u32x4*)((const unsigned char*)P.q + ((size_t)tok * P.g.Hq + hq) * ROWB);
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[ks * 2 + kg]);
+        }
+
+        int k_begin = 0, k_end = P.kv_len;
+        if (!whole) {
+            k_begin = part * P.chunk;
+            k_end = k_begin + P.chunk < k_end ? k_begin + P.chunk : k_end;
+        }
+        const int n_cached = k_end > k_begin ? (k_end - k_begin + 31) >> 5 : 0;
+        const int last_group = (k_end - 1) & ~15;
+
+        f32x16 oacc[NMT];
+#pragma unroll
+        for (int mt = 0; mt < NMT; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) oacc[mt][v] = 0.f;
+        float m_ref = SK_NEG_INF, l_run = 0.f, lx_run = 0.f;
+        sk_u32x4 ka[NKS], va[2][NMT];
+
+        // the two 16-key groups of cached tile t: base of each group's K (its V^T lies v_off further)
+        auto group_base = [&](const int t, const int j) __attribute__((always_inline)) -> const unsigned char* {
+            typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+            int tg = k_begin + t * 32 + 16 * j;
+            tg = tg < last_group ? tg : last_group;
+            const uint32_t blk = (uint32_t)((const_i32_ptr)(uintptr_t)P.g.tables)[(unsigned)P.tbl_off + ((unsigned)tg >> P.g.log2B)];
+            return P.g.kv + (int64_t)head * P.g.head_stride + ((uint64_t)blk << (P.g.log2B + LOG2_TOK_BYTES + 1)) +
+                   (((unsigned)tg & (unsigned)(P.g.B - 1)) << LOG2_TOK_BYTES);
+        };
+        auto load_k = [&](const unsigned char* b0, const unsigned char* b1) __attribute__((always_inline)) {
+            const unsigned char* p = ((r & 16) ? b1 : b0) + (tau & 15) * ROWB + kg * 16;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) ka[ks] = *(const sk_u32x4*)(p + ks * 32);
+        };
+        auto load_v = [&](const unsigned char* b0, const unsigned char* b1) __attribute__((always_inline)) {
+            const unsigned voff = (unsigned)(P.g.v_off + r * 32 + kg * 16);
+#pragma unroll
+            for (int mt = 0; mt < NMT; ++mt) {
+                va[0][mt] = *(const sk_u32x4*)(b0 + voff + mt * 1024);
+                va[1][mt] = *(const sk_u32x4*)(b1 + voff + mt * 1024);
+            }
+        };
+        f32x16 sacc;
+        bf16x8 pb[2];
+        auto scores = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ks]), qreg[ks], sacc, 0, 0, 0);
+        };
+        auto mask = [&](const int k0, const int limit, const int hole_lo, const int hole_n) __attribute__((always_inline)) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int key = k0 + 16 * (v >> 3) + 8 * kg + (v & 7);
+                const bool vis = key <= limit && (unsigned)(key - hole_lo) >= (unsigned)hole_n;
+                sacc[v] = vis ? sacc[v] : SK_NEG_INF;
+            }
+        };
+        auto softmax = [&]() __attribute__((always_inline)) {
+            float mx = SK_NEG_INF;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
+            { const sk_halves h = sk_both_halves(mx); mx = fmaxf(h.lo, h.hi) * c_scale; }
+            const bool raise = mx > m_ref + SK_RESCALE_SLACK;
+            if (__any(raise)) {
+                const float alpha = raise ? sk_exp2(m_ref - mx) : 1.0f;
+                l_run *= alpha; lx_run *= alpha;
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) oacc[mt][v] *= alpha;
+                m_ref = raise ? mx : m_ref;
+            }
+            const float neg_m = m_ref == SK_NEG_INF ? 0.f : -m_ref;
+            float lx0 = 0.f, lx1 = 0.f;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                const float p0 = sk_exp2(fmaf(sacc[v], c_scale, neg_m)), p1 = sk_exp2(fmaf(sacc[8 + v], c_scale, neg_m));
+                pb[0][v] = (__bf16)p0; pb[1][v] = (__bf16)p1;
+                lx0 += p0; lx1 += p1;
+            }
+            lx_run += lx0 + lx1;
+            const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+            float ls0 = 0.f, ls1 = 0.f;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {        // the row sum over the weights as the matrix pipe sees them (see above)
+                ls0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[q], pb[q], 0, 1), ones, ls0, false);
+                ls1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[q], pb[q], 2, 3), ones, ls1, false);
+                ls0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[q], pb[q], 4, 5), ones, ls0, false);
+                ls1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[q], pb[q], 6, 7), ones, ls1, false);
+            }
+            l_run += ls0 + ls1;
+        };
+        auto values = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt)
+                    oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va[q][mt]), pb[q], oacc[mt], 0, 0, 0);
+        };
+
+        if (wave < n_cached) {
+            const unsigned char *b0 = group_base(wave, 0), *b1 = group_base(wave, 1);
+            load_k(b0, b1); load_v(b0, b1);
+#pragma unroll 1
+            for (int t = wave; t < n_cached; t += NWV) {
+                const bool more = t + NWV < n_cached;
+                if (more) { b0 = group_base(t + NWV, 0); b1 = group_base(t + NWV, 1); }
+                scores();
+                if (more) load_k(b0, b1);
+                const int k0 = k_begin + t * 32;          // keys past the end of the part and evicted keys do not count
+                if (k0 + 32 > k_end || (k0 < P.hole_hi && k0 + 32 > P.hole_lo)) mask(k0, k_end - 1, P.hole_lo, P.hole_hi - P.hole_lo);
+                softmax();
+                values();
+                if (more) load_v(b0, b1);
+            }
+        }
+        // The call's own tokens: one tile, for a wave that has no cached one when the launch is cut into parts.
+        if ((whole || part == n_parts - 1) && P.own_cnt > 0 && wave == (n_cached & (NWV - 1))) {
+            const int key = tau < P.own_cnt ? tau : P.own_cnt - 1;
+            const unsigned char* p = (const unsigned char*)P.own_k + ((size_t)key * Hkv + head) * ROWB + kg * 16;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) ka[ks] = *(const sk_u32x4*)(p + ks * 32);
+            // token-major values: the rows go through this wave's quarter of the exchange area, where eight keys of
+            // one dimension are eight 2-byte reads; zero past the end
+            uint4* rows = (uint4*)&tr[wave][0][0];
+#pragma unroll
+            for (int i = 0; i < 32 * ROWB / 16 / 64; ++i) {
+                const int c = i * 64 + lane, vkey = c / (ROWB / 16), cc = c % (ROWB / 16);
+                uint4 x = make_uint4(0, 0, 0, 0);
+                if (vkey < P.own_cnt) x = *(const uint4*)((const unsigned char*)P.own_v + ((size_t)vkey * Hkv + head) * ROWB + cc * 16);
+                rows[c] = x;
+            }
+            scores();
+            mask(0, P.pos0 < SK_NO_CAUSAL ? tok : P.own_cnt - 1, 0, 0);
+            softmax();
+            const uint16_t* vt = (const uint16_t*)rows + 8 * kg * D + r;
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        va[q][mt][j] = (uint32_t)vt[(16 * q + 2 * j) * D + mt * 32] | ((uint32_t)vt[(16 * q + 2 * j + 1) * D + mt * 32] << 16);
+                }
+            values();
+        }
+
+        // ---- the four waves meet: common maximum, scaled accumulators side by side in LDS, sum ----
+        float l_tot, lx_tot;
+        { const sk_halves h = sk_both_halves(l_run); l_tot = h.lo + h.hi; }
+        { const sk_halves h = sk_both_halves(lx_run); lx_tot = h.lo + h.hi; }
+        if (r < nrows && kg == 0) stat[wave][r].x = m_ref;
+        __syncthreads();
+        float M = SK_NEG_INF;
+#pragma unroll
+        for (int w = 0; w < NWV; ++w) M = fmaxf(M, stat[w][r].x);
+        const float a = m_ref == SK_NEG_INF ? 0.f : sk_exp2(m_ref - M);
+        if (r < nrows) {
+#pragma unroll
+            for (int mt = 0; mt < NMT; ++mt)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const int c4 = mt * 8 + q4 * 2 + kg;
+                    tr[wave][r][(c4 ^ r) & (CPR - 1)] = make_float4(oacc[mt][q4 * 4 + 0] * a, oacc[mt][q4 * 4 + 1] * a,
+                                                                    oacc[mt][q4 * 4 + 2] * a, oacc[mt][q4 * 4 + 3] * a);
+                }
+            if (kg == 0) { stat[wave][r].y = l_tot * a; stat[wave][r].z = lx_tot * a; }
+        }
+        __syncthreads();
+        const size_t prow = ((size_t)part * Hkv + head) * P.rows_per_slot;
+        for (int i = tid; i < nrows * CPR; i += 256) {
+            const int row = i / CPR, c4 = i % CPR;
+            float4 x = tr[0][row][(c4 ^ row) & (CPR - 1)];
+            float m = stat[0][row].x, l = stat[0][row].y, lx = stat[0][row].z;
+#pragma unroll
+            for (int w = 1; w < NWV; ++w) {
+                const float4 y = tr[w][row][(c4 ^ row) & (CPR - 1)];
+                x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+                m = fmaxf(m, stat[w][row].x); l += stat[w][row].y; lx += stat[w][row].z;
+            }
+            if (whole) {
+                put_row(row, c4, x, 1.0f / l, (m + sk_log2(lx)) * SK_LN2);
+            } else {
+                *(float4*)(P.part_o + (prow + row) * D + c4 * 4) = x;
+                if (c4 == 0) *((float4*)P.part_ml + prow + row) = make_float4(m, l, lx, 0.f);
+            }
+        }
+        if (whole || !P.fuse) return;
+
+        // ---- arrival; the last workgroup of the head merges ----
+        SK_WAIT_VMCNT(0);                                 // this thread's part of the partial has reached the L2
+        __syncthreads();
+        if (tid == 0) {
+            const unsigned long long x = sk_xcd_id();
+            unsigned long long* word = (unsigned long long*)P.sync + head * 16;      // a 128-byte line per head: each is one XCD's
+            const unsigned long long add = 1ull | (x << 16) | ((x * x) << 36);
+            const unsigned long long got = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+            int d = 0;
+            if ((int)(got & 0xffffu) == n_parts) {
+                const unsigned long long sum = (got >> 16) & 0xfffffu, sq = got >> 36;
+                d = (!P.distrust && (unsigned long long)n_parts * sq == sum * sum) ? 1 : 2;
+                __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // ready for the next launch
+            }
+            decision = d;
+        }
+        __syncthreads();
+        const int d = decision;
+        if (d == 0) return;
+        if (d == 1) {
+            // All statistics in one round of loads, the weights of all parts to LDS, then every thread sums its 16-byte
+            // pieces of output rows over the parts, in part order, eight loads in flight (a short loop: code that
+            // runs once per launch costs its instruction fetches, so 32 unrolled loads took 1 us longer).
+            float4* ml = &tr[0][0][0];                    // [part][32 rows]
+            float4* tot = &stat[0][0];                    // [32 rows]
+            const size_t pstep = (size_t)Hkv * P.rows_per_slot;
+            const unsigned row0 = (unsigned)(head * P.rows_per_slot);
+            for (int p = tid >> 5; p < n_parts; p += 8)
+                if (r < nrows) ml[p * 32 + r] = *((const float4*)P.part_ml + p * pstep + (row0 + (unsigned)r));
+            __syncthreads();
+            {
+                const int row = tid >> 3, sub = tid & 7;
+                float M2 = SK_NEG_INF, L = 0.f, Lx = 0.f;
+                if (row < nrows) for (int p = sub; p < n_parts; p += 8) M2 = fmaxf(M2, ml[p * 32 + row].x);
+#pragma unroll
+                for (int off = 4; off >= 1; off >>= 1) M2 = fmaxf(M2, __shfl_xor(M2, off, 64));
+                if (row < nrows)
+#pragma unroll 1
+                    for (int p = sub; p < n_parts; p += 8) {
+                        const float4 t = ml[p * 32 + row];
+                        const float wgt = t.x == SK_NEG_INF ? 0.f : sk_exp2(t.x - M2);
+                        ml[p * 32 + row].x = wgt;
+                        L = fmaf(t.y, wgt, L); Lx = fmaf(t.z, wgt, Lx);
+                    }
+#pragma unroll
+                for (int off = 4; off >= 1; off >>= 1) { L += __shfl_xor(L, off, 64); Lx += __shfl_xor(Lx, off, 64); }
+                if (row < nrows && sub == 0) tot[row] = make_float4(M2, L, Lx, 0.f);
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (int i = tid; i < nrows * CPR; i += 256) {
+                const int row = i / CPR;
+                const unsigned at = row0 * CPR + (unsigned)i;                  // in float4, from a part's first row
+                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+                for (int p0 = 0; p0 < n_parts; p0 += 8) {
+                    float4 x[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)      // (past the last part: the last one again, with weight 0, so that no load waits for a branch)
+                        x[j] = *((const float4*)P.part_o + (size_t)(p0 + j < n_parts ? p0 + j : n_parts - 1) * (pstep * CPR) + at);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const float wgt = p0 + j < n_parts ? ml[(p0 + j) * 32 + row].x : 0.f;
+                        acc.x = fmaf(x[j].x, wgt, acc.x); acc.y = fmaf(x[j].y, wgt, acc.y);
+                        acc.z = fmaf(x[j].z, wgt, acc.z); acc.w = fmaf(x[j].w, wgt, acc.w);
+                    }
+                }
+                const float4 t = tot[row];
+                put_row(row, i % CPR, acc, 1.0f / t.y, (t.x + sk_log2(t.z)) * SK_LN2);
+            }
+            return;
+        }
+        whole = true;                                     // the parts ran on several XCDs: once more, alone
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // fp32-arithmetic attention kernel (fp32 pools, and bf16 pools whose shape the MFMA kernel does
 // not take).  Tile of up to 16 query rows x 32 keys; every product and sum is an fp32 FMA.
 // Thread (r = tid/16, c = tid%16): scores of row r for keys c and c+16; output
@@ -1083,6 +1450,7 @@ __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
     __shared__ float Vs[32][DMAX + 1];
     __shared__ float Ps[16][32 + 1];
 
+    sk_touch_arguments<sizeof(sk_launch)>();
     sk_work w;
     if (!sk_decode_work(P, blockIdx.x, w)) return;
     const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
@@ -1204,6 +1572,7 @@ __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
 {
+    sk_touch_arguments<sizeof(sk_launch)>();
     const int groups_per_tile = P.rows_per_slot >> 2;
     const int item = blockIdx.x / groups_per_tile;
     const int row = (blockIdx.x % groups_per_tile) * 4 + (threadIdx.x >> 6);
@@ -1212,11 +1581,11 @@ __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
     if (P.mode == SK_MODE_LIST) cb = P.comb[item];
     else {
         const int Hkv = P.g.Hkv;
-        int head = item % Hkv, tile = item / Hkv;
+        const int tile = sk_divide(item, P.by_heads), head = item - tile * Hkv;
         int tok0 = tile * P.tok_per_tile;
         int ntok = P.n_tok - tok0; ntok = ntok < P.tok_per_tile ? ntok : P.tok_per_tile;
         int kv_vis;
-        cb.n_parts = sk_tile_parts(P, tok0, ntok, &kv_vis);
+        cb.n_parts = P.head_pad > 0 ? P.n_splits : sk_tile_parts(P, tok0, ntok, &kv_vis);
         cb.part0 = tile * P.n_splits * Hkv + head; cb.part_stride = Hkv;
         cb.q_tok0 = tok0; cb.n_tok = ntok; cb.kv_head = head;
     }
@@ -1227,82 +1596,86 @@ __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
 }
 
 // ---------------------------------------------------------------------------------------------
-// K/V commit.  One workgroup per (destination 16-token group, KV head).  Pure bit copies through
-// integer lanes.  K rows are copied as 16-byte chunks; V is copied likewise for f32 pools and
-// transposed through LDS for bf16 pools ([dim][token] within each 16-token group).
+// K/V commit.  One workgroup of 256 threads per (destination 16-token group, KV head); pure bit copies
+// through integer lanes.
 // ---------------------------------------------------------------------------------------------
+
+// bf16, head_dim D: every thread takes one 16-byte chunk of a K row and of a V row; V goes through `vt` (16 rows
+// of LDS, 16 * (D + 8) elements) to leave as [dim][16 tokens], in 16-byte pieces when the group starts at its first slot.
+// Slots of the group behind the last committed token are zero-filled, so that a key the attention kernel masks
+// out never multiplies 0 by leftover bits.
+// Bound: one round trip to memory and the launch (128 groups of a 256-token chunk: 4.8 us; 1,304 of a 2,600-token one
+// 8.2 -> 5.9 us against a loop over elements with divisions by run-time row lengths).
+template <int D>
+__device__ __forceinline__ void sk_commit_group(const sk_geom& g, const void* k, const void* v, const sk_scatter& it, const int head,
+                                                int32_t* tables_rw, unsigned char* kv_rw, uint16_t* vt)
+{
+    constexpr int CPR = D / 8, LD = D + 8;                  // 16-byte chunks of a row; LDS row length
+    const int tid = threadIdx.x, row = tid / CPR, cc = tid % CPR;
+    unsigned char* dst = kv_rw + it.dst_off + (int64_t)head * (it.to_eph ? g.eph_head_stride : g.head_stride);
+    if (it.tbl_index >= 0 && head == 0 && tid == 0) tables_rw[it.tbl_index] = it.block_id;
+    if (row < it.count) {
+        const size_t src = ((size_t)(it.src_tok0 + row) * g.Hkv + head) * (D * 2) + cc * 16;
+        const uint4 x = *(const uint4*)((const unsigned char*)k + src), y = *(const uint4*)((const unsigned char*)v + src);
+        *(uint4*)(dst + (it.dst_slot0 + row) * (D * 2) + cc * 16) = x;
+        *(uint4*)(vt + row * LD + cc * 8) = y;
+    }
+    __syncthreads();
+    if (tid >= 2 * D) return;
+    const int first = it.dst_slot0 & 15;                    // position inside the 16-token group
+    const int dim = tid >> 1, s0 = (tid & 1) * 8 - first;   // two threads per dimension, eight slots each; s0: token of the first
+    uint16_t* vd = (uint16_t*)(dst + (it.to_eph ? g.eph_v_off : g.v_off)) + (size_t)(it.dst_slot0 >> 4) * D * 16 + dim * 16 + (tid & 1) * 8;
+    uint32_t e[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) e[j] = (s0 + j >= 0 && s0 + j < it.count) ? vt[(s0 + j) * LD + dim] : 0u;
+    if (first == 0) *(uint4*)vd = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+    else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (s0 + j >= 0) vd[j] = (uint16_t)e[j];
+    }
+}
+
 __device__ __forceinline__ void sk_scatter_item(const sk_geom& g, const void* k, const void* v, const sk_scatter& it,
                                                 const int head, int32_t* tables_rw, unsigned char* kv_rw, unsigned char* eph_rw)
 {
-    __shared__ uint16_t vt[16][128 + 2];
-    const int tid = threadIdx.x;
-    const int d = g.d, elem = g.elem;
-    const int rowbytes = d * elem;
-    unsigned char* dst = (it.to_eph ? eph_rw : kv_rw) + it.dst_off +
-                         (int64_t)head * (it.to_eph ? g.eph_head_stride : g.head_stride);
-    const int v_off = it.to_eph ? g.eph_v_off : g.v_off;
-    if (it.tbl_index >= 0 && head == 0 && tid == 0) tables_rw[it.tbl_index] = it.block_id;
-
-    const int cpr = rowbytes >> 4;                 // 16-byte chunks per row
-    const int total = it.count * cpr;
-    for (int cidx = tid; cidx < total; cidx += 256) {
-        const int row = cidx / cpr, cc = cidx % cpr;
-        const size_t src = ((size_t)(it.src_tok0 + row) * g.Hkv + head) * rowbytes + cc * 16;
-        uint4 x = *(const uint4*)((const unsigned char*)k + src);
-        *(uint4*)(dst + (size_t)(it.dst_slot0 + row) * rowbytes + cc * 16) = x;
-        if (elem == 4) {
-            uint4 y = *(const uint4*)((const unsigned char*)v + src);
-            *(uint4*)(dst + v_off + (size_t)(it.dst_slot0 + row) * rowbytes + cc * 16) = y;
-        }
+    __shared__ __attribute__((aligned(16))) uint16_t vt[16 * (128 + 8)];
+    if (g.elem == 2) {
+        unsigned char* base = it.to_eph ? eph_rw : kv_rw;
+        if (g.d == 128) sk_commit_group<128>(g, k, v, it, head, tables_rw, base, vt);
+        else sk_commit_group<64>(g, k, v, it, head, tables_rw, base, vt);
+        return;
     }
-    if (elem == 2) {
-        for (int idx = tid; idx < it.count * d; idx += 256) {
-            const int row = idx / d, t = idx % d;
-            vt[row][t] = ((const uint16_t*)v)[((size_t)(it.src_tok0 + row) * g.Hkv + head) * d + t];
-        }
-        __syncthreads();
-        // Slots of the 16-token group behind the last committed token are zero-filled, so that a
-        // key the attention kernel masks out never multiplies 0 by leftover bits.
-        const int first = it.dst_slot0 & 15;            // position inside the 16-token group
-        uint16_t* vd = (uint16_t*)(dst + v_off) + (size_t)(it.dst_slot0 >> 4) * d * 16;     // the group's [dim][16 tokens]
-        if (first == 0) {
-            // from the start of the group: 2 lanes per dimension, 8 tokens (16 bytes) each
-            for (int idx = tid; idx < 2 * d; idx += 256) {
-                const int t = idx >> 1, half = idx & 1;
-                uint32_t wv[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int s0 = half * 8 + 2 * j;
-                    const uint32_t lo = s0 < it.count ? vt[s0][t] : 0u;
-                    const uint32_t hi = s0 + 1 < it.count ? vt[s0 + 1][t] : 0u;
-                    wv[j] = lo | (hi << 16);
-                }
-                *(uint4*)(vd + (size_t)t * 16 + half * 8) = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-            }
-        } else {
-            const int span = 16 - first;                 // slots first..15: tokens, then zeros
-            for (int idx = tid; idx < span * d; idx += 256) {
-                const int t = idx / span, jj = idx % span;
-                vd[(size_t)t * 16 + first + jj] = jj < it.count ? vt[jj][t] : (uint16_t)0;
-            }
-        }
+    // f32: rows as they are
+    unsigned char* dst = (it.to_eph ? eph_rw : kv_rw) + it.dst_off + (int64_t)head * (it.to_eph ? g.eph_head_stride : g.head_stride);
+    const int v_off = it.to_eph ? g.eph_v_off : g.v_off, tid = threadIdx.x;
+    if (it.tbl_index >= 0 && head == 0 && tid == 0) tables_rw[it.tbl_index] = it.block_id;
+    const int log2_cpr = g.d == 128 ? 5 : 4;                // 16-byte chunks per row
+    for (int c = tid; c < it.count << log2_cpr; c += 256) {
+        const int row = c >> log2_cpr, cc = c & ((1 << log2_cpr) - 1);
+        const size_t src = (((size_t)(it.src_tok0 + row) * g.Hkv + head) << (log2_cpr + 4)) + cc * 16;
+        const size_t to = ((size_t)(it.dst_slot0 + row) << (log2_cpr + 4)) + cc * 16;
+        const uint4 x = *(const uint4*)((const unsigned char*)k + src), y = *(const uint4*)((const unsigned char*)v + src);
+        *(uint4*)(dst + to) = x;
+        *(uint4*)(dst + v_off + to) = y;
     }
 }
 
 // Items read from a list in the workspace (batched steps) ...
-__global__ __launch_bounds__(256) void sk_scatter_kernel(const sk_geom g, const void* k, const void* v,
+__global__ __launch_bounds__(256) void sk_scatter_kernel(const sk_geom g, const sk_div by_heads, const void* k, const void* v,
                                                          const sk_scatter* items, int32_t* tables_rw,
                                                          unsigned char* kv_rw, unsigned char* eph_rw)
 {
-    const sk_scatter it = items[blockIdx.x / g.Hkv];
-    sk_scatter_item(g, k, v, it, blockIdx.x % g.Hkv, tables_rw, kv_rw, eph_rw);
+    const int i = sk_divide(blockIdx.x, by_heads);
+    sk_scatter_item(g, k, v, items[i], blockIdx.x - i * g.Hkv, tables_rw, kv_rw, eph_rw);
 }
 // ... or carried in the kernel arguments (single-session calls: no host-to-device copy in front)
-__global__ __launch_bounds__(256) void sk_scatter_kernel_args(const sk_geom g, const void* k, const void* v,
+__global__ __launch_bounds__(256) void sk_scatter_kernel_args(const sk_geom g, const sk_div by_heads, const void* k, const void* v,
                                                               const sk_scatter_list items, int32_t* tables_rw,
                                                               unsigned char* kv_rw, unsigned char* eph_rw)
 {
-    sk_scatter_item(g, k, v, items.item[blockIdx.x / g.Hkv], blockIdx.x % g.Hkv, tables_rw, kv_rw, eph_rw);
+    const int i = sk_divide(blockIdx.x, by_heads);
+    sk_scatter_item(g, k, v, items.item[i], blockIdx.x - i * g.Hkv, tables_rw, kv_rw, eph_rw);
 }
 
 
@@ -1351,7 +1724,7 @@ int sk_launch_scatter(const sk_geom& g, const void* k, const void* v, const sk_s
 {
     if (n_items <= 0) return 0;
     hipLaunchKernelGGL(sk_scatter_kernel, dim3(n_items * g.Hkv), dim3(256), 0, (hipStream_t)stream,
-                       g, k, v, items, tables_rw, kv_rw, eph_rw);
+                       g, sk_make_div((uint32_t)g.Hkv), k, v, items, tables_rw, kv_rw, eph_rw);
     return (int)hipGetLastError();
 }
 
@@ -1361,7 +1734,7 @@ int sk_launch_scatter_args(const sk_geom& g, const void* k, const void* v, const
 {
     if (n_items <= 0) return 0;
     hipLaunchKernelGGL(sk_scatter_kernel_args, dim3(n_items * g.Hkv), dim3(256), 0, (hipStream_t)stream,
-                       g, k, v, items, tables_rw, kv_rw, eph_rw);
+                       g, sk_make_div((uint32_t)g.Hkv), k, v, items, tables_rw, kv_rw, eph_rw);
     return (int)hipGetLastError();
 }
 
@@ -1398,6 +1771,24 @@ int sk_launch_attention(const sk_launch& L, int variant, int32_t n_workgroups, v
         if (L.g.elem == 2) SK_LAUNCH(sk_attn_simple<true>, dim3(n_workgroups), dim3(256));
         else SK_LAUNCH(sk_attn_simple<false>, dim3(n_workgroups), dim3(256));
     }
+    return (int)hipGetLastError();
+}
+
+int sk_launch_attention_small(const sk_launch& L, const sk_commit& C, int32_t n_workgroups, void* stream, void* ev_start, void* ev_stop)
+{
+    if (n_workgroups <= 0) return 0;
+    hipStream_t st = (hipStream_t)stream;
+#define SK_LAUNCH_SMALL(kernel)                                                                                     \
+    do {                                                                                                            \
+        if (ev_start) hipExtLaunchKernelGGL(kernel, dim3(n_workgroups), dim3(256), 0, st, (hipEvent_t)ev_start, (hipEvent_t)ev_stop, 0, L, C); \
+        else hipLaunchKernelGGL(kernel, dim3(n_workgroups), dim3(256), 0, st, L, C);                                \
+    } while (0)
+    if (L.g.d == 128) {
+        SK_LAUNCH_SMALL(sk_attn_bf16_small<128>);
+    } else if (L.g.d == 64) {
+        SK_LAUNCH_SMALL(sk_attn_bf16_small<64>);
+    } else return (int)hipErrorInvalidValue;
+#undef SK_LAUNCH_SMALL
     return (int)hipGetLastError();
 }
 

@@ -137,7 +137,7 @@ struct sk_pool {
     // Tuning switches, read from the environment once when the pool is created (see sk_pool_create).
     int target_wgs = kDefaultTargetWgs;
     bool target_wgs_set = false;
-    bool force_simple = false, no_256 = false, no_pack = false, no_interleave = false, no_stream_loads = false;
+    bool force_simple = false, no_small = false, distrust = false, no_256 = false, no_pack = false, no_interleave = false, no_stream_loads = false;
     bool p128 = true;                    // SK_NO_P128=1: never the eight-wave 128-row instance
     int64_t p128_min_tokens = 30720;     // SK_P128_MIN_TOKENS: cached tokens from which it is taken (break-even measured near 32K)
     int64_t stream_min_tokens = 65536;   // SK_STREAM_MIN_TOKENS: cached tokens from which the 128-row instances load non-temporal
@@ -248,14 +248,21 @@ struct Variant { int id; int rows_per_slot; int tok_per_tile; };
 
 // `allow_256`: the caller can launch one workgroup per CU (single-session calls), which the
 // 256-row tile with its 128 KiB key ring needs.
-bool pick_variant(const sk_pool* p, int64_t n_tok, Variant& v, bool allow_256 = false)
+// `cached` >= 0: a single-session call over so many cached tokens, which may take the kernel for at most 32 rows.  Up to
+// 128 MiB of cached K/V: from there on the ring kernel's stream is the better one (us per query, ring and combine
+// kernel -> this one, at 32 query heads on 8 KV heads of 128 dims: one query token at 1,024 cached 12.5 -> 7.6, 2,600
+// 13.8 -> 8.1, 9,001 17.6 -> 12.9, 20,000 24.4 -> 19.5, 32,768 31.7 -> 31.6, 131,072 90.2 -> 96.8; eight at 2,600
+// 14.4 -> 12.0, 9,001 18.1 -> 14.9, 32,768 32.3 -> 32.9).
+constexpr int64_t kSmallMaxBytes = int64_t(128) << 20;
+bool pick_variant(const sk_pool* p, int64_t n_tok, Variant& v, bool allow_256 = false, int64_t cached = -1)
 {
     const int G = p->L.G;
     // any group size up to 128 (multi-query models): a tile holds floor(rows / G) tokens, at least one;
     // head_dim 64 has no 256-row instance
     const bool mfma_ok = p->d.dtype == SK_BF16 && (p->d.head_dim == 128 || p->d.head_dim == 64) && G <= 128;
     if (mfma_ok && !p->force_simple) {
-        if (allow_256 && p->d.head_dim == 128 && n_tok * G > 128) { v.id = SK_KV_MFMA256; v.rows_per_slot = 256; v.tok_per_tile = 256 / G; }
+        if (cached >= 0 && !p->no_small && n_tok * G <= 32 && cached * p->d.n_kv_heads * p->d.head_dim * 4 <= kSmallMaxBytes) { v.id = SK_KV_SMALL; v.rows_per_slot = 32; v.tok_per_tile = 32 / G; }
+        else if (allow_256 && p->d.head_dim == 128 && n_tok * G > 128) { v.id = SK_KV_MFMA256; v.rows_per_slot = 256; v.tok_per_tile = 256 / G; }
         else if (n_tok * G > 64 || G > 64) { v.id = SK_KV_MFMA128; v.rows_per_slot = 128; v.tok_per_tile = 128 / G; }
         else { v.id = SK_KV_MFMA64; v.rows_per_slot = 64; v.tok_per_tile = 64 / G; }
         return true;
@@ -287,13 +294,52 @@ struct RegPlan {
     sk_launch L;           // everything but the pointers
     int32_t wgs = 0, base_wgs = 0, parts = 1;
     int64_t kv_len = 0;
+    const void *own_k = nullptr, *own_v = nullptr;     // SMALL: the call's own K/V
+    sk_commit commit;                                  // SMALL: what an append commits in the same launch
+    int32_t commit_items = 0;
+    bool enqueued = false;                             // set by launch_regular once the attention kernel is on the stream
 };
+
+// The kernel for at most 32 rows per KV head: cached tokens in parts of whole 32-key tiles, four waves to a
+// part; own_cnt tokens of the call itself (uncommitted, or being appended) behind them.
+int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits_req, RegPlan& R)
+{
+    sk_launch& L = R.L;
+    const int64_t Hkv = p->d.n_kv_heads, cap = p->L.part_slots * kPartSlotRows / (Hkv * R.v.rows_per_slot);
+    int64_t S = n_splits_req > 0 ? n_splits_req : std::max<int64_t>(1, (p->target_wgs_set ? p->target_wgs : p->n_cus) / Hkv);
+    int64_t chunk = kv_len > 0 ? (kv_len + S - 1) / S : 64;
+    if (n_splits_req <= 0) chunk = std::max<int64_t>((chunk + 127) / 128 * 128, 128);      // a tile for every wave
+    chunk = (chunk + 63) / 64 * 64;
+    int64_t parts;
+    for (;; chunk *= 2) {
+        S = (kv_len + chunk - 1) / chunk;
+        const int64_t last = kv_len - (S - 1) * chunk;          // keys of the last part
+        // the own tokens are a tile of the last part if a wave is free there, else a part of their own
+        parts = std::max<int64_t>(1, S + ((own_cnt > 0 && S > 0 && (last + 31) / 32 > 3) ? 1 : 0));
+        if (S == 1 && parts == 2 && n_splits_req == 1) parts = 1;
+        if (parts <= 1 || parts <= cap) break;
+    }
+    L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts;
+    L.own_cnt = own_cnt;
+    // The last workgroup to finish merges the parts of a KV head (they lie a multiple of 8 workgroups apart, hence on
+    // one XCD) if they are few enough for one workgroup to read.
+    // Measured (parts x rows, us per query, merged by the last workgroup against the combine kernel): 21 x 4 rows 8.1
+    // against 10.8, 21 x 16 10.1 against 11.8, 20 x 20 12.8 against 12.5, 21 x 32 16.6 against 12.3.  It reads eight parts
+    // of 2,048 / head_dim output rows in one round.
+    const int64_t rounds = (int64_t(L.n_tok) * p->L.G * p->d.head_dim + 1023) / 1024 * ((parts + 7) / 8);
+    L.fuse = (parts > 1 && parts <= p->d.head_dim && rounds <= 8) ? 1 : 0;
+    L.head_pad = L.fuse ? (int32_t)((Hkv + 7) / 8 * 8) : (int32_t)Hkv;
+    L.by_pad = sk_make_div((uint32_t)L.head_pad);
+    L.distrust = p->distrust ? 1 : 0;
+    R.base_wgs = (int32_t)Hkv; R.parts = (int32_t)parts; R.wgs = int32_t(L.head_pad * parts); R.kv_len = kv_len;
+    return SK_OK;
+}
 
 int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int64_t kv_len, int32_t eph_cnt, int32_t eph_pos0,
                  int64_t hole_lo, int64_t hole_hi, int32_t n_splits_req, RegPlan& R)
 {
     Variant& v = R.v;
-    if (!pick_variant(p, n_tok, v, !p->no_256)) return SK_E_SHAPE;
+    if (!pick_variant(p, n_tok, v, !p->no_256, kv_len)) return SK_E_SHAPE;
     sk_launch& L = R.L;
     memset(&L, 0, sizeof L);
     L.rows_per_slot = v.rows_per_slot;
@@ -304,6 +350,9 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     L.n_tiles = int32_t((n_tok + v.tok_per_tile - 1) / v.tok_per_tile);
     L.pos0 = pos0;
     L.kv_len = (int32_t)kv_len;
+    L.hole_lo = (int32_t)hole_lo; L.hole_hi = (int32_t)hole_hi;
+    L.by_heads = sk_make_div((uint32_t)p->d.n_kv_heads);
+    if (v.id == SK_KV_SMALL) return plan_small(p, kv_len, eph_cnt, n_splits_req, R);
     const int64_t base_wgs = int64_t(L.n_tiles) * p->d.n_kv_heads;
     const int64_t slots_rows = p->L.part_slots * kPartSlotRows;
     const int has_eph = eph_cnt > 0 ? 1 : 0;
@@ -334,8 +383,8 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     if (base_wgs * parts > (int64_t(1) << 30)) return SK_E_WORKSPACE;
     L.chunk = (int32_t)chunk;
     L.n_splits = (int32_t)parts;
+    L.by_tiles = sk_make_div((uint32_t)L.n_tiles); L.by_chunk = sk_make_div((uint32_t)chunk);
     L.eph_blk[0] = 0; L.eph_cnt[0] = eph_cnt; L.eph_pos0[0] = eph_pos0;
-    L.hole_lo = (int32_t)hole_lo; L.hole_hi = (int32_t)hole_hi;
     // Small queries (at most 64 rows per KV head; every cached token visible to every row): the splits
     // interleave their 64-key pieces.  Measured 3-5 % faster there (16 tokens at 128K: 99.5 -> 96 us),
     // 2-3 % slower for the 128-row instance, which keeps contiguous chunks.  Larger blocks gain more
@@ -382,14 +431,21 @@ int launch_regular(sk_pool* p, RegPlan& R, const void* q, void* out, int out_dty
     {   // the plan holds everything but the pointers
         sk_launch& S = R.L;
         S.g = L.g; S.q = L.q; S.out = L.out; S.lse = L.lse; S.part_ml = L.part_ml; S.part_o = L.part_o; S.sync = L.sync;
-        S.out_dtype = L.out_dtype;
+        S.out_dtype = L.out_dtype; S.own_k = R.own_k; S.own_v = R.own_v;
     }
     const int32_t pc = prof_call(p);
     void *e0, *e1;
     prof_pair(p, pc, 0, &e0, &e1);
-    int e = sk_launch_attention(R.L, R.v.id, R.wgs, st, e0, e1);
+    int e;
+    if (R.v.id == SK_KV_SMALL) {
+        R.commit.first_wg = R.commit_items > 0 ? R.wgs : INT32_MAX;
+        R.commit.tables_rw = (int32_t*)((unsigned char*)p->d.workspace + p->L.off_tables);
+        R.commit.kv_rw = (unsigned char*)p->d.kv_mem;
+        e = sk_launch_attention_small(R.L, R.commit, R.wgs + R.commit_items * p->d.n_kv_heads, st, e0, e1);
+    } else e = sk_launch_attention(R.L, R.v.id, R.wgs, st, e0, e1);
     if (e) { g_last_hip = e; return SK_E_HIP; }
     p->stats.launches++;
+    R.enqueued = true;
     if (R.parts > 1 && !R.L.fuse) {
         // the attention kernel is enqueued and will write its partials; a failure here leaves out/lse unwritten
         prof_pair(p, pc, 1, &e0, &e1);
@@ -910,11 +966,14 @@ int sk_pool_create(const sk_pool_desc* desc, sk_pool** out)
     g.B = desc->block_tokens; g.log2B = ilog2_exact(desc->block_tokens);
     g.Hq = desc->n_q_heads; g.Hkv = desc->n_kv_heads; g.G = L.G; g.log2G = ilog2_exact(L.G);
     g.d = desc->head_dim; g.elem = L.elem;
+    g.g_magic = (65536u + (uint32_t)L.G - 1u) / (uint32_t)L.G;
     g.scale_log2e = scale * 1.4426950408889634f;
     if (const char* t = getenv("SK_TARGET_WGS")) { int x = atoi(t); if (x > 0) { p->target_wgs = x; p->target_wgs_set = true; } }
     auto env_on = [](const char* name) { const char* x = getenv(name); return x && x[0] == '1'; };
     p->force_simple = env_on("SK_FORCE_SIMPLE");
     p->no_256 = env_on("SK_NO_256");
+    p->no_small = env_on("SK_NO_SMALL");
+    p->distrust = env_on("SK_SMALL_DISTRUST");
     p->no_pack = env_on("SK_NO_PACK");
     p->no_interleave = env_on("SK_NO_INTERLEAVE");
     p->no_stream_loads = env_on("SK_NO_STREAM_LOADS");
@@ -1047,9 +1106,12 @@ int sk_session_append(sk_pool* p, int32_t id, const void* q, const void* k, cons
     const bool attend = p->device ? q != nullptr : true;
     RegPlan plan;
     if (attend) {
-        int rc = plan_regular(p, id, L, (int32_t)n, n + L, 0, 0, s->frozen, s->win, 0, plan);
+        Variant v;
+        const bool small = pick_variant(p, L, v, false, n) && v.id == SK_KV_SMALL;      // attends to the chunk where it lies
+        int rc = plan_regular(p, id, L, (int32_t)n, small ? n : n + L, small ? L : 0, 0, s->frozen, s->win, 0, plan);
         if (rc) return rc;
     }
+    const bool one_launch = attend && plan.v.id == SK_KV_SMALL;      // the attention launch commits too
     ScatterSlot ss;
     { int rc = scatter_reserve(p, scatter_groups(n, L), ss); if (rc) return rc; }
     // from here on only a failing HIP call can stop the call; what it changed is taken back
@@ -1058,11 +1120,17 @@ int sk_session_append(sk_pool* p, int32_t id, const void* q, const void* k, cons
     { int rc = grow_session(p, s, L, u, &first_new, st); if (rc) return rc; }
     std::vector<sk_scatter> items;
     build_scatter(p, s, id, n, 0, L, first_new, false, 0, items);
-    int rc = scatter_launch(p, ss, items, k, v, st);
+    int rc;
+    if (one_launch) {
+        plan.own_k = k; plan.own_v = v;
+        plan.commit_items = (int32_t)items.size();
+        memcpy(plan.commit.item, items.data(), items.size() * sizeof(sk_scatter));
+        rc = inject(p, SK_SITE_SCATTER) ? SK_E_HIP : SK_OK;
+    } else rc = scatter_launch(p, ss, items, k, v, st);
     if (rc) { rollback(p, u, false); return rc; }
     if (attend) {
         rc = launch_regular(p, plan, q, out, out_dtype, lse, st);
-        if (rc) { rollback(p, u, true); return rc; }
+        if (rc) { rollback(p, u, !one_launch || plan.enqueued); return rc; }
     }
     p->stats.tokens_appended += L;
     return SK_OK;
@@ -1090,7 +1158,8 @@ int sk_session_query(sk_pool* p, int32_t id, const void* q, const void* k, const
     if (k) rc = plan_regular(p, id, nq, (int32_t)s->len, s->len, nq, (int32_t)s->len, s->frozen, s->win, n_splits, plan);
     else rc = plan_regular(p, id, nq, SK_NO_CAUSAL, s->len, 0, 0, s->frozen, s->win, n_splits, plan);
     if (rc) return rc;
-    if (k) {
+    if (k && plan.v.id == SK_KV_SMALL) { plan.own_k = k; plan.own_v = v; }      // read where they lie
+    else if (k) {
         ScatterSlot ss;
         rc = scatter_reserve(p, scatter_groups(0, nq), ss);
         if (rc) return rc;

@@ -200,6 +200,44 @@ def test_large_logits_and_needle():
         assert torch.allclose(got, v[pos, 2].float(), atol=1e-2), "needle at %d not retrieved" % pos
 
 
+@pytest.mark.parametrize("hq,hkv,d,env", [(32, 8, 128, None), (32, 8, 64, None), (28, 4, 128, None), (8, 8, 128, None),
+                                          (32, 1, 128, None), (14, 2, 64, None), (32, 8, 128, {"SK_SMALL_DISTRUST": "1"}),
+                                          (28, 4, 128, {"SK_SMALL_DISTRUST": "1"})])
+def test_calls_of_at_most_32_rows(hq, hkv, d, env):
+    """The kernel for at most 32 query rows per KV head: empty caches, cached lengths around its tiles, its
+    parts and its workgroups' shares, the call's own tokens in a part of their own or in the last one, appends
+    whose commit runs in the same launch (starting inside a 16-token group and across two), the merge by the
+    last workgroup, the combine kernel behind it, and the recomputation it falls back to."""
+    shape = synth.Shape("bf16", hq, hkv, d)
+    G = hq // hkv
+    gen = synth.generator(2, stream=600 + hq + d)
+    lengths = [0, 1, 15, 31, 33, 96, 97, 128, 129, 500, 1100] if env is None else [0, 97, 500]
+    for n in lengths:
+        pr = Pair(shape, n_blocks=n // 16 + 12, max_sessions=1, kv_fill=0xFF, env=env)
+        sid = pr.create()
+        if n:
+            q, k, v = synth.draw_qkv(gen, n, shape)
+            pr.pool.sk_session_append(sid, None, dev(k), dev(v))
+            pr.oracles[sid].K, pr.oracles[sid].V = synth.to_raw(k), synth.to_raw(v)
+        for nq in sorted({1, max(1, 16 // G), 32 // G}):
+            q, k, v = synth.draw_qkv(gen, nq, shape)
+            for S in (0, 1, 3):
+                if n:
+                    pr.query(sid, q, n_splits=S, name="query A n=%d nq=%d S=%d" % (n, nq, S))
+                    assert pr.pool.sk_pool_last_launch()["kernel_variant"] == 5
+                pr.query(sid, q, k, v, n_splits=S, name="query B n=%d nq=%d S=%d" % (n, nq, S))
+            pr.query(sid, q, k, v, name="bf16 results", out_dtype="bf16")
+            pr.append(sid, q, k, v, name="append n=%d L=%d" % (n, nq))
+            assert pr.pool.sk_pool_last_launch()["kernel_variant"] == 5
+            pr.check_cache(sid)
+        if n >= 97:
+            pr.freeze(sid, 20)
+            pr.evict(sid, 45)
+            q, k, v = synth.draw_qkv(gen, 32 // G, shape)
+            pr.query(sid, q, k, v, name="query B behind a hole")
+            pr.append(sid, q, k, v, name="append behind a hole")
+
+
 @pytest.mark.parametrize("hd", [128, 64])
 @pytest.mark.parametrize("env", [None, LONG_CACHE_PATHS])
 def test_scores_that_grow_along_the_cache(hd, env):
