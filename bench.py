@@ -495,9 +495,9 @@ def head_dim_64(sk, n=32768, L=256, reps=100):
 
 
 def fp32_small(sk, reps=200):
-    """Workload 1's shape (fp32, 4/4 heads, d=64) through the fp32-FMA kernel: a 64-token append at 960
+    """Workload 1's shape (fp32, 4/4 heads, d=64) through the fp32 kernel: a 64-token append at 960
     cached tokens and a 16-token query at 1,024.  This path is the precision gate of the build, not a
-    performance path; timed so that its cost is on record.  Bound: fp32 vector ALU."""
+    performance path; timed so that its cost is on record.  Bound: launch and memory latency."""
     shape = synth.CFG1
     gen = synth.generator(1, stream=60)
     pool = sk.Pool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, 16, 80, max_sessions=1)
@@ -516,7 +516,7 @@ def fp32_small(sk, reps=200):
     fq = 4.0 * 64 * 4 * 16 * 1024
     pool.close()
     return {"append_64_at_960_us": a_us, "query_16_at_1024_us": q_us, "timing": "stream (commit + attention + combine per call)",
-            "roofline": {"kernel": "sk_attn_simple<false>", "bound": "alu", "achieved": fa / (a_us * 1e-6) / 1e12,
+            "roofline": {"kernel": "sk_attn_f32<64>", "bound": "alu", "achieved": fa / (a_us * 1e-6) / 1e12,
                          "peak": FP32_VALU_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": fa / (a_us * 1e-6) / 1e12 / FP32_VALU_PEAK_TFLOPS,
                          "traffic": None, "algorithmic_flops": fa,
                          "note": "6.5e7 flop per call: launch-bound at this size, the fraction says nothing about the kernel"},

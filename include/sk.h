@@ -84,7 +84,7 @@ typedef struct sk_pool_desc {
     int32_t n_kv_heads;
     int32_t head_dim;         /* 64 or 128.  bf16 pools with at most 128 query heads per KV head
                                  (any such group size) run on the matrix pipe; fp32 pools take the
-                                 fp32-FMA kernel (at most 16 per KV head) */
+                                 fp32 kernel (at most 16 per KV head) */
     int32_t block_tokens;     /* power of two, 16..1024 */
     int32_t max_sessions;     /* >= 1 */
     int64_t n_blocks;         /* blocks in the pool */
@@ -112,10 +112,10 @@ size_t sk_pool_workspace_bytes(const sk_pool_desc* desc);
  * Tuning switches, read from the environment here and fixed for the life of the pool (none
  * changes a result beyond the rounding order of the split merge; they exist for sweeps):
  *   SK_TARGET_WGS=n    workgroups a single-session call is cut into (default: 256 or 512 by shape)
- *   SK_FORCE_SIMPLE=1  always the fp32-FMA attention kernel
+ *   SK_FORCE_SIMPLE=1  bf16 pools: always the fp32-FMA attention kernel
  *   SK_NO_SMALL=1      never the kernel for calls of at most 32 query rows per KV head
- *   SK_SMALL_DISTRUST=1  in that kernel the last workgroup of a KV head computes the head's rows alone, as if
- *                      the parts had not run on one XCD (tests)
+ *   SK_SMALL_DISTRUST=1  in that kernel and the fp32 one the last workgroup of a row tile and KV head computes
+ *                      its rows alone, as if the parts had not run on one XCD (tests)
  *   SK_NO_256=1        never the 256-row eight-wave instance of the bf16 kernel
  *   SK_NO_PACK=1       a question batch gives every question a row tile of its own
  *   SK_NO_INTERLEAVE=1 the splits of a query take contiguous chunks of the cache instead of

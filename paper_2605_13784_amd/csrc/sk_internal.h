@@ -102,6 +102,7 @@ static inline sk_div sk_make_div(uint32_t d)
     return sk_div{(uint32_t)m, l - 1};
 }
 
+enum { SK_OWN_NONE = 0, SK_OWN_SMALL = 1, SK_OWN_F32 = 2 };
 enum { SK_MODE_REGULAR = 0, SK_MODE_LIST = 1 };
 // attention kernel variants: fp32-FMA kernel; bf16 MFMA kernel with 128-, 64- and 256-row tiles; the
 // 128-row tile again with eight waves (two key phases per row group, one workgroup per CU)
@@ -143,19 +144,20 @@ struct sk_launch {
     int32_t wait_polls;
     int32_t merge_fences;   // 1: full device-scope fences around the arrival (slow: an L2 walk each); 0: see the kernel
     sk_div by_heads, by_tiles, by_chunk;      // Hkv, n_tiles, chunk (regular mode)
-    // calls of at most 32 rows per KV head (sk_attn_bf16_small): the call's own tokens where the caller has them
+    // sk_attn_bf16_small and sk_attn_f32, single-session calls: the call's own tokens where the caller has them
     // ([own_cnt][Hkv][d], the last keys of the last part), and the launch geometry
     const void* own_k;
     const void* own_v;
     int32_t own_cnt;
-    int32_t head_pad;       // workgroups from one part of a head to the next (KV heads, padded to a multiple of 8)
+    int32_t own_mode;       // SK_OWN_*: how the launch is cut (bf16: one tile behind the last part's cached keys; f32: keys behind the cached ones)
+    int32_t head_pad;       // workgroups from one part to the next of its unit (row tile x KV head): the units, padded to a multiple of 8 if merged
     sk_div by_pad;
     int32_t distrust;       // 1: treat the parts as run on several XCDs (the last one computes the tile alone; tests)
     int32_t kv_once;        // 1: every key is read by exactly one workgroup of the launch (loaded non-temporal)
 };
 
 // The commit of a small append, done by workgroups first_wg, first_wg + 1, .. of its attention launch.
-#define SK_COMMIT_ITEMS 3             // 16-token groups that 32 tokens can touch
+#define SK_COMMIT_ITEMS 9             // 16-token groups: what 128 tokens can touch
 struct sk_commit {
     int32_t first_wg;       // INT32_MAX: nothing to commit
     int32_t* tables_rw;

@@ -65,6 +65,13 @@ __device__ __forceinline__ void sk_touch_arguments()
 // stay in that XCD's L2), then in row tile, then in split.
 __device__ __forceinline__ int sk_tile_parts(const sk_launch& P, int tok0, int ntok, int* kv_vis_out)
 {
+    if (P.own_mode == SK_OWN_F32) {               // cached keys padded to whole 16-key tiles, then the call's own tokens
+        int own = P.own_cnt;
+        if (P.pos0 < SK_NO_CAUSAL) own = tok0 + ntok < own ? tok0 + ntok : own;
+        *kv_vis_out = ((P.kv_len + 15) & ~15) + own;
+        const int np = sk_divide(*kv_vis_out + P.chunk - 1, P.by_chunk);
+        return np < 1 ? 1 : np;
+    }
     int kv_vis = P.kv_len;
     if (P.pos0 < SK_NO_CAUSAL) {
         int last = P.pos0 + tok0 + ntok;       // last position + 1
@@ -1120,6 +1127,123 @@ template <int D>
 __device__ __forceinline__ void sk_commit_group(const sk_geom& g, const void* k, const void* v, const sk_scatter& it, const int head,
                                                 int32_t* tables_rw, unsigned char* kv_rw, uint16_t* vt);
 
+// What a workgroup of the kernels below does once its four waves have scaled their accumulators to the common row
+// maxima and laid them side by side in LDS (tr[wave][row][16-byte chunk ^ row], stat[wave][row] = (m, l, lx, -)): adds
+// the four up, writes the rows out (`whole`) or to partial slot `slot`, and, with P.fuse, arrives at `unit` and merges
+// the unit's parts (slots slot0, slot0 + Hkv, ..) if it is the last one there.  False: the parts did not run on one
+// XCD and this workgroup has to compute the unit alone.  `orow_of`: row of the tile -> row of out / lse.
+template <int D, int ROWS, class OutRow>
+__device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D / 4], float4 (*stat)[ROWS], int* decision, const int tid,
+                                        const int nrows, const bool whole, const int slot, const int slot0, const int n_parts, const int unit,
+                                        const OutRow orow_of)
+{
+    constexpr int CPR = D / 4, SUBS = 256 / ROWS;
+    auto put_row = [&](const int row, const int c4, const float4 x, const float inv, const float lse) __attribute__((always_inline)) {
+        const size_t orow = orow_of(row);
+        if (P.out_dtype == 0) *(float4*)((float*)P.out + orow * D + c4 * 4) = make_float4(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
+        else {
+            const uint32_t lo = f32_to_bf16_bits(x.x * inv) | ((uint32_t)f32_to_bf16_bits(x.y * inv) << 16);
+            const uint32_t hi = f32_to_bf16_bits(x.z * inv) | ((uint32_t)f32_to_bf16_bits(x.w * inv) << 16);
+            *(uint2*)((uint16_t*)P.out + orow * D + c4 * 4) = make_uint2(lo, hi);
+        }
+        if (P.lse && c4 == 0) P.lse[orow] = lse;
+    };
+    __syncthreads();
+    const size_t prow = (size_t)slot * P.rows_per_slot;
+    for (int i = tid; i < nrows * CPR; i += 256) {
+        const int row = i / CPR, c4 = i % CPR;
+        float4 x = tr[0][row][(c4 ^ row) & (CPR - 1)];
+        float m = stat[0][row].x, l = stat[0][row].y, lx = stat[0][row].z;
+#pragma unroll
+        for (int w = 1; w < 4; ++w) {
+            const float4 y = tr[w][row][(c4 ^ row) & (CPR - 1)];
+            x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+            m = fmaxf(m, stat[w][row].x); l += stat[w][row].y; lx += stat[w][row].z;
+        }
+        if (whole) put_row(row, c4, x, 1.0f / l, (m + sk_log2(lx)) * SK_LN2);
+        else {
+            *(float4*)(P.part_o + (prow + row) * D + c4 * 4) = x;
+            if (c4 == 0) *((float4*)P.part_ml + prow + row) = make_float4(m, l, lx, 0.f);
+        }
+    }
+    if (whole || !P.fuse) return true;
+
+    // ---- arrival; the last workgroup of the unit merges ----
+    SK_WAIT_VMCNT(0);                                 // this thread's part of the partial has reached the L2
+    __syncthreads();
+    if (tid == 0) {
+        const unsigned long long x = sk_xcd_id();
+        unsigned long long* word = (unsigned long long*)P.sync + (size_t)unit * 16;      // a 128-byte line per unit: each is one XCD's
+        const unsigned long long add = 1ull | (x << 16) | ((x * x) << 36);
+        const unsigned long long got = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+        int d = 0;
+        if ((int)(got & 0xffffu) == n_parts) {
+            const unsigned long long sum = (got >> 16) & 0xfffffu, sq = got >> 36;
+            d = (!P.distrust && (unsigned long long)n_parts * sq == sum * sum) ? 1 : 2;
+            __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // ready for the next launch
+        }
+        *decision = d;
+    }
+    __syncthreads();
+    const int d = *decision;
+    if (d == 0) return true;
+    if (d == 2) return false;
+    // All statistics in one round of loads, the weights of all parts to LDS, then every thread sums its 16-byte
+    // pieces of output rows over the parts, in part order, eight loads in flight (a short loop: code that
+    // runs once per launch costs its instruction fetches, so 32 unrolled loads took 1 us longer).
+    float4* ml = &tr[0][0][0];                        // [part][ROWS]: at most D parts
+    float4* tot = &stat[0][0];                        // [ROWS]
+    const size_t pstep = (size_t)P.g.Hkv * P.rows_per_slot;
+    const unsigned row0 = (unsigned)(slot0 * P.rows_per_slot);
+    {
+        const int r = tid % ROWS;
+        for (int p = tid / ROWS; p < n_parts; p += SUBS)
+            if (r < nrows) ml[p * ROWS + r] = *((const float4*)P.part_ml + p * pstep + (row0 + (unsigned)r));
+    }
+    __syncthreads();
+    {
+        const int row = tid / SUBS, sub = tid % SUBS;
+        float M2 = SK_NEG_INF, L = 0.f, Lx = 0.f;
+        if (row < nrows) for (int p = sub; p < n_parts; p += SUBS) M2 = fmaxf(M2, ml[p * ROWS + row].x);
+#pragma unroll
+        for (int off = SUBS / 2; off >= 1; off >>= 1) M2 = fmaxf(M2, __shfl_xor(M2, off, 64));
+        if (row < nrows)
+#pragma unroll 1
+            for (int p = sub; p < n_parts; p += SUBS) {
+                const float4 t = ml[p * ROWS + row];
+                const float wgt = t.x == SK_NEG_INF ? 0.f : sk_exp2(t.x - M2);
+                ml[p * ROWS + row].x = wgt;
+                L = fmaf(t.y, wgt, L); Lx = fmaf(t.z, wgt, Lx);
+            }
+#pragma unroll
+        for (int off = SUBS / 2; off >= 1; off >>= 1) { L += __shfl_xor(L, off, 64); Lx += __shfl_xor(Lx, off, 64); }
+        if (row < nrows && sub == 0) tot[row] = make_float4(M2, L, Lx, 0.f);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int i = tid; i < nrows * CPR; i += 256) {
+        const int row = i / CPR;
+        const unsigned at = row0 * CPR + (unsigned)i;                  // in float4, from a part's first row
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+        for (int p0 = 0; p0 < n_parts; p0 += 8) {
+            float4 x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)      // (past the last part: the last one again, with weight 0, so that no load waits for a branch)
+                x[j] = *((const float4*)P.part_o + (size_t)(p0 + j < n_parts ? p0 + j : n_parts - 1) * (pstep * CPR) + at);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float wgt = p0 + j < n_parts ? ml[(p0 + j) * ROWS + row].x : 0.f;
+                acc.x = fmaf(x[j].x, wgt, acc.x); acc.y = fmaf(x[j].y, wgt, acc.y);
+                acc.z = fmaf(x[j].z, wgt, acc.z); acc.w = fmaf(x[j].w, wgt, acc.w);
+            }
+        }
+        const float4 t = tot[row];
+        put_row(row, i % CPR, acc, 1.0f / t.y, (t.x + sk_log2(t.z)) * SK_LN2);
+    }
+    return true;
+}
+
 template <int D>
 __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, const sk_commit C)
 {
@@ -1128,7 +1252,7 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
     __shared__ float4 tr[NWV][32][CPR];
     __shared__ float4 stat[NWV][32];
     __shared__ int decision;
-    sk_touch_arguments<sizeof(sk_launch) + sizeof(sk_commit)>();
+    sk_touch_arguments<sizeof(sk_launch) + offsetof(sk_commit, item)>();
     const int Hkv = P.g.Hkv;
     if (__builtin_expect((int)blockIdx.x >= C.first_wg, 0)) {                  // the commit of an append
         const int i = blockIdx.x - C.first_wg, item = sk_divide(i, P.by_heads);
@@ -1153,18 +1277,6 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
         const int tok = div_g(r < nrows ? r : 0), hq = head * G + (r < nrows ? r - tok * G : 0);
         const float c_scale = P.g.scale_log2e;
         const int tau = (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);      // key of S^T row r (bits 2 and 3 swapped)
-        auto put_row = [&](const int row, const int c4, const float4 x, const float inv, const float lse) __attribute__((always_inline)) {
-            const int t2 = div_g(row);
-            const size_t orow = (size_t)t2 * P.g.Hq + head * G + (row - t2 * G);
-            if (P.out_dtype == 0) *(float4*)((float*)P.out + orow * D + c4 * 4) = make_float4(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
-            else {
-                const uint32_t lo = f32_to_bf16_bits(x.x * inv) | ((uint32_t)f32_to_bf16_bits(x.y * inv) << 16);
-                const uint32_t hi = f32_to_bf16_bits(x.z * inv) | ((uint32_t)f32_to_bf16_bits(x.w * inv) << 16);
-                *(uint2*)((uint16_t*)P.out + orow * D + c4 * 4) = make_uint2(lo, hi);
-            }
-            if (P.lse && c4 == 0) P.lse[orow] = lse;
-        };
-
         bf16x8 qreg[NKS];
         {
             const sk_u32x4* qp = (const sk_u32x4*)((const unsigned char*)P.q + ((size_t)tok * P.g.Hq + hq) * ROWB);
@@ -1338,110 +1450,246 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
                 }
             if (kg == 0) { stat[wave][r].y = l_tot * a; stat[wave][r].z = lx_tot * a; }
         }
-        __syncthreads();
-        const size_t prow = ((size_t)part * Hkv + head) * P.rows_per_slot;
-        for (int i = tid; i < nrows * CPR; i += 256) {
-            const int row = i / CPR, c4 = i % CPR;
-            float4 x = tr[0][row][(c4 ^ row) & (CPR - 1)];
-            float m = stat[0][row].x, l = stat[0][row].y, lx = stat[0][row].z;
-#pragma unroll
-            for (int w = 1; w < NWV; ++w) {
-                const float4 y = tr[w][row][(c4 ^ row) & (CPR - 1)];
-                x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
-                m = fmaxf(m, stat[w][row].x); l += stat[w][row].y; lx += stat[w][row].z;
-            }
-            if (whole) {
-                put_row(row, c4, x, 1.0f / l, (m + sk_log2(lx)) * SK_LN2);
-            } else {
-                *(float4*)(P.part_o + (prow + row) * D + c4 * 4) = x;
-                if (c4 == 0) *((float4*)P.part_ml + prow + row) = make_float4(m, l, lx, 0.f);
-            }
-        }
-        if (whole || !P.fuse) return;
-
-        // ---- arrival; the last workgroup of the head merges ----
-        SK_WAIT_VMCNT(0);                                 // this thread's part of the partial has reached the L2
-        __syncthreads();
-        if (tid == 0) {
-            const unsigned long long x = sk_xcd_id();
-            unsigned long long* word = (unsigned long long*)P.sync + head * 16;      // a 128-byte line per head: each is one XCD's
-            const unsigned long long add = 1ull | (x << 16) | ((x * x) << 36);
-            const unsigned long long got = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
-            int d = 0;
-            if ((int)(got & 0xffffu) == n_parts) {
-                const unsigned long long sum = (got >> 16) & 0xfffffu, sq = got >> 36;
-                d = (!P.distrust && (unsigned long long)n_parts * sq == sum * sum) ? 1 : 2;
-                __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // ready for the next launch
-            }
-            decision = d;
-        }
-        __syncthreads();
-        const int d = decision;
-        if (d == 0) return;
-        if (d == 1) {
-            // All statistics in one round of loads, the weights of all parts to LDS, then every thread sums its 16-byte
-            // pieces of output rows over the parts, in part order, eight loads in flight (a short loop: code that
-            // runs once per launch costs its instruction fetches, so 32 unrolled loads took 1 us longer).
-            float4* ml = &tr[0][0][0];                    // [part][32 rows]
-            float4* tot = &stat[0][0];                    // [32 rows]
-            const size_t pstep = (size_t)Hkv * P.rows_per_slot;
-            const unsigned row0 = (unsigned)(head * P.rows_per_slot);
-            for (int p = tid >> 5; p < n_parts; p += 8)
-                if (r < nrows) ml[p * 32 + r] = *((const float4*)P.part_ml + p * pstep + (row0 + (unsigned)r));
-            __syncthreads();
-            {
-                const int row = tid >> 3, sub = tid & 7;
-                float M2 = SK_NEG_INF, L = 0.f, Lx = 0.f;
-                if (row < nrows) for (int p = sub; p < n_parts; p += 8) M2 = fmaxf(M2, ml[p * 32 + row].x);
-#pragma unroll
-                for (int off = 4; off >= 1; off >>= 1) M2 = fmaxf(M2, __shfl_xor(M2, off, 64));
-                if (row < nrows)
-#pragma unroll 1
-                    for (int p = sub; p < n_parts; p += 8) {
-                        const float4 t = ml[p * 32 + row];
-                        const float wgt = t.x == SK_NEG_INF ? 0.f : sk_exp2(t.x - M2);
-                        ml[p * 32 + row].x = wgt;
-                        L = fmaf(t.y, wgt, L); Lx = fmaf(t.z, wgt, Lx);
-                    }
-#pragma unroll
-                for (int off = 4; off >= 1; off >>= 1) { L += __shfl_xor(L, off, 64); Lx += __shfl_xor(Lx, off, 64); }
-                if (row < nrows && sub == 0) tot[row] = make_float4(M2, L, Lx, 0.f);
-            }
-            __syncthreads();
-#pragma unroll 1
-            for (int i = tid; i < nrows * CPR; i += 256) {
-                const int row = i / CPR;
-                const unsigned at = row0 * CPR + (unsigned)i;                  // in float4, from a part's first row
-                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 1
-                for (int p0 = 0; p0 < n_parts; p0 += 8) {
-                    float4 x[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)      // (past the last part: the last one again, with weight 0, so that no load waits for a branch)
-                        x[j] = *((const float4*)P.part_o + (size_t)(p0 + j < n_parts ? p0 + j : n_parts - 1) * (pstep * CPR) + at);
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const float wgt = p0 + j < n_parts ? ml[(p0 + j) * 32 + row].x : 0.f;
-                        acc.x = fmaf(x[j].x, wgt, acc.x); acc.y = fmaf(x[j].y, wgt, acc.y);
-                        acc.z = fmaf(x[j].z, wgt, acc.z); acc.w = fmaf(x[j].w, wgt, acc.w);
-                    }
-                }
-                const float4 t = tot[row];
-                put_row(row, i % CPR, acc, 1.0f / t.y, (t.x + sk_log2(t.z)) * SK_LN2);
-            }
-            return;
-        }
+        if (sk_meet<D, 32>(P, tr, stat, &decision, tid, nrows, whole, part * Hkv + head, head, n_parts, head,
+                           [&](const int row) __attribute__((always_inline)) {
+                               const int t2 = div_g(row);
+                               return (size_t)t2 * P.g.Hq + head * G + (row - t2 * G);
+                           })) return;
         whole = true;                                     // the parts ran on several XCDs: once more, alone
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32-arithmetic attention kernel (fp32 pools, and bf16 pools whose shape the MFMA kernel does
-// not take).  Tile of up to 16 query rows x 32 keys; every product and sum is an fp32 FMA.
+// fp32 attention kernel (fp32 pools): every product on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32: fp32
+// operands, fp32 accumulation).  Tile of up to 16 query rows; four waves that take the 16-key tiles w, w + 4, ..
+// straight from memory into registers and meet in LDS at the end, as in sk_attn_bf16_small.
+//   S^T[16 keys][16 rows] = K Q^T: lane (c = lane % 16, g = lane / 16) holds K[c] and Q[c] at dims 16 j + 4 g .. + 3
+//     (any order of the contraction will do, so a load instruction reads 64 consecutive bytes of a row);
+//   the lane then owns row c and keys 4 g .. 4 g + 3, whose weights are, register by register, the B operand of
+//   O^T[16 dims][16 rows] += V^T P^T with the keys 4 g + i of step i; the A operand is V[4 g + i] at dims 4 c .. 4 c + 3
+//     (+ 64): one 16-byte load serves four of the 16-dim blocks, whose row c then is dim 4 c + block.
+// In single-session calls the call's own K/V are read where the caller has them, as further keys behind the
+// cached ones (padded to whole tiles), and a short commit runs in the same launch; in batched calls they come from
+// the staging area.  Rows past the end of a tile's keys re-read the last one (a masked key multiplies a finite value).
+// Bound: round trips and launches at the sizes in use: a 64-token append at 960 cached tokens (4 heads of 64 dims) 29.2
+// -> 8.5 us in a stream of appends, a 16-token query at 1,024 25.2 -> 7.9 (a commit or nothing, an fp32-FMA kernel of
+// 24 / 20.6 us and a combine kernel of 4.4 / 3.9 before; one launch now).
+// ---------------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(4))) float sk_acc4;
+
+// Maximum / sum over the four lanes c, c + 16, c + 32, c + 48.
+__device__ __forceinline__ sk_halves sk_row_pairs(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return sk_halves{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ float sk_max_over_groups(float x)
+{
+    { const sk_halves h = sk_row_pairs(x); x = fmaxf(h.lo, h.hi); }
+    { const sk_halves h = sk_both_halves(x); x = fmaxf(h.lo, h.hi); }
+    return x;
+}
+__device__ __forceinline__ float sk_sum_over_groups(float x)
+{
+    { const sk_halves h = sk_row_pairs(x); x = h.lo + h.hi; }
+    { const sk_halves h = sk_both_halves(x); x = h.lo + h.hi; }
+    return x;
+}
+
+__device__ __forceinline__ void sk_commit_group_f32(const sk_geom& g, const void* k, const void* v, const sk_scatter& it, const int head,
+                                                    int32_t* tables_rw, unsigned char* base);
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const sk_commit C)
+{
+    constexpr int NJ = D / 16, NH = D / 64, CPR = D / 4, ROWB = D * 4;
+    __shared__ float4 tr[4][16][CPR];
+    __shared__ float4 stat[4][16];
+    __shared__ int decision;
+    sk_touch_arguments<sizeof(sk_launch) + offsetof(sk_commit, item)>();
+    const int Hkv = P.g.Hkv, G = P.g.G;
+    if (__builtin_expect((int)blockIdx.x >= C.first_wg, 0)) {                  // the commit of an append
+        const int i = blockIdx.x - C.first_wg, item = sk_divide(i, P.by_heads);
+        sk_commit_group_f32(P.g, P.own_k, P.own_v, C.item[item], i - item * Hkv, C.tables_rw, C.kv_rw);
+        return;
+    }
+    // the row tile, and its keys: cached [k_begin, k_end), then own tokens [o_begin, o_end) (where the caller has them) or
+    // staged segments
+    const bool listed = P.mode == SK_MODE_LIST;
+    sk_work w;
+    int part = 0, unit = 0, n_parts = 1, vis = 0;
+    if (listed) w = P.work[blockIdx.x];
+    else {
+        part = sk_divide(blockIdx.x, P.by_pad); unit = blockIdx.x - part * P.head_pad;
+        if (unit >= P.n_tiles * Hkv) return;
+        const int tile = sk_divide(unit, P.by_heads);
+        w.kv_head = unit - tile * Hkv;
+        w.q_tok0 = tile * P.tok_per_tile;
+        w.n_tok = P.n_tok - w.q_tok0 < P.tok_per_tile ? P.n_tok - w.q_tok0 : P.tok_per_tile;
+        n_parts = sk_tile_parts(P, w.q_tok0, w.n_tok, &vis);
+        if (part >= n_parts) return;
+        w.tbl_off = P.tbl_off; w.pos0 = P.pos0 < SK_NO_CAUSAL ? P.pos0 + w.q_tok0 : P.pos0;
+        w.hole_lo = P.hole_lo; w.hole_hi = P.hole_hi; w.kv_step = 0; w.sub_blocks = 0;
+        w.part = n_parts == 1 ? -1 : (tile * P.n_splits + part) * Hkv + w.kv_head;
+        w.part0 = tile * P.n_splits * Hkv + w.kv_head;
+        w.eph_cnt[0] = w.eph_cnt[1] = 0; w.eph_blk[0] = w.eph_blk[1] = 0; w.eph_pos0[0] = w.eph_pos0[1] = 0;
+    }
+    bool whole = w.part < 0;
+    for (;;) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));                     // (opaque: see sk_attn_bf16_small)
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int c = lane & 15, g4 = (lane >> 4) * 4;
+        const int head = w.kv_head, nrows = w.n_tok * G;
+        const unsigned g_magic = P.g.g_magic;
+        auto div_g = [&](const int row) __attribute__((always_inline)) { return (int)(((unsigned)row * g_magic) >> 16); };
+        const int tok = div_g(c < nrows ? c : 0), hq = head * G + (c < nrows ? c - tok * G : 0);
+        const float c_scale = P.g.scale_log2e;
+        const bool causal = w.pos0 < SK_NO_CAUSAL;
+        const int p_row = causal ? w.pos0 + tok : 0x7fffffff, p_first = causal ? w.pos0 : 0x7fffffff;
+        int k_begin, k_end, o_begin = 0, o_end = 0;
+        if (listed) { k_begin = w.kv_begin; k_end = w.kv_end; }
+        else {
+            const int pad = (P.kv_len + 15) & ~15;
+            const int b = whole ? 0 : part * P.chunk, e = whole || b + P.chunk > vis ? vis : b + P.chunk;
+            k_begin = b; k_end = e < P.kv_len ? e : P.kv_len;
+            o_begin = b > pad ? b - pad : 0; o_end = e - pad;
+        }
+
+        float4 q[NJ];
+        {
+            const float4* qp = (const float4*)((const float*)P.q + ((size_t)(w.q_tok0 + tok) * P.g.Hq + hq) * D + g4);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) q[j] = qp[j * 4];
+        }
+        sk_acc4 o[NH][4];
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) o[h][b] = sk_acc4{0.f, 0.f, 0.f, 0.f};
+        float m_ref = SK_NEG_INF, l_run = 0.f;
+
+#pragma unroll 1
+        for (int s = 0; s < 4; ++s) {             // cached, own (raw), staged, staged
+            int begin, end, pos_shift = 0, hole_lo = 0, hole_n = 0;
+            sk_seg sg;
+            if (s == 1) { begin = o_begin; end = o_end; pos_shift = P.pos0; if (!causal) pos_shift = 0; }
+            else {
+                sg = sk_make_seg(P, w, s == 0 ? 0 : s - 1);
+                if (s == 0) { begin = k_begin; end = k_end; hole_lo = sg.hole_lo; hole_n = sg.hole_n; }
+                else { begin = sg.begin; end = sg.end; pos_shift = sg.pos_shift; }
+            }
+            if (end <= begin) continue;
+            const int n_tiles = (end - begin + 15) >> 4;
+            const int rstride = s == 1 ? Hkv * ROWB : ROWB;
+            auto row_base = [&](const int t, const unsigned char*& kp, const unsigned char*& vp) __attribute__((always_inline)) {
+                const int t0 = begin + t * 16;
+                if (s == 1) {
+                    const size_t off = ((size_t)t0 * Hkv + head) * ROWB;
+                    kp = (const unsigned char*)P.own_k + off; vp = (const unsigned char*)P.own_v + off;
+                } else {
+                    kp = sk_group_base(sg, t0) + (t0 & (sg.B - 1)) * ROWB;
+                    vp = kp + sg.v_off;
+                }
+            };
+            float4 kr[NJ], vr[4][NH];
+            auto load_k = [&](const int t, const unsigned char* kp) __attribute__((always_inline)) {
+                const int left = end - (begin + t * 16) - 1, row = c < left ? c : left;
+                const float4* p = (const float4*)(kp + row * rstride) + (g4 >> 2);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) kr[j] = p[j * 4];
+            };
+            auto load_v = [&](const int t, const unsigned char* vp) __attribute__((always_inline)) {
+                const int left = end - (begin + t * 16) - 1;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = g4 + i < left ? g4 + i : left;
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) vr[i][h] = *((const float4*)(vp + row * rstride) + h * 16 + c);
+                }
+            };
+            const unsigned char *kp = nullptr, *vp = nullptr;
+            if (wave < n_tiles) { row_base(wave, kp, vp); load_k(wave, kp); load_v(wave, vp); }
+#pragma unroll 1
+            for (int t = wave; t < n_tiles; t += 4) {
+                const bool more = t + 4 < n_tiles;
+                if (more) row_base(t + 4, kp, vp);
+                sk_acc4 sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j].x, q[j].x, sc, 0, 0, 0);
+                    sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j].y, q[j].y, sc, 0, 0, 0);
+                    sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j].z, q[j].z, sc, 0, 0, 0);
+                    sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j].w, q[j].w, sc, 0, 0, 0);
+                }
+                if (more) load_k(t + 4, kp);
+                const int k0 = begin + t * 16;
+                if (k0 + 16 > end || k0 + 15 + pos_shift > p_first || (k0 < hole_lo + hole_n && k0 + 16 > hole_lo)) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int key = k0 + g4 + i;
+                        const bool seen = key < end && key + pos_shift <= p_row && (unsigned)(key - hole_lo) >= (unsigned)hole_n;
+                        sc[i] = seen ? sc[i] : SK_NEG_INF;
+                    }
+                }
+                const float mx = sk_max_over_groups(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]))) * c_scale;
+                const bool raise = mx > m_ref + SK_RESCALE_SLACK;
+                if (__any(raise)) {
+                    const float alpha = raise ? sk_exp2(m_ref - mx) : 1.0f;
+                    l_run *= alpha;
+#pragma unroll
+                    for (int h = 0; h < NH; ++h)
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) o[h][b] *= alpha;
+                    m_ref = raise ? mx : m_ref;
+                }
+                const float neg_m = m_ref == SK_NEG_INF ? 0.f : -m_ref;
+                float p[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p[i] = sk_exp2(fmaf(sc[i], c_scale, neg_m));
+                l_run += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) {
+                        o[h][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[i][h].x, p[i], o[h][0], 0, 0, 0);
+                        o[h][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[i][h].y, p[i], o[h][1], 0, 0, 0);
+                        o[h][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[i][h].z, p[i], o[h][2], 0, 0, 0);
+                        o[h][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[i][h].w, p[i], o[h][3], 0, 0, 0);
+                    }
+                if (more) load_v(t + 4, vp);
+            }
+        }
+
+        const float l_tot = sk_sum_over_groups(l_run);
+        if (c < nrows && g4 == 0) stat[wave][c].x = m_ref;
+        __syncthreads();
+        float M = SK_NEG_INF;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) M = fmaxf(M, stat[v][c].x);
+        const float a = m_ref == SK_NEG_INF ? 0.f : sk_exp2(m_ref - M);
+        if (c < nrows) {
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    tr[wave][c][((h * 16 + g4 + i) ^ c) & (CPR - 1)] = make_float4(o[h][0][i] * a, o[h][1][i] * a, o[h][2][i] * a, o[h][3][i] * a);
+            if (g4 == 0) { stat[wave][c].y = l_tot * a; stat[wave][c].z = l_tot * a; }
+        }
+        if (sk_meet<D, 16>(P, tr, stat, &decision, tid, nrows, whole, w.part, w.part0, n_parts, unit,
+                           [&](const int row) __attribute__((always_inline)) {
+                               const int t2 = div_g(row);
+                               return (size_t)(w.q_tok0 + t2) * P.g.Hq + head * G + (row - t2 * G);
+                           })) return;
+        whole = true;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// fp32-arithmetic attention kernel for bf16 pools (only on request, for comparison).  Tile of up to 16 query rows x 32 keys; every product and sum is an fp32 FMA.
 // Thread (r = tid/16, c = tid%16): scores of row r for keys c and c+16; output
 // dimensions c + 16 j of row r.
 // ---------------------------------------------------------------------------------------------
-template <bool BF16>
 __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
 {
     constexpr int DMAX = 128;
@@ -1469,7 +1717,7 @@ __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
         float x = 0.f;
         if (rr < nrows) {
             size_t off = ((size_t)(w.q_tok0 + rr / G) * Hq + (w.kv_head * G + rr % G)) * d + t;
-            x = BF16 ? bf16_bits_to_f32(((const uint16_t*)P.q)[off]) : ((const float*)P.q)[off];
+            x = bf16_bits_to_f32(((const uint16_t*)P.q)[off]);
         }
         Qs[rr][t] = x;
     }
@@ -1490,13 +1738,8 @@ __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
                 if (tok < g.end) {
                     const unsigned char* bb = sk_group_base(g, tok & ~15);
                     int slot = tok & (g.B - 1);
-                    if (BF16) {
-                        kx = bf16_bits_to_f32(((const uint16_t*)bb)[(size_t)slot * d + t]);
-                        vx = bf16_bits_to_f32(((const uint16_t*)(bb + g.v_off))[((size_t)(slot >> 4) * d + t) * 16 + (slot & 15)]);
-                    } else {
-                        kx = ((const float*)bb)[(size_t)slot * d + t];
-                        vx = ((const float*)(bb + g.v_off))[(size_t)slot * d + t];
-                    }
+                    kx = bf16_bits_to_f32(((const uint16_t*)bb)[(size_t)slot * d + t]);
+                    vx = bf16_bits_to_f32(((const uint16_t*)(bb + g.v_off))[((size_t)(slot >> 4) * d + t) * 16 + (slot & 15)]);
                 }
                 Ks[tt][t] = kx; Vs[tt][t] = vx;
             }
@@ -1585,7 +1828,8 @@ __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
         int tok0 = tile * P.tok_per_tile;
         int ntok = P.n_tok - tok0; ntok = ntok < P.tok_per_tile ? ntok : P.tok_per_tile;
         int kv_vis;
-        cb.n_parts = P.head_pad > 0 ? P.n_splits : sk_tile_parts(P, tok0, ntok, &kv_vis);
+        cb.n_parts = P.own_mode == SK_OWN_SMALL ? P.n_splits : sk_tile_parts(P, tok0, ntok, &kv_vis);
+        if (P.own_mode == SK_OWN_F32 && cb.n_parts == 1) return;              // written by the attention kernel
         cb.part0 = tile * P.n_splits * Hkv + head; cb.part_stride = Hkv;
         cb.q_tok0 = tok0; cb.n_tok = ntok; cb.kv_head = head;
     }
@@ -1636,18 +1880,11 @@ __device__ __forceinline__ void sk_commit_group(const sk_geom& g, const void* k,
     }
 }
 
-__device__ __forceinline__ void sk_scatter_item(const sk_geom& g, const void* k, const void* v, const sk_scatter& it,
-                                                const int head, int32_t* tables_rw, unsigned char* kv_rw, unsigned char* eph_rw)
+// f32: rows as they are
+__device__ __forceinline__ void sk_commit_group_f32(const sk_geom& g, const void* k, const void* v, const sk_scatter& it, const int head,
+                                                    int32_t* tables_rw, unsigned char* base)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t vt[16 * (128 + 8)];
-    if (g.elem == 2) {
-        unsigned char* base = it.to_eph ? eph_rw : kv_rw;
-        if (g.d == 128) sk_commit_group<128>(g, k, v, it, head, tables_rw, base, vt);
-        else sk_commit_group<64>(g, k, v, it, head, tables_rw, base, vt);
-        return;
-    }
-    // f32: rows as they are
-    unsigned char* dst = (it.to_eph ? eph_rw : kv_rw) + it.dst_off + (int64_t)head * (it.to_eph ? g.eph_head_stride : g.head_stride);
+    unsigned char* dst = base + it.dst_off + (int64_t)head * (it.to_eph ? g.eph_head_stride : g.head_stride);
     const int v_off = it.to_eph ? g.eph_v_off : g.v_off, tid = threadIdx.x;
     if (it.tbl_index >= 0 && head == 0 && tid == 0) tables_rw[it.tbl_index] = it.block_id;
     const int log2_cpr = g.d == 128 ? 5 : 4;                // 16-byte chunks per row
@@ -1659,6 +1896,19 @@ __device__ __forceinline__ void sk_scatter_item(const sk_geom& g, const void* k,
         *(uint4*)(dst + to) = x;
         *(uint4*)(dst + v_off + to) = y;
     }
+}
+
+__device__ __forceinline__ void sk_scatter_item(const sk_geom& g, const void* k, const void* v, const sk_scatter& it,
+                                                const int head, int32_t* tables_rw, unsigned char* kv_rw, unsigned char* eph_rw)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t vt[16 * (128 + 8)];
+    if (g.elem == 2) {
+        unsigned char* base = it.to_eph ? eph_rw : kv_rw;
+        if (g.d == 128) sk_commit_group<128>(g, k, v, it, head, tables_rw, base, vt);
+        else sk_commit_group<64>(g, k, v, it, head, tables_rw, base, vt);
+        return;
+    }
+    sk_commit_group_f32(g, k, v, it, head, tables_rw, it.to_eph ? eph_rw : kv_rw);
 }
 
 // Items read from a list in the workspace (batched steps) ...
@@ -1768,12 +2018,14 @@ int sk_launch_attention(const sk_launch& L, int variant, int32_t n_workgroups, v
         else SK_LAUNCH((sk_attn_bf16_d128<4, 2, 2>), dim3(n_workgroups), dim3(512));
         break;
     default:
-        if (L.g.elem == 2) SK_LAUNCH(sk_attn_simple<true>, dim3(n_workgroups), dim3(256));
-        else SK_LAUNCH(sk_attn_simple<false>, dim3(n_workgroups), dim3(256));
+        if (L.g.elem != 2) return (int)hipErrorInvalidValue;
+        SK_LAUNCH(sk_attn_simple, dim3(n_workgroups), dim3(256));
     }
     return (int)hipGetLastError();
 }
 
+// The kernels that can read the call's own K/V in place and commit them: sk_attn_bf16_small, and sk_attn_f32 (every call
+// of an fp32 pool; a batched one with own_mode none and nothing to commit).
 int sk_launch_attention_small(const sk_launch& L, const sk_commit& C, int32_t n_workgroups, void* stream, void* ev_start, void* ev_stop)
 {
     if (n_workgroups <= 0) return 0;
@@ -1783,7 +2035,11 @@ int sk_launch_attention_small(const sk_launch& L, const sk_commit& C, int32_t n_
         if (ev_start) hipExtLaunchKernelGGL(kernel, dim3(n_workgroups), dim3(256), 0, st, (hipEvent_t)ev_start, (hipEvent_t)ev_stop, 0, L, C); \
         else hipLaunchKernelGGL(kernel, dim3(n_workgroups), dim3(256), 0, st, L, C);                                \
     } while (0)
-    if (L.g.d == 128) {
+    if (L.g.elem == 4) {
+        if (L.g.d == 128) SK_LAUNCH_SMALL(sk_attn_f32<128>);
+        else if (L.g.d == 64) SK_LAUNCH_SMALL(sk_attn_f32<64>);
+        else return (int)hipErrorInvalidValue;
+    } else if (L.g.d == 128) {
         SK_LAUNCH_SMALL(sk_attn_bf16_small<128>);
     } else if (L.g.d == 64) {
         SK_LAUNCH_SMALL(sk_attn_bf16_small<64>);

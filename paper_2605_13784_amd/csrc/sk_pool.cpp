@@ -320,7 +320,7 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
         if (parts <= 1 || parts <= cap) break;
     }
     L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts;
-    L.own_cnt = own_cnt;
+    L.own_cnt = own_cnt; L.own_mode = SK_OWN_SMALL;
     // The last workgroup to finish merges the parts of a KV head (they lie a multiple of 8 workgroups apart, hence on
     // one XCD) if they are few enough for one workgroup to read.
     // Measured (parts x rows, us per query, merged by the last workgroup against the combine kernel): 21 x 4 rows 8.1
@@ -332,6 +332,33 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
     L.by_pad = sk_make_div((uint32_t)L.head_pad);
     L.distrust = p->distrust ? 1 : 0;
     R.base_wgs = (int32_t)Hkv; R.parts = (int32_t)parts; R.wgs = int32_t(L.head_pad * parts); R.kv_len = kv_len;
+    return SK_OK;
+}
+
+// fp32 pools: keys are the cached tokens, padded to whole 16-key tiles, then the call's own; parts of at least 64 keys
+// (a tile for each of the four waves).
+int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits_req, RegPlan& R)
+{
+    sk_launch& L = R.L;
+    const int64_t Hkv = p->d.n_kv_heads, units = L.n_tiles * Hkv, cap = p->L.part_slots * kPartSlotRows / (units * R.v.rows_per_slot);
+    const int64_t keys = (kv_len + 15) / 16 * 16 + own_cnt;
+    const int64_t S = n_splits_req > 0 ? n_splits_req : std::max<int64_t>(1, (p->target_wgs + units / 2) / units);
+    int64_t chunk = std::max<int64_t>(64, ((keys + S - 1) / S + 63) / 64 * 64), parts;
+    for (;; chunk *= 2) {
+        parts = std::max<int64_t>(1, (keys + chunk - 1) / chunk);
+        if (parts <= 1 || parts <= cap) break;
+    }
+    if (parts > 1 && parts > cap) return SK_E_WORKSPACE;
+    L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts; L.by_chunk = sk_make_div((uint32_t)chunk);
+    L.own_cnt = own_cnt; L.own_mode = SK_OWN_F32;
+    // merged by the last workgroup of a unit while that is a few rounds of loads (see plan_small)
+    const int64_t rounds = (int64_t(R.v.tok_per_tile) * p->L.G * p->d.head_dim + 1023) / 1024 * ((parts + 7) / 8);
+    L.fuse = (parts > 1 && parts <= p->d.head_dim && rounds <= 8 && units * 16 <= p->L.sync_units) ? 1 : 0;
+    const int64_t pad = L.fuse ? (units + 7) / 8 * 8 : units;
+    if (pad * parts > (int64_t(1) << 30)) return SK_E_WORKSPACE;
+    L.head_pad = (int32_t)pad; L.by_pad = sk_make_div((uint32_t)pad); L.by_tiles = sk_make_div((uint32_t)L.n_tiles);
+    L.distrust = p->distrust ? 1 : 0;
+    R.base_wgs = (int32_t)units; R.parts = (int32_t)parts; R.wgs = int32_t(pad * parts); R.kv_len = kv_len;
     return SK_OK;
 }
 
@@ -353,6 +380,7 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     L.hole_lo = (int32_t)hole_lo; L.hole_hi = (int32_t)hole_hi;
     L.by_heads = sk_make_div((uint32_t)p->d.n_kv_heads);
     if (v.id == SK_KV_SMALL) return plan_small(p, kv_len, eph_cnt, n_splits_req, R);
+    if (p->L.elem == 4) return plan_f32(p, kv_len, eph_cnt, n_splits_req, R);
     const int64_t base_wgs = int64_t(L.n_tiles) * p->d.n_kv_heads;
     const int64_t slots_rows = p->L.part_slots * kPartSlotRows;
     const int has_eph = eph_cnt > 0 ? 1 : 0;
@@ -437,7 +465,7 @@ int launch_regular(sk_pool* p, RegPlan& R, const void* q, void* out, int out_dty
     void *e0, *e1;
     prof_pair(p, pc, 0, &e0, &e1);
     int e;
-    if (R.v.id == SK_KV_SMALL) {
+    if (R.L.own_mode != SK_OWN_NONE) {
         R.commit.first_wg = R.commit_items > 0 ? R.wgs : INT32_MAX;
         R.commit.tables_rw = (int32_t*)((unsigned char*)p->d.workspace + p->L.off_tables);
         R.commit.kv_rw = (unsigned char*)p->d.kv_mem;
@@ -892,7 +920,10 @@ int launch_list(sk_pool* p, ListPlan& P, const ScatterBatch* sb, int n_sb, ListG
         L[gi].wait_polls = 0;          // the workgroups of a long list are not resident together
         L[gi].merge_fences = p->merge_fences ? 1 : 0;
         prof_pair(p, pc, 0, &e0, &e1);
-        int e = sk_launch_attention(L[gi], g.v.id, (int32_t)P.work[gi].size(), st, e0, e1);
+        sk_commit none = {};
+        none.first_wg = INT32_MAX;
+        int e = p->L.elem == 4 ? sk_launch_attention_small(L[gi], none, (int32_t)P.work[gi].size(), st, e0, e1)
+                               : sk_launch_attention(L[gi], g.v.id, (int32_t)P.work[gi].size(), st, e0, e1);
         if (e) { g_last_hip = e; return SK_E_HIP; }
         p->stats.launches++;
         wgs += (int32_t)P.work[gi].size();
@@ -1107,11 +1138,12 @@ int sk_session_append(sk_pool* p, int32_t id, const void* q, const void* k, cons
     RegPlan plan;
     if (attend) {
         Variant v;
-        const bool small = pick_variant(p, L, v, false, n) && v.id == SK_KV_SMALL;      // attends to the chunk where it lies
+        const bool small = (pick_variant(p, L, v, false, n) && v.id == SK_KV_SMALL) || p->L.elem == 4;      // attends to the chunk where it lies
         int rc = plan_regular(p, id, L, (int32_t)n, small ? n : n + L, small ? L : 0, 0, s->frozen, s->win, 0, plan);
         if (rc) return rc;
     }
-    const bool one_launch = attend && plan.v.id == SK_KV_SMALL;      // the attention launch commits too
+    const bool in_place = attend && plan.L.own_mode != SK_OWN_NONE;
+    const bool one_launch = in_place && scatter_groups(n, L) <= SK_COMMIT_ITEMS;      // the attention launch commits too
     ScatterSlot ss;
     { int rc = scatter_reserve(p, scatter_groups(n, L), ss); if (rc) return rc; }
     // from here on only a failing HIP call can stop the call; what it changed is taken back
@@ -1121,8 +1153,8 @@ int sk_session_append(sk_pool* p, int32_t id, const void* q, const void* k, cons
     std::vector<sk_scatter> items;
     build_scatter(p, s, id, n, 0, L, first_new, false, 0, items);
     int rc;
+    if (in_place) { plan.own_k = k; plan.own_v = v; }
     if (one_launch) {
-        plan.own_k = k; plan.own_v = v;
         plan.commit_items = (int32_t)items.size();
         memcpy(plan.commit.item, items.data(), items.size() * sizeof(sk_scatter));
         rc = inject(p, SK_SITE_SCATTER) ? SK_E_HIP : SK_OK;
@@ -1158,7 +1190,7 @@ int sk_session_query(sk_pool* p, int32_t id, const void* q, const void* k, const
     if (k) rc = plan_regular(p, id, nq, (int32_t)s->len, s->len, nq, (int32_t)s->len, s->frozen, s->win, n_splits, plan);
     else rc = plan_regular(p, id, nq, SK_NO_CAUSAL, s->len, 0, 0, s->frozen, s->win, n_splits, plan);
     if (rc) return rc;
-    if (k && plan.v.id == SK_KV_SMALL) { plan.own_k = k; plan.own_v = v; }      // read where they lie
+    if (k && plan.L.own_mode != SK_OWN_NONE) { plan.own_k = k; plan.own_v = v; }      // read where they lie
     else if (k) {
         ScatterSlot ss;
         rc = scatter_reserve(p, scatter_groups(0, nq), ss);

@@ -238,6 +238,39 @@ def test_calls_of_at_most_32_rows(hq, hkv, d, env):
             pr.append(sid, q, k, v, name="append behind a hole")
 
 
+@pytest.mark.parametrize("hq,hkv,d,env", [(4, 4, 64, None), (8, 2, 128, None), (16, 1, 64, None), (10, 2, 128, None),
+                                          (8, 2, 128, {"SK_SMALL_DISTRUST": "1"})])
+def test_fp32_kernel(hq, hkv, d, env):
+    """The fp32 kernel: cached lengths around its 16-key tiles and 64-key parts, row tiles with idle rows (5 heads
+    per KV head), the call's own tokens behind a padded last tile, commits in the attention launch and (more than
+    128 tokens) in front of it, evicted tokens, every merge."""
+    shape = synth.Shape("f32", hq, hkv, d)
+    gen = synth.generator(1, stream=700 + hq + d)
+    for n in ([0, 1, 15, 16, 17, 63, 65, 200, 1300] if env is None else [65, 200]):
+        pr = Pair(shape, n_blocks=n // 16 + 40, max_sessions=1, kv_fill=0xFF, env=env)
+        sid = pr.create()
+        if n:
+            q, k, v = synth.draw_qkv(gen, n, shape)
+            pr.pool.sk_session_append(sid, None, dev(k), dev(v))
+            pr.oracles[sid].K, pr.oracles[sid].V = synth.to_raw(k), synth.to_raw(v)
+        for nq in (1, 3, 20):
+            q, k, v = synth.draw_qkv(gen, nq, shape)
+            for S in (0, 1, 3):
+                if n:
+                    pr.query(sid, q, n_splits=S, name="query A n=%d nq=%d S=%d" % (n, nq, S))
+                pr.query(sid, q, k, v, n_splits=S, name="query B n=%d nq=%d S=%d" % (n, nq, S))
+        if n >= 65:
+            pr.freeze(sid, 20)
+            pr.evict(sid, 33)
+        for L in (5, 64, 150):
+            q, k, v = synth.draw_qkv(gen, L, shape)
+            pr.append(sid, q, k, v, name="append n=%d L=%d" % (n, L))
+        k, v = pr.pool.sk_session_gather(sid)
+        Kc, Vc = pr.oracles[sid].cache()
+        np.testing.assert_array_equal(synth.to_raw(k.cpu()), Kc)
+        np.testing.assert_array_equal(synth.to_raw(v.cpu()), Vc)
+
+
 @pytest.mark.parametrize("hd", [128, 64])
 @pytest.mark.parametrize("env", [None, LONG_CACHE_PATHS])
 def test_scores_that_grow_along_the_cache(hd, env):
