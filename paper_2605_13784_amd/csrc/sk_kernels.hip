@@ -88,7 +88,12 @@ __device__ __forceinline__ bool sk_decode_work(const sk_launch& P, int b, sk_wor
     if (P.mode == SK_MODE_LIST) { w = P.work[b]; return true; }
     const int Hkv = P.g.Hkv;
     const int rest = sk_divide(b, P.by_heads), head = b - rest * Hkv;
-    const int split = sk_divide(rest, P.by_tiles), tile = rest - split * P.n_tiles;
+    const int split = sk_divide(rest, P.by_tiles);
+    int tile = rest - split * P.n_tiles;
+    // The last tokens of a chunk see the most keys: they start first, so that a launch of more workgroups than the
+    // chip holds ends with its short ones (2,600 tokens into an empty session, 328 workgroups of 1 to 41 iterations on
+    // 256 CUs: append and 16-token query 115.6 -> 99.8 us).
+    if (P.pos0 < SK_NO_CAUSAL) tile = P.n_tiles - 1 - tile;
     int tok0 = tile * P.tok_per_tile;
     int ntok = P.n_tok - tok0; ntok = ntok < P.tok_per_tile ? ntok : P.tok_per_tile;
     int kv_vis;
