@@ -435,9 +435,10 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     // phases per row group running freely (128 rows: half the arithmetic per wave of the four-wave
     // 128-row instance, two waves per SIMD)
     constexpr bool LOCKSTEP = NW == 8 && NPH == 1;
-    // how the reference maximum is kept (step_softmax); the four-wave 128-row instance has no registers to keep
-    // the scores of two tiles beside their V^T operands
-    constexpr bool LAZY_MAX = LOCKSTEP || TPW == 1;
+    // how the reference maximum is kept (step_softmax); at head_dim 128 the four-wave 128-row instance has no registers
+    // to keep the scores of two tiles beside their V^T operands (at 64, where those are half as many: 256-token append
+    // and 16-token query at 32,512 tokens 124.6 -> 120.7 us)
+    constexpr bool LAZY_MAX = LOCKSTEP || TPW == 1 || D == 64;
     constexpr int NLG = NW / 4;              // groups of four waves; each loads whole tiles
     static_assert(NW == 4 || (LOCKSTEP && NSS == 4) || (NW == 8 && NPH == 2 && NSS == 2), "four waves, or eight as described");
     static_assert(NSS == 2 || NSS == 4, "ring depth in iterations: 64 KiB (two workgroups per CU) or 128 KiB (one)");
