@@ -39,6 +39,7 @@ struct sk_geom {
     uint32_t g_magic;             // ceil(2^16 / G): row / G of a tile's row is (row * g_magic) >> 16
 };
 
+#define SK_STAGE_TOKENS 64        // own tokens that a workgroup of the ring kernels stages itself
 #define SK_NO_CAUSAL (1 << 30)    // pos0 at or above this: rows see every key of every segment
 
 // One workgroup of an attention kernel: a tile of query rows of one KV head against a range of
@@ -144,8 +145,9 @@ struct sk_launch {
     int32_t wait_polls;
     int32_t merge_fences;   // 1: full device-scope fences around the arrival (slow: an L2 walk each); 0: see the kernel
     sk_div by_heads, by_tiles, by_chunk;      // Hkv, n_tiles, chunk (regular mode)
-    // sk_attn_bf16_small and sk_attn_f32, single-session calls: the call's own tokens where the caller has them
-    // ([own_cnt][Hkv][d], the last keys of the last part), and the launch geometry
+    // single-session calls: the call's own tokens where the caller has them ([own_cnt][Hkv][d]).  sk_attn_bf16_small and
+    // sk_attn_f32 attend to them there, as the last keys of the last part; the ring kernels stage them first, in the
+    // workgroup of the own part (null: a launch in front has staged them).  Below, the small kernels' launch geometry.
     const void* own_k;
     const void* own_v;
     int32_t own_cnt;

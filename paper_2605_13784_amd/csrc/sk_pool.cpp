@@ -1190,7 +1190,12 @@ int sk_session_query(sk_pool* p, int32_t id, const void* q, const void* k, const
     if (k) rc = plan_regular(p, id, nq, (int32_t)s->len, s->len, nq, (int32_t)s->len, s->frozen, s->win, n_splits, plan);
     else rc = plan_regular(p, id, nq, SK_NO_CAUSAL, s->len, 0, 0, s->frozen, s->win, n_splits, plan);
     if (rc) return rc;
-    if (k && plan.L.own_mode != SK_OWN_NONE) { plan.own_k = k; plan.own_v = v; }      // read where they lie
+    // Own K/V are read where they lie, or staged by the attention kernel: with one row tile per KV head one workgroup of
+    // each head attends to them, and up to 64 tokens take it less time than the others their keys.
+    const bool in_place = plan.L.own_mode != SK_OWN_NONE;
+    const bool stages = !in_place && plan.L.n_tiles == 1 && plan.v.id != SK_KV_SIMPLE && nq <= SK_STAGE_TOKENS;
+    if (k && stages && inject(p, SK_SITE_SCATTER)) return SK_E_HIP;
+    if (k && (in_place || stages)) { plan.own_k = k; plan.own_v = v; }
     else if (k) {
         ScatterSlot ss;
         rc = scatter_reserve(p, scatter_groups(0, nq), ss);

@@ -271,6 +271,32 @@ def test_fp32_kernel(hq, hkv, d, env):
         np.testing.assert_array_equal(synth.to_raw(v.cpu()), Vc)
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (32, 8, 64), (4, 4, 128), (4, 4, 64), (28, 4, 128), (71, 1, 64)])
+def test_own_tokens_of_a_query_staged_by_the_attention_kernel(hq, hkv, d):
+    """Queries of one row tile per KV head stage their own K/V (up to 64 tokens) in the workgroup of the own part: token
+    counts around 16-token groups, at the row tiles' edges, and around the two limits behind which a launch in front
+    stages them; empty and short caches, and a cache long enough for the eight-wave 128-row instance; what an
+    earlier call left behind the last token (NaN) never counts."""
+    shape = synth.Shape("bf16", hq, hkv, d)
+    G = hq // hkv
+    gen = synth.generator(2, stream=900 + hq + d)
+    counts = sorted({c for c in (1, 15, 16, 17, 33, 48, 63, 64, 65, 32 // G + 1, 64 // G, 64 // G + 1, 128 // G, 128 // G + 1,
+                                 256 // G, 256 // G + 1) if c > 0 and 32 < c * G <= 300})
+    for n, env in ((0, None), (33, None), (700, None), (700, LONG_CACHE_PATHS)):
+        pr = Pair(shape, n_blocks=n // 16 + 12, max_sessions=1, kv_fill=0xFF, env=env)
+        sid = pr.create()
+        if n:
+            q, k, v = synth.draw_qkv(gen, n, shape)
+            pr.pool.sk_session_append(sid, None, dev(k), dev(v))
+            pr.oracles[sid].K, pr.oracles[sid].V = synth.to_raw(k), synth.to_raw(v)
+        for nq in counts:
+            q, k, v = synth.draw_qkv(gen, 64, shape)
+            pr.pool.sk_session_query(sid, dev(q), dev(k), dev(v * float("nan")))
+            q, k, v = synth.draw_qkv(gen, nq, shape)
+            pr.query(sid, q, k, v, n_splits=0 if nq % 2 else 3, name="query B n=%d nq=%d" % (n, nq))
+        pr.query(sid, q, k, v, name="bf16 results", out_dtype="bf16")
+
+
 @pytest.mark.parametrize("hd", [128, 64])
 @pytest.mark.parametrize("env", [None, LONG_CACHE_PATHS])
 def test_scores_that_grow_along_the_cache(hd, env):
