@@ -107,7 +107,7 @@ def test_bf16_output_dtype_bf16_and_no_lse():
                                    synth.Shape("bf16", 8, 8, 128), synth.Shape("bf16", 32, 2, 128),
                                    synth.Shape("bf16", 32, 1, 128)])
 def test_other_shapes(shape):
-    """fp32 goes through the fp32-FMA kernel; bf16 with G = 32, 16, 8, 3 and 1 through the MFMA kernel
+    """fp32 goes through the fp32 kernel; bf16 with G = 32, 16, 8, 3 and 1 through the MFMA kernel
     (a wave's 32 rows are then one token's heads, two tokens, four tokens, ten tokens and two thirds
     of another, 32 tokens), head_dim 64 included."""
     gen = synth.generator(9, stream=shape.n_q_heads)
