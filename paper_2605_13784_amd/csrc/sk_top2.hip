@@ -47,11 +47,12 @@ __device__ __forceinline__ void merge(float& v1, int32_t& i1, float& v2, int32_t
     v1 = w1v; i1 = w1i;
     v2 = sf ? o2v : l1v; i2 = sf ? o2i : l1i;
 }
-// reduction over the 256 threads of a workgroup; the result is valid in thread 0
+// reduction over the 64 * NW threads of a workgroup; the result is valid in thread 0
+template <int NW>
 __device__ __forceinline__ void block_reduce(float& v1, int32_t& i1, float& v2, int32_t& i2)
 {
-    __shared__ float pv1[4], pv2[4];
-    __shared__ int32_t pi1[4], pi2[4];
+    __shared__ float pv1[NW], pv2[NW];
+    __shared__ int32_t pi1[NW], pi2[NW];
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) {
         const float bv1 = __shfl_xor(v1, m, 64), bv2 = __shfl_xor(v2, m, 64);
@@ -63,46 +64,74 @@ __device__ __forceinline__ void block_reduce(float& v1, int32_t& i1, float& v2, 
     __syncthreads();
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int k = 1; k < 4; ++k) merge(v1, i1, v2, i2, pv1[k], pi1[k], pv2[k], pi2[k]);
+        for (int k = 1; k < NW; ++k) merge(v1, i1, v2, i2, pv1[k], pi1[k], pv2[k], pi2[k]);
     }
 }
 
-constexpr int kChunk = 8192;      // logits per workgroup of the first pass (32 KiB)
+constexpr int kChunk = 8192;      // logits that 256 threads scan at once (32 KiB)
+
+// Scans the chunk of `row` that starts at `begin` with 256 threads, of which this is thread t: eight 16-byte loads per
+// thread, all issued before the first comparison (rows are 16-byte aligned, chunk starts are multiples of 4), then what
+// is left behind the last float4.  In a chunk that ends early the loads behind its end repeat its last float4, and -inf,
+// which displaces nothing, is pushed in their place.  The logits are read once: non-temporal loads (the plain-read
+// probe gains 8 % by them).
+__device__ __forceinline__ void scan_chunk(const float* __restrict__ row, const int begin, const int vocab, const int t,
+                                           float& v1, int32_t& i1, float& v2, int32_t& i2)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    const int end = min(begin + kChunk, vocab), n4 = (end - begin) >> 2;
+    const f32x4* row4 = (const f32x4*)(row + begin);
+    f32x4 x[8];
+    if (n4 == kChunk / 4) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = __builtin_nontemporal_load(row4 + t + 256 * u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = begin + 4 * (t + 256 * u);
+            SK_TOP2_PUSH(x[u].x, i); SK_TOP2_PUSH(x[u].y, i + 1); SK_TOP2_PUSH(x[u].z, i + 2); SK_TOP2_PUSH(x[u].w, i + 3);
+        }
+    } else {
+        const float none = -__builtin_inff();
+        const int rest = begin + 4 * n4 + t;
+        const float last = rest < end ? row[rest] : none;
+        if (n4 > 0) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = __builtin_nontemporal_load(row4 + min(t + 256 * u, n4 - 1));
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (256 * u >= n4) break;
+                const int i = begin + 4 * (t + 256 * u);
+                if (t + 256 * u >= n4) x[u] = f32x4{none, none, none, none};
+                SK_TOP2_PUSH(x[u].x, i); SK_TOP2_PUSH(x[u].y, i + 1); SK_TOP2_PUSH(x[u].z, i + 2); SK_TOP2_PUSH(x[u].w, i + 3);
+            }
+        }
+        SK_TOP2_PUSH(last, rest);
+    }
+}
+
+// Writes row r's result from the pair of its two largest logits.
+__device__ __forceinline__ void write_row(const int r, const float v1, int32_t i1, const float v2, int32_t i2,
+                                          int32_t* idx1, int32_t* idx2, float* val1, float* val2, float* gap)
+{
+    // places still held by the initial pair: every entry that could stand there is -inf, and
+    // the lowest index not taken yet is the answer
+    if (i1 == INT_MAX) { i1 = 0; i2 = 1; }
+    else if (i2 == INT_MAX) i2 = i1 == 0 ? 1 : 0;
+    idx1[r] = i1; idx2[r] = i2;
+    if (val1) val1[r] = v1;
+    if (val2) val2[r] = v2;
+    if (gap) gap[r] = v1 - v2;
+}
 
 // pass 1: workgroup (chunk c, row r) -> partial[r][c]
 __global__ __launch_bounds__(256) void sk_top2_partial(const float* __restrict__ logits, int64_t row_stride, int32_t vocab,
                                                        int32_t n_chunks, Top2* __restrict__ partial)
 {
     const int c = blockIdx.x, r = blockIdx.y;
-    const float* row = logits + (int64_t)r * row_stride;
-    const int begin = c * kChunk;
-    const int end = min(begin + kChunk, vocab);
     float v1 = -__builtin_inff(), v2 = -__builtin_inff();
     int32_t i1 = INT_MAX, i2 = INT_MAX;
-    // float4 loads over the aligned body (rows are 16-byte aligned, chunk starts are multiples of 4);
-    // a full chunk is eight loads per thread, all issued before the first comparison
-    const int n4 = (end - begin) >> 2;
-    const float4* row4 = (const float4*)(row + begin);
-    if (n4 == kChunk / 4) {
-        // the logits are read once: non-temporal loads (the plain-read probe gains 8 % by them)
-        typedef __attribute__((ext_vector_type(4))) float f32x4;
-        f32x4 x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = __builtin_nontemporal_load((const f32x4*)row4 + threadIdx.x + 256 * u);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = begin + 4 * (threadIdx.x + 256 * u);
-            SK_TOP2_PUSH(x[u].x, i); SK_TOP2_PUSH(x[u].y, i + 1); SK_TOP2_PUSH(x[u].z, i + 2); SK_TOP2_PUSH(x[u].w, i + 3);
-        }
-    } else {
-        for (int j = threadIdx.x; j < n4; j += 256) {
-            const float4 x = row4[j];
-            const int i = begin + 4 * j;
-            SK_TOP2_PUSH(x.x, i); SK_TOP2_PUSH(x.y, i + 1); SK_TOP2_PUSH(x.z, i + 2); SK_TOP2_PUSH(x.w, i + 3);
-        }
-        for (int i = begin + 4 * n4 + threadIdx.x; i < end; i += 256) SK_TOP2_PUSH(row[i], i);
-    }
-    block_reduce(v1, i1, v2, i2);
+    scan_chunk(logits + (int64_t)r * row_stride, c * kChunk, vocab, threadIdx.x, v1, i1, v2, i2);
+    block_reduce<4>(v1, i1, v2, i2);
     if (threadIdx.x == 0) partial[(int64_t)r * n_chunks + c] = Top2{v1, i1, v2, i2};
 }
 
@@ -117,18 +146,23 @@ __global__ __launch_bounds__(256) void sk_top2_final(const Top2* __restrict__ pa
         const Top2 b = partial[(int64_t)r * n_chunks + c];
         merge(v1, i1, v2, i2, b.v1, b.i1, b.v2, b.i2);
     }
-    block_reduce(v1, i1, v2, i2);
-    if (threadIdx.x == 0) {
-        // places still held by the initial pair: every entry that could stand there is -inf, and
-        // the lowest index not taken yet is the answer
-        if (i1 == INT_MAX) { i1 = 0; i2 = 1; }
-        else if (i2 == INT_MAX) i2 = i1 == 0 ? 1 : 0;
-        const Top2 t = {v1, i1, v2, i2};
-        idx1[r] = t.i1; idx2[r] = t.i2;
-        if (val1) val1[r] = t.v1;
-        if (val2) val2[r] = t.v2;
-        if (gap) gap[r] = t.v1 - t.v2;
-    }
+    block_reduce<4>(v1, i1, v2, i2);
+    if (threadIdx.x == 0) write_row(r, v1, i1, v2, i2, idx1, idx2, val1, val2, gap);
+}
+
+// Both passes in one launch: one workgroup per row, 256 threads for each of its NC chunks.  A thread scans as in the
+// first pass, so the results are those of the two passes bit for bit.
+// Bound: the launch and one round trip for the logits.
+template <int NC>
+__global__ __launch_bounds__(256 * NC) void sk_top2_row(const float* __restrict__ logits, int64_t row_stride, int32_t vocab,
+                                                        int32_t* idx1, int32_t* idx2, float* val1, float* val2, float* gap)
+{
+    const int r = blockIdx.x;
+    float v1 = -__builtin_inff(), v2 = -__builtin_inff();
+    int32_t i1 = INT_MAX, i2 = INT_MAX;
+    scan_chunk(logits + (int64_t)r * row_stride, (int)(threadIdx.x >> 8) * kChunk, vocab, threadIdx.x & 255, v1, i1, v2, i2);
+    block_reduce<4 * NC>(v1, i1, v2, i2);
+    if (threadIdx.x == 0) write_row(r, v1, i1, v2, i2, idx1, idx2, val1, val2, gap);
 }
 
 }  // namespace
@@ -153,6 +187,16 @@ int sk_top2(const float* logits, int32_t rows, int32_t vocab, int64_t row_stride
     if (workspace_bytes < sk_top2_workspace_bytes(rows, vocab)) return SK_E_WORKSPACE;
     const int32_t n_chunks = int32_t((int64_t(vocab) + kChunk - 1) / kChunk);
     hipStream_t st = (hipStream_t)hip_stream;
+    // Rows of at most two chunks in one launch.  Measured (rows x logits, us per call in a stream of calls, two launches
+    // -> one): 1 x 4,334 7.2 -> 4.7, 4,096 x 4,334 22.6 -> 14.8, 64 x 8,192 6.7 -> 4.0, 1,024 x 8,192 10.0 -> 6.6, 200 x
+    // 8,200 7.6 -> 4.6, 1,024 x 8,200 13.6 -> 8.1, 1,024 x 16,384 14.9 -> 12.9, 4,096 x 16,384 47.7 -> 44.4.  With four
+    // chunks to a workgroup of 1,024 threads 64 x 27,195 7.4 -> 7.5, 1,024 x 32,768 24.1 -> 27.9, and a row of 128,256
+    // alone 7.5 -> 14.8: longer rows keep the two launches.
+    if (n_chunks <= 2) {
+        if (n_chunks == 1) hipLaunchKernelGGL(sk_top2_row<1>, dim3(rows), dim3(256), 0, st, logits, row_stride, vocab, idx1, idx2, val1, val2, gap);
+        else hipLaunchKernelGGL(sk_top2_row<2>, dim3(rows), dim3(512), 0, st, logits, row_stride, vocab, idx1, idx2, val1, val2, gap);
+        return hipGetLastError() == hipSuccess ? SK_OK : SK_E_HIP;
+    }
     hipLaunchKernelGGL(sk_top2_partial, dim3(n_chunks, rows), dim3(256), 0, st, logits, row_stride, vocab, n_chunks, (Top2*)workspace);
     hipLaunchKernelGGL(sk_top2_final, dim3(rows), dim3(256), 0, st, (const Top2*)workspace, n_chunks, idx1, idx2, val1, val2, gap);
     return hipGetLastError() == hipSuccess ? SK_OK : SK_E_HIP;

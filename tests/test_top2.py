@@ -50,9 +50,15 @@ def test_library_rejects_bad_arguments_without_a_gpu():
     assert lib.sk_top2(None, 0, 100, 100, None, 0, None, None, None, None, None, None) == sk.SK_OK
 
 
+# rows of one or two 8,192-logit chunks, which one workgroup scans: no whole float4, one and a remainder, either side of
+# one chunk, of a second chunk without a whole float4, and of the two chunks' end
+ONE_LAUNCH = [(6, 3, 4), (6, 5, 8), (600, 1021, 1024), (9, 8192, 8192), (5, 8195, 8196), (300, 12290, 12292), (6, 16383, 16384),
+              (7, 16384, 16384), (6, 16385, 16388)]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows,vocab,stride", [(1, 128256, 128256), (64, 128256, 128256), (5, 2, 4), (3, 8191, 8192),
-                                               (7, 8193, 8196), (2, 32000, 40000), (130, 50257, 50260)])
+                                               (7, 8193, 8196), (2, 32000, 40000), (130, 50257, 50260)] + ONE_LAUNCH)
 def test_gpu_top2_equals_oracle_exactly(rows, vocab, stride):
     """Synthetic logits N(0, 2.5) in the shapes of a 128k-vocabulary model (and ragged ones that end
     inside a float4, inside and just behind a workgroup's chunk), planted ties included."""
