@@ -114,8 +114,9 @@ size_t sk_pool_workspace_bytes(const sk_pool_desc* desc);
  *   SK_TARGET_WGS=n    workgroups a single-session call is cut into (default: 256 or 512 by shape)
  *   SK_FORCE_SIMPLE=1  bf16 pools: always the fp32-FMA attention kernel
  *   SK_NO_SMALL=1      never the kernel for calls of at most 32 query rows per KV head
- *   SK_SMALL_DISTRUST=1  in that kernel and the fp32 one the last workgroup of a row tile and KV head computes
- *                      its rows alone, as if the parts had not run on one XCD (tests)
+ *   SK_SMALL_DISTRUST=n  tests: bit 0 set, in that kernel and the fp32 one the last workgroup of a row tile and KV
+ *                      head computes every part again itself, as if the parts had not run on one XCD (same
+ *                      result); bit 1 set, it leaves the rows unwritten where it would have to do that
  *   SK_NO_256=1        never the 256-row eight-wave instance of the bf16 kernel
  *   SK_NO_PACK=1       a question batch gives every question a row tile of its own
  *   SK_NO_INTERLEAVE=1 the splits of a query take contiguous chunks of the cache instead of

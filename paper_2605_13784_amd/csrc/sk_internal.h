@@ -154,7 +154,7 @@ struct sk_launch {
     int32_t own_mode;       // SK_OWN_*: how the launch is cut (bf16: one tile behind the last part's cached keys; f32: keys behind the cached ones)
     int32_t head_pad;       // workgroups from one part to the next of its unit (row tile x KV head): the units, padded to a multiple of 8 if merged
     sk_div by_pad;
-    int32_t distrust;       // 1: treat the parts as run on several XCDs (the last one computes the tile alone; tests)
+    int32_t distrust;       // tests: bit 0, treat the parts as run on several XCDs (the last one computes them all); bit 1, leave the rows unwritten then
     int32_t kv_once;        // 1: every key is read by exactly one workgroup of the launch (loaded non-temporal)
 };
 

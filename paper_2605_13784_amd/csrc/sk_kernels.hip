@@ -1154,7 +1154,9 @@ __global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 1 : 2) void sk_att
 // ordinary stores are visible there once they have completed.  That they did run on one XCD is checked, not
 // assumed: every workgroup adds its XCD number and its square to the unit's 64-bit arrival word (one
 // device-scope atomic), and the last one merges only if n * sum(x^2) == sum(x)^2, i.e. all x are equal.
-// If not, it computes the whole row tile by itself.  Nobody waits for anybody.
+// If not, it computes every part again by itself, one after the other and each as its own workgroup did, and
+// merges those (the slots get the bytes they hold already): the result is the same to the last bit wherever the
+// parts ran.  Nobody waits for anybody.
 //
 // Bound: round trips.  One query token with its own K/V at 2,600 cached tokens: one launch of 8.1 us where a staging,
 // an attention and a combine kernel took 16.3 back to back; 1.0 us from a workgroup's start to its first loads
@@ -1169,14 +1171,16 @@ __device__ __forceinline__ void sk_commit_group(const sk_geom& g, const void* k,
 
 // What a workgroup of the kernels below does once its four waves have scaled their accumulators to the common row
 // maxima and laid them side by side in LDS (tr[wave][row][16-byte chunk ^ row], stat[wave][row] = (m, l, lx, -)): adds
-// the four up, writes the rows out (`whole`) or to partial slot `slot`, and, with P.fuse, arrives at `unit` and merges
-// the unit's parts (slots slot0, slot0 + Hkv, ..) if it is the last one there.  False: the parts did not run on one
-// XCD and this workgroup has to compute the unit alone.  `orow_of`: row of the tile -> row of out / lse.
+// the four up, writes the rows out (n_parts == 1) or to the slot of `part` (slot0 + part * Hkv), and, with P.fuse,
+// arrives at `unit` and merges the unit's parts if it is the last one there.  False: the parts did not run on
+// one XCD and this workgroup has to compute them all, part 0 first (`alone` from then on).  `orow_of`: row of the
+// tile -> row of out / lse.
 template <int D, int ROWS, class OutRow>
 __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D / 4], float4 (*stat)[ROWS], int* decision, const int tid,
-                                        const int nrows, const bool whole, const int slot, const int slot0, const int n_parts, const int unit,
+                                        const int nrows, const int part, const bool alone, const int slot0, const int n_parts, const int unit,
                                         const OutRow orow_of)
 {
+    const bool whole = n_parts == 1;
     constexpr int CPR = D / 4, SUBS = 256 / ROWS;
     auto put_row = [&](const int row, const int c4, const float4 x, const float inv, const float lse) __attribute__((always_inline)) {
         const size_t orow = orow_of(row);
@@ -1189,7 +1193,7 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
         if (P.lse && c4 == 0) P.lse[orow] = lse;
     };
     __syncthreads();
-    const size_t prow = (size_t)slot * P.rows_per_slot;
+    const size_t prow = (size_t)(slot0 + part * P.g.Hkv) * P.rows_per_slot;
     for (int i = tid; i < nrows * CPR; i += 256) {
         const int row = i / CPR, c4 = i % CPR;
         float4 x = tr[0][row][(c4 ^ row) & (CPR - 1)];
@@ -1211,23 +1215,27 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
     // ---- arrival; the last workgroup of the unit merges ----
     SK_WAIT_VMCNT(0);                                 // this thread's part of the partial has reached the L2
     __syncthreads();
-    if (tid == 0) {
-        const unsigned long long x = sk_xcd_id();
-        unsigned long long* word = (unsigned long long*)P.sync + (size_t)unit * 16;      // a 128-byte line per unit: each is one XCD's
-        const unsigned long long add = 1ull | (x << 16) | ((x * x) << 36);
-        const unsigned long long got = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
-        int d = 0;
-        if ((int)(got & 0xffffu) == n_parts) {
-            const unsigned long long sum = (got >> 16) & 0xfffffu, sq = got >> 36;
-            d = (!P.distrust && (unsigned long long)n_parts * sq == sum * sum) ? 1 : 2;
-            __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // ready for the next launch
+    if (alone) {
+        if (part + 1 < n_parts) return false;
+    } else {
+        if (tid == 0) {
+            const unsigned long long x = sk_xcd_id();
+            unsigned long long* word = (unsigned long long*)P.sync + (size_t)unit * 16;      // a 128-byte line per unit: each is one XCD's
+            const unsigned long long add = 1ull | (x << 16) | ((x * x) << 36);
+            const unsigned long long got = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+            int d = 0;
+            if ((int)(got & 0xffffu) == n_parts) {
+                const unsigned long long sum = (got >> 16) & 0xfffffu, sq = got >> 36;
+                d = (!(P.distrust & 1) && (unsigned long long)n_parts * sq == sum * sum) ? 1 : ((P.distrust & 2) ? 0 : 2);
+                __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // ready for the next launch
+            }
+            *decision = d;
         }
-        *decision = d;
+        __syncthreads();
+        const int d = *decision;
+        if (d == 0) return true;
+        if (d == 2) return false;
     }
-    __syncthreads();
-    const int d = *decision;
-    if (d == 0) return true;
-    if (d == 2) return false;
     // All statistics in one round of loads, the weights of all parts to LDS, then every thread sums its 16-byte
     // pieces of output rows over the parts, in part order, eight loads in flight (a short loop: code that
     // runs once per launch costs its instruction fetches, so 32 unrolled loads took 1 us longer).
@@ -1300,10 +1308,11 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
         return;
     }
     // workgroup -> (part, KV head); the heads of a part are padded to a multiple of the XCD count
-    const int part = sk_divide(blockIdx.x, P.by_pad), head = blockIdx.x - part * P.head_pad;
+    int part = sk_divide(blockIdx.x, P.by_pad);
+    const int head = blockIdx.x - part * P.head_pad;
     if (head >= Hkv) return;
     const int n_parts = P.n_splits;
-    bool whole = n_parts == 1;                            // this workgroup computes the row tile from end to end
+    bool alone = false;                                   // the parts ran on several XCDs: this workgroup computes them all
     for (;;) {
         // (opaque, or everything below that depends on the lane only is computed before the first load is
         // requested: the loop almost never runs twice)
@@ -1325,7 +1334,7 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
         }
 
         int k_begin = 0, k_end = P.kv_len;
-        if (!whole) {
+        if (n_parts > 1) {
             k_begin = part * P.chunk;
             k_end = k_begin + P.chunk < k_end ? k_begin + P.chunk : k_end;
         }
@@ -1439,7 +1448,7 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
             }
         }
         // The call's own tokens: one tile, for a wave that has no cached one when the launch is cut into parts.
-        if ((whole || part == n_parts - 1) && P.own_cnt > 0 && wave == (n_cached & (NWV - 1))) {
+        if (part == n_parts - 1 && P.own_cnt > 0 && wave == (n_cached & (NWV - 1))) {
             const int key = tau < P.own_cnt ? tau : P.own_cnt - 1;
             const unsigned char* p = (const unsigned char*)P.own_k + ((size_t)key * Hkv + head) * ROWB + kg * 16;
 #pragma unroll
@@ -1490,12 +1499,13 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
                 }
             if (kg == 0) { stat[wave][r].y = l_tot * a; stat[wave][r].z = lx_tot * a; }
         }
-        if (sk_meet<D, 32>(P, tr, stat, &decision, tid, nrows, whole, part * Hkv + head, head, n_parts, head,
+        if (sk_meet<D, 32>(P, tr, stat, &decision, tid, nrows, part, alone, head, n_parts, head,
                            [&](const int row) __attribute__((always_inline)) {
                                const int t2 = div_g(row);
                                return (size_t)t2 * P.g.Hq + head * G + (row - t2 * G);
                            })) return;
-        whole = true;                                     // the parts ran on several XCDs: once more, alone
+        part = alone ? part + 1 : 0;
+        alone = true;
     }
 }
 
@@ -1558,7 +1568,7 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
     const bool listed = P.mode == SK_MODE_LIST;
     sk_work w;
     int part = 0, unit = 0, n_parts = 1, vis = 0;
-    if (listed) w = P.work[blockIdx.x];
+    if (listed) { w = P.work[blockIdx.x]; n_parts = w.n_parts; }
     else {
         part = sk_divide(blockIdx.x, P.by_pad); unit = blockIdx.x - part * P.head_pad;
         if (unit >= P.n_tiles * Hkv) return;
@@ -1570,11 +1580,11 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
         if (part >= n_parts) return;
         w.tbl_off = P.tbl_off; w.pos0 = P.pos0 < SK_NO_CAUSAL ? P.pos0 + w.q_tok0 : P.pos0;
         w.hole_lo = P.hole_lo; w.hole_hi = P.hole_hi; w.kv_step = 0; w.sub_blocks = 0;
-        w.part = n_parts == 1 ? -1 : (tile * P.n_splits + part) * Hkv + w.kv_head;
         w.part0 = tile * P.n_splits * Hkv + w.kv_head;
         w.eph_cnt[0] = w.eph_cnt[1] = 0; w.eph_blk[0] = w.eph_blk[1] = 0; w.eph_pos0[0] = w.eph_pos0[1] = 0;
     }
-    bool whole = w.part < 0;
+    const int slot0 = listed ? w.part : w.part0;          // (a listed part is not merged here)
+    bool alone = false;                                   // see sk_attn_bf16_small
     for (;;) {
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));                     // (opaque: see sk_attn_bf16_small)
@@ -1591,7 +1601,7 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
         if (listed) { k_begin = w.kv_begin; k_end = w.kv_end; }
         else {
             const int pad = (P.kv_len + 15) & ~15;
-            const int b = whole ? 0 : part * P.chunk, e = whole || b + P.chunk > vis ? vis : b + P.chunk;
+            const int b = part * P.chunk, e = b + P.chunk > vis ? vis : b + P.chunk;
             k_begin = b; k_end = e < P.kv_len ? e : P.kv_len;
             o_begin = b > pad ? b - pad : 0; o_end = e - pad;
         }
@@ -1716,12 +1726,13 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
                     tr[wave][c][((h * 16 + g4 + i) ^ c) & (CPR - 1)] = make_float4(o[h][0][i] * a, o[h][1][i] * a, o[h][2][i] * a, o[h][3][i] * a);
             if (g4 == 0) { stat[wave][c].y = l_tot * a; stat[wave][c].z = l_tot * a; }
         }
-        if (sk_meet<D, 16>(P, tr, stat, &decision, tid, nrows, whole, w.part, w.part0, n_parts, unit,
+        if (sk_meet<D, 16>(P, tr, stat, &decision, tid, nrows, part, alone, slot0, n_parts, unit,
                            [&](const int row) __attribute__((always_inline)) {
                                const int t2 = div_g(row);
                                return (size_t)(w.q_tok0 + t2) * P.g.Hq + head * G + (row - t2 * G);
                            })) return;
-        whole = true;
+        part = alone ? part + 1 : 0;
+        alone = true;
     }
 }
 

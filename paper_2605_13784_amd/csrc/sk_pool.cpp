@@ -137,7 +137,8 @@ struct sk_pool {
     // Tuning switches, read from the environment once when the pool is created (see sk_pool_create).
     int target_wgs = kDefaultTargetWgs;
     bool target_wgs_set = false;
-    bool force_simple = false, no_small = false, distrust = false, no_256 = false, no_pack = false, no_interleave = false, no_stream_loads = false;
+    bool force_simple = false, no_small = false, no_256 = false, no_pack = false, no_interleave = false, no_stream_loads = false;
+    int distrust = 0;                    // SK_SMALL_DISTRUST (tests)
     bool p128 = true;                    // SK_NO_P128=1: never the eight-wave 128-row instance
     int64_t p128_min_tokens = 30720;     // SK_P128_MIN_TOKENS: cached tokens from which it is taken (break-even measured near 32K)
     int64_t stream_min_tokens = 65536;   // SK_STREAM_MIN_TOKENS: cached tokens from which the 128-row instances load non-temporal
@@ -330,7 +331,7 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
     L.fuse = (parts > 1 && parts <= p->d.head_dim && rounds <= 8) ? 1 : 0;
     L.head_pad = L.fuse ? (int32_t)((Hkv + 7) / 8 * 8) : (int32_t)Hkv;
     L.by_pad = sk_make_div((uint32_t)L.head_pad);
-    L.distrust = p->distrust ? 1 : 0;
+    L.distrust = p->distrust;
     R.base_wgs = (int32_t)Hkv; R.parts = (int32_t)parts; R.wgs = int32_t(L.head_pad * parts); R.kv_len = kv_len;
     return SK_OK;
 }
@@ -357,7 +358,7 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
     const int64_t pad = L.fuse ? (units + 7) / 8 * 8 : units;
     if (pad * parts > (int64_t(1) << 30)) return SK_E_WORKSPACE;
     L.head_pad = (int32_t)pad; L.by_pad = sk_make_div((uint32_t)pad); L.by_tiles = sk_make_div((uint32_t)L.n_tiles);
-    L.distrust = p->distrust ? 1 : 0;
+    L.distrust = p->distrust;
     R.base_wgs = (int32_t)units; R.parts = (int32_t)parts; R.wgs = int32_t(pad * parts); R.kv_len = kv_len;
     return SK_OK;
 }
@@ -1004,7 +1005,7 @@ int sk_pool_create(const sk_pool_desc* desc, sk_pool** out)
     p->force_simple = env_on("SK_FORCE_SIMPLE");
     p->no_256 = env_on("SK_NO_256");
     p->no_small = env_on("SK_NO_SMALL");
-    p->distrust = env_on("SK_SMALL_DISTRUST");
+    if (const char* t = getenv("SK_SMALL_DISTRUST")) p->distrust = atoi(t) & 3;
     p->no_pack = env_on("SK_NO_PACK");
     p->no_interleave = env_on("SK_NO_INTERLEAVE");
     p->no_stream_loads = env_on("SK_NO_STREAM_LOADS");

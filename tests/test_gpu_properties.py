@@ -259,6 +259,61 @@ def test_merge_inside_the_kernel_equals_the_separate_combine_bit_for_bit():
         p.close()
 
 
+ONE_LAUNCH = [synth.Shape("bf16", 32, 8, 128), synth.Shape("bf16", 28, 4, 128), synth.Shape("bf16", 32, 1, 128),
+              synth.Shape("bf16", 14, 2, 64), synth.Shape("f32", 4, 4, 64), synth.Shape("f32", 8, 2, 128)]
+
+
+@pytest.mark.parametrize("shape", ONE_LAUNCH, ids=lambda s: "%s-%d-%d-%d" % (s.dtype, s.n_q_heads, s.n_kv_heads, s.head_dim))
+def test_result_does_not_depend_on_where_the_parts_ran(shape):
+    """Calls of at most 32 rows per KV head and calls of fp32 pools merge their parts in the attention launch if the
+    device says that they ran on one XCD, and compute them again if not.  With SK_SMALL_DISTRUST=1 every unit is
+    computed again: the same bits.  With 2 rows would stay unwritten where the parts did not share an XCD: they are all written,
+    so the merge is what runs here.  With 3 none is, so the switch reaches the kernel."""
+    gen = synth.generator(2, stream=800 + shape.n_q_heads + shape.n_kv_heads + shape.head_dim)
+    kw = dict(block_tokens=16, n_blocks=260, max_sessions=1, max_batch_tokens=4096)
+    pools = [_pool_with_env({"SK_SMALL_DISTRUST": str(n)}, shape, **kw) for n in range(4)]
+    sids = [p.sk_session_create() for p in pools]
+    G, nan = shape.n_q_heads // shape.n_kv_heads, float("nan")
+    merged = 0
+    for n in (300, 333, 2600):                              # cached tokens, a commit between them
+        grow = n - pools[0].sk_session_length(sids[0])
+        _, k, v = [dev(t) for t in synth.draw_qkv(gen, grow, shape)]
+        for p, s in zip(pools, sids):
+            p.sk_session_append(s, None, k, v)
+        for T in sorted({1, max(1, 16 // G), 32 // G}):
+            q, k, v = [dev(t) for t in synth.draw_qkv(gen, T, shape)]
+
+            def calls(p, s):
+                got = []
+                for what in ("append", "query A", "query B"):
+                    out = torch.full((T, shape.n_q_heads, shape.head_dim), nan, device="cuda")
+                    lse = torch.full((T, shape.n_q_heads), nan, device="cuda")
+                    launches = p.sk_pool_get_stats()["launches"]
+                    if what == "append":
+                        p.sk_session_append(s, q, k, v, out=out, lse=lse)
+                        p.sk_session_truncate(s, n)
+                    else:
+                        kv = (k, v) if what == "query B" else (None, None)
+                        p.sk_session_query(s, q, *kv, out=out, lse=lse)
+                    fused = p.sk_pool_last_launch()["fused_merge"]
+                    assert not fused or p.sk_pool_get_stats()["launches"] == launches + 1, "more than one launch"
+                    got.append((what, fused, out, lse))
+                return got
+
+            results = [calls(p, s) for p, s in zip(pools, sids)]
+            for (what, fused, out, lse), again, checked, dropped in zip(*results):
+                name = "%s n=%d T=%d" % (what, n, T)
+                assert torch.isfinite(out).all() and torch.isfinite(lse).all(), name
+                assert torch.equal(out, again[2]) and torch.equal(lse, again[3]), name + ": computed again"
+                assert torch.equal(out, checked[2]) and torch.equal(lse, checked[3]), name + ": not merged"
+                if fused:
+                    merged += 1
+                    assert torch.isnan(dropped[2]).all() and torch.isnan(dropped[3]).all(), name
+    assert merged >= 6
+    for p in pools:
+        p.close()
+
+
 def test_query_replays_from_a_hip_graph():
     """A single-session query enqueues kernels only (its decomposition and its short scatter list
     travel in the kernel arguments), so a caller can capture it in a HIP graph and replay it: every
