@@ -1594,7 +1594,10 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
         const unsigned g_magic = P.g.g_magic;
         auto div_g = [&](const int row) __attribute__((always_inline)) { return (int)(((unsigned)row * g_magic) >> 16); };
         const int tok = div_g(c < nrows ? c : 0), hq = head * G + (c < nrows ? c - tok * G : 0);
-        const float c_scale = P.g.scale_log2e;
+        // a negative scale as its size and the other sign of the scores, so that the largest score is the largest weight and a
+        // masked one has none
+        const float c_scale = fabsf(P.g.scale_log2e);
+        const uint32_t flip = P.g.scale_log2e < 0.f ? 0x80000000u : 0u;
         const bool causal = w.pos0 < SK_NO_CAUSAL;
         const int p_row = causal ? w.pos0 + tok : 0x7fffffff, p_first = causal ? w.pos0 : 0x7fffffff;
         int k_begin, k_end, o_begin = 0, o_end = 0;
@@ -1673,6 +1676,8 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
                     sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j].w, q[j].w, sc, 0, 0, 0);
                 }
                 if (more) load_k(t + 4, kp);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sc[i] = __uint_as_float(__float_as_uint(sc[i]) ^ flip);
                 const int k0 = begin + t * 16;
                 if (k0 + 16 > end || k0 + 15 + pos_shift > p_first || (k0 < hole_lo + hole_n && k0 + 16 > hole_lo)) {
 #pragma unroll

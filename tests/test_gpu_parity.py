@@ -322,6 +322,40 @@ def test_scores_that_grow_along_the_cache(hd, env):
             pr.query(sid, q[:nq], k[-nq:], v[-nq:], n_splits=S, name="query B nq=%d S=%d" % (nq, S))
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 64), (10, 2, 128)])
+def test_fp32_negative_softmax_scale(hq, hkv, d):
+    """softmax_scale may be negative: the smallest product then has the largest weight.  Scores of a few hundred (a
+    scale of -8), so that a weight taken against the wrong end of a row overflows; tiles that end inside a 16-key group,
+    causal limits and evicted tokens, so that masked keys are among them.  Scores of that size cost digits: a
+    product of d terms carries 2^-24 * |score| * log2(e) of absolute error into the exponent, here about 1e-4, which is
+    a weight's relative error, and with it the output's and the log-sum-exp's."""
+    shape = synth.Shape("f32", hq, hkv, d)
+    gen = synth.generator(1, stream=40 + hq)
+    pr = Pair(shape, n_blocks=80, max_sessions=1, kv_fill=0xFF, softmax_scale=-8.0)
+    sid = pr.create()
+
+    def close(name, out, lse, ro, rl):
+        og, lg = out.double().cpu().numpy(), lse.double().cpu().numpy()
+        assert np.isfinite(og).all() and np.isfinite(lg).all(), name
+        assert np.abs(og - ro).max() <= 2e-3 and np.abs(lg - rl).max() <= 2e-3, name
+
+    ref = pr.oracles[sid]
+    for n in (1, 40, 205, 3, 400):
+        q, k, v = synth.draw_qkv(gen, n, shape)
+        raw = [synth.to_raw(t) for t in (q, k, v)]
+        close("append %d" % n, *pr.pool.sk_session_append(sid, dev(q), dev(k), dev(v)), *ref.append(*raw))
+    for evicted in (0, 33):
+        if evicted:
+            pr.freeze(sid, 20)
+            pr.evict(sid, evicted)
+        for nq in (1, 20):
+            q, k, v = synth.draw_qkv(gen, nq, shape)
+            raw = [synth.to_raw(t) for t in (q, k, v)]
+            for S in (0, 1, 3):
+                close("query A", *pr.pool.sk_session_query(sid, dev(q), n_splits=S), *ref.query(raw[0]))
+                close("query B", *pr.pool.sk_session_query(sid, dev(q), dev(k), dev(v), n_splits=S), *ref.query(*raw))
+
+
 @pytest.mark.parametrize("scale", [0.05, 0.2])
 def test_custom_softmax_scale(scale):
     """Eq. 1's 1/sqrt(d_k) is the default, not the only scale: a pool created with softmax_scale set
