@@ -1277,11 +1277,12 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
         for (int p0 = 0; p0 < n_parts; p0 += 8) {
             float4 x[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)      // (past the last part: the last one again, with weight 0, so that no load waits for a branch)
+            for (int j = 0; j < 8; ++j)      // (past the last part: the last one again, unused, so that no load waits for a branch)
                 x[j] = *((const float4*)P.part_o + (size_t)(p0 + j < n_parts ? p0 + j : n_parts - 1) * (pstep * CPR) + at);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float wgt = p0 + j < n_parts ? ml[(p0 + j) * ROWS + row].x : 0.f;
+                if (p0 + j >= n_parts) break;
+                const float wgt = ml[(p0 + j) * ROWS + row].x;
                 acc.x = fmaf(x[j].x, wgt, acc.x); acc.y = fmaf(x[j].y, wgt, acc.y);
                 acc.z = fmaf(x[j].z, wgt, acc.z); acc.w = fmaf(x[j].w, wgt, acc.w);
             }

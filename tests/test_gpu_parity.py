@@ -356,6 +356,32 @@ def test_fp32_negative_softmax_scale(hq, hkv, d):
                 close("query B", *pr.pool.sk_session_query(sid, dev(q), dev(k), dev(v), n_splits=S), *ref.query(*raw))
 
 
+@pytest.mark.parametrize("shape,n,parts", [(synth.Shape("bf16", 32, 8, 128), 2592, 21), (synth.Shape("bf16", 14, 2, 64), 1184, 10),
+                                           (synth.Shape("f32", 4, 2, 64), 80, 2)])
+def test_infinite_value_in_the_last_part_of_a_merged_call(shape, n, parts):
+    """The workgroup that merges reads eight parts at a time: an infinite value of the last part reaches the output
+    dimension it stands in and is not met by a weight of 0 where the eight are not full."""
+    gen = synth.generator(2, stream=60 + n)
+    inf = float("inf")
+    pr = Pair(shape, n_blocks=n // 16 + 8, max_sessions=1)
+    sid = pr.create()
+    ref = pr.oracles[sid]
+    q, k, v = synth.draw_qkv(gen, n, shape)
+    v[-1, 0, 3] = 0.0
+    ref.K, ref.V = synth.to_raw(k), synth.to_raw(v)
+    v[-1, 0, 3] = inf
+    pr.pool.sk_session_append(sid, None, dev(k), dev(v))
+    q, _, _ = synth.draw_qkv(gen, 2, shape)
+    out, lse = pr.pool.sk_session_query(sid, dev(q))
+    geo = pr.pool.sk_pool_last_launch()
+    assert geo["fused_merge"] == 1 and geo["n_splits"] == parts and parts % 8
+    G = shape.n_q_heads // shape.n_kv_heads
+    assert bool((out[:, :G, 3] == inf).all())
+    ro, rl = ref.query(synth.to_raw(q))
+    out[:, :G, 3] = 0.0; ro[:, :G, 3] = 0.0
+    compare("last part", out, lse, ro, rl, shape.dtype)
+
+
 @pytest.mark.parametrize("scale", [0.05, 0.2])
 def test_custom_softmax_scale(scale):
     """Eq. 1's 1/sqrt(d_k) is the default, not the only scale: a pool created with softmax_scale set
