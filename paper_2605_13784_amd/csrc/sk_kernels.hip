@@ -1521,7 +1521,7 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
 //     (+ 64): one 16-byte load serves four of the 16-dim blocks, whose row c then is dim 4 c + block.
 // In single-session calls the call's own K/V are read where the caller has them, as further keys behind the
 // cached ones (padded to whole tiles), and a short commit runs in the same launch; in batched calls they come from
-// the staging area.  Rows past the end of a tile's keys re-read the last one (a masked key multiplies a finite value).
+// the staging area.  Rows past the end of a tile's keys re-read the last one; they count as zeros.
 // Bound: round trips and launches at the sizes in use: a 64-token append at 960 cached tokens (4 heads of 64 dims) 29.2
 // -> 8.5 us in a stream of appends, a 16-token query at 1,024 25.2 -> 7.9 (a commit or nothing, an fp32-FMA kernel of
 // 24 / 20.6 us and a combine kernel of 4.4 / 3.9 before; one launch now).
@@ -1687,6 +1687,13 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
                         const bool seen = key < end && key + pos_shift <= p_row && (unsigned)(key - hole_lo) >= (unsigned)hole_n;
                         sc[i] = seen ? sc[i] : SK_NEG_INF;
                     }
+                }
+                if (k0 + 16 > end) {              // rows behind the last key repeat it: their weight of 0 must not meet an infinity
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int h = 0; h < NH; ++h)
+                            if (k0 + g4 + i >= end) vr[i][h] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
                 const float mx = sk_max_over_groups(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]))) * c_scale;
                 const bool raise = mx > m_ref + SK_RESCALE_SLACK;

@@ -356,6 +356,51 @@ def test_fp32_negative_softmax_scale(hq, hkv, d):
                 close("query B", *pr.pool.sk_session_query(sid, dev(q), dev(k), dev(v), n_splits=S), *ref.query(*raw))
 
 
+@pytest.mark.parametrize("n", [1, 5, 16, 17, 31, 70])
+def test_fp32_infinite_value_of_the_last_token(n):
+    """An infinite value reaches the output dimension it stands in, and nothing else: also from the last cached token
+    and the last token of the call, whose tile is not full."""
+    shape = synth.Shape("f32", 4, 2, 64)
+    gen = synth.generator(1, stream=60 + n)
+    inf = float("inf")
+
+    def check(name, got, ref, tokens, lse, rl):
+        """ref, rl: the oracle's, with a zero in place of the infinities; `tokens`: the rows"""
+        got = got.double().cpu().numpy()
+        for head, dim in ((0, 3), (1, 40)):
+            for t in tokens:
+                assert (got[t, 2 * head:2 * head + 2, dim] == inf).all(), name
+            got[:, 2 * head:2 * head + 2, dim] = 0.0
+            ref[:, 2 * head:2 * head + 2, dim] = 0.0
+        assert np.abs(got - ref).max() <= 1e-5 and np.abs(lse.double().cpu().numpy() - rl).max() <= 2e-5, name
+
+    def planted(v):
+        w = v.clone()
+        w[-1, 0, 3] = inf; w[-1, 1, 40] = inf
+        return w
+
+    for own in (False, True):
+        pr = Pair(shape, n_blocks=20, max_sessions=1, kv_fill=0xFF)
+        sid = pr.create()
+        ref = pr.oracles[sid]
+        q, k, v = synth.draw_qkv(gen, n, shape)
+        v[-1, 0, 3] = 0.0; v[-1, 1, 40] = 0.0
+        pr.pool.sk_session_append(sid, None, dev(k), dev(v if own else planted(v)))
+        ref.K, ref.V = synth.to_raw(k), synth.to_raw(v)
+        q, k, v = synth.draw_qkv(gen, 2, shape)
+        for S in (0, 1):
+            if own:                                  # one token of its own, which is the last
+                k1, v1 = k[:1], v[:1].clone()
+                v1[-1, 0, 3] = 0.0; v1[-1, 1, 40] = 0.0
+                out, lse = pr.pool.sk_session_query(sid, dev(q[:1]), dev(k1), dev(planted(v1)), n_splits=S)
+                ro, rl = ref.query(synth.to_raw(q[:1]), synth.to_raw(k1), synth.to_raw(v1))
+                check("own", out, ro, [0], lse, rl)
+            else:
+                out, lse = pr.pool.sk_session_query(sid, dev(q), n_splits=S)
+                ro, rl = ref.query(synth.to_raw(q))
+                check("cached", out, ro, range(2), lse, rl)
+
+
 @pytest.mark.parametrize("shape,n,parts", [(synth.Shape("bf16", 32, 8, 128), 2592, 21), (synth.Shape("bf16", 14, 2, 64), 1184, 10),
                                            (synth.Shape("f32", 4, 2, 64), 80, 2)])
 def test_infinite_value_in_the_last_part_of_a_merged_call(shape, n, parts):
