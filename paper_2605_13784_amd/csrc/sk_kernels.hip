@@ -1389,6 +1389,19 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
                 sacc[v] = vis ? sacc[v] : SK_NEG_INF;
             }
         };
+        // Clears the values behind the first `left` keys of the tile.  Where the tile ends inside a 16-token group, the commit
+        // of this launch may be writing the slots behind its end: their weight of 0 must not meet what is found there.
+        auto drop_values = [&](const int left) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int key = 16 * q + 8 * kg + 2 * j;
+                    const uint32_t keep = (key < left ? 0xffffu : 0u) | (key + 1 < left ? 0xffff0000u : 0u);
+#pragma unroll
+                    for (int mt = 0; mt < NMT; ++mt) va[q][mt][j] &= keep;
+                }
+        };
         auto softmax = [&]() __attribute__((always_inline)) {
             float mx = SK_NEG_INF;
 #pragma unroll
@@ -1444,6 +1457,7 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
                 const int k0 = k_begin + t * 32;          // keys past the end of the part and evicted keys do not count
                 if (k0 + 32 > k_end || (k0 < P.hole_hi && k0 + 32 > P.hole_lo)) mask(k0, k_end - 1, P.hole_lo, P.hole_hi - P.hole_lo);
                 softmax();
+                if (k0 + 32 > k_end) drop_values(k_end - k0);
                 values();
                 if (more) load_v(b0, b1);
             }

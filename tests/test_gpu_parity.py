@@ -401,6 +401,40 @@ def test_fp32_infinite_value_of_the_last_token(n):
                 check("cached", out, ro, range(2), lse, rl)
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (14, 2, 64)])
+@pytest.mark.parametrize("n", [1, 15, 17, 47, 130, 777])
+def test_infinite_value_of_a_token_committed_in_the_attention_launch(hq, hkv, d, n):
+    """A short append attends to its tokens where the caller has them while the same launch commits them into the
+    16-token group in which the cached ones end: what stands behind the cached tokens there never counts, an infinite value
+    neither, whenever the commit writes it."""
+    shape = synth.Shape("bf16", hq, hkv, d)
+    gen = synth.generator(2, stream=1000 + n + d)
+    inf = float("inf")
+    pr = Pair(shape, n_blocks=n // 16 + 8, max_sessions=1)
+    sid = pr.create()
+    q, k, v = synth.draw_qkv(gen, n, shape)
+    pr.pool.sk_session_append(sid, None, dev(k), dev(v))
+    ref = pr.oracles[sid]
+    ref.K, ref.V = synth.to_raw(k), synth.to_raw(v)
+    q, k, v = synth.draw_qkv(gen, 1, shape)
+    v[-1, 0, 3] = 0.0; v[-1, hkv - 1, 40] = 0.0
+    ro, rl = ref.query(synth.to_raw(q), synth.to_raw(k), synth.to_raw(v))
+    v[-1, 0, 3] = inf; v[-1, hkv - 1, 40] = inf
+    qd, kd, vd, G = dev(q), dev(k), dev(v), hq // hkv
+    clean = torch.zeros_like(vd)
+    for rep in range(8):                       # (the group's free slots hold zeros at first, then what was there before)
+        out, lse = pr.pool.sk_session_append(sid, qd, kd, vd)
+        pr.pool.sk_session_truncate(sid, n)
+        for head, dim in ((0, 3), (hkv - 1, 40)):
+            rows = slice(head * G, (head + 1) * G)
+            assert bool((out[:, rows, dim] == inf).all()), "pass %d" % rep
+            out[:, rows, dim] = 0.0; ro[:, rows, dim] = 0.0
+        compare("pass %d" % rep, out, lse, ro, rl, shape.dtype)
+        if rep % 2:                            # zeros again
+            pr.pool.sk_session_append(sid, None, kd, clean)
+            pr.pool.sk_session_truncate(sid, n)
+
+
 @pytest.mark.parametrize("shape,n,parts", [(synth.Shape("bf16", 32, 8, 128), 2592, 21), (synth.Shape("bf16", 14, 2, 64), 1184, 10),
                                            (synth.Shape("f32", 4, 2, 64), 80, 2)])
 def test_infinite_value_in_the_last_part_of_a_merged_call(shape, n, parts):
