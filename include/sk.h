@@ -33,6 +33,7 @@
  *     pool must be issued from one thread at a time and on one stream (or be
  *     ordered externally), mirroring the paper's single GPU worker (Sec. 3.6).
  *   - Device pointers must be 16-byte aligned.
+ *   - A call's results (out, lse) may lie over its own k and v, not over its q.
  *   - Same inputs, same block tables, same n_splits => bit-identical outputs.
  *   - Token-major layouts: q [T][Hq][d], k and v [T][Hkv][d], out [T][Hq][d],
  *     lse [T][Hq] (natural-log log-sum-exp of the scaled scores, float).

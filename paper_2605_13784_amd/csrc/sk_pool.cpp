@@ -564,6 +564,32 @@ int scatter_launch(sk_pool* p, const ScatterSlot& ss, const std::vector<sk_scatt
     return SK_OK;
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + nb && y < x + na;
+}
+
+// Whether a call of T tokens writes its results over its own k or v.  Where the attention launch reads those in place, some of
+// its workgroups would do so after others have written.
+bool results_over_own(const sk_pool* p, int64_t T, const void* k, const void* v, const void* out, int out_dtype, const float* lse)
+{
+    const size_t kv = size_t(T) * p->d.n_kv_heads * p->d.head_dim * p->L.elem, rows = size_t(T) * p->d.n_q_heads;
+    const size_t n_out = rows * p->d.head_dim * (out_dtype == SK_F32 ? 4 : 2);
+    return overlap(out, n_out, k, kv) || overlap(out, n_out, v, kv) || overlap(lse, rows * 4, k, kv) || overlap(lse, rows * 4, v, kv);
+}
+
+// Copies a call's own k and v, as they are, to the staging area, which holds twice max_batch_tokens rows.
+int copy_own(sk_pool* p, int64_t T, const void** k, const void** v, hipStream_t st)
+{
+    const size_t bytes = size_t(T) * p->d.n_kv_heads * p->d.head_dim * p->L.elem;
+    unsigned char* to = (unsigned char*)p->d.workspace + p->L.off_eph;
+    SK_HIP(hipMemcpyAsync(to, *k, bytes, hipMemcpyDeviceToDevice, st));
+    SK_HIP(hipMemcpyAsync(to + bytes, *v, bytes, hipMemcpyDeviceToDevice, st));
+    *k = to; *v = to + bytes;
+    return SK_OK;
+}
+
 // Takes `need` blocks for the session (caller has checked availability).
 void take_blocks(sk_pool* p, Session* s, int64_t need)
 {
@@ -1147,6 +1173,7 @@ int sk_session_append(sk_pool* p, int32_t id, const void* q, const void* k, cons
     const bool one_launch = in_place && scatter_groups(n, L) <= SK_COMMIT_ITEMS;      // the attention launch commits too
     ScatterSlot ss;
     { int rc = scatter_reserve(p, scatter_groups(n, L), ss); if (rc) return rc; }
+    if (in_place && p->device && results_over_own(p, L, k, v, out, out_dtype, lse)) { int rc = copy_own(p, L, &k, &v, st); if (rc) return rc; }
     // from here on only a failing HIP call can stop the call; what it changed is taken back
     Undo u;
     int64_t first_new = 0;
@@ -1194,8 +1221,10 @@ int sk_session_query(sk_pool* p, int32_t id, const void* q, const void* k, const
     // Own K/V are read where they lie, or staged by the attention kernel: with one row tile per KV head one workgroup of
     // each head attends to them, and up to 64 tokens take it less time than the others their keys.
     const bool in_place = plan.L.own_mode != SK_OWN_NONE;
-    const bool stages = !in_place && plan.L.n_tiles == 1 && plan.v.id != SK_KV_SIMPLE && nq <= SK_STAGE_TOKENS;
+    const bool over = k && results_over_own(p, nq, k, v, out, out_dtype, lse);
+    const bool stages = !in_place && !over && plan.L.n_tiles == 1 && plan.v.id != SK_KV_SIMPLE && nq <= SK_STAGE_TOKENS;
     if (k && stages && inject(p, SK_SITE_SCATTER)) return SK_E_HIP;
+    if (in_place && over) { rc = copy_own(p, nq, &k, &v, st); if (rc) return rc; }
     if (k && (in_place || stages)) { plan.own_k = k; plan.own_v = v; }
     else if (k) {
         ScatterSlot ss;

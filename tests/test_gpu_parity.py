@@ -435,6 +435,49 @@ def test_infinite_value_of_a_token_committed_in_the_attention_launch(hq, hkv, d,
             pr.pool.sk_session_truncate(sid, n)
 
 
+@pytest.mark.parametrize("shape,tokens", [(synth.Shape("bf16", 8, 8, 128), (1, 20, 60)), (synth.Shape("bf16", 4, 4, 64), (3, 32, 70)),
+                                          (synth.Shape("bf16", 32, 8, 128), (5, 16)), (synth.Shape("f32", 4, 4, 64), (3, 60, 150))])
+@pytest.mark.parametrize("n", [0, 40, 1100])
+def test_results_over_the_calls_own_keys_and_values(shape, tokens, n):
+    """The buffers of a call's own k and v may be given for its results too: the keys and values count as they were when
+    the call was made, and an append commits them so.  fp32 results over k and v that lie one behind the other, results
+    of the pool's type exactly over v, and the log-sum-exp over k."""
+    gen = synth.generator(2, stream=1100 + n + shape.n_q_heads)
+    pr = Pair(shape, n_blocks=n // 16 + 60, max_sessions=1)
+    sid = pr.create()
+    ref = pr.oracles[sid]
+    if n:
+        q, k, v = synth.draw_qkv(gen, n, shape)
+        pr.pool.sk_session_append(sid, None, dev(k), dev(v))
+        ref.K, ref.V = synth.to_raw(k), synth.to_raw(v)
+    el = 2 if shape.dtype == "bf16" else 4
+    rows, d = shape.n_q_heads, shape.head_dim
+    for T in tokens:
+        for call in (pr.pool.sk_session_query, pr.pool.sk_session_append):
+            for how in ("f32 over both", "over v", "lse over k"):
+                q, k, v = synth.draw_qkv(gen, T, shape)
+                if call == pr.pool.sk_session_query:
+                    ro, rl = ref.query(synth.to_raw(q), synth.to_raw(k), synth.to_raw(v))
+                else:
+                    ro, rl = ref.append(synth.to_raw(q), synth.to_raw(k), synth.to_raw(v))
+                own = k.numel() * el
+                buf = torch.empty(max(2 * own, own + T * rows * d * 4), dtype=torch.uint8, device="cuda")
+                kd, vd = (buf[a:a + own].view(k.dtype).view(k.shape) for a in (0, own))
+                kd.copy_(dev(k)); vd.copy_(dev(v))
+                out_dtype = shape.dtype if how == "over v" else "f32"
+                out = torch.empty((T, rows, d), dtype=torch.float32, device="cuda")
+                lse = torch.empty((T, rows), dtype=torch.float32, device="cuda")
+                if how == "f32 over both":
+                    out = buf[:T * rows * d * 4].view(torch.float32).view(T, rows, d)
+                elif how == "over v":
+                    out = buf[own:own + T * rows * d * el].view(k.dtype).view(T, rows, d)
+                else:
+                    lse = buf[:T * rows * 4].view(torch.float32).view(T, rows)
+                call(sid, dev(q), kd, vd, out=out, lse=lse, out_dtype=out_dtype)
+                compare("%s T=%d %s" % (call.__name__, T, how), out, lse, ro, rl, shape.dtype, out_dtype == "bf16")
+    pr.check_cache(sid)
+
+
 @pytest.mark.parametrize("shape,n,parts", [(synth.Shape("bf16", 32, 8, 128), 2592, 21), (synth.Shape("bf16", 14, 2, 64), 1184, 10),
                                            (synth.Shape("f32", 4, 2, 64), 80, 2)])
 def test_infinite_value_in_the_last_part_of_a_merged_call(shape, n, parts):
