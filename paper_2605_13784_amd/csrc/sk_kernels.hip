@@ -451,7 +451,8 @@ __device__ __forceinline__ void sk_stage_own(const sk_launch& P, const sk_work& 
         *(uint4*)(base + (int64_t)grp * P.g.eph_blk_stride + P.g.eph_v_off + dim * 32 + (i & 1) * 16) =
             make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
     }
-    __syncthreads();                                        // the stores have completed; LDS is free again
+    SK_WAIT_VMCNT(0);                                       // this wave's stores have completed (the barrier alone orders LDS)
+    __syncthreads();                                        // so have the others'; LDS is free again
 }
 
 template <int NRG, int NPH, int NSS, int D>
