@@ -1269,23 +1269,26 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
         if (row < nrows && sub == 0) tot[row] = make_float4(M2, L, Lx, 0.f);
     }
     __syncthreads();
+    // (buffer loads return zeros behind the unit's last part, so that the last round needs no branch around its loads)
+    const unsigned step = (unsigned)(pstep * D * 4);                   // bytes from part to part
+    const __amdgpu_buffer_rsrc_t parts = __builtin_amdgcn_make_buffer_rsrc(P.part_o + (size_t)row0 * D, 0, (int)((unsigned)n_parts * step), 0x00020000);
 #pragma unroll 1
     for (int i = tid; i < nrows * CPR; i += 256) {
         const int row = i / CPR;
-        const unsigned at = row0 * CPR + (unsigned)i;                  // in float4, from a part's first row
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 1
         for (int p0 = 0; p0 < n_parts; p0 += 8) {
             float4 x[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j)      // (past the last part: the last one again, unused, so that no load waits for a branch)
-                x[j] = *((const float4*)P.part_o + (size_t)(p0 + j < n_parts ? p0 + j : n_parts - 1) * (pstep * CPR) + at);
+            float wgt[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                if (p0 + j >= n_parts) break;
-                const float wgt = ml[(p0 + j) * ROWS + row].x;
-                acc.x = fmaf(x[j].x, wgt, acc.x); acc.y = fmaf(x[j].y, wgt, acc.y);
-                acc.z = fmaf(x[j].z, wgt, acc.z); acc.w = fmaf(x[j].w, wgt, acc.w);
+                x[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(parts, (unsigned)(p0 + j) * step + (unsigned)i * 16, 0, 0));
+                wgt[j] = ml[(p0 + j < n_parts ? p0 + j : n_parts - 1) * ROWS + row].x;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                acc.x = fmaf(x[j].x, wgt[j], acc.x); acc.y = fmaf(x[j].y, wgt[j], acc.y);
+                acc.z = fmaf(x[j].z, wgt[j], acc.z); acc.w = fmaf(x[j].w, wgt[j], acc.w);
             }
         }
         const float4 t = tot[row];

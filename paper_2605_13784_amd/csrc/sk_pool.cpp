@@ -301,6 +301,15 @@ struct RegPlan {
     bool enqueued = false;                             // set by launch_regular once the attention kernel is on the stream
 };
 
+// Whether the last workgroup of a unit can merge its parts: few enough for one workgroup to read, and within reach of
+// 32-bit offsets in the rounds of eight it reads them in.
+bool can_merge(const sk_pool* p, const Variant& v, int64_t tile_rows, int64_t parts)
+{
+    const int64_t rounds = (tile_rows * p->d.head_dim + 1023) / 1024 * ((parts + 7) / 8);
+    const int64_t step = int64_t(p->d.n_kv_heads) * v.rows_per_slot * p->d.head_dim * 4;
+    return parts > 1 && parts <= p->d.head_dim && rounds <= 8 && (parts + 7) * step < (int64_t(1) << 32);
+}
+
 // The kernel for at most 32 rows per KV head: cached tokens in parts of whole 32-key tiles, four waves to a
 // part; own_cnt tokens of the call itself (uncommitted, or being appended) behind them.
 int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits_req, RegPlan& R)
@@ -327,8 +336,7 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
     // Measured (parts x rows, us per query, merged by the last workgroup against the combine kernel): 21 x 4 rows 8.1
     // against 10.8, 21 x 16 10.1 against 11.8, 20 x 20 12.8 against 12.5, 21 x 32 16.6 against 12.3.  It reads eight parts
     // of 2,048 / head_dim output rows in one round.
-    const int64_t rounds = (int64_t(L.n_tok) * p->L.G * p->d.head_dim + 1023) / 1024 * ((parts + 7) / 8);
-    L.fuse = (parts > 1 && parts <= p->d.head_dim && rounds <= 8) ? 1 : 0;
+    L.fuse = can_merge(p, R.v, int64_t(L.n_tok) * p->L.G, parts) ? 1 : 0;
     L.head_pad = L.fuse ? (int32_t)((Hkv + 7) / 8 * 8) : (int32_t)Hkv;
     L.by_pad = sk_make_div((uint32_t)L.head_pad);
     L.distrust = p->distrust;
@@ -353,8 +361,7 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
     L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts; L.by_chunk = sk_make_div((uint32_t)chunk);
     L.own_cnt = own_cnt; L.own_mode = SK_OWN_F32;
     // merged by the last workgroup of a unit while that is a few rounds of loads (see plan_small)
-    const int64_t rounds = (int64_t(R.v.tok_per_tile) * p->L.G * p->d.head_dim + 1023) / 1024 * ((parts + 7) / 8);
-    L.fuse = (parts > 1 && parts <= p->d.head_dim && rounds <= 8 && units * 16 <= p->L.sync_units) ? 1 : 0;
+    L.fuse = (can_merge(p, R.v, int64_t(R.v.tok_per_tile) * p->L.G, parts) && units * 16 <= p->L.sync_units) ? 1 : 0;
     const int64_t pad = L.fuse ? (units + 7) / 8 * 8 : units;
     if (pad * parts > (int64_t(1) << 30)) return SK_E_WORKSPACE;
     L.head_pad = (int32_t)pad; L.by_pad = sk_make_div((uint32_t)pad); L.by_tiles = sk_make_div((uint32_t)L.n_tiles);
