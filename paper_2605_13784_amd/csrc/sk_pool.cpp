@@ -326,7 +326,7 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
         const int64_t last = kv_len - (S - 1) * chunk;          // keys of the last part
         // the own tokens are a tile of the last part if a wave is free there, else a part of their own
         parts = std::max<int64_t>(1, S + ((own_cnt > 0 && S > 0 && (last + 31) / 32 > 3) ? 1 : 0));
-        if (S == 1 && parts == 2 && n_splits_req == 1) parts = 1;
+        if (S == 1 && parts == 2 && (n_splits_req == 1 || cap < 2)) parts = 1;      // (or a fifth tile of one workgroup)
         if (parts <= 1 || parts <= cap) break;
     }
     L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts;
@@ -336,7 +336,7 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
     // Measured (parts x rows, us per query, merged by the last workgroup against the combine kernel): 21 x 4 rows 8.1
     // against 10.8, 21 x 16 10.1 against 11.8, 20 x 20 12.8 against 12.5, 21 x 32 16.6 against 12.3.  It reads eight parts
     // of 2,048 / head_dim output rows in one round.
-    L.fuse = can_merge(p, R.v, int64_t(L.n_tok) * p->L.G, parts) ? 1 : 0;
+    L.fuse = (can_merge(p, R.v, int64_t(L.n_tok) * p->L.G, parts) && Hkv * 16 <= p->L.sync_units) ? 1 : 0;
     L.head_pad = L.fuse ? (int32_t)((Hkv + 7) / 8 * 8) : (int32_t)Hkv;
     L.by_pad = sk_make_div((uint32_t)L.head_pad);
     L.distrust = p->distrust;
@@ -357,7 +357,6 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
         parts = std::max<int64_t>(1, (keys + chunk - 1) / chunk);
         if (parts <= 1 || parts <= cap) break;
     }
-    if (parts > 1 && parts > cap) return SK_E_WORKSPACE;
     L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts; L.by_chunk = sk_make_div((uint32_t)chunk);
     L.own_cnt = own_cnt; L.own_mode = SK_OWN_F32;
     // merged by the last workgroup of a unit while that is a few rounds of loads (see plan_small)

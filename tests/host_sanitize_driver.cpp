@@ -119,6 +119,17 @@ int main(int argc, char** argv)
         CHECK(sk_pool_blocks_free(p, &f) == SK_OK && f == d.n_blocks);
         CHECK(sk_pool_destroy(p) == SK_OK);
     }
+    {   // Thousands of KV heads and a small batch limit: the workspace holds one partial per head.  A short append whose
+        // last part has no free wave for its own tokens (from 97 cached ones on) then takes one part.
+        sk_pool_desc d = {};
+        d.dtype = SK_BF16; d.n_q_heads = d.n_kv_heads = 5000; d.head_dim = 64; d.block_tokens = 16; d.max_sessions = 1;
+        d.n_blocks = 8; d.max_batch_tokens = 1; d.flags = SK_POOL_METADATA_ONLY;
+        sk_pool* p = nullptr;
+        int32_t id = -1;
+        CHECK(sk_pool_create(&d, &p) == SK_OK && sk_session_create(p, &id) == SK_OK);
+        for (int i = 0; i < 104; ++i) CHECK(sk_session_append(p, id, nullptr, nullptr, nullptr, 1, nullptr, SK_F32, nullptr, nullptr) == SK_OK);
+        CHECK(sk_pool_destroy(p) == SK_OK);
+    }
     std::printf("host walk ok\n");
     return 0;
 }
