@@ -250,10 +250,15 @@ struct Variant { int id; int rows_per_slot; int tok_per_tile; };
 // `allow_256`: the caller can launch one workgroup per CU (single-session calls), which the
 // 256-row tile with its 128 KiB key ring needs.
 // `cached` >= 0: a single-session call over so many cached tokens, which may take the kernel for at most 32 rows.  Up to
-// 128 MiB of cached K/V: from there on the ring kernel's stream is the better one (us per query, ring and combine
-// kernel -> this one, at 32 query heads on 8 KV heads of 128 dims: one query token at 1,024 cached 12.5 -> 7.6, 2,600
-// 13.8 -> 8.1, 9,001 17.6 -> 12.9, 20,000 24.4 -> 19.5, 32,768 31.7 -> 31.6, 131,072 90.2 -> 96.8; eight at 2,600
-// 14.4 -> 12.0, 9,001 18.1 -> 14.9, 32,768 32.3 -> 32.9).
+// 128 MiB of cached K/V, where the ring kernel's stream gets close (us per cache-only query in a stream of them, ring and combine
+// kernel -> this one, one query token / 32 rows):
+//   heads         2,600 cached              9,001                     32,768                    65,536       131,072
+//   32/8  d 128   13.6 ->  8.5/14.6 -> 12.8 17.9 -> 11.9/18.0 -> 15.0 32.8 -> 26.6/33.1 -> 28.8 -            (90.2 -> 96.8)
+//   28/4  d 128   13.6 ->  8.5/14.5 -> 11.9 16.6 -> 12.8/17.1 -> 14.4 24.3 -> 21.1/24.8 -> 22.1 34.6 -> 29.4 -
+//    8/1  d 128   13.5 ->  8.7/14.5 -> 11.5 15.4 -> 12.6/16.2 -> 13.6 22.7 -> 16.4/23.2 -> 17.5 33.1 -> 21.0 38.6 -> 28.0
+//   24/12 d 128   13.9 ->  8.9/14.8 -> 11.9 19.9 -> 15.3/20.2 -> 16.9 -                         -            -
+//   14/2  d 64    11.8 ->  8.5/12.1 ->  8.6 13.6 ->  8.4/14.1 ->  9.7 20.3 -> 13.1/20.5 -> 13.7 24.0 -> 17.0 30.8 -> 24.6
+//   32/8  d 64    12.0 ->  8.3/12.3 ->  8.8 14.3 ->  8.5/14.5 ->  9.8 24.3 -> 17.0/24.3 -> 19.6 38.1 -> 26.5 -
 constexpr int64_t kSmallMaxBytes = int64_t(128) << 20;
 bool pick_variant(const sk_pool* p, int64_t n_tok, Variant& v, bool allow_256 = false, int64_t cached = -1)
 {
@@ -316,27 +321,43 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
 {
     sk_launch& L = R.L;
     const int64_t Hkv = p->d.n_kv_heads, cap = p->L.part_slots * kPartSlotRows / (Hkv * R.v.rows_per_slot);
-    int64_t S = n_splits_req > 0 ? n_splits_req : std::max<int64_t>(1, (p->target_wgs_set ? p->target_wgs : p->n_cus) / Hkv);
-    int64_t chunk = kv_len > 0 ? (kv_len + S - 1) / S : 64;
-    if (n_splits_req <= 0) chunk = std::max<int64_t>((chunk + 127) / 128 * 128, 128);      // a tile for every wave
-    chunk = (chunk + 63) / 64 * 64;
-    int64_t parts;
-    for (;; chunk *= 2) {
-        S = (kv_len + chunk - 1) / chunk;
-        const int64_t last = kv_len - (S - 1) * chunk;          // keys of the last part
-        // the own tokens are a tile of the last part if a wave is free there, else a part of their own
-        parts = std::max<int64_t>(1, S + ((own_cnt > 0 && S > 0 && (last + 31) / 32 > 3) ? 1 : 0));
-        if (S == 1 && parts == 2 && (n_splits_req == 1 || cap < 2)) parts = 1;      // (or a fifth tile of one workgroup)
-        if (parts <= 1 || parts <= cap) break;
-    }
-    L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts;
-    L.own_cnt = own_cnt; L.own_mode = SK_OWN_SMALL;
+    int64_t chunk = 0, parts = 1;
+    auto cut = [&](int64_t S) {
+        chunk = kv_len > 0 ? (kv_len + S - 1) / S : 64;
+        if (n_splits_req <= 0) chunk = std::max<int64_t>((chunk + 127) / 128 * 128, 128);      // a tile for every wave
+        chunk = (chunk + 63) / 64 * 64;
+        for (;; chunk *= 2) {
+            S = (kv_len + chunk - 1) / chunk;
+            const int64_t last = kv_len - (S - 1) * chunk;          // keys of the last part
+            // the own tokens are a tile of the last part if a wave is free there, else a part of their own
+            parts = std::max<int64_t>(1, S + ((own_cnt > 0 && S > 0 && (last + 31) / 32 > 3) ? 1 : 0));
+            if (S == 1 && parts == 2 && (n_splits_req == 1 || cap < 2)) parts = 1;      // (or a fifth tile of one workgroup)
+            if (parts <= 1 || parts <= cap) break;
+        }
+    };
     // The last workgroup to finish merges the parts of a KV head (they lie a multiple of 8 workgroups apart, hence on
     // one XCD) if they are few enough for one workgroup to read.
-    // Measured (parts x rows, us per query, merged by the last workgroup against the combine kernel): 21 x 4 rows 8.1
-    // against 10.8, 21 x 16 10.1 against 11.8, 20 x 20 12.8 against 12.5, 21 x 32 16.6 against 12.3.  It reads eight parts
+    // Measured (parts x rows, us per query, merged by the last workgroup against the combine kernel): 21 x 4 rows 8.6
+    // against 12.0, 21 x 16 9.4 against 12.4, 20 x 20 12.8 against 12.5, 21 x 32 13.7 against 13.3.  It reads eight parts
     // of 2,048 / head_dim output rows in one round.
-    L.fuse = (can_merge(p, R.v, int64_t(L.n_tok) * p->L.G, parts) && Hkv * 16 <= p->L.sync_units) ? 1 : 0;
+    // A head then has the CUs of one XCD.  Where the heads are no multiple of 8, others have less to do or nothing: up to
+    // 4 MiB of K/V for the busiest XCD the launch saved is worth more than that (us per query of one token, merged in the
+    // launch against by the combine kernel: 8 heads on 1, 5,000 cached tokens 9.4 against 11.9, 6,500 10.0 - 12.0, 9,001
+    // 12.0 - 12.8, 13,000 14.5 - 13.7, 32,768 21.7 - 16.4; 12 on 4, 6,500 9.9 - 11.9, 13,000 15.5 - 13.1, 65,536 42.8 - 29.6; 24
+    // on 12, 3,500 9.2 - 11.9, 5,000 13.8 - 11.9, 13,000 22.5 - 18.5), and the parts are cut for its CUs alone.
+    // For the combine kernel, which reads the statistics of 64 parts at once, no more than 64 of up to 1,024 keys (8
+    // heads on 1: 32,768 tokens in 256 parts 27.9, 128 19.9, 64 16.4, 32 18.3; 65,536 28.9 - 21.3 - 20.7 - 26.9).
+    constexpr int64_t kXcds = 8, kOneXcdBytes = int64_t(4) << 20;
+    const int64_t wanted = std::max<int64_t>(1, (p->target_wgs_set ? p->target_wgs : p->n_cus) / Hkv);
+    const int64_t heads_per_xcd = (Hkv + kXcds - 1) / kXcds;
+    const bool even = Hkv % kXcds == 0;
+    if (even || kv_len * heads_per_xcd * p->d.head_dim * 4 <= kOneXcdBytes) {
+        cut(n_splits_req > 0 ? n_splits_req : even ? wanted : std::min(wanted, std::max<int64_t>(1, p->n_cus / kXcds / heads_per_xcd)));
+        L.fuse = (can_merge(p, R.v, int64_t(L.n_tok) * p->L.G, parts) && Hkv * 16 <= p->L.sync_units) ? 1 : 0;
+    }
+    if (!L.fuse) cut(n_splits_req > 0 ? n_splits_req : std::min(wanted, std::max<int64_t>(64, kv_len / 1024)));
+    L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts;
+    L.own_cnt = own_cnt; L.own_mode = SK_OWN_SMALL;
     L.head_pad = L.fuse ? (int32_t)((Hkv + 7) / 8 * 8) : (int32_t)Hkv;
     L.by_pad = sk_make_div((uint32_t)L.head_pad);
     L.distrust = p->distrust;

@@ -238,6 +238,40 @@ def test_calls_of_at_most_32_rows(hq, hkv, d, env):
             pr.append(sid, q, k, v, name="append behind a hole")
 
 
+@pytest.mark.parametrize("hq,hkv,d,most,parts", [(4, 1, 128, 8192, 32), (4, 4, 64, 16384, 32), (12, 12, 128, 4096, 16), (10, 10, 64, 8192, 16)])
+def test_short_calls_where_the_kv_heads_do_not_fill_the_xcds(hq, hkv, d, most, parts):
+    """With KV heads that are no multiple of 8 the parts are merged in the launch (and cut for the CUs of one XCD) up to
+    `most` cached tokens, behind that by the combine kernel; 40 parts that only a caller's n_splits asks for, and the
+    64 parts that the combine kernel is given at most, among them."""
+    shape = synth.Shape("bf16", hq, hkv, d)
+    gen = synth.generator(2, stream=1200 + hq + d)
+    pr = Pair(shape, n_blocks=(most + 40) // 16 + 300, max_sessions=1, max_batch_tokens=4096)
+    sid = pr.create()
+    ref = pr.oracles[sid]
+    k, v = [], []
+
+    def grow(n):
+        while ref.K.shape[0] < n:
+            _, k, v = synth.draw_qkv(gen, min(4096, n - ref.K.shape[0]), shape)
+            pr.pool.sk_session_append(sid, None, dev(k), dev(v))
+            ref.K, ref.V = np.concatenate([ref.K, synth.to_raw(k)]), np.concatenate([ref.V, synth.to_raw(v)])
+
+    for n, merged in ((most, True), (most + 1, False), (most + 4000, False)):
+        grow(n)
+        for nq, S in ((1, 0), (2, 0), (2, 40)):
+            q, k, v = synth.draw_qkv(gen, nq, shape)
+            pr.query(sid, q, n_splits=S, name="query A n=%d nq=%d S=%d" % (n, nq, S))
+            geo = pr.pool.sk_pool_last_launch()
+            assert geo["kernel_variant"] == 5 and geo["fused_merge"] == (merged and (S == 0 or d == 64 or nq * hq // hkv <= 8))
+            if S == 0:
+                assert geo["n_splits"] == parts if merged else geo["n_splits"] <= 64
+            pr.query(sid, q, k, v, n_splits=S, name="query B n=%d nq=%d S=%d" % (n, nq, S))
+        q, k, v = synth.draw_qkv(gen, 1, shape)
+        pr.append(sid, q, k, v, name="append n=%d" % n)
+        pr.pool.sk_session_truncate(sid, n)
+        ref.truncate(n)
+
+
 @pytest.mark.parametrize("hq,hkv,d,env", [(4, 4, 64, None), (8, 2, 128, None), (16, 1, 64, None), (10, 2, 128, None),
                                           (8, 2, 128, {"SK_SMALL_DISTRUST": "1"})])
 def test_fp32_kernel(hq, hkv, d, env):
