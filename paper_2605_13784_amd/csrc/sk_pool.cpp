@@ -748,8 +748,10 @@ void add_tiles(ListGroup& g, const TileReq& base, int32_t q_row0, int32_t T)
     }
 }
 
-int64_t list_parts(const TileReq& t, int64_t chunk) { return std::max<int64_t>(1, (t.kv_vis + chunk - 1) / chunk); }
-int32_t list_bucket(int64_t len, int64_t chunk) { return int32_t(len * 8 / chunk); }
+// Pieces of at most `chunk` keys that a tile is cut into (a tile that sees no cached key is one piece), and which eighth of
+// a chunk a piece's length falls into.  Lengths and chunks stay below 2^30.
+uint32_t list_parts(const TileReq& t, uint32_t chunk) { return t.kv_vis > 0 ? ((uint32_t)t.kv_vis + chunk - 1) / chunk : 1; }
+uint32_t list_bucket(uint32_t len, uint32_t chunk) { return len == chunk ? 8 : uint32_t(uint64_t(len) * 8 / chunk); }
 
 // Length of the pieces a launch's tiles are cut into: the one for which the launch is expected to end first.
 // The workgroups are taken up in order by the CUs that become free (those of a KV head by that head's share of
@@ -761,6 +763,8 @@ int32_t list_bucket(int64_t len, int64_t chunk) { return int32_t(len * 8 / chunk
 // 4.05 ms (append launch 4.25 -> 3.76: no 19,648-key pieces that end in a ragged last round, tiles whole and
 // longest first; combine kernels 0.16 -> 0.02); 64 questions at 64K 1.13 -> 1.04 ms (7 pieces per tile, 3.5
 // rounds of the chip -> 2 pieces, one round).
+// The schedule is only played through where simple bounds of its end (the average load, the longest piece) do not
+// say already that the length is no better, and no further than to where it is known to be none.
 int64_t list_chunk(const sk_pool* p, const ListGroup& g)
 {
     int64_t longest = 0;
@@ -768,42 +772,58 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g)
     if (longest == 0) return 256;
     const int Hkv = p->d.n_kv_heads;
     const bool big = g.v.id == SK_KV_MFMA256;
+    const size_t n_tiles = g.tiles.size();
     double best = 0; int64_t best_chunk = 0, last = 0;
-    std::vector<double> free_at;
-    std::vector<int32_t> rest[9];
+    std::vector<double> lane;                              // when each lane is free: a heap, the first one on top
+    std::vector<int32_t> rest(n_tiles), ordered(n_tiles);  // iterations of each tile's last piece; the same, longest eighths first
+    std::vector<uint8_t> bucket(n_tiles);
     for (int64_t k = 1; k <= 256; k += std::max<int64_t>(1, k / 4)) {
         const int64_t chunk = std::max<int64_t>(256, ((longest + k - 1) / k + 63) / 64 * 64);
         if (chunk == last) break;
         last = chunk;
-        int64_t whole = 0, parts = 0, n = 0;
-        for (auto& r : rest) r.clear();
-        for (const TileReq& t : g.tiles) {
-            const int64_t np = list_parts(t, chunk);
-            n += np;
+        int64_t whole = 0, parts = 0, its_sum = 0, its_max = 0;
+        size_t count[9] = {};
+        for (size_t i = 0; i < n_tiles; ++i) {
+            const uint32_t np = list_parts(g.tiles[i], (uint32_t)chunk), left = (uint32_t)g.tiles[i].kv_vis - (np - 1) * (uint32_t)chunk;
             if (np > 1) parts += np;
-            const int64_t left = t.kv_vis - (np - 1) * chunk;
             whole += np - 1;
-            rest[list_bucket(left, chunk)].push_back(int32_t((left + 63) / 64));
+            rest[i] = int32_t((left + 63) / 64);
+            bucket[i] = (uint8_t)list_bucket(left, (uint32_t)chunk);
+            ++count[bucket[i]];
+            its_sum += rest[i]; its_max = std::max<int64_t>(its_max, rest[i]);
         }
+        const int64_t n = whole + (int64_t)n_tiles;
         const bool sparse = big || n * Hkv <= p->n_cus;
         const double it = big ? 1.7 : (sparse ? 1.4 : 2.7), ends = 6.0;
-        const size_t lanes = (size_t)std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
+        const int64_t lanes = std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
+        const double merge = double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0;
         // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
-        const double c = double(chunk / 64) * it + ends;
-        free_at.assign(lanes, c * double(whole / (int64_t)lanes));
-        for (int64_t i = 0; i < whole % (int64_t)lanes; ++i) free_at[(size_t)i] += c;
-        auto later = [](double x, double y) { return x > y; };
-        std::make_heap(free_at.begin(), free_at.end(), later);
-        double end = *std::max_element(free_at.begin(), free_at.end());
-        for (int b = 8; b >= 0; --b)
-            for (int32_t its : rest[b]) {
-                std::pop_heap(free_at.begin(), free_at.end(), later);
-                free_at.back() += double(its) * it + ends;
-                end = std::max(end, free_at.back());
-                std::push_heap(free_at.begin(), free_at.end(), later);
+        const double c = double(chunk / 64) * it + ends, base = c * double(whole / lanes);
+        const int64_t ahead = whole % lanes;               // lanes with one whole chunk more than the others
+        auto no_better = [&](double end) { return best_chunk != 0 && !(end + merge < 0.995 * best); };
+        double end = std::max(ahead > 0 ? base + c : base, base + (double(its_max) * it + ends));
+        const double load = (double(whole) * c + double(its_sum) * it + double(n_tiles) * ends) / double(lanes);
+        if (no_better(std::max(end, load * (1 - 1e-9)))) continue;
+        if ((int64_t)n_tiles > lanes - ahead) {            // (else each gets a lane that is free at `base`)
+            size_t at[9], sum = 0;
+            for (int b = 8; b >= 0; --b) { at[b] = sum; sum += count[b]; }
+            for (size_t i = 0; i < n_tiles; ++i) ordered[at[bucket[i]]++] = rest[i];
+            lane.assign((size_t)lanes, base + c);
+            std::fill(lane.begin(), lane.begin() + (lanes - ahead), base);
+            for (size_t i = 0; i < n_tiles && !no_better(end); ++i) {
+                const double x = lane[0] + (double(ordered[i]) * it + ends);
+                end = std::max(end, x);
+                size_t hole = 0;                           // x takes its place in the heap from the top
+                for (size_t kid = 1; kid < (size_t)lanes; kid = 2 * hole + 1) {
+                    if (kid + 1 < (size_t)lanes && lane[kid + 1] < lane[kid]) ++kid;
+                    if (!(lane[kid] < x)) break;
+                    lane[hole] = lane[kid]; hole = kid;
+                }
+                lane[hole] = x;
             }
-        end += double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0;
-        if (best_chunk == 0 || end < 0.995 * best) { best = end; best_chunk = chunk; }
+            if (no_better(end)) continue;
+        }
+        best = end + merge; best_chunk = chunk;
     }
     return best_chunk;
 }
@@ -848,11 +868,13 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
             P.rows_base[gi] = rows_used;
             int64_t slot = 0;       // in units of this group's rows_per_slot, from rows_base
             struct Piece { int32_t tile, part, bucket; };
-            std::vector<Piece> pieces;
+            std::vector<Piece> pieces, ordered;
             std::vector<int32_t> nparts(g.tiles.size()), slot0(g.tiles.size()), unit0(g.tiles.size());
+            size_t n_pieces = 0, at[9] = {};
             for (size_t i = 0; i < g.tiles.size(); ++i) {
-                const int32_t np = (int32_t)list_parts(g.tiles[i], chunk);
+                const int32_t np = (int32_t)list_parts(g.tiles[i], (uint32_t)chunk);
                 nparts[i] = np;
+                n_pieces += (size_t)np;
                 slot0[i] = np > 1 ? (int32_t)slot : -1;
                 unit0[i] = np > 1 ? (int32_t)unit : -1;
                 if (np > 1) { slot += int64_t(np) * Hkv; unit += Hkv; }
@@ -861,6 +883,7 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
             // each tile, falling in eighths of a chunk), so that the launch ends evenly; among equals the tiles
             // of a session side by side, one part after the other, so that what runs at the same time reads
             // the same keys through the L2.
+            pieces.reserve(n_pieces);
             size_t i0 = 0;
             while (i0 < g.tiles.size()) {
                 size_t i1 = i0;
@@ -870,27 +893,33 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
                     for (size_t i = i0; i < i1; ++i)
                         if (part < nparts[i]) {
                             const int64_t len = std::min<int64_t>(g.tiles[i].kv_vis - int64_t(part) * chunk, chunk);
-                            pieces.push_back(Piece{(int32_t)i, part, list_bucket(len, chunk)});
+                            const int32_t bucket = (int32_t)list_bucket((uint32_t)len, (uint32_t)chunk);
+                            pieces.push_back(Piece{(int32_t)i, part, bucket});
+                            if (bucket > 0) ++at[bucket - 1];
                         }
                 i0 = i1;
             }
-            std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.bucket > y.bucket; });
-            for (const Piece& pc : pieces) {
+            for (int b = 7; b > 0; --b) at[b - 1] += at[b];       // at[b]: pieces of longer eighths than b
+            ordered.resize(n_pieces);
+            for (const Piece& pc : pieces) ordered[at[pc.bucket]++] = pc;
+            P.work[gi].reserve(n_pieces * (size_t)Hkv);
+            for (const Piece& pc : ordered) {
                 const TileReq& t = g.tiles[(size_t)pc.tile];
                 const int32_t np = nparts[(size_t)pc.tile], part = pc.part, s0 = slot0[(size_t)pc.tile], u0 = unit0[(size_t)pc.tile];
+                sk_work w = {};
+                w.tbl_off = t.tbl_off; w.q_tok0 = t.q_tok0; w.n_tok = t.n_tok; w.pos0 = t.pos0;
+                w.kv_begin = int32_t(part * chunk);
+                w.kv_end = int32_t(std::min<int64_t>(t.kv_vis, (part + 1) * chunk));
+                w.n_parts = np;
+                w.hole_lo = t.hole_lo; w.hole_hi = t.hole_hi;
+                w.tok_period = t.tok_period; w.sub_blocks = t.sub_blocks;
+                if (part == np - 1)
+                    for (int e = 0; e < 2; ++e) { w.eph_blk[e] = t.eph_blk[e]; w.eph_cnt[e] = t.eph_cnt[e]; w.eph_pos0[e] = t.eph_pos0[e]; }
                 for (int h = 0; h < Hkv; ++h) {
-                    sk_work w = {};
-                    w.tbl_off = t.tbl_off; w.kv_head = h; w.q_tok0 = t.q_tok0; w.n_tok = t.n_tok; w.pos0 = t.pos0;
-                    w.kv_begin = int32_t(part * chunk);
-                    w.kv_end = int32_t(std::min<int64_t>(t.kv_vis, (part + 1) * chunk));
+                    w.kv_head = h;
                     w.part = np > 1 ? s0 + part * Hkv + h : -1;
                     w.unit = np > 1 ? u0 + h : -1;
                     w.part0 = np > 1 ? s0 + h : -1;
-                    w.n_parts = np;
-                    w.hole_lo = t.hole_lo; w.hole_hi = t.hole_hi;
-                    w.tok_period = t.tok_period; w.sub_blocks = t.sub_blocks;
-                    if (part == np - 1)
-                        for (int e = 0; e < 2; ++e) { w.eph_blk[e] = t.eph_blk[e]; w.eph_cnt[e] = t.eph_cnt[e]; w.eph_pos0[e] = t.eph_pos0[e]; }
                     P.work[gi].push_back(w);
                 }
             }
@@ -917,7 +946,7 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
             bytes += align_up(P.work[gi].size() * sizeof(sk_work), 256) + align_up(P.comb[gi].size() * sizeof(sk_comb), 256);
         if (ok && bytes <= p->L.meta_bytes) break;
         if (chunk_g[0] > (int64_t(1) << 30)) return SK_E_WORKSPACE;
-        for (int gi = 0; gi < n_groups; ++gi) chunk_g[gi] *= 2;
+        for (int gi = 0; gi < n_groups; ++gi) chunk_g[gi] = std::min<int64_t>(2 * chunk_g[gi], int64_t(1) << 31);      // (longer than any session)
     }
     return ring_acquire(p, &P.slot, &P.host);
 }
