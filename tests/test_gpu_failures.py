@@ -45,6 +45,37 @@ def test_failed_append_leaves_the_session_as_it_was(site):
     pr.check_cache(sid)
 
 
+@pytest.mark.parametrize("shape,L,n", [(SHAPE, 8, 2600), (synth.Shape("f32", 4, 4, 64), 16, 5000)])
+@pytest.mark.parametrize("site", [sk.SK_SITE_SCATTER, sk.SK_SITE_ATTENTION, sk.SK_SITE_COMBINE])
+def test_failed_append_whose_attention_launch_commits(site, shape, L, n):
+    """The commit runs in the attention launch, whose parts are too many to be merged there.  Into a block shared with a fork's
+    source: a failure in front of the launch gives the copy of that block back, one at the combine kernel leaves it to
+    the session, since the commit has pointed the device table at it.  Either way nothing else shows."""
+    gen = synth.generator(2, stream=720 + site + L)
+    pr = Pair(shape, block_tokens=16, n_blocks=n // 16 + 40, max_sessions=2, max_batch_tokens=n)
+    a = pr.create()
+    q, k, v = synth.draw_qkv(gen, n, shape)
+    pr.pool.sk_session_append(a, None, dev(k), dev(v))
+    pr.oracles[a].K, pr.oracles[a].V = synth.to_raw(k), synth.to_raw(v)
+    f = pr.pool.sk_session_fork(a, n)
+    pr.oracles[f] = pr.oracles[a].fork(n)
+    m = n - 25                                  # the fork ends inside a block that the source holds too
+    pr.pool.sk_session_truncate(f, m); pr.oracles[f].truncate(m)
+    free0 = pr.pool.sk_pool_blocks_free()
+    q, k, v = synth.draw_qkv(gen, L, shape)
+    assert _fail(pr.pool, site, lambda: pr.pool.sk_session_append(f, dev(q), dev(k), dev(v))) == sk.SK_E_HIP
+    assert pr.pool.sk_session_length(f) == m and pr.pool.sk_pool_blocks_free() == free0 - (site == sk.SK_SITE_COMBINE)
+    pr.check_cache(f); pr.check_cache(a)
+    qq, kq, vq = synth.draw_qkv(gen, 2, shape)
+    for sid in (f, a):
+        pr.query(sid, qq, kq, vq, name="after the failed append")
+    launches = pr.pool.sk_pool_get_stats()["launches"]
+    pr.append(f, q, k, v, name="append after the failed one")
+    assert pr.pool.sk_pool_last_launch()["fused_merge"] == 0 and pr.pool.sk_pool_get_stats()["launches"] == launches + 2
+    pr.check_cache(f); pr.check_cache(a)
+    pr.query(f, qq, name="query after it")
+
+
 @pytest.mark.parametrize("site", [sk.SK_SITE_PLAN, sk.SK_SITE_UPLOAD, sk.SK_SITE_SCATTER, sk.SK_SITE_ATTENTION])
 def test_failed_batch_step_leaves_every_session_as_it_was(site):
     gen = synth.generator(4, stream=600 + site)

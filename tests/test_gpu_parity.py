@@ -238,6 +238,43 @@ def test_calls_of_at_most_32_rows(hq, hkv, d, env):
             pr.append(sid, q, k, v, name="append behind a hole")
 
 
+@pytest.mark.parametrize("block", [64, 256])
+@pytest.mark.parametrize("shape", [synth.Shape("bf16", 32, 8, 128), synth.Shape("bf16", 14, 2, 64), synth.Shape("f32", 8, 2, 128)])
+def test_one_launch_calls_with_larger_blocks_and_many_parts(shape, block):
+    """The kernels that read a call's own tokens in place, with blocks of several 16-token groups: commits that start
+    inside a group, at a block's end and across it, evicted tokens, and as many parts as one workgroup merges (59: eight
+    rounds of eight; in fp32, where a round takes half as many, 30)."""
+    gen = synth.generator(2, stream=1300 + block + shape.head_dim)
+    pr = Pair(shape, block_tokens=block, n_blocks=4200 // block + 6, max_sessions=1, max_batch_tokens=4096, kv_fill=0xFF)
+    sid = pr.create()
+    ref = pr.oracles[sid]
+    G = shape.n_q_heads // shape.n_kv_heads
+    for grow in (block - 3, 1000, 2700 - block):
+        _, k, v = synth.draw_qkv(gen, grow, shape)
+        pr.pool.sk_session_append(sid, None, dev(k), dev(v))
+        ref.K, ref.V = np.concatenate([ref.K, synth.to_raw(k)]), np.concatenate([ref.V, synth.to_raw(v)])
+        for T in (1, 32 // G, 7):
+            if T * G <= 32 or shape.dtype == "f32":
+                q, k, v = synth.draw_qkv(gen, T, shape)
+                launches = pr.pool.sk_pool_get_stats()["launches"]
+                pr.append(sid, q, k, v, name="append %d behind %d" % (T, len(ref.K)))
+                geo = pr.pool.sk_pool_last_launch()
+                assert pr.pool.sk_pool_get_stats()["launches"] == launches + (2 if geo["n_splits"] > 1 and not geo["fused_merge"] else 1)
+                pr.query(sid, q, k, v, name="query B")
+    pr.check_cache(sid)
+    n = len(ref.K)
+    q, k, v = synth.draw_qkv(gen, 1, shape)
+    for S in (33, 60):
+        pr.query(sid, q, n_splits=S, name="S=%d" % S)
+        geo = pr.pool.sk_pool_last_launch()
+        assert geo["fused_merge"] == (S == 33 or shape.dtype == "bf16") and geo["n_splits"] == -(-n // (128 if S == 33 else 64)), geo
+    pr.freeze(sid, 20)
+    pr.evict(sid, block + 9)
+    pr.append(sid, q, k, v, name="append behind a hole")
+    pr.query(sid, q, k, v, n_splits=60, name="query B behind a hole")
+    pr.check_cache(sid)
+
+
 @pytest.mark.parametrize("hq,hkv,d,most,parts", [(4, 1, 128, 8192, 32), (4, 4, 64, 16384, 32), (12, 12, 128, 4096, 16), (10, 10, 64, 8192, 16)])
 def test_short_calls_where_the_kv_heads_do_not_fill_the_xcds(hq, hkv, d, most, parts):
     """With KV heads that are no multiple of 8 the parts are merged in the launch (and cut for the CUs of one XCD) up to

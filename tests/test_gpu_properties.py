@@ -223,9 +223,10 @@ def test_merge_inside_the_kernel_equals_the_separate_combine_bit_for_bit():
     shape = synth.CFG2
     gen = synth.generator(2, stream=77)
     kw = dict(block_tokens=16, n_blocks=700, max_sessions=3, max_batch_tokens=2048)
-    pools = [_pool_with_env({"SK_FUSE": "1"}, shape, **kw), _pool_with_env({"SK_FUSE": "1", "SK_WAIT_POLLS": "0"}, shape, **kw),
-             _pool_with_env({}, shape, **kw), _pool_with_env({"SK_FUSE": "1", "SK_FUSE_LIST": "1"}, shape, **kw),
-             _pool_with_env({"SK_FUSE": "1", "SK_MERGE_FENCES": "1"}, shape, **kw)]
+    ring = {"SK_NO_SMALL": "1"}                # the kernel for at most 32 rows has a merge of its own
+    pools = [_pool_with_env(dict(ring, **env), shape, **kw) for env in
+             ({"SK_FUSE": "1"}, {"SK_FUSE": "1", "SK_WAIT_POLLS": "0"}, {}, {"SK_FUSE": "1", "SK_FUSE_LIST": "1"},
+              {"SK_FUSE": "1", "SK_MERGE_FENCES": "1"})]
     sids = [(p.sk_session_create(), p.sk_session_create()) for p in pools]
 
     def same(results, what):
@@ -241,6 +242,7 @@ def test_merge_inside_the_kernel_equals_the_separate_combine_bit_for_bit():
         q, k, v = [dev(t) for t in synth.draw_qkv(gen, nq, shape)]
         for S in (0, 3, 40):
             same([p.sk_session_query(s[0], q, n_splits=S) for p, s in zip(pools, sids)], "query A %d S=%d" % (nq, S))
+            assert [p.sk_pool_last_launch()["fused_merge"] for p in pools] == [1, 1, 0, 1, 1]
             same([p.sk_session_query(s[0], q, k, v, n_splits=S) for p, s in zip(pools, sids)], "query B %d S=%d" % (nq, S))
     # batched step (append on the second session, queries on the first) and a question batch
     counts = [700, 40]

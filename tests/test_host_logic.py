@@ -352,6 +352,31 @@ def test_append_into_a_shared_tail_that_fails_late_keeps_or_returns_the_copy():
         assert p.sk_session_length(f) == 50 and p.sk_session_length(a) == 40
 
 
+@pytest.mark.parametrize("shape,L,one_launch", [((32, 8, 128, "bf16"), 3, True), ((4, 4, 64, "f32"), 20, True), ((4, 4, 64, "f32"), 150, False)])
+@pytest.mark.parametrize("site", [sk.SK_SITE_BLOCK_COPY, sk.SK_SITE_SCATTER, sk.SK_SITE_ATTENTION])
+def test_short_append_into_a_shared_tail_that_fails_late(shape, L, one_launch, site):
+    """An append whose attention launch commits too has nothing on the stream when it fails at either of the two sites, so
+    the copy of the shared tail is given back at both; with a commit launch in front it is kept at the second."""
+    hq, hkv, d, dtype = shape
+    p = meta_pool(dtype=dtype, n_q_heads=hq, n_kv_heads=hkv, head_dim=d)
+    a = p.sk_session_create()
+    p.reserve(a, 40)
+    f = p.sk_session_fork(a, 40)
+    p.sk_session_truncate(f, 20)               # inside a block that a also holds
+    before = _state(p, [a, f])
+    p.sk_pool_inject_failure(site, 1)
+    with pytest.raises(sk.SkError) as e:
+        p.reserve(f, L)
+    assert e.value.status == sk.SK_E_HIP
+    after = _state(p, [a, f])
+    if one_launch or site != sk.SK_SITE_ATTENTION:
+        assert after == before
+    else:
+        assert after[0][0] == before[0][0] and after[0][1][0] == 20 and after[1] == before[1] - 1
+    p.reserve(f, L)
+    assert p.sk_session_length(f) == 20 + L and p.sk_session_length(a) == 40
+
+
 @pytest.mark.parametrize("site", [sk.SK_SITE_PLAN, sk.SK_SITE_RING, sk.SK_SITE_UPLOAD, sk.SK_SITE_SCATTER, sk.SK_SITE_ATTENTION])
 def test_batch_step_that_fails_late_changes_no_session(site):
     """A multi-session step that is stopped after some (or all) of its appends were booked - the lists
