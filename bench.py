@@ -515,7 +515,7 @@ def fp32_small(sk, reps=200):
     fa = append_flops(shape, 960, 64)
     fq = 4.0 * 64 * 4 * 16 * 1024
     pool.close()
-    return {"append_64_at_960_us": a_us, "query_16_at_1024_us": q_us, "timing": "stream (commit + attention + combine per call)",
+    return {"append_64_at_960_us": a_us, "query_16_at_1024_us": q_us, "timing": "stream (one launch per call)",
             "roofline": {"kernel": "sk_attn_f32<64>", "bound": "alu", "achieved": fa / (a_us * 1e-6) / 1e12,
                          "peak": FP32_VALU_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": fa / (a_us * 1e-6) / 1e12 / FP32_VALU_PEAK_TFLOPS,
                          "traffic": None, "algorithmic_flops": fa,

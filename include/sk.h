@@ -34,7 +34,8 @@
  *     ordered externally), mirroring the paper's single GPU worker (Sec. 3.6).
  *   - Device pointers must be 16-byte aligned.
  *   - A call's results (out, lse) may lie over its own k and v, not over its q.
- *   - Same inputs, same block tables, same n_splits => bit-identical outputs.
+ *   - Same inputs, same block tables, same n_splits => bit-identical outputs, wherever on the
+ *     device a call's workgroups run.
  *   - Token-major layouts: q [T][Hq][d], k and v [T][Hkv][d], out [T][Hq][d],
  *     lse [T][Hq] (natural-log log-sum-exp of the scaled scores, float).
  *   - Precision, bf16 pools: scores, softmax statistics and accumulators are fp32; the softmax
@@ -129,10 +130,12 @@ size_t sk_pool_workspace_bytes(const sk_pool_desc* desc);
  *                      policy instead of non-temporal
  *   SK_STREAM_MIN_TOKENS=n  cached tokens from which the 128-row instances do so (default 65536;
  *                      the 64-row instance always does)
- *   SK_FUSE=1          single-session calls merge their split partials inside the attention kernel
+ *   SK_FUSE=1          single-session calls of the ring kernels (more than 32 rows per KV head, or more than 128 MiB
+ *                      of cached K/V) merge their split partials inside the attention kernel
  *                      instead of in a second kernel (one launch per call; measured slower on
  *                      MI355X, so not the default; the same function merges a row either way, the
- *                      results are bit-identical)
+ *                      results are bit-identical).  Shorter calls and fp32 ones merge in their launch
+ *                      by a rule of their own, whatever this says (see sk_launch_info.fused_merge)
  *   SK_WAIT_POLLS=n    with SK_FUSE: how many polls a workgroup waits for the other workgroups
  *                      of its row tile before it leaves the merge to the last one (default 256;
  *                      0: never wait)

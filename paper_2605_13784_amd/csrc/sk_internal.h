@@ -133,13 +133,13 @@ struct sk_launch {
     // s + 2S, .. of the cache instead of one contiguous chunk, so that the workgroups of a head walk
     // through memory side by side instead of as S separate streams (the host decides when)
     int32_t interleave;
-    // In-kernel merge of the split partials (optional; the default is the combine kernel, which
-    // measured faster).  sync holds two counters per unit, both zero between
-    // launches: arrivals (low 16 bits; the high bits count workgroups that gave up waiting) and
-    // departures.  A workgroup writes its partial, arrives, and waits up to wait_polls polls for the
+    // In-kernel merge of the split partials.  sync is zero between launches.  Ring kernels (only on request: the combine kernel
+    // measured faster): two counters per unit, arrivals (low 16 bits; the high bits count workgroups that gave
+    // up waiting) and departures.  A workgroup writes its partial, arrives, and waits up to wait_polls polls for the
     // others; then every workgroup of the unit merges its own share of the rows.  One that gives up
     // leaves its share to the last arriver, which always sees everything (no wait is unbounded).
-    // The last to leave clears the counters.
+    // The last to leave clears the counters.  sk_attn_bf16_small and sk_attn_f32 (where the host sets fuse): one 64-bit
+    // arrival word per unit, in a 128-byte line of its own; the last to arrive merges, nobody waits (see sk_meet).
     uint32_t* sync;
     int32_t fuse;
     int32_t wait_polls;

@@ -828,10 +828,10 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // addresses of the current slot are rebuilt from the per-unit bases once per iteration.
             // Every wave does every iteration (rows or keys that do not count are masked): the slots
             // are synchronised, so skipping work would not save time.
-            // Bound: power.  At 32,512 cached tokens an iteration takes 2,900 cycles for 2,048 of matrix
-            // instructions per SIMD, and the chip lowers its clock as they get fewer (3,070 cycles at 1.86 GHz
-            // before the waves feeding the matrix pipe had priority, 2,895 at 1.80 GHz with it): 512 tokens at
-            // 130,560 run at 1.26 PFLOP/s against 1.38 of a large library product.
+            // Bound: the matrix slot (its operands come from LDS, and the two kinds of slot overlap only partly) at the clock the
+            // chip holds under it: at 32,512 cached tokens an iteration takes about 3,000 cycles for 2,048 of matrix
+            // instructions per SIMD (counters: matrix pipe busy 0.62 of the cycles), 256 tokens 122-124 us = 1.10-1.12 PFLOP/s;
+            // 512 at 130,560 run at 1.18-1.22 where the bare matrix loop holds 1.85 and a library product of 8192^3 1.41.
             constexpr int LPW = 4;               // direct-to-LDS loads per wave per iteration (one tile)
             const int my_tile = 1 - grp;
             const int ahead = 2 + grp;           // iterations loaded before the loop
@@ -1163,9 +1163,9 @@ __global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 1 : 2) void sk_att
 // parts ran.  Nobody waits for anybody.
 //
 // Bound: round trips.  One query token with its own K/V at 2,600 cached tokens: one launch of 8.1 us where a staging,
-// an attention and a combine kernel took 16.3 back to back; 1.0 us from a workgroup's start to its first loads
-// (arguments, block table), 2.2 to the end of its keys, 1.1 for the meeting in LDS, 0.4 for the arrival and 2.2 for
-// the merge (three round trips).  10.7 MB of cache at the rate of a plain read would be 1.7 us.
+// an attention and a combine kernel took 17.3 back to back.  By time stamps, when it took 8.4: 1.0 us from a workgroup's start
+// to its first loads (arguments, block table), 2.2 to the end of its keys, 1.1 for the meeting in LDS, 0.4 for the arrival
+// and 2.2 for the merge (three round trips).  10.7 MB of cache at the rate of a plain read would be 1.7 us.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ unsigned sk_xcd_id() { return (unsigned)__builtin_amdgcn_s_getreg((3 << 11) | 20); }    // HW_REG_XCC_ID, bits 3:0
 
@@ -1543,9 +1543,9 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
 // In single-session calls the call's own K/V are read where the caller has them, as further keys behind the
 // cached ones (padded to whole tiles), and a short commit runs in the same launch; in batched calls they come from
 // the staging area.  Rows past the end of a tile's keys re-read the last one; they count as zeros.
-// Bound: round trips and launches at the sizes in use: a 64-token append at 960 cached tokens (4 heads of 64 dims) 29.2
-// -> 8.5 us in a stream of appends, a 16-token query at 1,024 25.2 -> 7.9 (a commit or nothing, an fp32-FMA kernel of
-// 24 / 20.6 us and a combine kernel of 4.4 / 3.9 before; one launch now).
+// Bound: round trips and launches at the sizes in use: a 64-token append at 960 cached tokens (4 heads of 64 dims) 29.1
+// -> 8.1 us in a stream of appends, a cache-only 16-token query at 1,024 25.2 -> 7.7 (a commit or nothing, an fp32-FMA kernel
+// of 24 / 20.6 us and a combine kernel of 4.4 / 3.9 before; one launch now).
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(4))) float sk_acc4;
 

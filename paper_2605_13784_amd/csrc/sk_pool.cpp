@@ -47,7 +47,7 @@ struct Layout {
     int32_t max_batch_tokens = 0;
     int64_t eph_blocks = 0;
     int64_t part_slots = 0;
-    int64_t sync_units = 0;           // pairs of merge counters
+    int64_t sync_units = 0;           // 8-byte merge counters (a pair of 32-bit ones, or a sixteenth of a line)
     size_t meta_bytes = 0;            // device region for uploaded lists; also the size of a pinned ring slot
     size_t kv_bytes = 0;
     // workspace offsets
@@ -104,8 +104,8 @@ bool derive_layout(const sk_pool_desc& d, Layout& L)
     L.off_tables = off; off = align_up(off + size_t(d.max_sessions) * L.max_blocks_per_session * 4, 256);
     L.off_ident = off;  off = align_up(off + size_t(L.eph_blocks) * 4, 256);
     L.off_meta = off;   off = align_up(off + L.meta_bytes, 256);
-    // one unit of merge counters per (row tile, KV head) of a call; the matrix-pipe kernels, which merge
-    // in the kernel, have tiles of at least 64 rows
+    // Merge counters: a pair per (row tile, KV head) of a call of the ring kernels, whose tiles have at least 64 rows; for the
+    // kernels with one 128-byte line per unit the planners check that their units fit
     L.sync_units = (rows / 64 + std::max(d.max_sessions, 1024) + 2) * d.n_kv_heads;
     L.off_sync = off;   off = align_up(off + size_t(L.sync_units) * 8, 256);
     L.off_part_ml = off; off = align_up(off + size_t(L.part_slots) * kPartSlotRows * 4 * 4, 256);
@@ -447,7 +447,7 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     // (16 tokens at 128K: 98 / 96 / 92 us with 16- / 64- / 256-token blocks).
     L.interleave = (!p->no_interleave && v.id == SK_KV_MFMA64 && S > 1 && kv_len <= (int64_t)pos0) ? 1 : 0;
     R.base_wgs = (int32_t)base_wgs; R.parts = (int32_t)parts; R.wgs = int32_t(base_wgs * parts); R.kv_len = kv_len;
-    // On request (SK_FUSE=1) the matrix-pipe kernels merge their split partials themselves (one launch per
+    // On request (SK_FUSE=1) the ring kernels merge their split partials themselves (one launch per
     // call).  Workgroups only wait for each other when the whole launch fits on the device at once (the
     // 256-row instance holds a CU alone, the others share it in pairs); otherwise the last workgroup of a
     // unit merges alone.  Not the default: a device-scope round trip (atomic, coherent load) measured about
