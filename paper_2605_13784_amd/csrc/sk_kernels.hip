@@ -1163,9 +1163,9 @@ __global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 1 : 2) void sk_att
 // parts ran.  Nobody waits for anybody.
 //
 // Bound: round trips.  One query token with its own K/V at 2,600 cached tokens: one launch of 8.1 us where a staging,
-// an attention and a combine kernel took 17.3 back to back.  By time stamps, when it took 8.4: 1.0 us from a workgroup's start
-// to its first loads (arguments, block table), 2.2 to the end of its keys, 1.1 for the meeting in LDS, 0.4 for the arrival
-// and 2.2 for the merge (three round trips).  10.7 MB of cache at the rate of a plain read would be 1.7 us.
+// an attention and a combine kernel took 17.3 back to back.  By time stamps (taken before the merge
+// read through bounded buffer loads, 0.3 us slower): 1.0 us from a workgroup's start to its first loads (arguments, block
+// table), 2.2 to the end of its keys, 1.1 for the meeting in LDS, 0.4 for the arrival and 2.2 for the merge (three round trips).  10.7 MB of cache at the rate of a plain read would be 1.7 us.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ unsigned sk_xcd_id() { return (unsigned)__builtin_amdgcn_s_getreg((3 << 11) | 20); }    // HW_REG_XCC_ID, bits 3:0
 

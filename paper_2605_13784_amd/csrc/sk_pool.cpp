@@ -380,7 +380,9 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
     }
     L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts; L.by_chunk = sk_make_div((uint32_t)chunk);
     L.own_cnt = own_cnt; L.own_mode = SK_OWN_F32;
-    // merged by the last workgroup of a unit while that is a few rounds of loads (see plan_small)
+    // Merged by the last workgroup of a unit while that is a few rounds of loads (see plan_small).  Few units leave XCDs idle here
+    // too, but such calls stay short: 1/1, 16/1, 10/2, 4/4 and 8/2 heads with 1 to 1,024 tokens at 128 to 32,768 cached are 1.4
+    // to 17 times as fast as with the fp32-FMA kernel and its combine, none slower.
     L.fuse = (can_merge(p, R.v, int64_t(R.v.tok_per_tile) * p->L.G, parts) && units * 16 <= p->L.sync_units) ? 1 : 0;
     const int64_t pad = L.fuse ? (units + 7) / 8 * 8 : units;
     if (pad * parts > (int64_t(1) << 30)) return SK_E_WORKSPACE;
