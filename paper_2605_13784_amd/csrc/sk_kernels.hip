@@ -28,6 +28,33 @@ __device__ __forceinline__ sk_halves sk_both_halves(float x)
     return sk_halves{__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
 
+// The same for lane (i ^ 16).
+__device__ __forceinline__ sk_halves sk_row_pairs(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return sk_halves{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+
+// Maximum / sum over the 64 lanes, in every lane, without LDS: partners within a quad, quad against quad (mirrored halves
+// of a row, whose quads hold one value each by then), half rows, rows, row pairs.  Six dependent vector instructions where
+// six shuffles are round trips to the LDS unit, some 100 cycles each.
+template <int CTRL> __device__ __forceinline__ float sk_dpp(float x)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float sk_wave_max(float x)
+{
+    x = fmaxf(x, sk_dpp<0xB1>(x)); x = fmaxf(x, sk_dpp<0x4E>(x)); x = fmaxf(x, sk_dpp<0x141>(x)); x = fmaxf(x, sk_dpp<0x140>(x));
+    { const sk_halves h = sk_row_pairs(x); x = fmaxf(h.lo, h.hi); }
+    { const sk_halves h = sk_both_halves(x); return fmaxf(h.lo, h.hi); }
+}
+__device__ __forceinline__ float sk_wave_sum(float x)
+{
+    x += sk_dpp<0xB1>(x); x += sk_dpp<0x4E>(x); x += sk_dpp<0x141>(x); x += sk_dpp<0x140>(x);
+    { const sk_halves h = sk_row_pairs(x); x = h.lo + h.hi; }
+    { const sk_halves h = sk_both_halves(x); return h.lo + h.hi; }
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f)
 {   // round to nearest even; NaN stays NaN
@@ -177,43 +204,32 @@ __device__ __forceinline__ const unsigned char* sk_group_base(const sk_seg& g, i
 // others pstride rows apart):
 //   M = max_s m_s ; w_s = 2^(m_s - M) ; O = sum_s O_s w_s / sum_s l_s w_s ; LSE = (M + log2 sum_s lx_s w_s) ln 2
 // Lane s holds the statistics of splits s, s + 64, ..; every lane two output dimensions (one when
-// d = 64).  The splits are added in index order whoever calls this (the combine kernel, or a
-// workgroup of the attention kernel), with explicit FMAs, so the result depends on the partials only.
-// Rows are read BATCH splits at a time, the next batch requested before the current one is used.
-// COHERENT: the partials were written by other workgroups of the same launch (with write-through
+// d = 64).  The splits are added in index order whoever does this (the combine kernel, sk_combine_row, or a
+// workgroup of the attention kernel, here), with explicit FMAs, so the result depends on the partials only.
+// Rows are read 16 splits at a time, the next ones requested before the current ones are used.  The partials were
+// written by other workgroups of the same launch (with write-through
 // stores); they are read with device-scope loads, which see them wherever the reader runs, so the
 // reader needs no cache invalidate (measured at over 10 us when every workgroup issues one).
-template <bool COHERENT>
-__device__ __forceinline__ float sk_ld_partial(const float* p)
-{
-    if (COHERENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return *p;
-}
+__device__ __forceinline__ float sk_ld_partial(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-template <bool COHERENT, int BATCH>
 __device__ __forceinline__ void sk_merge_row(const sk_launch& P, const size_t prow0, const size_t pstride, const int n_parts,
                                              const size_t orow, const int lane)
 {
+    constexpr int BATCH = 16;
     const int d = P.g.d;
     const bool two = d == 128;
-    // dimensions of a lane: COHERENT (32-bit loads) lane and lane + 64; else (64-bit loads) 2 lane, 2 lane + 1
-    const int d0 = COHERENT ? lane : (two ? 2 * lane : lane);
-    const int d1 = COHERENT ? lane + 64 : 2 * lane + 1;
-    const float* obase = P.part_o + prow0 * d + d0;
+    const float* obase = P.part_o + prow0 * d + lane;          // dimensions of a lane: lane and lane + 64
     const size_t ostride = pstride * d;
     const float* mlbase = P.part_ml + prow0 * 4;
     const size_t mlstride = pstride * 4;
     auto load_o = [&](const int s, float& x0, float& x1) __attribute__((always_inline)) {
         const float* op = obase + (size_t)s * ostride;
-        if (COHERENT) { x0 = sk_ld_partial<true>(op); x1 = two ? sk_ld_partial<true>(op + 64) : 0.f; }
-        else if (two) { const float2 t = *(const float2*)op; x0 = t.x; x1 = t.y; }
-        else { x0 = *op; x1 = 0.f; }
+        x0 = sk_ld_partial(op); x1 = two ? sk_ld_partial(op + 64) : 0.f;
     };
     float M = SK_NEG_INF;
     if (n_parts > 64) {              // rare: the maximum needs its own pass
-        for (int s = lane; s < n_parts; s += 64) M = fmaxf(M, sk_ld_partial<COHERENT>(mlbase + (size_t)s * mlstride));
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+        for (int s = lane; s < n_parts; s += 64) M = fmaxf(M, sk_ld_partial(mlbase + (size_t)s * mlstride));
+        M = sk_wave_max(M);
     }
     float L = 0.f, Lx = 0.f, a0 = 0.f, a1 = 0.f;
     for (int base = 0; base < n_parts; base += 64) {
@@ -227,14 +243,9 @@ __device__ __forceinline__ void sk_merge_row(const sk_launch& P, const size_t pr
         float m_s = SK_NEG_INF, l_s = 0.f, lx_s = 0.f;
         if (lane < cnt) {
             const float* mp = mlbase + (size_t)(base + lane) * mlstride;
-            if (COHERENT) { m_s = sk_ld_partial<true>(mp); l_s = sk_ld_partial<true>(mp + 1); lx_s = sk_ld_partial<true>(mp + 2); }
-            else { const float4 t = *(const float4*)mp; m_s = t.x; l_s = t.y; lx_s = t.z; }
+            m_s = sk_ld_partial(mp); l_s = sk_ld_partial(mp + 1); lx_s = sk_ld_partial(mp + 2);
         }
-        if (n_parts <= 64) {
-            M = m_s;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
-        }
+        if (n_parts <= 64) M = sk_wave_max(m_s);
         const float wgt = (m_s == SK_NEG_INF) ? 0.f : sk_exp2(m_s - M);
         L = fmaf(l_s, wgt, L); Lx = fmaf(lx_s, wgt, Lx);
         for (int j0 = 0; j0 < cnt; j0 += BATCH) {
@@ -252,17 +263,16 @@ __device__ __forceinline__ void sk_merge_row(const sk_launch& P, const size_t pr
             for (int j = 0; j < BATCH; ++j) { x0[j] = y0[j]; x1[j] = y1[j]; }
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) { L += __shfl_xor(L, off, 64); Lx += __shfl_xor(Lx, off, 64); }
+    L = sk_wave_sum(L); Lx = sk_wave_sum(Lx);
     const float inv = 1.0f / L;
     if (P.out_dtype == 0) {
-        float* o = (float*)P.out + orow * d;
-        if (COHERENT || !two) { o[d0] = a0 * inv; if (two) o[d1] = a1 * inv; }
-        else *(float2*)(o + d0) = make_float2(a0 * inv, a1 * inv);
+        float* o = (float*)P.out + orow * d + lane;
+        o[0] = a0 * inv;
+        if (two) o[64] = a1 * inv;
     } else {
-        uint16_t* o = (uint16_t*)P.out + orow * d;
-        if (COHERENT || !two) { o[d0] = f32_to_bf16_bits(a0 * inv); if (two) o[d1] = f32_to_bf16_bits(a1 * inv); }
-        else *(uint32_t*)(o + d0) = f32_to_bf16_bits(a0 * inv) | ((uint32_t)f32_to_bf16_bits(a1 * inv) << 16);
+        uint16_t* o = (uint16_t*)P.out + orow * d + lane;
+        o[0] = f32_to_bf16_bits(a0 * inv);
+        if (two) o[64] = f32_to_bf16_bits(a1 * inv);
     }
     if (P.lse && lane == 0) P.lse[orow] = (M + sk_log2(Lx)) * SK_LN2;
 }
@@ -1115,7 +1125,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             for (int row = k * rps + wave; row < row_end; row += NW) {
                 const int tok3 = div_g(row);
                 const size_t orow = (size_t)(w.q_tok0 + tok3) * P.g.Hq + w.kv_head * G + (row - tok3 * G);
-                sk_merge_row<true, 16>(P, (size_t)w.part0 * P.rows_per_slot + row, (size_t)P.g.Hkv * P.rows_per_slot, w.n_parts, orow, lane);
+                sk_merge_row(P, (size_t)w.part0 * P.rows_per_slot + row, (size_t)P.g.Hkv * P.rows_per_slot, w.n_parts, orow, lane);
             }
         }
     }
@@ -1550,11 +1560,6 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
 typedef __attribute__((ext_vector_type(4))) float sk_acc4;
 
 // Maximum / sum over the four lanes c, c + 16, c + 32, c + 48.
-__device__ __forceinline__ sk_halves sk_row_pairs(float x)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return sk_halves{__uint_as_float(r[0]), __uint_as_float(r[1])};
-}
 __device__ __forceinline__ float sk_max_over_groups(float x)
 {
     { const sk_halves h = sk_row_pairs(x); x = fmaxf(h.lo, h.hi); }
@@ -1897,13 +1902,24 @@ __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
 // Cross-split combine: one wave per output row.
 //   M = max_s m_s ; L = sum_s l_s 2^(m_s - M) ; O = sum_s O_s 2^(m_s - M) / L
 //   LSE = (M + log2 sum_s lx_s 2^(m_s - M)) ln 2       (lx: the row sums before bf16 rounding)
+// The parts of a round (R of them) are requested at once, beside the statistics: buffer loads return zeros behind the
+// last part, so no branch stands between the loads.  R is the smallest of 8, 16 and 32 that takes the launch's parts in one
+// round (kernels of few registers for launches of few parts: more rows in flight), 1 where a round would reach beyond
+// 32-bit offsets.
+// Bound: launch, two round trips (statistics and rows come in one), and the read of the parts for large calls (256 tokens of 32 heads in
+// eight parts: 34 MB).  Against rounds of eight, each branch around its load and shuffles through LDS (us per call, whole): 23-token
+// query at 14,800 cached 23.3 -> 21.6; 16 at 32,768 33.7 -> 31.8; 77-token append and 5-token query at 9,001 51.0 -> 48.3; 256-token
+// append at 32,512 134.5 -> 132.2.
 // ---------------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(2))) unsigned sk_u32x2;
+
+template <int D, int R>
 __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
 {
     sk_touch_arguments<sizeof(sk_launch)>();
     const int groups_per_tile = P.rows_per_slot >> 2;
     const int item = blockIdx.x / groups_per_tile;
-    const int row = (blockIdx.x % groups_per_tile) * 4 + (threadIdx.x >> 6);
+    const int row = (blockIdx.x % groups_per_tile) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     sk_comb cb;
     if (P.mode == SK_MODE_LIST) cb = P.comb[item];
@@ -1918,10 +1934,59 @@ __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
         cb.part0 = tile * P.n_splits * Hkv + head; cb.part_stride = Hkv;
         cb.q_tok0 = tok0; cb.n_tok = ntok; cb.kv_head = head;
     }
-    const int G = P.g.G;
+    const int G = P.g.G, n_parts = cb.n_parts;
     if (row >= cb.n_tok * G) return;
     const size_t orow = ((size_t)(cb.q_tok0 + row / G) * P.g.Hq + cb.kv_head * G + row % G);
-    sk_merge_row<false, 8>(P, (size_t)cb.part0 * P.rows_per_slot + row, (size_t)cb.part_stride * P.rows_per_slot, cb.n_parts, orow, lane);
+    const size_t prow0 = (size_t)cb.part0 * P.rows_per_slot + row, pstride = (size_t)cb.part_stride * P.rows_per_slot;
+    const float* ml = P.part_ml + prow0 * 4;
+    const unsigned step = R > 1 ? (unsigned)(pstride * D * 4) : 0;
+    float M = SK_NEG_INF, L = 0.f, Lx = 0.f, a0 = 0.f, a1 = 0.f;
+    if (n_parts > 64) {              // rare: the maximum needs its own pass
+        for (int s = lane; s < n_parts; s += 64) M = fmaxf(M, ml[(size_t)s * pstride * 4]);
+        M = sk_wave_max(M);
+    }
+    for (int base = 0; base < n_parts; base += 64) {
+        const int cnt = n_parts - base < 64 ? n_parts - base : 64;
+        const float4 t = *(const float4*)(ml + (size_t)(base + (lane < cnt ? lane : cnt - 1)) * pstride * 4);
+        float x0[R], x1[R];
+        auto request = [&](const int j0) __attribute__((always_inline)) {
+            const int left = cnt - j0 < R ? cnt - j0 : R;
+            const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(P.part_o + (prow0 + (size_t)(base + j0) * pstride) * D, 0,
+                                                                                  (int)((unsigned)(left - 1) * step + D * 4), 0x00020000);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (D == 128) {
+                    const sk_u32x2 x = __builtin_bit_cast(sk_u32x2, __builtin_amdgcn_raw_buffer_load_b64(rows, (unsigned)j * step + (unsigned)lane * 8, 0, 0));
+                    x0[j] = __uint_as_float(x[0]); x1[j] = __uint_as_float(x[1]);
+                } else {
+                    x0[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, (unsigned)j * step + (unsigned)lane * 4, 0, 0)); x1[j] = 0.f;
+                }
+            }
+        };
+        request(0);
+        const float m_s = lane < cnt ? t.x : SK_NEG_INF;
+        if (n_parts <= 64) M = sk_wave_max(m_s);
+        const float wgt = (m_s == SK_NEG_INF) ? 0.f : sk_exp2(m_s - M);
+        L = fmaf(lane < cnt ? t.y : 0.f, wgt, L); Lx = fmaf(lane < cnt ? t.z : 0.f, wgt, Lx);
+        for (int j0 = 0; j0 < cnt; j0 += R) {
+            if (j0 > 0) request(j0);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const float wj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wgt), j0 + j));    // 0 for parts past the end
+                a0 = fmaf(x0[j], wj, a0); a1 = fmaf(x1[j], wj, a1);
+            }
+        }
+    }
+    L = sk_wave_sum(L); Lx = sk_wave_sum(Lx);
+    const float inv = 1.0f / L;
+    if (D == 128) {
+        if (P.out_dtype == 0) *(float2*)((float*)P.out + orow * D + 2 * lane) = make_float2(a0 * inv, a1 * inv);
+        else *(uint32_t*)((uint16_t*)P.out + orow * D + 2 * lane) = f32_to_bf16_bits(a0 * inv) | ((uint32_t)f32_to_bf16_bits(a1 * inv) << 16);
+    } else {
+        if (P.out_dtype == 0) ((float*)P.out)[orow * D + lane] = a0 * inv;
+        else ((uint16_t*)P.out)[orow * D + lane] = f32_to_bf16_bits(a0 * inv);
+    }
+    if (P.lse && lane == 0) P.lse[orow] = (M + sk_log2(Lx)) * SK_LN2;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2133,11 +2198,25 @@ int sk_launch_attention_small(const sk_launch& L, const sk_commit& C, int32_t n_
     return (int)hipGetLastError();
 }
 
-int sk_launch_combine(const sk_launch& L, int32_t n_row_tiles, void* stream, void* ev_start, void* ev_stop)
+// max_parts: the most parts of a row tile of the launch; part_stride: slots from one part to the next.
+int sk_launch_combine(const sk_launch& L, int32_t n_row_tiles, int32_t max_parts, int64_t part_stride, void* stream, void* ev_start, void* ev_stop)
 {
     if (n_row_tiles <= 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-    SK_LAUNCH(sk_combine, dim3(n_row_tiles * (L.rows_per_slot >> 2)), dim3(256));
+    const dim3 grid(n_row_tiles * (L.rows_per_slot >> 2)), block(256);
+    const int64_t step = part_stride * L.rows_per_slot * L.g.d * 4;
+    int round = max_parts <= 8 ? 8 : max_parts <= 16 ? 16 : 32;
+    while (round > 1 && round * step >= (int64_t(1) << 32)) round = round > 8 ? round / 2 : 1;
+#define SK_LAUNCH_COMBINE(D)                                                                                        \
+    do {                                                                                                            \
+        if (round == 32) SK_LAUNCH((sk_combine<D, 32>), grid, block);                                               \
+        else if (round == 16) SK_LAUNCH((sk_combine<D, 16>), grid, block);                                          \
+        else if (round == 8) SK_LAUNCH((sk_combine<D, 8>), grid, block);                                            \
+        else SK_LAUNCH((sk_combine<D, 1>), grid, block);                                                            \
+    } while (0)
+    if (L.g.d == 128) SK_LAUNCH_COMBINE(128);
+    else SK_LAUNCH_COMBINE(64);
+#undef SK_LAUNCH_COMBINE
     return (int)hipGetLastError();
 }
 #undef SK_LAUNCH

@@ -507,7 +507,7 @@ int launch_regular(sk_pool* p, RegPlan& R, const void* q, void* out, int out_dty
     if (R.parts > 1 && !R.L.fuse) {
         // the attention kernel is enqueued and will write its partials; a failure here leaves out/lse unwritten
         prof_pair(p, pc, 1, &e0, &e1);
-        e = inject(p, SK_SITE_COMBINE) ? (int)hipErrorUnknown : sk_launch_combine(R.L, R.base_wgs, st, e0, e1);
+        e = inject(p, SK_SITE_COMBINE) ? (int)hipErrorUnknown : sk_launch_combine(R.L, R.base_wgs, R.parts, p->d.n_kv_heads, st, e0, e1);
         if (e) { g_last_hip = e; return SK_E_HIP; }
         p->stats.launches++;
     }
@@ -991,7 +991,7 @@ int launch_list(sk_pool* p, ListPlan& P, const ScatterBatch* sb, int n_sb, ListG
     const int32_t pc = prof_call(p);
     void *e0, *e1;
     sk_launch L[kMaxGroups];
-    int32_t wgs = 0, max_parts = 1;
+    int32_t wgs = 0, max_parts = 1, most[kMaxGroups] = {};
     for (int gi = 0; gi < n_groups; ++gi) {
         if (P.work[gi].empty()) continue;
         ListGroup& g = groups[gi];
@@ -1012,12 +1012,13 @@ int launch_list(sk_pool* p, ListPlan& P, const ScatterBatch* sb, int n_sb, ListG
         if (e) { g_last_hip = e; return SK_E_HIP; }
         p->stats.launches++;
         wgs += (int32_t)P.work[gi].size();
-        for (const sk_comb& c : P.comb[gi]) max_parts = std::max(max_parts, c.n_parts);
+        for (const sk_comb& c : P.comb[gi]) most[gi] = std::max(most[gi], c.n_parts);
+        max_parts = std::max(max_parts, most[gi]);
     }
     for (int gi = 0; gi < n_groups && !P.fuse; ++gi) {
         if (P.comb[gi].empty()) continue;
         prof_pair(p, pc, 1, &e0, &e1);
-        int e = sk_launch_combine(L[gi], (int32_t)P.comb[gi].size(), st, e0, e1);
+        int e = sk_launch_combine(L[gi], (int32_t)P.comb[gi].size(), most[gi], Hkv, st, e0, e1);
         if (e) { g_last_hip = e; return SK_E_HIP; }
         p->stats.launches++;
     }

@@ -626,3 +626,25 @@ def test_custom_softmax_scale(scale):
     q, k, v = synth.draw_qkv(gen, 9, synth.CFG1)
     pf.query(s, q, n_splits=3, name="fp32 scale %.2f query A" % scale)
     pf.query(s, q, k, v, name="fp32 scale %.2f query B" % scale)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (14, 2, 64)])
+def test_combine_rounds(hq, hkv, d):
+    """The combine kernel asks for 8, 16 or 32 parts at once, by the parts of the launch: both sides of each border, more parts
+    than one round and than the 64 whose statistics one wave holds, results in fp32 and bf16."""
+    shape = synth.Shape("bf16", hq, hkv, d)
+    gen = synth.generator(2, stream=1500 + d)
+    nq = 40 // (hq // hkv)
+    pr = Pair(shape, n_blocks=72 * 4 + 8, max_sessions=1, max_batch_tokens=4096)
+    sid = pr.create()
+    for t in range(0, 72 * 64, 1152):
+        _, k, v = synth.draw_qkv(gen, 1152, shape)
+        pr.append(sid, None, k, v, check=False)
+    q, k, v = synth.draw_qkv(gen, nq, shape)
+    for S in (72, 65, 64, 33, 32, 31, 17, 16, 9, 8, 7, 2):
+        pr.pool.sk_session_truncate(sid, 64 * S)
+        pr.oracles[sid].truncate(64 * S)
+        for own in (False, True):              # the own part is one more
+            pr.query(sid, q, k if own else None, v if own else None, n_splits=S, out_dtype="bf16" if S % 2 else "f32", name="S=%d own=%d" % (S, own))
+            geo = pr.pool.sk_pool_last_launch()
+            assert geo["n_splits"] == S + own and geo["fused_merge"] == 0, geo
