@@ -9,6 +9,8 @@
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float sk_f32x4;
+typedef __attribute__((ext_vector_type(4))) short sk_s16x4;
 
 #define SK_NEG_INF (-__builtin_inff())
 #define SK_LN2 0.6931471805599453f
@@ -212,12 +214,12 @@ __device__ __forceinline__ const unsigned char* sk_group_base(const sk_seg& g, i
 // reader needs no cache invalidate (measured at over 10 us when every workgroup issues one).
 __device__ __forceinline__ float sk_ld_partial(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+template <int D>
 __device__ __forceinline__ void sk_merge_row(const sk_launch& P, const size_t prow0, const size_t pstride, const int n_parts,
                                              const size_t orow, const int lane)
 {
-    constexpr int BATCH = 16;
-    const int d = P.g.d;
-    const bool two = d == 128;
+    constexpr int BATCH = 16, d = D;
+    constexpr bool two = D == 128;
     const float* obase = P.part_o + prow0 * d + lane;          // dimensions of a lane: lane and lane + 64
     const size_t ostride = pstride * d;
     const float* mlbase = P.part_ml + prow0 * 4;
@@ -280,13 +282,15 @@ __device__ __forceinline__ void sk_merge_row(const sk_launch& P, const size_t pr
 // ---------------------------------------------------------------------------------------------
 // bf16 MFMA attention kernel, head_dim D = 128 (described below) or 64 (the same with four instead
 // of eight 16-dim slices of the first contraction and two instead of four 32-dim blocks of the
-// second, in the same LDS layout, half filled; the free-running instances only).
+// second, tiles of half the bytes, and a 256-row instance whose waves do not take turns).
 //
 // Workgroup = NRG row groups x NPH key phases = 4 or 8 waves: a row group owns 32 query rows, a
 // phase owns every NPH-th key tile.  Instances: <4,1,2> 128-row tile; <2,2,2> 64-row tile, the two
 // phases merged through LDS at the end; <4,2,2> 128-row tile, eight waves as four row groups x two
 // phases; <8,1,4> 256-row tile, eight waves in two groups that take turns on the matrix pipe and
-// the vector ALU (described at the segment loop).
+// the vector ALU (head_dim 64: eight waves that interleave both; described at the segment loop).
+// Head_dim 64 has no <4,2,2>: with two or three workgroups on a CU the four waves overlap as well (one instance of 32 tokens at
+// 131,072 cached, eight waves, one workgroup a CU 65.5 us; four waves, two workgroups 62.0).
 //
 // Keys move HBM -> LDS with direct-to-LDS loads (global_load_lds_dwordx4), never through
 // registers, into a ring of NSS iterations of two 32-key tiles (K 8 KiB + V^T 8 KiB each): 64 KiB
@@ -365,23 +369,23 @@ __device__ __forceinline__ void sk_dma16(const void* base, unsigned lane_off, un
 // on another XCD, and a release fence wide enough for that would have to walk the whole L2 for dirty
 // lines (measured: about 25 us per kernel).  Written as inline assembly (the compiler has no store
 // with these bits outside atomics), so the caller waits for it by hand (SK_WAIT_VMCNT(0)).
-typedef __attribute__((ext_vector_type(4))) float sk_f32x4;
 __device__ __forceinline__ void sk_store16_through(float* p, const float4 v)
 {
     const sk_f32x4 x = {v.x, v.y, v.z, v.w};
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" : : "v"(p), "v"(x) : "memory");
 }
 
-// Pool blocks holding the two 16-key groups of the tile that starts at key t0 (scalar loads).
-// Groups past the end of the segment fall back to its last group.
+// Pool blocks holding the 16-key groups that wave `sub` loads of the tile that starts at key t0 (scalar loads): both, or with
+// head_dim 64 group sub >> 1 alone.  Groups past the end of the segment fall back to its last group.
 struct sk_tile_blocks { uint32_t blk[2]; };
-__device__ __forceinline__ sk_tile_blocks sk_lookup_tile(const sk_seg& g, int t0, int last_group)
+template <int D>
+__device__ __forceinline__ sk_tile_blocks sk_lookup_tile(const sk_seg& g, int t0, int last_group, int sub)
 {
     typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
     sk_tile_blocks b;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        int tg = t0 + 16 * j;
+    for (int j = 0; j < D / 64; ++j) {
+        int tg = t0 + 16 * (D == 128 ? j : sub >> 1);
         tg = tg < last_group ? tg : last_group;
         b.blk[j] = (uint32_t)((const_i32_ptr)(uintptr_t)g.table)[(unsigned)tg >> g.log2B];
     }
@@ -400,35 +404,34 @@ __device__ __forceinline__ sk_tile_blocks sk_lookup_tile(const sk_seg& g, int t0
 // and the 16-key group's offset inside a block of more than 16 tokens is added to those.
 // In LDS the sixteen 1 KiB units of a tile (K units 0-7, V^T units 8-15) lie US bytes apart, with
 // the same unit of the other tiles of the ring in between; `unit_addr` is the address of unit `sub`.
-// With head_dim 64 a tile has half the bytes.  K: rows of 128 bytes, eight to a 1 KiB unit, units
-// 0-3; one load per wave and tile (wave sub loads rows 8 (sub & 1) .. + 7 of group sub >> 1, `k_group`,
-// into unit sub).  V^T: the same units as with head_dim 128, of which 64 dims fill two per group, so
-// only the waves with sub < 2 load it (`v_wave`).
+// With head_dim 64 a tile has half the bytes, eight units: K units 0-3 (rows of 128 bytes, eight to a unit), V^T units
+// 4-7 (of each 16-key group two).  Wave sub loads K unit sub and V^T unit sub, both of group sub >> 1.
 template <unsigned US, int J, int D, bool MAY_STREAM>
 __device__ __forceinline__ void sk_issue_group(const sk_seg& g, int t0, int last_group, uint32_t blk,
-                                               unsigned unit_addr, unsigned koff, unsigned voff, int k_group, bool v_wave)
+                                               unsigned unit_addr, unsigned koff, unsigned voff, int j)
 {
     constexpr int LOG2_TOK_BYTES = D == 128 ? 8 : 7;       // K bytes per token and head = V^T bytes per token
-    int tg = t0 + 16 * J;
+    int tg = t0 + 16 * j;                                   // j: the group; the constant J with head_dim 128
     tg = tg < last_group ? tg : last_group;
     // the group's place in the block: 256 (128) bytes per token for K, 4 (2) KiB per 16-token group for V^T
     const unsigned char* bb = g.base + ((uint64_t)blk << (g.log2B + LOG2_TOK_BYTES + 1)) + (((unsigned)tg & (unsigned)(g.B - 1)) << LOG2_TOK_BYTES);
+    constexpr unsigned KU = J * 4 * US, VU = (D / 16 + J * 4) * US;
     if (MAY_STREAM && g.once) {       // uniform over the workgroup
-        if (D == 128) sk_dma16<J * 4 * US, true>(bb, koff, unit_addr);
-        else if (k_group == J) sk_dma16<0, true>(bb, koff, unit_addr);
-        if (D == 128 || v_wave) sk_dma16<(8 + J * 4) * US, true>(bb, voff, unit_addr);
+        sk_dma16<KU, true>(bb, koff, unit_addr);
+        sk_dma16<VU, true>(bb, voff, unit_addr);
     } else {
-        if (D == 128) sk_dma16<J * 4 * US, false>(bb, koff, unit_addr);
-        else if (k_group == J) sk_dma16<0, false>(bb, koff, unit_addr);
-        if (D == 128 || v_wave) sk_dma16<(8 + J * 4) * US, false>(bb, voff, unit_addr);
+        sk_dma16<KU, false>(bb, koff, unit_addr);
+        sk_dma16<VU, false>(bb, voff, unit_addr);
     }
 }
 template <unsigned US, int D, bool MAY_STREAM>
 __device__ __forceinline__ void sk_issue_tile(const sk_seg& g, int t0, int last_group, const sk_tile_blocks& tb,
-                                              unsigned unit_addr, unsigned koff, unsigned voff, int k_group, bool v_wave)
+                                              unsigned unit_addr, unsigned koff, unsigned voff, int sub)
 {
-    sk_issue_group<US, 0, D, MAY_STREAM>(g, t0, last_group, tb.blk[0], unit_addr, koff, voff, k_group, v_wave);
-    sk_issue_group<US, 1, D, MAY_STREAM>(g, t0, last_group, tb.blk[1], unit_addr, koff, voff, k_group, v_wave);
+    if (D == 128) {
+        sk_issue_group<US, 0, D, MAY_STREAM>(g, t0, last_group, tb.blk[0], unit_addr, koff, voff, 0);
+        sk_issue_group<US, 1, D, MAY_STREAM>(g, t0, last_group, tb.blk[1], unit_addr, koff, voff, 1);
+    } else sk_issue_group<US, 0, D, MAY_STREAM>(g, t0, last_group, tb.blk[0], unit_addr, koff, voff, sub >> 1);
 }
 
 // Writes a query's own K/V (at most SK_STAGE_TOKENS tokens, packed rows where the caller has them) into the staging
@@ -471,23 +474,22 @@ __device__ __forceinline__ void sk_stage_own(const sk_launch& P, const sk_work& 
 template <int NRG, int NPH, int NSS, int D>
 __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
 {
-    static_assert(D == 128 || (D == 64 && NSS == 2 && !(NRG == 8 && NPH == 1)),
-                  "head_dim 128, or 64 on the free-running instances (whose waits are all for every load)");
+    static_assert(D == 128 || D == 64, "head_dim");
     constexpr int NKS = D / 16;              // 16-dim slices of the QK^T contraction
     constexpr int NMT = D / 32;              // 32-dim blocks of the output
     constexpr int NW = NRG * NPH;            // waves: 4 or 8
     constexpr int TPI = 2;                   // tiles per iteration (64 keys)
     constexpr int TPW = TPI / NPH;           // tiles per wave per iteration
+    constexpr int TPS = D == 128 ? TPW : 1;  // tiles whose scores it holds at a time
     // eight waves either as two groups of row groups that take turns (LOCKSTEP, 256 rows), or as two key
     // phases per row group running freely (128 rows: half the arithmetic per wave of the four-wave
     // 128-row instance, two waves per SIMD)
-    constexpr bool LOCKSTEP = NW == 8 && NPH == 1;
+    constexpr bool LOCKSTEP = NW == 8 && NPH == 1 && D == 128, PIPELINED = NW == 8 && NPH == 1 && D == 64;
     // how the reference maximum is kept (step_softmax); at head_dim 128 the four-wave 128-row instance has no registers
-    // to keep the scores of two tiles beside their V^T operands (at 64, where those are half as many: 256-token append
-    // and 16-token query at 32,512 tokens 124.6 -> 120.7 us)
+    // to keep the scores of two tiles beside their V^T operands
     constexpr bool LAZY_MAX = LOCKSTEP || TPW == 1 || D == 64;
     constexpr int NLG = NW / 4;              // groups of four waves; each loads whole tiles
-    static_assert(NW == 4 || (LOCKSTEP && NSS == 4) || (NW == 8 && NPH == 2 && NSS == 2), "four waves, or eight as described");
+    static_assert(NW == 4 || ((LOCKSTEP || PIPELINED) && NSS == 4) || (NW == 8 && NPH == 2 && NSS == 2), "four waves, or eight as described");
     static_assert(NSS == 2 || NSS == 4, "ring depth in iterations: 64 KiB (two workgroups per CU) or 128 KiB (one)");
     static_assert(NSS * TPI >= (NPH == 1 ? NW : NRG), "the epilogue transposes one 16 KiB tile per wave (per row group with two phases) in the ring");
     // The ring holds NSS iterations of TPI tiles.  Its 1 KiB units are interleaved: unit u of tile t
@@ -496,8 +498,8 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     constexpr unsigned US = TPI * NSS * 1024;                 // bytes from unit u to unit u + 1
 #define SK_SLOT_OFF(s, t) (((t) * NSS + (s)) * 1024)          // tile t of ring slot s, relative to unit bases
     // (with two key phases the merge of the phases needs 17 KiB per row group: 68 KiB for four row groups)
-    constexpr unsigned RING_BYTES = NSS * TPI * SK_TILE_BYTES;
-    constexpr unsigned XCH_BYTES = NPH > 1 ? NRG * 17 * 64 * 16 : 0;
+    constexpr unsigned RING_BYTES = NSS * TPI * SK_TILE_BYTES * D / 128;
+    constexpr unsigned XCH_BYTES = NPH > 1 ? NRG * (4 * NMT + 1) * 64 * 16 : 0;
     __shared__ __attribute__((aligned(16))) unsigned char lds[RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES];
 
     sk_touch_arguments<sizeof(sk_launch)>();
@@ -546,7 +548,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     const int p_wave_max = causal ? w.pos0 + (int)((unsigned)wave_tok_last % period) : 0x7fffffff;
 
     // Q^T operand: lane (row r, k-group kg) keeps Q[row][16*ks + 8*kg .. +7] for ks = 0..7
-    bf16x8 qreg[8];
+    bf16x8 qreg[NKS];
     {
         // Rows past the tile re-read its first token's head row; what they compute goes nowhere.  Nothing here waits for
         // the loads: the segment loop issues its own first.
@@ -556,12 +558,15 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
         for (int ks = 0; ks < NKS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[ks * 2 + kg]);
     }
 
-    f32x16 oacc[4];
+    f32x16 oacc[NMT];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[mt][v] = 0.f;
-    float m_ref = SK_NEG_INF, l_run = 0.f;
+    float m_ref = SK_NEG_INF;
+    sk_f32x4 l_acc = {0.f, 0.f, 0.f, 0.f};          // sum of the weights as rounded: element 0 (the others are not kept to the reference)
+    sk_s16x4 ones4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};          // bf16 ones
+    if (!LOCKSTEP) asm volatile("" : "+v"(ones4));
     float lx_run = 0.f;                  // sum of the weights before rounding: what the log-sum-exp is taken from
     const float c_scale = P.g.scale_log2e;
     // key tau(rho): swap bits 2 and 3 of the S^T row index
@@ -569,16 +574,16 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
 
     // lane-dependent LDS addresses of the MFMA operands inside a tile (the XOR swizzles make them
     // irregular in ks, so they are kept in registers; tile and ring-slot offsets are immediates)
-    sk_lds_cptr kptr[8];
-    sk_lds_cptr vptr[4];
+    sk_lds_cptr kptr[NKS];
+    sk_lds_cptr vptr[NMT];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks)       // K row tau is row tau % 4 of unit tau / 4 (head_dim 64: row tau % 8 of unit tau / 8)
+    for (int ks = 0; ks < NKS; ++ks)       // K row tau is row tau % 4 of unit tau / 4 (head_dim 64: row tau % 8 of unit tau / 8)
         kptr[ks] = D == 128 ? (sk_lds_cptr)lds + SK_SLOT_OFF(0, ph * TPW) + (tau >> 2) * US + (tau & 3) * 256 + (((ks * 2 + kg) ^ (tau & 15)) << 4)
                             : (sk_lds_cptr)lds + SK_SLOT_OFF(0, ph * TPW) + (tau >> 3) * US + (tau & 7) * 128 + (((ks * 2 + kg) ^ (tau & 7)) << 4);
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
+    for (int mt = 0; mt < NMT; ++mt) {
         const int dd = mt * 32 + r;
-        vptr[mt] = (sk_lds_cptr)lds + SK_SLOT_OFF(0, ph * TPW) + (8 + mt) * US + r * 32 + ((kg ^ ((dd >> 3) & 1)) << 4);   // 16-key group q: + 4 q units
+        vptr[mt] = (sk_lds_cptr)lds + SK_SLOT_OFF(0, ph * TPW) + (D / 16 + mt) * US + r * 32 + ((kg ^ ((dd >> 3) & 1)) << 4);   // 16-key group q: + NMT q units
     }
 
 #pragma unroll 1
@@ -595,69 +600,67 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
 
         // lane-dependent parts of the DMA source addresses for this segment
         // (head_dim 64: lane -> (row rr of eight, chunk position of eight), source chunk (position ^ rr),
-        // the wave's rows being 8 (sub & 1) .. + 7 of group sub >> 1; V^T has dims for the first two waves only)
+        // the wave's rows and dims being those of unit sub & 1 of group sub >> 1)
         const int krow = D == 128 ? sub * 4 + (lane >> 4) : (sub & 1) * 8 + (lane >> 3);
         const unsigned koff = D == 128 ? (unsigned)(krow * 256 + (((lane & 15) ^ krow) << 4))
                                        : (unsigned)(krow * 128 + (((lane & 7) ^ (krow & 7)) << 4));
-        const int k_group = sub >> 1;
-        const int vdd = sub * 32 + (lane >> 1);
+        const int vdd = (D == 128 ? sub : sub & 1) * 32 + (lane >> 1);
         const unsigned voff = (unsigned)(g.v_off + vdd * 32 + ((((lane & 1) ^ ((vdd >> 3) & 1))) << 4));
-        const bool v_wave = sub < NMT;
 
         // ---- the three steps of one iteration (64 keys) for this wave; the ring slot is a
         // compile-time constant so that it folds into the offset field of the LDS instructions ----
-        f32x16 sacc[TPW];          // S^T of the iteration in flight
-        sk_u32x4 va[TPW][2][4];       // its V^T operands (four waves)
+        f32x16 sacc[TPS];          // S^T of the iteration in flight
+        sk_u32x4 va[TPS][2][NMT];       // its V^T operands (four waves)
         sk_u32x4 va0[4];              // V^T operands of the first 16 keys (eight waves)
-        bf16x8 pb[TPW][2];         // its P^T operands
+        bf16x8 pb[TPS][2];         // its P^T operands
 
         // first key position of the wave's tiles of iteration `it`, and whether it has work there
-        auto first_pos = [&](const int it) __attribute__((always_inline)) { return g.begin + it * g.step + ph * TPW * SK_TILE + g.pos_shift; };
-        auto is_active = [&](const int it) __attribute__((always_inline)) {
-            return wave_has_rows && g.begin + it * g.step + ph * TPW * SK_TILE < g.end && first_pos(it) <= lim_wave_max;
+        auto first_pos = [&](const int it, const int t0) __attribute__((always_inline)) { return g.begin + it * g.step + (ph * TPW + t0) * SK_TILE + g.pos_shift; };
+        auto is_active = [&](const int it, const int t0) __attribute__((always_inline)) {
+            return wave_has_rows && first_pos(it, t0) < g.end + g.pos_shift && first_pos(it, t0) <= lim_wave_max;
         };
 
         // S^T = K Q^T, TPW independent accumulator chains
         // (`soff`: byte offset of the ring slot read, a constant when the loop is unrolled over the slots)
-        auto step_scores = [&](const int soff) __attribute__((always_inline)) {
+        auto step_scores = [&](const int soff, const int t0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int t = 0; t < TPW; ++t)
+            for (int t = 0; t < TPS; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) sacc[t][v] = 0.f;
-            sk_u32x4 ka[TPW][NKS];
+            sk_u32x4 ka[TPS][NKS];
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-                for (int t = 0; t < TPW; ++t)
-                    ka[t][ks] = *(sk_lds_u4ptr)(kptr[ks] + soff + SK_SLOT_OFF(0, t));
+                for (int t = 0; t < TPS; ++t)
+                    ka[t][ks] = *(sk_lds_u4ptr)(kptr[ks] + soff + SK_SLOT_OFF(0, t0 + t));
             __builtin_amdgcn_s_setprio(2);     // the wave feeding the matrix pipe goes first
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-                for (int t = 0; t < TPW; ++t)
+                for (int t = 0; t < TPS; ++t)
                     sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[t][ks]), qreg[ks], sacc[t], 0, 0, 0);
             __builtin_amdgcn_s_setprio(0);
             // all LDS reads first, then the MFMAs back to back (two independent chains)
-            __builtin_amdgcn_sched_group_barrier(0x100, NKS * TPW, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, NKS * TPW, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, NKS * TPS, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, NKS * TPS, 0);
         };
-        auto load_v_tile = [&](const int t, const int soff) __attribute__((always_inline)) {
+        auto load_v_tile = [&](const int t, const int soff, const int t0) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
                 for (int mt = 0; mt < NMT; ++mt)
-                    va[t][q][mt] = *(sk_lds_u4ptr)(vptr[mt] + soff + SK_SLOT_OFF(0, t) + q * 4 * US);
+                    va[t][q][mt] = *(sk_lds_u4ptr)(vptr[mt] + soff + SK_SLOT_OFF(0, t0 + t) + q * NMT * US);
         };
         // a tile is masked when it crosses a causal or end-of-segment limit, or touches evicted tokens
-        auto needs_mask = [&](const int it) __attribute__((always_inline)) {
-            const int pos_first = first_pos(it);
-            return pos_first + TPW * SK_TILE - 1 > lim_wave_min ||
-                   (pos_first < g.hole_lo + g.hole_n && pos_first + TPW * SK_TILE > g.hole_lo);
+        auto needs_mask = [&](const int it, const int t0) __attribute__((always_inline)) {
+            const int pos_first = first_pos(it, t0);
+            return pos_first + TPS * SK_TILE - 1 > lim_wave_min ||
+                   (pos_first < g.hole_lo + g.hole_n && pos_first + TPS * SK_TILE > g.hole_lo);
         };
-        auto mask_scores = [&](const int it) __attribute__((always_inline)) {
-            const int pos_first = first_pos(it);
+        auto mask_scores = [&](const int it, const int t0) __attribute__((always_inline)) {
+            const int pos_first = first_pos(it, t0);
 #pragma unroll
-            for (int t = 0; t < TPW; ++t)
+            for (int t = 0; t < TPS; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int pos = pos_first + t * SK_TILE + 16 * (v >> 3) + 8 * kg + (v & 7);
@@ -665,11 +668,26 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                     sacc[t][v] = vis ? sacc[t][v] : SK_NEG_INF;
                 }
         };
+        // The row sum that normalises the output is taken over the weights as the matrix pipe sees
+        // them (rounded to bf16), with fp32 accumulation: numerator and
+        // denominator of the output then carry the same weights, so a row that one key dominates
+        // keeps that key's value to fp32 accuracy whatever the rounding of its weight (with the lazy
+        // maximum that weight is not 1).  The log-sum-exp is taken from the unrounded weights
+        // (lx_run), so it does not carry the rounding.
+        // Four weights of the lane at a time, in the smallest matrix instruction (sixteen 4 x 4 products: with ones on the
+        // left, every lane's own four weights are summed; 8 cycles of the matrix pipe), beside the products that use the
+        // same weights.  (v_dot2_f32_bf16 sums two, and takes three times its 4.9 cycles while the other wave of the SIMD keeps
+        // the matrix pipe busy.  The instance whose groups take turns sums by it all the same, in the vector slot: with it a
+        // 48-session step takes 4.12 ms, with the small products in the matrix slot 4.19.)
+        auto add_weights = [&](const bf16x8 p, const int h) __attribute__((always_inline)) {
+            typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+            l_acc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones4, __builtin_bit_cast(sk_s16x4, (uint64_t)__builtin_bit_cast(u64x2, p)[h]), l_acc, 0, 0, 0);
+        };
         // P = exp2(s * scale - m) for the reference maximum m as it stands, and the lane's sum of it (unrounded)
         auto weights = [&](const float neg_m) __attribute__((always_inline)) -> float {
             float lx0 = 0.f, lx1 = 0.f;
 #pragma unroll
-            for (int t = 0; t < TPW; ++t)
+            for (int t = 0; t < TPS; ++t)
 #pragma unroll
                 for (int v = 0; v < 8; ++v) {
                     const float p0 = sk_exp2(fmaf(sacc[t][v], c_scale, neg_m)), p1 = sk_exp2(fmaf(sacc[t][8 + v], c_scale, neg_m));
@@ -695,16 +713,16 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             if (look) {
                 float mt_ = SK_NEG_INF;
 #pragma unroll
-                for (int t = 0; t < TPW; ++t)
+                for (int t = 0; t < TPS; ++t)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) mt_ = fmaxf(mt_, sacc[t][v]);
                 { const sk_halves h = sk_both_halves(mt_); mt_ = fmaxf(h.lo, h.hi) * c_scale; }      // log2 units (c_scale > 0)
                 const bool raise = mt_ > m_ref + (LAZY_MAX ? 0.f : SK_RESCALE_SLACK);
                 if (LAZY_MAX || __any(raise)) {
                     const float alpha = raise ? sk_exp2(m_ref - mt_) : 1.0f;
-                    l_run *= alpha; lx_run *= alpha;
+                    l_acc[0] *= alpha; lx_run *= alpha;
 #pragma unroll
-                    for (int mt = 0; mt < 4; ++mt)
+                    for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
                         for (int v = 0; v < 16; ++v) oacc[mt][v] *= alpha;
                     m_ref = raise ? mt_ : m_ref;
@@ -712,32 +730,30 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 lx = weights(m_ref == SK_NEG_INF ? 0.f : -m_ref);      // no key seen yet: all weights 0
             }
             lx_run += lx;
-            // The row sum that normalises the output is taken over the weights as the matrix pipe sees
-            // them (rounded to bf16), two per instruction with fp32 accumulation: numerator and
-            // denominator of the output then carry the same weights, so a row that one key dominates
-            // keeps that key's value to fp32 accuracy whatever the rounding of its weight (with the lazy
-            // maximum that weight is not 1).  The log-sum-exp is taken from the unrounded weights
-            // (lx_run, above), so it does not carry the rounding.
-            const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-            float ls0 = 0.f, ls1 = 0.f;
+            if constexpr (LOCKSTEP) {
+                const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+                float ls0 = 0.f, ls1 = 0.f;
 #pragma unroll
-            for (int t = 0; t < TPW; ++t)
+                for (int t = 0; t < TPS; ++t)
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    ls0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 0, 1), ones, ls0, false);
-                    ls1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 2, 3), ones, ls1, false);
-                    ls0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 4, 5), ones, ls0, false);
-                    ls1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 6, 7), ones, ls1, false);
-                }
-            l_run += ls0 + ls1;
+                    for (int q = 0; q < 2; ++q) {
+                        ls0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 0, 1), ones, ls0, false);
+                        ls1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 2, 3), ones, ls1, false);
+                        ls0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 4, 5), ones, ls0, false);
+                        ls1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 6, 7), ones, ls1, false);
+                    }
+                l_acc[0] += ls0 + ls1;
+            }
         };
         // O^T += V^T P^T for one tile
         auto pv_tile = [&](const int t) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
-                for (int mt = 0; mt < NMT; ++mt)
+                for (int mt = 0; mt < NMT; ++mt) {
                     oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va[t][q][mt]), pb[t][q], oacc[mt], 0, 0, 0);
+                    if (mt < 2) add_weights(pb[t][q], mt);
+                }
         };
 
         sk_lds_barrier();                      // ring free (previous segment fully consumed)
@@ -749,7 +765,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             for (int ks = 0; ks < NKS; ++ks) asm volatile("" : : "v"(qreg[ks]));
         };
 
-        if constexpr (!LOCKSTEP) {
+        if constexpr (!LOCKSTEP && !PIPELINED) {
             // ---- free-running waves: every wave walks S, softmax, PV of an iteration in turn; overlap of
             // matrix and vector work comes from the other wave of the SIMD (the other workgroup on the
             // CU for the four-wave instances, the other key phase for the eight-wave one) ----
@@ -762,8 +778,8 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                     for (int p = 0; p < TPI; ++p) {
                         if (NLG > 1 && (p % NLG) != lg) continue;
                         const int t0 = g.begin + a * g.step + p * SK_TILE;
-                        const sk_tile_blocks tb = sk_lookup_tile(g, t0, last_group);
-                        sk_issue_tile<US, D, true>(g, t0, last_group, tb, unit_base + SK_SLOT_OFF(a, p), koff, voff, k_group, v_wave);
+                        const sk_tile_blocks tb = sk_lookup_tile<D>(g, t0, last_group, sub);
+                        sk_issue_tile<US, D, true>(g, t0, last_group, tb, unit_base + SK_SLOT_OFF(a, p), koff, voff, sub);
                     }
                 }
             }
@@ -772,7 +788,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             sk_tile_blocks nb[TPI];
 #pragma unroll
             for (int p = 0; p < TPI; ++p)
-                nb[p] = sk_lookup_tile(g, g.begin + (NSS - 1) * g.step + p * SK_TILE, last_group);
+                nb[p] = sk_lookup_tile<D>(g, g.begin + (NSS - 1) * g.step + p * SK_TILE, last_group, sub);
 
             // `slot` is the ring slot the iteration reads; the slot read by the previous iteration is
             // refilled with iteration it + NSS - 1.  With the two-slot ring the loop is unrolled over the
@@ -793,22 +809,25 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                     for (int p = 0; p < TPI; ++p) {
                         if (NLG > 1 && (p % NLG) != lg) continue;
                         sk_issue_tile<US, D, true>(g, g.begin + (it + NSS - 1) * g.step + p * SK_TILE, last_group, nb[p],
-                                                       unit_base + SK_SLOT_OFF((slot + NSS - 1) % NSS, p), koff, voff, k_group, v_wave);
+                                                       unit_base + SK_SLOT_OFF((slot + NSS - 1) % NSS, p), koff, voff, sub);
                     }
                     if (it + NSS < niter) {
 #pragma unroll
                         for (int p = 0; p < TPI; ++p)
-                            nb[p] = sk_lookup_tile(g, g.begin + (it + NSS) * g.step + p * SK_TILE, last_group);
+                            nb[p] = sk_lookup_tile<D>(g, g.begin + (it + NSS) * g.step + p * SK_TILE, last_group, sub);
                     }
                 }
-                if (!is_active(it)) return;
-                step_scores(slot * 1024);
 #pragma unroll
-                for (int t = 0; t < TPW; ++t) load_v_tile(t, slot * 1024);   // requested now: their LDS latency hides behind the softmax
-                if (needs_mask(it)) mask_scores(it);
-                step_softmax();
+                for (int t0 = 0; t0 < TPW; t0 += TPS) {
+                    if (!is_active(it, t0)) return;
+                    step_scores(slot * 1024, t0);
 #pragma unroll
-                for (int t = 0; t < TPW; ++t) pv_tile(t);
+                    for (int t = 0; t < TPS; ++t) load_v_tile(t, slot * 1024, t0);   // requested now: their LDS latency hides behind the softmax
+                    if (needs_mask(it, t0)) mask_scores(it, t0);
+                    step_softmax();
+#pragma unroll
+                    for (int t = 0; t < TPS; ++t) pv_tile(t);
+                }
             };
             if constexpr (NSS == 2) {
                 for (int it = 0; it < niter; it += 2) {
@@ -819,6 +838,221 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
 #pragma unroll 1
                 for (int it = 0; it < niter; ++it) iteration(it, it & (NSS - 1));
             }
+        } else if constexpr (PIPELINED) {
+            // ---- eight waves, each of which interleaves matrix and vector work instruction by instruction.  A stage
+            // is one tile: S of the next tile and P V of the last one (matrix instructions, alternating, so that neither chain
+            // waits for itself) with the weights of this one in between; the operand of a matrix instruction is read from
+            // LDS eight of them ahead.  An iteration is two stages with one workgroup barrier in front.
+            // Ring: a tile's K is read one stage before its weights and its V^T one stage behind, so K tile i lies in
+            // slot i - 1 and V^T tile i in slot i + 1 (mod 8): iteration j reads slots 2j and 2j + 1 of both.  In iteration j a
+            // wave issues its loads of the K tiles 2j + 7, 2j + 8 and the V^T tiles 2j + 5, 2j + 6 (one of each, by
+            // `half`), whose slots iteration j - 1 has read for the last time; it waits for them before the barrier of
+            // iteration j + 2, whose second stage reads ahead into iteration j + 3.
+            // Bound: issue.  A vector instruction beside matrix instructions of the same SIMD takes 8.8 cycles instead of 4.9
+            // (v_exp_f32 12.7 instead of 8.8; v_dot2_f32_bf16 14.8, hence add_weights): a stage of a SIMD's two waves takes about
+            // 1,200 cycles for 576 of matrix and 700 of vector instructions.  256 tokens of 32/8 heads at 32,512 cached, with the
+            // combine and the commit kernel: 96.5 us with 128-row tiles of four waves that walk S, softmax and P V in turn, 88.4
+            // with these; 512 at 130,560: 665 -> 618; the last ones of 2,600 into an empty session 63.4 -> 60.9.
+            constexpr int LPT = D / 64, LPW = 2 * LPT;      // direct-to-LDS loads per wave: of a tile's K (and V^T), per iteration
+            constexpr int NP = 2 * NKS;          // matrix instructions of a stage
+            constexpr int VP = 16 / NP;          // weights formed beside each
+            static_assert(NKS == 2 * NMT, "a stage has as many matrix instructions of either product");
+            const int half = wave >> 2;
+            const int n_iter = (g.end - g.begin + 2 * SK_TILE - 1) / (2 * SK_TILE);
+            auto& kc = kptr;                     // operand addresses: they follow the iteration through the ring
+            auto& vc = vptr;
+            f32x16 sc[2];
+            sk_u32x4 pw[2][2];
+            sk_u32x4 op[8];
+
+            // block ids of the K tile loaded next and of the V tile, which is the K tile of the iteration before
+            int t_k = g.begin + (half - 1) * SK_TILE;               // K tile -1 + half .. of "iteration -4"
+            sk_tile_blocks kb = sk_lookup_tile<D>(g, t_k < g.begin ? g.begin : t_k, last_group, sub), vb = kb;
+            constexpr int LOG2_TOK_BYTES = D == 128 ? 8 : 7;
+            auto group_base = [&](const int t0, const sk_tile_blocks& tb, const int j) __attribute__((always_inline)) {
+                int tg = t0 + 16 * (D == 128 ? j : sub >> 1);
+                tg = tg < last_group ? tg : last_group;
+                return g.base + ((uint64_t)tb.blk[j] << (g.log2B + LOG2_TOK_BYTES + 1)) + (((unsigned)tg & (unsigned)(g.B - 1)) << LOG2_TOK_BYTES);
+            };
+            // load J of LPT of a wave for the next K tile / V^T tile
+            auto issue_k = [&](const unsigned slot_addr, auto j_const) __attribute__((always_inline)) {
+                constexpr int J = decltype(j_const)::value;
+                if (J < LPT) sk_dma16<J * 4 * US, false>(group_base(t_k, kb, J < LPT ? J : 0), koff, slot_addr);
+            };
+            auto issue_v = [&](const unsigned slot_addr, auto j_const) __attribute__((always_inline)) {
+                constexpr int J = decltype(j_const)::value;
+                if (J < LPT) sk_dma16<(NKS + J * 4) * US, false>(group_base(t_k - 2 * SK_TILE, vb, J < LPT ? J : 0), voff, slot_addr);
+            };
+            auto next_blocks = [&]() __attribute__((always_inline)) {
+                t_k += 2 * SK_TILE;
+                vb = kb;
+                kb = sk_lookup_tile<D>(g, t_k, last_group, sub);
+            };
+            auto slot_addr_of = [&](const int it) __attribute__((always_inline)) { return unit_base + (unsigned)((((it + 3) & 3) * 2 + half) * 1024); };
+            // iterations -4 .. -1 (tiles in front of the segment are not loaded)
+            if (half == 1) { issue_k(slot_addr_of(-4), sk_int<0>{}); issue_k(slot_addr_of(-4), sk_int<1>{}); }
+            next_blocks();
+            issue_k(slot_addr_of(-3), sk_int<0>{}); issue_k(slot_addr_of(-3), sk_int<1>{});
+            if (half == 1) { issue_v(slot_addr_of(-3), sk_int<0>{}); issue_v(slot_addr_of(-3), sk_int<1>{}); }
+#pragma unroll
+            for (int it = -2; it < 0; ++it) {
+                next_blocks();
+                issue_k(slot_addr_of(it), sk_int<0>{}); issue_k(slot_addr_of(it), sk_int<1>{});
+                issue_v(slot_addr_of(it), sk_int<0>{}); issue_v(slot_addr_of(it), sk_int<1>{});
+            }
+            next_blocks();
+            await_query();
+
+            // tiles that need a mask
+            const int last_0 = g.begin + g.pos_shift + SK_TILE - 1;             // last position of tile 0
+            const int n_free = lim_wave_min < last_0 ? 0 : (int)((unsigned)(lim_wave_min - last_0) / SK_TILE) + 1;
+            int hole_t = 0, hole_ts = 0;
+            if (g.hole_n > 0 && g.hole_lo < g.end && g.hole_lo + g.hole_n > g.begin) {
+                hole_t = g.hole_lo > g.begin ? (g.hole_lo - g.begin) / SK_TILE : 0;
+                hole_ts = (g.hole_lo + g.hole_n - g.begin) / SK_TILE + 1 - hole_t;
+            }
+            auto mask_tile = [&](const int t, f32x16& s) __attribute__((always_inline)) {
+                if (!(t >= n_free || (unsigned)(t - hole_t) < (unsigned)hole_ts)) return;
+                const int pos_first = g.begin + t * SK_TILE + g.pos_shift;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int pos = pos_first + 16 * (v >> 3) + 8 * kg + (v & 7);
+                    const bool vis = pos <= lim_row && (unsigned)(pos - g.hole_lo) >= (unsigned)g.hole_n;
+                    s[v] = vis ? s[v] : SK_NEG_INF;
+                }
+            };
+            // operand of position p of a stage: even, K slice p / 2; odd, V^T block p / 2 (16-key group, then 32 dims)
+            auto ld_op = [&](const int p, const int off) __attribute__((always_inline)) -> sk_u32x4 {
+                if ((p & 1) == 0) return *(sk_lds_u4ptr)(kc[p >> 1] + off);
+                const int i = p >> 1;
+                return *(sk_lds_u4ptr)(vc[i % NMT] + off + (i / NMT) * NMT * US);
+            };
+            // One stage: S of the next tile, the weights of this one, P V of the last one, instruction by instruction.
+            auto stage = [&](auto half_const, auto pv_const, const int tile, const int delta, const f32x16& zero, f32x16& cur, f32x16& nxt,
+                             sk_u32x4 (&p_old)[2], sk_u32x4 (&p_new)[2], auto extra) __attribute__((always_inline)) {
+                constexpr int HALF = decltype(half_const)::value;
+                constexpr bool PV = decltype(pv_const)::value != 0;
+                mask_tile(tile, cur);
+                const float neg_m = -m_ref;
+                float x[17], e[16], lx0 = 0.f, lx1 = 0.f;
+                auto pair = [&](const int i) __attribute__((always_inline)) {
+                    uint32_t w2 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)e[2 * i], (__bf16)e[2 * i + 1]});
+                    asm volatile("" : "+v"(w2));         // here, not behind the branch below
+                    p_new[i >> 2][i & 3] = w2;
+                };
+                x[0] = fmaf(cur[0], c_scale, neg_m);
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    if ((p & 1) == 0) nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op[p & 7]), qreg[p >> 1], p == 0 ? zero : nxt, 0, 0, 0);
+                    else if (PV) {
+                        const int i = p >> 1;
+                        oacc[i % NMT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op[p & 7]), __builtin_bit_cast(bf16x8, p_old[i / NMT]), oacc[i % NMT], 0, 0, 0);
+                        if (i % NMT < 2) add_weights(__builtin_bit_cast(bf16x8, p_old[i / NMT]), i % NMT);
+                    }
+                    // the operand of eight positions later
+                    if (p + 8 < NP) op[p & 7] = ld_op(p + 8, HALF * 1024);
+                    else {
+                        const int t = p + 8 - NP, i = t >> 1;
+                        if (HALF == 1) {
+                            if ((t & 1) == 0) { kc[i] += delta; if (i + 4 < NKS) kc[i + 4] += delta; }
+                            else if (i < NMT) vc[i] += delta;
+                        }
+                        op[p & 7] = ld_op(t, HALF == 0 ? 1024 : 0);
+                    }
+#pragma unroll
+                    for (int u = 0; u < VP; ++u) {
+                        const int v = p * VP + u;
+                        if (v < 15) x[v + 1] = fmaf(cur[v + 1], c_scale, neg_m);
+                        e[v] = sk_exp2(x[v]);
+                        if (v >= 1) { if (v & 1) lx0 += e[v - 1]; else lx1 += e[v - 1]; }
+                        if (v >= 2 && (v & 1) == 0) pair(v / 2 - 1);
+                    }
+                    extra(p);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                lx1 += e[15];
+                pair(7);
+                float lx = lx0 + lx1;
+                if (__builtin_expect(__any(!(lx <= SK_SUM_LIMIT)), 0)) {
+                    float mt_ = SK_NEG_INF;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) mt_ = fmaxf(mt_, cur[v]);
+                    { const sk_halves h = sk_both_halves(mt_); mt_ = fmaxf(h.lo, h.hi) * c_scale; }
+                    const bool raise = mt_ > m_ref;
+                    const float alpha = raise ? sk_exp2(m_ref - mt_) : 1.0f;
+                    l_acc[0] *= alpha; lx_run *= alpha;
+#pragma unroll
+                    for (int mt = 0; mt < NMT; ++mt)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) oacc[mt][v] *= alpha;
+                    m_ref = raise ? mt_ : m_ref;
+                    const float neg = m_ref == SK_NEG_INF ? 0.f : -m_ref;
+                    lx0 = lx1 = 0.f;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        e[v] = sk_exp2(fmaf(cur[v], c_scale, neg));
+                        if (v & 1) lx1 += e[v]; else lx0 += e[v];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) pair(i);
+                    lx = lx0 + lx1;
+                }
+                lx_run += lx;
+            };
+            f32x16 zero;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) zero[v] = 0.f;
+
+            // S of tile 0
+            if (half == 1) SK_WAIT_VMCNT(5 * LPT);
+            sk_lds_barrier();
+            // K tile 0 lies in slot 7 (a tile's K one slot below its number, its V one above)
+            {
+                sk_u32x4 k0[NKS];
+#pragma unroll
+                for (int i = 0; i < NKS; ++i) k0[i] = *(sk_lds_u4ptr)(kc[i] + 7 * 1024);
+                sc[0] = zero;
+#pragma unroll
+                for (int i = 0; i < NKS; ++i) sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k0[i]), qreg[i], sc[0], 0, 0, 0);
+            }
+            auto begin_iteration = [&]() __attribute__((always_inline)) {
+                SK_WAIT_VMCNT(LPW);
+                sk_lds_barrier();
+            };
+            begin_iteration();
+#pragma unroll
+            for (int p = 0; p < 8; ++p) op[p] = ld_op(p, 0);
+            auto iteration = [&](auto pv_const, const int it) __attribute__((always_inline)) {
+                const unsigned sa = slot_addr_of(it);
+                const int delta = ((it + 1) & 3) == 0 ? -6 * 1024 : 2 * 1024;
+                stage(sk_int<0>{}, pv_const, 2 * it, delta, zero, sc[0], sc[1], pw[1], pw[0], [&](const int p) __attribute__((always_inline)) {
+                    if (p == 3) issue_k(sa, sk_int<0>{});
+                    if (p == NP - 5) issue_k(sa, sk_int<1>{});
+                });
+                stage(sk_int<1>{}, sk_int<1>{}, 2 * it + 1, delta, zero, sc[1], sc[0], pw[0], pw[1], [&](const int p) __attribute__((always_inline)) {
+                    if (p == 3) issue_v(sa, sk_int<0>{});
+                    if (p == NP / 2) issue_v(sa, sk_int<1>{});
+                    if (p == NP - 3) next_blocks();
+                });
+            };
+            iteration(sk_int<0>{}, 0);
+#pragma unroll 1
+            for (int it = 1; it < n_iter; ++it) {
+                begin_iteration();
+                iteration(sk_int<1>{}, it);
+            }
+            // P V of the last tile: its V^T lies where the next iteration's first stage would read it
+#pragma unroll
+            for (int i = 0; i < 2 * NMT; ++i) {
+                oacc[i % NMT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ld_op(2 * i + 1, 0)), __builtin_bit_cast(bf16x8, pw[1][i / NMT]), oacc[i % NMT], 0, 0, 0);
+                if (i % NMT < 2) add_weights(__builtin_bit_cast(bf16x8, pw[1][i / NMT]), i % NMT);
+            }
+            SK_WAIT_VMCNT(0);                    // nothing is still on its way into the ring
+            sk_lds_barrier();
+#pragma unroll
+            for (int i = 0; i < NKS; ++i) kc[i] -= (n_iter & 3) * 2048;
+#pragma unroll
+            for (int i = 0; i < NMT; ++i) vc[i] -= (n_iter & 3) * 2048;
         } else {
             // ---- eight waves in two groups of four that take turns.  Every wave alternates between
             // a matrix slot (P V of iteration j-1, then S of iteration j) and a vector slot (softmax
@@ -848,11 +1082,11 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // Loads are issued for `ahead` iterations past the end too (they re-read the segment's last
             // group and nothing reads them), so that the number of loads in flight at each wait is a constant.
             int t_next = g.begin + my_tile * SK_TILE;
-            sk_tile_blocks nb = sk_lookup_tile(g, t_next, last_group);
+            sk_tile_blocks nb = sk_lookup_tile<D>(g, t_next, last_group, sub);
             auto issue_next = [&](const int slot) __attribute__((always_inline)) {
-                sk_issue_tile<US, D, false>(g, t_next, last_group, nb, unit_base + SK_SLOT_OFF(slot, my_tile), koff, voff, k_group, v_wave);
+                sk_issue_tile<US, D, false>(g, t_next, last_group, nb, unit_base + SK_SLOT_OFF(slot, my_tile), koff, voff, sub);
                 t_next += g.step;
-                nb = sk_lookup_tile(g, t_next, last_group);
+                nb = sk_lookup_tile<D>(g, t_next, last_group, sub);
             };
             issue_next(0);
             issue_next(1);
@@ -925,7 +1159,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 hole_its = (g.hole_lo + g.hole_n - g.begin) / g.step + 1 - hole_it;
             }
             auto mask_iteration = [&](const int j) __attribute__((always_inline)) {
-                if (j >= n_free || (unsigned)(j - hole_it) < (unsigned)hole_its) mask_scores(j);
+                if (j >= n_free || (unsigned)(j - hole_it) < (unsigned)hole_its) mask_scores(j, 0);
             };
             // Vector slot: softmax of iteration j, and the operands of the first group of matrix
             // instructions of the slot that follows (V^T, first 16 keys of the iteration).
@@ -980,25 +1214,25 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
         }
     }
 
-    float l_tot; { const sk_halves h = sk_both_halves(l_run); l_tot = h.lo + h.hi; }
+    float l_tot; { const sk_halves h = sk_both_halves(l_acc[0]); l_tot = h.lo + h.hi; }
     float lx_tot; { const sk_halves h = sk_both_halves(lx_run); lx_tot = h.lo + h.hi; }
 
     if (NPH > 1) {
         // merge the key phases of each row group through LDS: per row group 17 x 64 float4 (lane-major, so a
         // wave's 16-byte accesses are conflict-free): entries 0..15 the accumulators, entry 16 = (m, l, lx, -)
         __syncthreads();                                  // every wave is done reading key tiles
-        float4* xch = (float4*)lds + rg * (17 * 64) + lane;
+        float4* xch = (float4*)lds + rg * ((4 * NMT + 1) * 64) + lane;
         if (ph == 1) {
 #pragma unroll
             for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4)
                     xch[(mt * 4 + q4) * 64] = make_float4(oacc[mt][q4 * 4 + 0], oacc[mt][q4 * 4 + 1], oacc[mt][q4 * 4 + 2], oacc[mt][q4 * 4 + 3]);
-            xch[16 * 64] = make_float4(m_ref, l_tot, lx_tot, 0.f);
+            xch[4 * NMT * 64] = make_float4(m_ref, l_tot, lx_tot, 0.f);
         }
         __syncthreads();
         if (ph == 0) {
-            const float4 s1 = xch[16 * 64];
+            const float4 s1 = xch[4 * NMT * 64];
             const float m1 = s1.x, l1 = s1.y, lx1 = s1.z;
             const float M = fmaxf(m_ref, m1);
             const float a0 = (m_ref == SK_NEG_INF) ? 0.f : sk_exp2(m_ref - M);
@@ -1029,13 +1263,13 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     const bool direct = w.part < 0;
     if (NPH == 1 || ph == 0) {                        // with two key phases, phase 0 holds the merged rows
         const float inv = direct ? 1.0f / l_tot : 1.0f;
-        float* tr = (float*)lds + (NPH == 1 ? wave : rg) * 4096;
+        float* tr = (float*)lds + (NPH == 1 ? wave : rg) * (32 * D);
 #pragma unroll
         for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
                 const int c4 = mt * 8 + q4 * 2 + kg;
-                *(float4*)(tr + r * 128 + ((c4 ^ r) & 31) * 4) =
+                *(float4*)(tr + r * D + ((c4 ^ r) & (D / 4 - 1)) * 4) =
                     make_float4(oacc[mt][q4 * 4 + 0] * inv, oacc[mt][q4 * 4 + 1] * inv, oacc[mt][q4 * 4 + 2] * inv, oacc[mt][q4 * 4 + 3] * inv);
             }
         const size_t orow_lane = ((size_t)(w.q_tok0 + tok_local) * P.g.Hq + hq);
@@ -1052,7 +1286,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // contexts) would otherwise all write the same offset of their partial slots, which lie a
             // power of two apart, at the same time, and crowd onto a few memory channels
             const int row = ((it + blockIdx.x) & (NIT - 1)) * RPI + lane / CPR;
-            const float4 val = *(const float4*)(tr + row * 128 + ((c4 ^ row) & 31) * 4);
+            const float4 val = *(const float4*)(tr + row * D + ((c4 ^ row) & (D / 4 - 1)) * 4);
             const int rit = rg * 32 + row;                 // row inside the tile
             const int tok2 = div_g(rit);
             if (tok2 >= w.n_tok) continue;
@@ -1125,7 +1359,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             for (int row = k * rps + wave; row < row_end; row += NW) {
                 const int tok3 = div_g(row);
                 const size_t orow = (size_t)(w.q_tok0 + tok3) * P.g.Hq + w.kv_head * G + (row - tok3 * G);
-                sk_merge_row(P, (size_t)w.part0 * P.rows_per_slot + row, (size_t)P.g.Hkv * P.rows_per_slot, w.n_parts, orow, lane);
+                sk_merge_row<D>(P, (size_t)w.part0 * P.rows_per_slot + row, (size_t)P.g.Hkv * P.rows_per_slot, w.n_parts, orow, lane);
             }
         }
     }
@@ -1145,7 +1379,7 @@ __global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 1 : 2) void sk_att
     sk_attn_bf16_body<NRG, NPH, NSS, 128>(P);
 }
 template <int NRG, int NPH, int NSS>
-__global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 1 : 2) void sk_attn_bf16_d64(const sk_launch P)
+__global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 2 : 3) void sk_attn_bf16_d64(const sk_launch P)
 {
     sk_attn_bf16_body<NRG, NPH, NSS, 64>(P);
 }
@@ -2151,10 +2385,13 @@ int sk_launch_attention(const sk_launch& L, int variant, int32_t n_workgroups, v
 {
     if (n_workgroups <= 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-    if (variant != SK_KV_SIMPLE && L.g.d != 128 && !(L.g.d == 64 && variant != SK_KV_MFMA256)) return (int)hipErrorInvalidValue;
+    if (variant != SK_KV_SIMPLE && L.g.d != 128 && !(L.g.d == 64 && variant != SK_KV_MFMA128P)) return (int)hipErrorInvalidValue;
     const bool d64 = L.g.d == 64;
     switch (variant) {
-    case SK_KV_MFMA256:      SK_LAUNCH((sk_attn_bf16_d128<8, 1, 4>), dim3(n_workgroups), dim3(512)); break;
+    case SK_KV_MFMA256:
+        if (d64) SK_LAUNCH((sk_attn_bf16_d64<8, 1, 4>), dim3(n_workgroups), dim3(512));
+        else SK_LAUNCH((sk_attn_bf16_d128<8, 1, 4>), dim3(n_workgroups), dim3(512));
+        break;
     case SK_KV_MFMA128:
         if (d64) SK_LAUNCH((sk_attn_bf16_d64<4, 1, 2>), dim3(n_workgroups), dim3(256));
         else SK_LAUNCH((sk_attn_bf16_d128<4, 1, 2>), dim3(n_workgroups), dim3(256));
@@ -2163,10 +2400,7 @@ int sk_launch_attention(const sk_launch& L, int variant, int32_t n_workgroups, v
         if (d64) SK_LAUNCH((sk_attn_bf16_d64<2, 2, 2>), dim3(n_workgroups), dim3(256));
         else SK_LAUNCH((sk_attn_bf16_d128<2, 2, 2>), dim3(n_workgroups), dim3(256));
         break;
-    case SK_KV_MFMA128P:
-        if (d64) SK_LAUNCH((sk_attn_bf16_d64<4, 2, 2>), dim3(n_workgroups), dim3(512));
-        else SK_LAUNCH((sk_attn_bf16_d128<4, 2, 2>), dim3(n_workgroups), dim3(512));
-        break;
+    case SK_KV_MFMA128P:     SK_LAUNCH((sk_attn_bf16_d128<4, 2, 2>), dim3(n_workgroups), dim3(512)); break;
     default:
         if (L.g.elem != 2) return (int)hipErrorInvalidValue;
         SK_LAUNCH(sk_attn_simple, dim3(n_workgroups), dim3(256));

@@ -263,12 +263,11 @@ constexpr int64_t kSmallMaxBytes = int64_t(128) << 20;
 bool pick_variant(const sk_pool* p, int64_t n_tok, Variant& v, bool allow_256 = false, int64_t cached = -1)
 {
     const int G = p->L.G;
-    // any group size up to 128 (multi-query models): a tile holds floor(rows / G) tokens, at least one;
-    // head_dim 64 has no 256-row instance
+    // any group size up to 128 (multi-query models): a tile holds floor(rows / G) tokens, at least one
     const bool mfma_ok = p->d.dtype == SK_BF16 && (p->d.head_dim == 128 || p->d.head_dim == 64) && G <= 128;
     if (mfma_ok && !p->force_simple) {
         if (cached >= 0 && !p->no_small && n_tok * G <= 32 && cached * p->d.n_kv_heads * p->d.head_dim * 4 <= kSmallMaxBytes) { v.id = SK_KV_SMALL; v.rows_per_slot = 32; v.tok_per_tile = 32 / G; }
-        else if (allow_256 && p->d.head_dim == 128 && n_tok * G > 128) { v.id = SK_KV_MFMA256; v.rows_per_slot = 256; v.tok_per_tile = 256 / G; }
+        else if (allow_256 && n_tok * G > 128) { v.id = SK_KV_MFMA256; v.rows_per_slot = 256; v.tok_per_tile = 256 / G; }
         else if (n_tok * G > 64 || G > 64) { v.id = SK_KV_MFMA128; v.rows_per_slot = 128; v.tok_per_tile = 128 / G; }
         else { v.id = SK_KV_MFMA64; v.rows_per_slot = 64; v.tok_per_tile = 64 / G; }
         return true;
@@ -420,7 +419,12 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
         // A call with few row tiles (a query) is bound by streaming the cache once: one workgroup
         // per CU measured faster than two (fewer split partials to write and merge).  Calls with
         // many row tiles (appends) are bound by arithmetic and want two workgroups per CU.
-        const int64_t target = p->target_wgs_set ? p->target_wgs : ((L.n_tiles <= 2 || v.id == SK_KV_MFMA256) ? 256 : 512);
+        // Not so with head_dim 64, whose smaller workgroups overlap on a CU (us per query, one -> two per CU, 32/8 heads):
+        //   128 rows   14,800 cached 16.9 -> 16.4, 32,768 25.1 -> 22.0, 65,536 41.5 -> 38.6, 131,072 73.9 -> 62.5
+        //    64 rows   14,800 14.3 -> 14.7, 20,000 15.9 -> 16.2, 26,000 18.4 -> 17.9, 32,768 20.9 -> 20.0, 65,536 33.3 -> 29.3, 131,072 59.3 -> 49.1
+        // (three: 25.0 at 32,768 with 128 rows, 52.7 at 131,072 with 64)
+        const bool two_per_cu = p->d.head_dim == 64 && (v.id == SK_KV_MFMA128 || (v.id == SK_KV_MFMA64 && kv_len >= 24576));
+        const int64_t target = p->target_wgs_set ? p->target_wgs : (((L.n_tiles <= 2 && !two_per_cu) || v.id == SK_KV_MFMA256) ? 256 : 512);
         S = std::max<int64_t>(1, (target + base_wgs / 2) / base_wgs);
     }
     int64_t chunk = kv_len > 0 ? (kv_len + S - 1) / S : 64;
@@ -461,7 +465,7 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     // tokens 18.5 -> 20.1, 8K 22.8 -> 24.7, 14,800 28.3 -> 29.4, 32K 42.3 -> 42.1, 64K 69.5 -> 65.3,
     // 128K 123.8 -> 113.2: the eight waves pay off once the stream outweighs their longer start and
     // their merge of the two phases.
-    if (p->p128 && v.id == SK_KV_MFMA128 && R.wgs <= p->n_cus && kv_len >= p->p128_min_tokens) v.id = SK_KV_MFMA128P;
+    if (p->p128 && v.id == SK_KV_MFMA128 && p->d.head_dim == 128 && R.wgs <= p->n_cus && kv_len >= p->p128_min_tokens) v.id = SK_KV_MFMA128P;
     L.fuse = (p->fuse && mfma && parts > 1 && base_wgs <= p->L.sync_units && parts < 65536) ? 1 : 0;
     const int64_t resident = int64_t(p->n_cus) * ((v.id == SK_KV_MFMA256 || v.id == SK_KV_MFMA128P) ? 1 : 2);
     L.wait_polls = (L.fuse && R.wgs <= resident) ? p->wait_polls : 0;
@@ -796,7 +800,7 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g)
         }
         const int64_t n = whole + (int64_t)n_tiles;
         const bool sparse = big || n * Hkv <= p->n_cus;
-        const double it = big ? 1.7 : (sparse ? 1.4 : 2.7), ends = 6.0;
+        const double it = big ? (p->d.head_dim == 128 ? 1.7 : 1.2) : (sparse ? 1.4 : 2.7), ends = 6.0;
         const int64_t lanes = std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
         const double merge = double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0;
         // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
@@ -1451,7 +1455,7 @@ int sk_session_query_shared_prefix(sk_pool* p, int32_t id, const void* qp, const
         // kernel (their rows see the same cache and prefix; each sees its own suffix), when a
         // question's rows are a multiple of a wave's 32 and divide 256.
         const int64_t rows_q = int64_t(Sfx) * p->L.G;
-        const bool pack = groups[1].v.id != SK_KV_SIMPLE && p->d.head_dim == 128 && rows_q < 256 && rows_q % 32 == 0 &&
+        const bool pack = groups[1].v.id != SK_KV_SIMPLE && rows_q < 256 && rows_q % 32 == 0 &&
                           256 % rows_q == 0 && NQ > 1 && !p->no_pack;
         const int32_t per_tile = pack ? int32_t(256 / rows_q) : 1;
         if (pack) groups[1].v = Variant{SK_KV_MFMA256, 256, 256 / p->L.G};

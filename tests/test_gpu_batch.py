@@ -170,3 +170,30 @@ def test_shared_prefix_question_batch(n, P, NQ, Sfx):
     compare("suffix rows", os_, ls, ros.reshape(NQ * Sfx, shape.n_q_heads, -1), rls.reshape(NQ * Sfx, -1), shape.dtype)
     torch.cuda.synchronize()
     assert torch.equal(before, pool.kv_mem) and pool.sk_session_length(sid) == n
+
+
+@pytest.mark.parametrize("n,P,NQ,Sfx", [(700, 16, 6, 8), (0, 16, 9, 16), (330, 40, 3, 32), (65, 0, 5, 5)])
+def test_shared_prefix_question_batch_head_dim_64(n, P, NQ, Sfx):
+    """Questions of a head_dim 64 layer, packed into 256-row tiles where their rows allow it."""
+    shape = synth.Shape("bf16", 32, 8, 64)
+    gen = synth.generator(5, stream=3000 + n + P)
+    pool = sk.Pool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, 16, n // 16 + 8, max_sessions=1, kv_fill=0xFF)
+    ref = oracle.OracleSession(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim)
+    sid = pool.sk_session_create()
+    if n:
+        q, k, v = synth.draw_qkv(gen, n, shape)
+        pool.sk_session_append(sid, None, dev(k), dev(v))
+        ref.K, ref.V = synth.to_raw(k), synth.to_raw(v)
+    qp, kp, vp = synth.draw_qkv(gen, P, shape)
+    qs, ks, vs = synth.draw_qkv(gen, NQ * Sfx, shape)
+    r4 = lambda t, H: t.reshape(NQ, Sfx, H, shape.head_dim)
+    op, lp, os_, ls = pool.sk_session_query_shared_prefix(
+        sid, dev(qp) if P else None, dev(kp) if P else None, dev(vp) if P else None,
+        dev(r4(qs, shape.n_q_heads)), dev(r4(ks, shape.n_kv_heads)), dev(r4(vs, shape.n_kv_heads)))
+    rop, rlp, ros, rls = ref.query_shared_prefix(
+        synth.to_raw(qp), synth.to_raw(kp), synth.to_raw(vp),
+        synth.to_raw(qs).reshape(NQ, Sfx, shape.n_q_heads, -1), synth.to_raw(ks).reshape(NQ, Sfx, shape.n_kv_heads, -1),
+        synth.to_raw(vs).reshape(NQ, Sfx, shape.n_kv_heads, -1))
+    if P:
+        compare("prefix rows", op, lp, rop, rlp, shape.dtype)
+    compare("suffix rows", os_, ls, ros.reshape(NQ * Sfx, shape.n_q_heads, -1), rls.reshape(NQ * Sfx, -1), shape.dtype)

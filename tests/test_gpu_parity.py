@@ -648,3 +648,38 @@ def test_combine_rounds(hq, hkv, d):
             pr.query(sid, q, k if own else None, v if own else None, n_splits=S, out_dtype="bf16" if S % 2 else "f32", name="S=%d own=%d" % (S, own))
             geo = pr.pool.sk_pool_last_launch()
             assert geo["n_splits"] == S + own and geo["fused_merge"] == 0, geo
+
+
+@pytest.mark.parametrize("hq,hkv,frozen", [(32, 8, 5), (14, 2, 300)])
+def test_head_dim_64_tiles_of_256_rows(hq, hkv, frozen):
+    """The 256-row instance at head_dim 64: cached lengths at the edges of a tile (32 keys), of an iteration (64) and of
+    the ring (eight tiles), one and several row tiles with ragged last rows, direct and split results, queries with and without
+    their own K/V, evicted tokens in the first and in a middle tile."""
+    shape = synth.Shape("bf16", hq, hkv, 64)
+    gen = synth.generator(2, stream=1600 + hq)
+    G = hq // hkv
+    pr = Pair(shape, n_blocks=200, max_sessions=1, max_batch_tokens=1024, kv_fill=0xFF)
+    sid = pr.create()
+    ref = pr.oracles[sid]
+    for n in (0, 1, 31, 33, 64, 96, 97, 160, 224, 255, 257, 288, 320, 545, 900):
+        if n > len(ref.K):
+            _, k, v = synth.draw_qkv(gen, n - len(ref.K), shape)
+            pr.append(sid, None, k, v, check=False)
+        for T in (128 // G + 1, 256 // G, 256 // G + 1) if n in (0, 33, 257, 900) else (256 // G - 3,):
+            q, k, v = synth.draw_qkv(gen, T, shape)
+            if n:
+                pr.query(sid, q, name="A n=%d T=%d" % (n, T))
+                assert pr.pool.sk_pool_last_launch()["kernel_variant"] == 3
+            pr.query(sid, q, k, v, n_splits=1, name="B n=%d T=%d" % (n, T))
+            pr.append(sid, q, k, v, name="append n=%d T=%d" % (n, T))
+            assert pr.pool.sk_pool_last_launch()["kernel_variant"] == 3
+            pr.pool.sk_session_truncate(sid, n)
+            ref.truncate(n)
+    pr.freeze(sid, frozen)
+    for gone in (20, 40, 200):
+        pr.evict(sid, gone)
+        q, k, v = synth.draw_qkv(gen, 256 // G, shape)
+        pr.query(sid, q, k, v, name="%d more evicted" % gone)
+        pr.query(sid, q, n_splits=1, name="%d more evicted, one part" % gone)
+        pr.append(sid, q, k, v, name="append behind a hole")
+    pr.check_cache(sid)
