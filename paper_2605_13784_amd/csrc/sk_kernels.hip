@@ -142,7 +142,7 @@ __device__ __forceinline__ bool sk_decode_work(const sk_launch& P, int b, sk_wor
         int e = w.kv_begin + P.chunk;
         w.kv_end = e < kv_vis ? e : kv_vis;
     }
-    w.part = (P.n_splits == 1) ? -1 : (tile * P.n_splits + split) * Hkv + head;
+    w.part = np == 1 ? -1 : (tile * P.n_splits + split) * Hkv + head;         // a tile of one part is written directly
     w.unit = tile * Hkv + head; w.part0 = tile * P.n_splits * Hkv + head; w.n_parts = np;
     w.hole_lo = P.hole_lo; w.hole_hi = P.hole_hi;
     w.tok_period = 0; w.sub_blocks = 0;
@@ -480,7 +480,6 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     constexpr int NW = NRG * NPH;            // waves: 4 or 8
     constexpr int TPI = 2;                   // tiles per iteration (64 keys)
     constexpr int TPW = TPI / NPH;           // tiles per wave per iteration
-    constexpr int TPS = D == 128 ? TPW : 1;  // tiles whose scores it holds at a time
     // eight waves either as two groups of row groups that take turns (LOCKSTEP, 256 rows), or as two key
     // phases per row group running freely (128 rows: half the arithmetic per wave of the four-wave
     // 128-row instance, two waves per SIMD)
@@ -609,58 +608,58 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
 
         // ---- the three steps of one iteration (64 keys) for this wave; the ring slot is a
         // compile-time constant so that it folds into the offset field of the LDS instructions ----
-        f32x16 sacc[TPS];          // S^T of the iteration in flight
-        sk_u32x4 va[TPS][2][NMT];       // its V^T operands (four waves)
+        f32x16 sacc[TPW];          // S^T of the iteration in flight
+        sk_u32x4 va[TPW][2][NMT];       // its V^T operands (four waves)
         sk_u32x4 va0[4];              // V^T operands of the first 16 keys (eight waves)
-        bf16x8 pb[TPS][2];         // its P^T operands
+        bf16x8 pb[TPW][2];         // its P^T operands
 
         // first key position of the wave's tiles of iteration `it`, and whether it has work there
-        auto first_pos = [&](const int it, const int t0) __attribute__((always_inline)) { return g.begin + it * g.step + (ph * TPW + t0) * SK_TILE + g.pos_shift; };
-        auto is_active = [&](const int it, const int t0) __attribute__((always_inline)) {
-            return wave_has_rows && first_pos(it, t0) < g.end + g.pos_shift && first_pos(it, t0) <= lim_wave_max;
+        auto first_pos = [&](const int it) __attribute__((always_inline)) { return g.begin + it * g.step + ph * TPW * SK_TILE + g.pos_shift; };
+        auto is_active = [&](const int it) __attribute__((always_inline)) {
+            return wave_has_rows && g.begin + it * g.step + ph * TPW * SK_TILE < g.end && first_pos(it) <= lim_wave_max;
         };
 
         // S^T = K Q^T, TPW independent accumulator chains
         // (`soff`: byte offset of the ring slot read, a constant when the loop is unrolled over the slots)
-        auto step_scores = [&](const int soff, const int t0) __attribute__((always_inline)) {
+        auto step_scores = [&](const int soff) __attribute__((always_inline)) {
 #pragma unroll
-            for (int t = 0; t < TPS; ++t)
+            for (int t = 0; t < TPW; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) sacc[t][v] = 0.f;
-            sk_u32x4 ka[TPS][NKS];
+            sk_u32x4 ka[TPW][NKS];
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-                for (int t = 0; t < TPS; ++t)
-                    ka[t][ks] = *(sk_lds_u4ptr)(kptr[ks] + soff + SK_SLOT_OFF(0, t0 + t));
+                for (int t = 0; t < TPW; ++t)
+                    ka[t][ks] = *(sk_lds_u4ptr)(kptr[ks] + soff + SK_SLOT_OFF(0, t));
             __builtin_amdgcn_s_setprio(2);     // the wave feeding the matrix pipe goes first
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-                for (int t = 0; t < TPS; ++t)
+                for (int t = 0; t < TPW; ++t)
                     sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[t][ks]), qreg[ks], sacc[t], 0, 0, 0);
             __builtin_amdgcn_s_setprio(0);
             // all LDS reads first, then the MFMAs back to back (two independent chains)
-            __builtin_amdgcn_sched_group_barrier(0x100, NKS * TPS, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, NKS * TPS, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, NKS * TPW, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, NKS * TPW, 0);
         };
-        auto load_v_tile = [&](const int t, const int soff, const int t0) __attribute__((always_inline)) {
+        auto load_v_tile = [&](const int t, const int soff) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
                 for (int mt = 0; mt < NMT; ++mt)
-                    va[t][q][mt] = *(sk_lds_u4ptr)(vptr[mt] + soff + SK_SLOT_OFF(0, t0 + t) + q * NMT * US);
+                    va[t][q][mt] = *(sk_lds_u4ptr)(vptr[mt] + soff + SK_SLOT_OFF(0, t) + q * NMT * US);
         };
         // a tile is masked when it crosses a causal or end-of-segment limit, or touches evicted tokens
-        auto needs_mask = [&](const int it, const int t0) __attribute__((always_inline)) {
-            const int pos_first = first_pos(it, t0);
-            return pos_first + TPS * SK_TILE - 1 > lim_wave_min ||
-                   (pos_first < g.hole_lo + g.hole_n && pos_first + TPS * SK_TILE > g.hole_lo);
+        auto needs_mask = [&](const int it) __attribute__((always_inline)) {
+            const int pos_first = first_pos(it);
+            return pos_first + TPW * SK_TILE - 1 > lim_wave_min ||
+                   (pos_first < g.hole_lo + g.hole_n && pos_first + TPW * SK_TILE > g.hole_lo);
         };
-        auto mask_scores = [&](const int it, const int t0) __attribute__((always_inline)) {
-            const int pos_first = first_pos(it, t0);
+        auto mask_scores = [&](const int it) __attribute__((always_inline)) {
+            const int pos_first = first_pos(it);
 #pragma unroll
-            for (int t = 0; t < TPS; ++t)
+            for (int t = 0; t < TPW; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int pos = pos_first + t * SK_TILE + 16 * (v >> 3) + 8 * kg + (v & 7);
@@ -687,7 +686,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
         auto weights = [&](const float neg_m) __attribute__((always_inline)) -> float {
             float lx0 = 0.f, lx1 = 0.f;
 #pragma unroll
-            for (int t = 0; t < TPS; ++t)
+            for (int t = 0; t < TPW; ++t)
 #pragma unroll
                 for (int v = 0; v < 8; ++v) {
                     const float p0 = sk_exp2(fmaf(sacc[t][v], c_scale, neg_m)), p1 = sk_exp2(fmaf(sacc[t][8 + v], c_scale, neg_m));
@@ -713,7 +712,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             if (look) {
                 float mt_ = SK_NEG_INF;
 #pragma unroll
-                for (int t = 0; t < TPS; ++t)
+                for (int t = 0; t < TPW; ++t)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) mt_ = fmaxf(mt_, sacc[t][v]);
                 { const sk_halves h = sk_both_halves(mt_); mt_ = fmaxf(h.lo, h.hi) * c_scale; }      // log2 units (c_scale > 0)
@@ -734,7 +733,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
                 float ls0 = 0.f, ls1 = 0.f;
 #pragma unroll
-                for (int t = 0; t < TPS; ++t)
+                for (int t = 0; t < TPW; ++t)
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
                         ls0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[t][q], pb[t][q], 0, 1), ones, ls0, false);
@@ -817,17 +816,14 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                             nb[p] = sk_lookup_tile<D>(g, g.begin + (it + NSS) * g.step + p * SK_TILE, last_group, sub);
                     }
                 }
+                if (!is_active(it)) return;
+                step_scores(slot * 1024);
 #pragma unroll
-                for (int t0 = 0; t0 < TPW; t0 += TPS) {
-                    if (!is_active(it, t0)) return;
-                    step_scores(slot * 1024, t0);
+                for (int t = 0; t < TPW; ++t) load_v_tile(t, slot * 1024);   // requested now: their LDS latency hides behind the softmax
+                if (needs_mask(it)) mask_scores(it);
+                step_softmax();
 #pragma unroll
-                    for (int t = 0; t < TPS; ++t) load_v_tile(t, slot * 1024, t0);   // requested now: their LDS latency hides behind the softmax
-                    if (needs_mask(it, t0)) mask_scores(it, t0);
-                    step_softmax();
-#pragma unroll
-                    for (int t = 0; t < TPS; ++t) pv_tile(t);
-                }
+                for (int t = 0; t < TPW; ++t) pv_tile(t);
             };
             if constexpr (NSS == 2) {
                 for (int it = 0; it < niter; it += 2) {
@@ -1159,7 +1155,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 hole_its = (g.hole_lo + g.hole_n - g.begin) / g.step + 1 - hole_it;
             }
             auto mask_iteration = [&](const int j) __attribute__((always_inline)) {
-                if (j >= n_free || (unsigned)(j - hole_it) < (unsigned)hole_its) mask_scores(j, 0);
+                if (j >= n_free || (unsigned)(j - hole_it) < (unsigned)hole_its) mask_scores(j);
             };
             // Vector slot: softmax of iteration j, and the operands of the first group of matrix
             // instructions of the slot that follows (V^T, first 16 keys of the iteration).
@@ -1379,7 +1375,7 @@ __global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 1 : 2) void sk_att
     sk_attn_bf16_body<NRG, NPH, NSS, 128>(P);
 }
 template <int NRG, int NPH, int NSS>
-__global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 2 : 3) void sk_attn_bf16_d64(const sk_launch P)
+__global__ __launch_bounds__(64 * NRG * NPH, 2) void sk_attn_bf16_d64(const sk_launch P)
 {
     sk_attn_bf16_body<NRG, NPH, NSS, 64>(P);
 }
@@ -2164,7 +2160,7 @@ __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
         int ntok = P.n_tok - tok0; ntok = ntok < P.tok_per_tile ? ntok : P.tok_per_tile;
         int kv_vis;
         cb.n_parts = P.own_mode == SK_OWN_SMALL ? P.n_splits : sk_tile_parts(P, tok0, ntok, &kv_vis);
-        if (P.own_mode == SK_OWN_F32 && cb.n_parts == 1) return;              // written by the attention kernel
+        if (cb.n_parts == 1) return;              // written by the attention kernel
         cb.part0 = tile * P.n_splits * Hkv + head; cb.part_stride = Hkv;
         cb.q_tok0 = tok0; cb.n_tok = ntok; cb.kv_head = head;
     }

@@ -391,6 +391,117 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
     return SK_OK;
 }
 
+struct TileReq {            // one tile of query rows and the keys it may see
+    int32_t tbl_off, q_tok0, n_tok;
+    int32_t pos0;           // absolute position of its first token, or SK_NO_CAUSAL
+    int32_t kv_vis;         // cached tokens visible to the tile (positions 0 .. kv_vis-1)
+    int32_t eph_blk[2], eph_cnt[2], eph_pos0[2];
+    int32_t hole_lo, hole_hi;   // evicted cached tokens of the session
+    int32_t tok_period, sub_blocks;   // > 0: the tile packs sequences of tok_period tokens (see sk_work)
+};
+struct ListGroup {          // tiles that share a kernel variant and the q/out/lse arrays
+    Variant v = {SK_KV_SIMPLE, 16, 1};
+    const void* q = nullptr; void* out = nullptr; float* lse = nullptr;
+    std::vector<TileReq> tiles;
+};
+
+// Cuts T tokens (packed rows q_row0..) that share `base` into row tiles of the group's height.
+void add_tiles(ListGroup& g, const TileReq& base, int32_t q_row0, int32_t T)
+{
+    for (int32_t t0 = 0; t0 < T; t0 += g.v.tok_per_tile) {
+        TileReq r = base;
+        r.q_tok0 = q_row0 + t0;
+        r.n_tok = std::min(g.v.tok_per_tile, T - t0);
+        if (base.pos0 < SK_NO_CAUSAL) {
+            r.pos0 = base.pos0 + t0;
+            r.kv_vis = std::min<int64_t>(base.kv_vis, int64_t(r.pos0) + r.n_tok);
+        }
+        g.tiles.push_back(r);
+    }
+}
+
+// Pieces of at most `chunk` keys that a tile is cut into (a tile that sees no cached key is one piece), and which eighth of
+// a chunk a piece's length falls into.  Lengths and chunks stay below 2^30.
+uint32_t list_parts(const TileReq& t, uint32_t chunk) { return t.kv_vis > 0 ? ((uint32_t)t.kv_vis + chunk - 1) / chunk : 1; }
+uint32_t list_bucket(uint32_t len, uint32_t chunk) { return len == chunk ? 8 : uint32_t(uint64_t(len) * 8 / chunk); }
+
+// Length of the pieces a launch's tiles are cut into: the one for which the launch is expected to end first.
+// The workgroups are taken up in order by the CUs that become free (those of a KV head by that head's share of
+// the CUs), so the end is that of a list schedule; more pieces end more evenly, but each costs its start and
+// end and a partial that the combine kernel reads back.  Times in us, measured: an iteration of 64 keys in the
+// 256-row kernel 1.7 (one workgroup per CU); in the smaller ones 1.4 with one workgroup per CU and 2.7 with
+// two (the stream from HBM); start and end of a workgroup 6; a partial of 128 rows 0.018.
+// Measured against pieces of one length for about 2,048 workgroups, in session order: 48-session step 4.58 ->
+// 4.05 ms (append launch 4.25 -> 3.76: no 19,648-key pieces that end in a ragged last round, tiles whole and
+// longest first; combine kernels 0.16 -> 0.02); 64 questions at 64K 1.13 -> 1.04 ms (7 pieces per tile, 3.5
+// rounds of the chip -> 2 pieces, one round).
+// The schedule is only played through where simple bounds of its end (the average load, the longest piece) do not
+// say already that the length is no better, and no further than to where it is known to be none.
+int64_t list_chunk(const sk_pool* p, const ListGroup& g, bool one_session = false, double* expected_end = nullptr)
+{
+    int64_t longest = 0;
+    for (const TileReq& t : g.tiles) longest = std::max<int64_t>(longest, t.kv_vis);
+    if (longest == 0) return 256;
+    const int Hkv = p->d.n_kv_heads;
+    const bool big = g.v.id == SK_KV_MFMA256, wide = p->d.head_dim == 128;
+    const size_t n_tiles = g.tiles.size();
+    double best = 0; int64_t best_chunk = 0, last = 0;
+    std::vector<double> lane;                              // when each lane is free: a heap, the first one on top
+    std::vector<int32_t> rest(n_tiles), ordered(n_tiles);  // iterations of each tile's last piece; the same, longest eighths first
+    std::vector<uint8_t> bucket(n_tiles);
+    for (int64_t k = 1; k <= 256; k += one_session && k < 64 ? 1 : std::max<int64_t>(1, k / 4)) {
+        const int64_t chunk = std::max<int64_t>(256, ((longest + k - 1) / k + 63) / 64 * 64);
+        if (chunk == last) { if (chunk == 256) break; continue; }
+        last = chunk;
+        int64_t whole = 0, parts = 0, its_sum = 0, its_max = 0;
+        size_t count[9] = {};
+        for (size_t i = 0; i < n_tiles; ++i) {
+            const uint32_t np = list_parts(g.tiles[i], (uint32_t)chunk), left = (uint32_t)g.tiles[i].kv_vis - (np - 1) * (uint32_t)chunk;
+            if (np > 1) parts += np;
+            whole += np - 1;
+            rest[i] = int32_t((left + 63) / 64);
+            bucket[i] = (uint8_t)list_bucket(left, (uint32_t)chunk);
+            ++count[bucket[i]];
+            its_sum += rest[i]; its_max = std::max<int64_t>(its_max, rest[i]);
+        }
+        const int64_t n = whole + (int64_t)n_tiles;
+        const bool sparse = big || n * Hkv <= p->n_cus;
+        const double it = big ? (wide ? 1.7 : 1.15) : one_session && !wide ? (sparse ? 0.8 : 1.15) : (sparse ? 1.4 : 2.7), ends = 6.0;
+        const int64_t lanes = std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
+        const double partials = double(parts) * Hkv * g.v.rows_per_slot / 128.0;
+        const double merge = one_session ? (parts > 0 ? 4.0 : 0.0) + partials * (wide ? 0.02 : 0.01) : partials * 0.018;
+        // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
+        const double c = double(chunk / 64) * it + ends, base = c * double(whole / lanes);
+        const int64_t ahead = whole % lanes;               // lanes with one whole chunk more than the others
+        auto no_better = [&](double end) { return best_chunk != 0 && !(end + merge < 0.995 * best); };
+        double end = std::max(ahead > 0 ? base + c : base, base + (double(its_max) * it + ends));
+        const double load = (double(whole) * c + double(its_sum) * it + double(n_tiles) * ends) / double(lanes);
+        if (no_better(std::max(end, load * (1 - 1e-9)))) continue;
+        if ((int64_t)n_tiles > lanes - ahead) {            // (else each gets a lane that is free at `base`)
+            size_t at[9], sum = 0;
+            for (int b = 8; b >= 0; --b) { at[b] = sum; sum += count[b]; }
+            for (size_t i = 0; i < n_tiles; ++i) ordered[at[bucket[i]]++] = rest[i];
+            lane.assign((size_t)lanes, base + c);
+            std::fill(lane.begin(), lane.begin() + (lanes - ahead), base);
+            for (size_t i = 0; i < n_tiles && !no_better(end); ++i) {
+                const double x = lane[0] + (double(ordered[i]) * it + ends);
+                end = std::max(end, x);
+                size_t hole = 0;                           // x takes its place in the heap from the top
+                for (size_t kid = 1; kid < (size_t)lanes; kid = 2 * hole + 1) {
+                    if (kid + 1 < (size_t)lanes && lane[kid + 1] < lane[kid]) ++kid;
+                    if (!(lane[kid] < x)) break;
+                    lane[hole] = lane[kid]; hole = kid;
+                }
+                lane[hole] = x;
+            }
+            if (no_better(end)) continue;
+        }
+        best = end + merge; best_chunk = chunk;
+    }
+    if (expected_end) *expected_end = best;
+    return best_chunk;
+}
+
 int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int64_t kv_len, int32_t eph_cnt, int32_t eph_pos0,
                  int64_t hole_lo, int64_t hole_hi, int32_t n_splits_req, RegPlan& R)
 {
@@ -410,7 +521,7 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     L.by_heads = sk_make_div((uint32_t)p->d.n_kv_heads);
     if (v.id == SK_KV_SMALL) return plan_small(p, kv_len, eph_cnt, n_splits_req, R);
     if (p->L.elem == 4) return plan_f32(p, kv_len, eph_cnt, n_splits_req, R);
-    const int64_t base_wgs = int64_t(L.n_tiles) * p->d.n_kv_heads;
+    int64_t base_wgs = int64_t(L.n_tiles) * p->d.n_kv_heads;
     const int64_t slots_rows = p->L.part_slots * kPartSlotRows;
     const int has_eph = eph_cnt > 0 ? 1 : 0;
     int64_t S;
@@ -428,6 +539,36 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
         S = std::max<int64_t>(1, (target + base_wgs / 2) / base_wgs);
     }
     int64_t chunk = kv_len > 0 ? (kv_len + S - 1) / S : 64;
+    // The 256-row instance: by the expected end of the launch.  One workgroup to a CU makes the number of workgroups count: with
+    // the pieces cut for about 256 of them, 264 were two rounds of the chip.  Measured (us per append, before -> after; the model's
+    // times are in list_chunk): 9,001 cached and 129 tokens of 32/8 heads (24 tiles, 264 workgroups -> 240) 63.8 -> 41.5; 131,072
+    // and 183 575 -> 388; 32,512 and 377 of 64/8 540 -> 380; 410 into an empty session 29.7 -> 21.9; 131,072 and 198 of 28/4 581
+    // -> 379; 2,600 and 298 37.9 -> 34.9.  83 appends of 0 to 131,072 cached and 58 to 3,376 tokens over six layer shapes: 1.12 times as
+    // fast in the mean.
+    if (n_splits_req <= 0 && !p->target_wgs_set && v.id == SK_KV_MFMA256 && kv_len > 256) {
+        ListGroup tiles;
+        tiles.v = v;
+        TileReq base = {};
+        base.pos0 = pos0; base.kv_vis = (int32_t)kv_len;
+        add_tiles(tiles, base, 0, (int32_t)n_tok);
+        double end256 = 0;
+        chunk = list_chunk(p, tiles, true, &end256);
+        if (p->d.head_dim == 64) {
+            // 128-row tiles of four waves, two workgroups to a CU, where they are expected to end earlier: less padding, or an evener
+            // end
+            ListGroup low;
+            low.v = Variant{SK_KV_MFMA128, 128, 128 / p->L.G};
+            add_tiles(low, base, 0, (int32_t)n_tok);
+            double end128 = 0;
+            const int64_t chunk128 = list_chunk(p, low, true, &end128);
+            if (end128 < end256) {
+                v = low.v; chunk = chunk128;
+                L.rows_per_slot = v.rows_per_slot; L.tok_per_tile = v.tok_per_tile;
+                L.n_tiles = int32_t((n_tok + v.tok_per_tile - 1) / v.tok_per_tile);
+                base_wgs = int64_t(L.n_tiles) * p->d.n_kv_heads;
+            }
+        }
+    }
     // at least four 64-key iterations per workgroup of the matrix-pipe kernels; the fp32-FMA kernel
     // (32-key tiles, far slower per key) takes shorter pieces so that small caches still spread over the chip
     if (n_splits_req <= 0) chunk = std::max<int64_t>(chunk, v.id == SK_KV_SIMPLE ? 64 : 256);
@@ -724,115 +865,7 @@ int check_out_dtype(const sk_pool* p, int out_dtype)
 
 // ---- list mode: many row tiles (of several sessions, or of one question batch) in one launch ----
 
-struct TileReq {            // one tile of query rows and the keys it may see
-    int32_t tbl_off, q_tok0, n_tok;
-    int32_t pos0;           // absolute position of its first token, or SK_NO_CAUSAL
-    int32_t kv_vis;         // cached tokens visible to the tile (positions 0 .. kv_vis-1)
-    int32_t eph_blk[2], eph_cnt[2], eph_pos0[2];
-    int32_t hole_lo, hole_hi;   // evicted cached tokens of the session
-    int32_t tok_period, sub_blocks;   // > 0: the tile packs sequences of tok_period tokens (see sk_work)
-};
-struct ListGroup {          // tiles that share a kernel variant and the q/out/lse arrays
-    Variant v = {SK_KV_SIMPLE, 16, 1};
-    const void* q = nullptr; void* out = nullptr; float* lse = nullptr;
-    std::vector<TileReq> tiles;
-};
 struct ScatterBatch { const void* k = nullptr; const void* v = nullptr; std::vector<sk_scatter> items; };
-
-// Cuts T tokens (packed rows q_row0..) that share `base` into row tiles of the group's height.
-void add_tiles(ListGroup& g, const TileReq& base, int32_t q_row0, int32_t T)
-{
-    for (int32_t t0 = 0; t0 < T; t0 += g.v.tok_per_tile) {
-        TileReq r = base;
-        r.q_tok0 = q_row0 + t0;
-        r.n_tok = std::min(g.v.tok_per_tile, T - t0);
-        if (base.pos0 < SK_NO_CAUSAL) {
-            r.pos0 = base.pos0 + t0;
-            r.kv_vis = std::min<int64_t>(base.kv_vis, int64_t(r.pos0) + r.n_tok);
-        }
-        g.tiles.push_back(r);
-    }
-}
-
-// Pieces of at most `chunk` keys that a tile is cut into (a tile that sees no cached key is one piece), and which eighth of
-// a chunk a piece's length falls into.  Lengths and chunks stay below 2^30.
-uint32_t list_parts(const TileReq& t, uint32_t chunk) { return t.kv_vis > 0 ? ((uint32_t)t.kv_vis + chunk - 1) / chunk : 1; }
-uint32_t list_bucket(uint32_t len, uint32_t chunk) { return len == chunk ? 8 : uint32_t(uint64_t(len) * 8 / chunk); }
-
-// Length of the pieces a launch's tiles are cut into: the one for which the launch is expected to end first.
-// The workgroups are taken up in order by the CUs that become free (those of a KV head by that head's share of
-// the CUs), so the end is that of a list schedule; more pieces end more evenly, but each costs its start and
-// end and a partial that the combine kernel reads back.  Times in us, measured: an iteration of 64 keys in the
-// 256-row kernel 1.7 (one workgroup per CU); in the smaller ones 1.4 with one workgroup per CU and 2.7 with
-// two (the stream from HBM); start and end of a workgroup 6; a partial of 128 rows 0.018.
-// Measured against pieces of one length for about 2,048 workgroups, in session order: 48-session step 4.58 ->
-// 4.05 ms (append launch 4.25 -> 3.76: no 19,648-key pieces that end in a ragged last round, tiles whole and
-// longest first; combine kernels 0.16 -> 0.02); 64 questions at 64K 1.13 -> 1.04 ms (7 pieces per tile, 3.5
-// rounds of the chip -> 2 pieces, one round).
-// The schedule is only played through where simple bounds of its end (the average load, the longest piece) do not
-// say already that the length is no better, and no further than to where it is known to be none.
-int64_t list_chunk(const sk_pool* p, const ListGroup& g)
-{
-    int64_t longest = 0;
-    for (const TileReq& t : g.tiles) longest = std::max<int64_t>(longest, t.kv_vis);
-    if (longest == 0) return 256;
-    const int Hkv = p->d.n_kv_heads;
-    const bool big = g.v.id == SK_KV_MFMA256;
-    const size_t n_tiles = g.tiles.size();
-    double best = 0; int64_t best_chunk = 0, last = 0;
-    std::vector<double> lane;                              // when each lane is free: a heap, the first one on top
-    std::vector<int32_t> rest(n_tiles), ordered(n_tiles);  // iterations of each tile's last piece; the same, longest eighths first
-    std::vector<uint8_t> bucket(n_tiles);
-    for (int64_t k = 1; k <= 256; k += std::max<int64_t>(1, k / 4)) {
-        const int64_t chunk = std::max<int64_t>(256, ((longest + k - 1) / k + 63) / 64 * 64);
-        if (chunk == last) break;
-        last = chunk;
-        int64_t whole = 0, parts = 0, its_sum = 0, its_max = 0;
-        size_t count[9] = {};
-        for (size_t i = 0; i < n_tiles; ++i) {
-            const uint32_t np = list_parts(g.tiles[i], (uint32_t)chunk), left = (uint32_t)g.tiles[i].kv_vis - (np - 1) * (uint32_t)chunk;
-            if (np > 1) parts += np;
-            whole += np - 1;
-            rest[i] = int32_t((left + 63) / 64);
-            bucket[i] = (uint8_t)list_bucket(left, (uint32_t)chunk);
-            ++count[bucket[i]];
-            its_sum += rest[i]; its_max = std::max<int64_t>(its_max, rest[i]);
-        }
-        const int64_t n = whole + (int64_t)n_tiles;
-        const bool sparse = big || n * Hkv <= p->n_cus;
-        const double it = big ? (p->d.head_dim == 128 ? 1.7 : 1.2) : (sparse ? 1.4 : 2.7), ends = 6.0;
-        const int64_t lanes = std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
-        const double merge = double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0;
-        // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
-        const double c = double(chunk / 64) * it + ends, base = c * double(whole / lanes);
-        const int64_t ahead = whole % lanes;               // lanes with one whole chunk more than the others
-        auto no_better = [&](double end) { return best_chunk != 0 && !(end + merge < 0.995 * best); };
-        double end = std::max(ahead > 0 ? base + c : base, base + (double(its_max) * it + ends));
-        const double load = (double(whole) * c + double(its_sum) * it + double(n_tiles) * ends) / double(lanes);
-        if (no_better(std::max(end, load * (1 - 1e-9)))) continue;
-        if ((int64_t)n_tiles > lanes - ahead) {            // (else each gets a lane that is free at `base`)
-            size_t at[9], sum = 0;
-            for (int b = 8; b >= 0; --b) { at[b] = sum; sum += count[b]; }
-            for (size_t i = 0; i < n_tiles; ++i) ordered[at[bucket[i]]++] = rest[i];
-            lane.assign((size_t)lanes, base + c);
-            std::fill(lane.begin(), lane.begin() + (lanes - ahead), base);
-            for (size_t i = 0; i < n_tiles && !no_better(end); ++i) {
-                const double x = lane[0] + (double(ordered[i]) * it + ends);
-                end = std::max(end, x);
-                size_t hole = 0;                           // x takes its place in the heap from the top
-                for (size_t kid = 1; kid < (size_t)lanes; kid = 2 * hole + 1) {
-                    if (kid + 1 < (size_t)lanes && lane[kid + 1] < lane[kid]) ++kid;
-                    if (!(lane[kid] < x)) break;
-                    lane[hole] = lane[kid]; hole = kid;
-                }
-                lane[hole] = x;
-            }
-            if (no_better(end)) continue;
-        }
-        best = end + merge; best_chunk = chunk;
-    }
-    return best_chunk;
-}
 
 constexpr int kMaxGroups = 3;   // one launch per kernel variant in use
 

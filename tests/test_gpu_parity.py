@@ -661,25 +661,51 @@ def test_head_dim_64_tiles_of_256_rows(hq, hkv, frozen):
     pr = Pair(shape, n_blocks=200, max_sessions=1, max_batch_tokens=1024, kv_fill=0xFF)
     sid = pr.create()
     ref = pr.oracles[sid]
+    variants = set()
     for n in (0, 1, 31, 33, 64, 96, 97, 160, 224, 255, 257, 288, 320, 545, 900):
         if n > len(ref.K):
             _, k, v = synth.draw_qkv(gen, n - len(ref.K), shape)
             pr.append(sid, None, k, v, check=False)
         for T in (128 // G + 1, 256 // G, 256 // G + 1) if n in (0, 33, 257, 900) else (256 // G - 3,):
             q, k, v = synth.draw_qkv(gen, T, shape)
-            if n:
-                pr.query(sid, q, name="A n=%d T=%d" % (n, T))
+            for S in (1, 3):                   # (with a number of parts of the caller's always this instance)
+                if n:
+                    pr.query(sid, q, n_splits=S, name="A n=%d T=%d S=%d" % (n, T, S))
+                    assert pr.pool.sk_pool_last_launch()["kernel_variant"] == 3
+                pr.query(sid, q, k, v, n_splits=S, name="B n=%d T=%d S=%d" % (n, T, S))
                 assert pr.pool.sk_pool_last_launch()["kernel_variant"] == 3
-            pr.query(sid, q, k, v, n_splits=1, name="B n=%d T=%d" % (n, T))
             pr.append(sid, q, k, v, name="append n=%d T=%d" % (n, T))
-            assert pr.pool.sk_pool_last_launch()["kernel_variant"] == 3
+            variants.add(pr.pool.sk_pool_last_launch()["kernel_variant"])
             pr.pool.sk_session_truncate(sid, n)
             ref.truncate(n)
+    assert variants == {1, 3}                  # 128- and 256-row tiles, by the expected end
     pr.freeze(sid, frozen)
     for gone in (20, 40, 200):
         pr.evict(sid, gone)
         q, k, v = synth.draw_qkv(gen, 256 // G, shape)
-        pr.query(sid, q, k, v, name="%d more evicted" % gone)
+        pr.query(sid, q, k, v, n_splits=4, name="%d more evicted" % gone)
         pr.query(sid, q, n_splits=1, name="%d more evicted, one part" % gone)
         pr.append(sid, q, k, v, name="append behind a hole")
+    pr.check_cache(sid)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,T", [(28, 4, 128, 0, 502), (12, 4, 128, 100, 500), (4, 1, 64, 0, 600), (16, 1, 128, 0, 900)])
+def test_appends_cut_by_the_expected_end(hq, hkv, d, n, T):
+    """Appends whose row tiles have different numbers of parts: tiles of one part are written directly, the others go
+    through the combine kernel, in one launch; then the same rows with every tile in one part."""
+    shape = synth.Shape("bf16", hq, hkv, d)
+    gen = synth.generator(2, stream=1700 + hq + d)
+    pr = Pair(shape, n_blocks=100, max_sessions=1, max_batch_tokens=1024, kv_fill=0xFF)
+    sid = pr.create()
+    if n:
+        _, k, v = synth.draw_qkv(gen, n, shape)
+        pr.append(sid, None, k, v, check=False)
+    q, k, v = synth.draw_qkv(gen, T, shape)
+    for dt in ("f32", "bf16"):
+        pr.append(sid, q, k, v, out_dtype=dt, name="append %d at %d %s" % (T, n, dt))
+        geo = pr.pool.sk_pool_last_launch()
+        assert geo["n_splits"] > 1 and geo["row_tiles"] > 1, geo
+        pr.pool.sk_session_truncate(sid, n)
+        pr.oracles[sid].truncate(n)
+    pr.append(sid, q, k, v)
     pr.check_cache(sid)
