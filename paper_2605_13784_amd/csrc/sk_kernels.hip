@@ -2295,13 +2295,14 @@ __device__ __forceinline__ void sk_scatter_item(const sk_geom& g, const void* k,
     sk_commit_group_f32(g, k, v, it, head, tables_rw, it.to_eph ? eph_rw : kv_rw);
 }
 
-// Items read from a list in the workspace (batched steps) ...
+// Items read from a list in the workspace (batched steps) or in pinned host memory (long single-session appends) ...
 __global__ __launch_bounds__(256) void sk_scatter_kernel(const sk_geom g, const sk_div by_heads, const void* k, const void* v,
                                                          const sk_scatter* items, int32_t* tables_rw,
                                                          unsigned char* kv_rw, unsigned char* eph_rw)
 {
     const int i = sk_divide(blockIdx.x, by_heads);
-    sk_scatter_item(g, k, v, items[i], blockIdx.x - i * g.Hkv, tables_rw, kv_rw, eph_rw);
+    const sk_scatter it = items[i];                          // at once: the list may lie in host memory
+    sk_scatter_item(g, k, v, it, blockIdx.x - i * g.Hkv, tables_rw, kv_rw, eph_rw);
 }
 // ... or carried in the kernel arguments (single-session calls: no host-to-device copy in front)
 __global__ __launch_bounds__(256) void sk_scatter_kernel_args(const sk_geom g, const sk_div by_heads, const void* k, const void* v,

@@ -140,7 +140,7 @@ struct sk_pool {
     bool force_simple = false, no_small = false, no_256 = false, no_pack = false, no_interleave = false, no_stream_loads = false;
     int distrust = 0;                    // SK_SMALL_DISTRUST (tests)
     bool p128 = true;                    // SK_NO_P128=1: never the eight-wave 128-row instance
-    int64_t p128_min_tokens = 30720;     // SK_P128_MIN_TOKENS: cached tokens from which it is taken (break-even measured near 32K)
+    int64_t p128_min_tokens = 13312;     // SK_P128_MIN_TOKENS: cached tokens from which it is taken (break-even between 8,000 and 14,800: plan_regular)
     int64_t stream_min_tokens = 65536;   // SK_STREAM_MIN_TOKENS: cached tokens from which the 128-row instances load non-temporal
     bool fuse = false;                   // SK_FUSE=1: single-session calls merge their split partials inside the attention kernel
     bool fuse_list = false;              // batched calls too (the last workgroup of a unit merges alone)
@@ -207,14 +207,20 @@ int ring_acquire(sk_pool* p, int* slot, unsigned char** host)
     return SK_OK;
 }
 
+// Marks ring slot `slot` busy until what the stream holds now, which reads it, is done.
+void ring_busy(sk_pool* p, int slot, hipStream_t st)
+{
+    if (hipEventRecord(p->ring_ev[slot], st) != hipSuccess) (void)hipStreamSynchronize(st);   // the slot is free either way
+    p->ring_used[slot] = true;
+}
+
 // Copies `bytes` from ring slot `slot` to `dev` on the stream and marks the slot busy until then.
 int ring_copy(sk_pool* p, int slot, void* dev, size_t bytes, hipStream_t st)
 {
     if (inject(p, SK_SITE_UPLOAD)) return SK_E_HIP;
     if (!p->device) return SK_OK;
     SK_HIP(hipMemcpyAsync(dev, p->ring + size_t(slot) * p->L.meta_bytes, bytes, hipMemcpyHostToDevice, st));
-    if (hipEventRecord(p->ring_ev[slot], st) != hipSuccess) (void)hipStreamSynchronize(st);   // the slot is free either way
-    p->ring_used[slot] = true;
+    ring_busy(p, slot, st);
     return SK_OK;
 }
 
@@ -453,11 +459,11 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g, bool one_session = fals
         const int64_t chunk = std::max<int64_t>(256, ((longest + k - 1) / k + 63) / 64 * 64);
         if (chunk == last) { if (chunk == 256) break; continue; }
         last = chunk;
-        int64_t whole = 0, parts = 0, its_sum = 0, its_max = 0;
+        int64_t whole = 0, parts = 0, split = 0, its_sum = 0, its_max = 0;
         size_t count[9] = {};
         for (size_t i = 0; i < n_tiles; ++i) {
             const uint32_t np = list_parts(g.tiles[i], (uint32_t)chunk), left = (uint32_t)g.tiles[i].kv_vis - (np - 1) * (uint32_t)chunk;
-            if (np > 1) parts += np;
+            if (np > 1) { parts += np; ++split; }
             whole += np - 1;
             rest[i] = int32_t((left + 63) / 64);
             bucket[i] = (uint8_t)list_bucket(left, (uint32_t)chunk);
@@ -468,8 +474,14 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g, bool one_session = fals
         const bool sparse = big || n * Hkv <= p->n_cus;
         const double it = big ? (wide ? 1.7 : 1.15) : one_session && !wide ? (sparse ? 0.8 : 1.15) : (sparse ? 1.4 : 2.7), ends = 6.0;
         const int64_t lanes = std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
+        // (one session: the combine launch 4, a partial of 128 rows 0.02, at head_dim 64 0.01.  Tiles of an append into an empty session
+        // are short and of all lengths, so that splitting them gains less than it seems: 7.5 for the launch and the split's own uneven
+        // end, 0.0004 for a row, 8 TB/s for the partials; fitted to us per call, whole - in two parts: 2,000 tokens of 32/8 heads
+        // 64.4 - 74.1, 1,500 50 - 53.8, 1,750 of 28/4 55.8 - 57.3)
         const double partials = double(parts) * Hkv * g.v.rows_per_slot / 128.0;
-        const double merge = one_session ? (parts > 0 ? 4.0 : 0.0) + partials * (wide ? 0.02 : 0.01) : partials * 0.018;
+        const double merge = !one_session ? partials * 0.018 : split == 0 ? 0.0
+                             : g.tiles[0].pos0 > 0 ? 4.0 + partials * (wide ? 0.02 : 0.01)
+                             : 7.5 + 0.0004 * double(split) * Hkv * g.v.rows_per_slot + partials * (wide ? 0.008 : 0.004);
         // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
         const double c = double(chunk / 64) * it + ends, base = c * double(whole / lanes);
         const int64_t ahead = whole % lanes;               // lanes with one whole chunk more than the others
@@ -541,16 +553,22 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     int64_t chunk = kv_len > 0 ? (kv_len + S - 1) / S : 64;
     // The 256-row instance: by the expected end of the launch.  One workgroup to a CU makes the number of workgroups count: with
     // the pieces cut for about 256 of them, 264 were two rounds of the chip.  Measured (us per append, before -> after; the model's
-    // times are in list_chunk): 9,001 cached and 129 tokens of 32/8 heads (24 tiles, 264 workgroups -> 240) 63.8 -> 41.5; 131,072
-    // and 183 575 -> 388; 32,512 and 377 of 64/8 540 -> 380; 410 into an empty session 29.7 -> 21.9; 131,072 and 198 of 28/4 581
-    // -> 379; 2,600 and 298 37.9 -> 34.9.  83 appends of 0 to 131,072 cached and 58 to 3,376 tokens over six layer shapes: 1.12 times as
-    // fast in the mean.
+    // times are in list_chunk): 9,001 cached and 129 tokens of 32/8 heads (24 tiles, 264 workgroups -> 240) 62.5 -> 40.5; 131,072
+    // and 183 575 -> 388; 32,512 and 377 of 64/8 530 -> 378; 330 of 28/4 into an empty session 27.0 -> 21.6; 1,160 of 32/8 54.4
+    // -> 38.9; 2,600 and 298 38.4 -> 35.0.  Over 150 calls of 0 to 131,072 cached and 31 to 3,376 tokens of six layer shapes 1.11 to 1.12
+    // times as fast in the mean, none more than 2 % slower.
     if (n_splits_req <= 0 && !p->target_wgs_set && v.id == SK_KV_MFMA256 && kv_len > 256) {
         ListGroup tiles;
         tiles.v = v;
         TileReq base = {};
         base.pos0 = pos0; base.kv_vis = (int32_t)kv_len;
-        add_tiles(tiles, base, 0, (int32_t)n_tok);
+        TileReq own = {};                                   // the own part of each row tile is a workgroup more
+        own.pos0 = SK_NO_CAUSAL; own.kv_vis = eph_cnt;
+        auto cut = [&](ListGroup& g) {
+            add_tiles(g, base, 0, (int32_t)n_tok);
+            if (has_eph) g.tiles.resize(2 * g.tiles.size(), own);
+        };
+        cut(tiles);
         double end256 = 0;
         chunk = list_chunk(p, tiles, true, &end256);
         if (p->d.head_dim == 64) {
@@ -558,7 +576,7 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
             // end
             ListGroup low;
             low.v = Variant{SK_KV_MFMA128, 128, 128 / p->L.G};
-            add_tiles(low, base, 0, (int32_t)n_tok);
+            cut(low);
             double end128 = 0;
             const int64_t chunk128 = list_chunk(p, low, true, &end128);
             if (end128 < end256) {
@@ -602,9 +620,9 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     const bool mfma = v.id != SK_KV_SIMPLE;
     // A 128-row call that gives every CU at most one workgroup takes the eight-wave instance: two key
     // phases per row group, so a wave has half the arithmetic per 64 keys and its SIMD a second wave
-    // to overlap it with.  Measured (32-token query, us per query, four waves -> eight): 2,600 cached
-    // tokens 18.5 -> 20.1, 8K 22.8 -> 24.7, 14,800 28.3 -> 29.4, 32K 42.3 -> 42.1, 64K 69.5 -> 65.3,
-    // 128K 123.8 -> 113.2: the eight waves pay off once the stream outweighs their longer start and
+    // to overlap it with.  Measured (us per query, four waves -> eight; 32 tokens unless said otherwise): 8,000 cached tokens
+    // 17.6 -> 18.8, 14,800 23.1 -> 22.6 (23 tokens with their own K/V 22.1 -> 21.4), 20,000 26.1 -> 25.6, 24,000 with 24 tokens
+    // 27.4 -> 25.7, 32,768 34.4 -> 32.6, 60,000 with 16 of 28/4 heads 32.6 -> 30.8: the eight waves pay off once the stream outweighs their longer start and
     // their merge of the two phases.
     if (p->p128 && v.id == SK_KV_MFMA128 && p->d.head_dim == 128 && R.wgs <= p->n_cus && kv_len >= p->p128_min_tokens) v.id = SK_KV_MFMA128P;
     L.fuse = (p->fuse && mfma && parts > 1 && base_wgs <= p->L.sync_units && parts < 65536) ? 1 : 0;
@@ -725,15 +743,16 @@ int scatter_launch(sk_pool* p, const ScatterSlot& ss, const std::vector<sk_scatt
         p->stats.launches++;
         return SK_OK;
     }
-    const size_t bytes = items.size() * sizeof(sk_scatter);
-    if (ss.host) memcpy(ss.host, items.data(), bytes);
-    int rc = ring_upload(p, ss.slot, bytes, st);
-    if (rc) return rc;
-    if (inject(p, SK_SITE_SCATTER)) return SK_E_HIP;
+    // A longer one is read where it lies, in the pinned slot: each workgroup reads 32 bytes of it once, one round trip to
+    // the host where a copy in front is a launch of its own (2,600 tokens into an
+    // empty session and a question 97.1 -> 94.8 us).
+    if (ss.host) memcpy(ss.host, items.data(), items.size() * sizeof(sk_scatter));
+    if (inject(p, SK_SITE_UPLOAD) || inject(p, SK_SITE_SCATTER)) return SK_E_HIP;
     if (!p->device) return SK_OK;
-    int e = sk_launch_scatter(p->geom, k, v, (const sk_scatter*)(ws + p->L.off_meta), (int32_t)items.size(),
+    int e = sk_launch_scatter(p->geom, k, v, (const sk_scatter*)ss.host, (int32_t)items.size(),
                               (int32_t*)(ws + p->L.off_tables), (unsigned char*)p->d.kv_mem, ws + p->L.off_eph, st);
     if (e) { g_last_hip = e; return SK_E_HIP; }
+    ring_busy(p, ss.slot, st);
     p->stats.launches++;
     return SK_OK;
 }

@@ -43,7 +43,7 @@ def test_bf16_gqa_ragged_appends_and_queries(block_tokens, env):
     appends of ragged lengths (several row tiles, partial tiles, single tokens, block-straddling),
     then queries of several lengths in both modes with several split counts; once more with the
     eight-wave 128-row instance and the non-temporal loads that single-session calls of 65-128 rows
-    otherwise only take from 30,720 / 65,536 cached tokens on."""
+    otherwise only take from 13,312 / 65,536 cached tokens on."""
     shape = synth.CFG2
     gen = synth.generator(2, stream=1)
     pr = Pair(shape, block_tokens=block_tokens, n_blocks=4096 // block_tokens + 8, kv_fill=0xFF, max_batch_tokens=1024, env=env)
@@ -689,13 +689,14 @@ def test_head_dim_64_tiles_of_256_rows(hq, hkv, frozen):
     pr.check_cache(sid)
 
 
+@pytest.mark.parametrize("env", [None, {"SK_TARGET_WGS": "256"}])
 @pytest.mark.parametrize("hq,hkv,d,n,T", [(28, 4, 128, 0, 502), (12, 4, 128, 100, 500), (4, 1, 64, 0, 600), (16, 1, 128, 0, 900)])
-def test_appends_cut_by_the_expected_end(hq, hkv, d, n, T):
-    """Appends whose row tiles have different numbers of parts: tiles of one part are written directly, the others go
-    through the combine kernel, in one launch; then the same rows with every tile in one part."""
+def test_appends_whose_tiles_have_different_numbers_of_parts(hq, hkv, d, n, T, env):
+    """Tiles of one part are written directly, the others go through the combine kernel, in one launch: with pieces of at
+    least 256 keys for 256 workgroups (env), and with those that are expected to end first."""
     shape = synth.Shape("bf16", hq, hkv, d)
     gen = synth.generator(2, stream=1700 + hq + d)
-    pr = Pair(shape, n_blocks=100, max_sessions=1, max_batch_tokens=1024, kv_fill=0xFF)
+    pr = Pair(shape, n_blocks=100, max_sessions=1, max_batch_tokens=1024, kv_fill=0xFF, env=env)
     sid = pr.create()
     if n:
         _, k, v = synth.draw_qkv(gen, n, shape)
@@ -704,8 +705,23 @@ def test_appends_cut_by_the_expected_end(hq, hkv, d, n, T):
     for dt in ("f32", "bf16"):
         pr.append(sid, q, k, v, out_dtype=dt, name="append %d at %d %s" % (T, n, dt))
         geo = pr.pool.sk_pool_last_launch()
-        assert geo["n_splits"] > 1 and geo["row_tiles"] > 1, geo
+        assert geo["row_tiles"] > 1 and (env is None or geo["n_splits"] > 1), geo
         pr.pool.sk_session_truncate(sid, n)
         pr.oracles[sid].truncate(n)
     pr.append(sid, q, k, v)
     pr.check_cache(sid)
+
+
+@pytest.mark.parametrize("shape", [synth.Shape("bf16", 8, 4, 128), synth.Shape("f32", 4, 2, 64)])
+def test_long_appends_in_a_row(shape):
+    """Appends whose commit lists are too long for the kernel arguments are read from pinned memory by the commit kernel:
+    more of them in flight than there are slots, starting inside a group, then one that fits the arguments."""
+    gen = synth.generator(2, stream=1800 + shape.head_dim)
+    pr = Pair(shape, n_blocks=800, max_sessions=1, max_batch_tokens=2048, kv_fill=0xFF)
+    sid = pr.create()
+    for L in (1283, 1500, 1300, 1299, 1601, 1290, 2048, 100):
+        _, k, v = synth.draw_qkv(gen, L, shape)
+        pr.append(sid, None, k, v, check=False)
+    pr.check_cache(sid)
+    q, k, v = synth.draw_qkv(gen, 5, shape)
+    pr.query(sid, q, k, v)
