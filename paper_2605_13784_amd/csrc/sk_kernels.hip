@@ -855,6 +855,12 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             static_assert(NKS == 2 * NMT, "a stage has as many matrix instructions of either product");
             const int half = wave >> 2;
             const int n_iter = (g.end - g.begin + 2 * SK_TILE - 1) / (2 * SK_TILE);
+            // Iterations that any row of this wave sees a key of.  In the others it loads its share of the tiles and computes
+            // nothing: a weight of 0 times an infinite value would be NaN, and reach rows of questions and of tokens that lie in
+            // front of that value (the 32 keys of one tile, and the two tiles of an iteration, are not told apart).
+            const int first_0 = g.begin + g.pos_shift;
+            int n_live = !wave_has_rows || lim_wave_max < first_0 ? 0 : (int)((unsigned)(lim_wave_max - first_0) / (2 * SK_TILE)) + 1;
+            n_live = n_live < n_iter ? n_live : n_iter;
             auto& kc = kptr;                     // operand addresses: they follow the iteration through the ring
             auto& vc = vptr;
             f32x16 sc[2];
@@ -1003,7 +1009,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             if (half == 1) SK_WAIT_VMCNT(5 * LPT);
             sk_lds_barrier();
             // K tile 0 lies in slot 7 (a tile's K one slot below its number, its V one above)
-            {
+            if (n_live > 0) {
                 sk_u32x4 k0[NKS];
 #pragma unroll
                 for (int i = 0; i < NKS; ++i) k0[i] = *(sk_lds_u4ptr)(kc[i] + 7 * 1024);
@@ -1015,9 +1021,6 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 SK_WAIT_VMCNT(LPW);
                 sk_lds_barrier();
             };
-            begin_iteration();
-#pragma unroll
-            for (int p = 0; p < 8; ++p) op[p] = ld_op(p, 0);
             auto iteration = [&](auto pv_const, const int it) __attribute__((always_inline)) {
                 const unsigned sa = slot_addr_of(it);
                 const int delta = ((it + 1) & 3) == 0 ? -6 * 1024 : 2 * 1024;
@@ -1031,24 +1034,38 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                     if (p == NP - 3) next_blocks();
                 });
             };
-            iteration(sk_int<0>{}, 0);
-#pragma unroll 1
-            for (int it = 1; it < n_iter; ++it) {
+            if (n_live > 0) {
                 begin_iteration();
-                iteration(sk_int<1>{}, it);
-            }
-            // P V of the last tile: its V^T lies where the next iteration's first stage would read it
 #pragma unroll
-            for (int i = 0; i < 2 * NMT; ++i) {
-                oacc[i % NMT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ld_op(2 * i + 1, 0)), __builtin_bit_cast(bf16x8, pw[1][i / NMT]), oacc[i % NMT], 0, 0, 0);
-                if (i % NMT < 2) add_weights(__builtin_bit_cast(bf16x8, pw[1][i / NMT]), i % NMT);
+                for (int p = 0; p < 8; ++p) op[p] = ld_op(p, 0);
+                iteration(sk_int<0>{}, 0);
+#pragma unroll 1
+                for (int it = 1; it < n_live; ++it) {
+                    begin_iteration();
+                    iteration(sk_int<1>{}, it);
+                }
+                // P V of the last tile: its V^T lies where the next iteration's first stage would read it (loaded three
+                // iterations ahead, so the barrier in front of this iteration has published it)
+#pragma unroll
+                for (int i = 0; i < 2 * NMT; ++i) {
+                    oacc[i % NMT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ld_op(2 * i + 1, 0)), __builtin_bit_cast(bf16x8, pw[1][i / NMT]), oacc[i % NMT], 0, 0, 0);
+                    if (i % NMT < 2) add_weights(__builtin_bit_cast(bf16x8, pw[1][i / NMT]), i % NMT);
+                }
+#pragma unroll
+                for (int i = 0; i < NKS; ++i) kc[i] -= (n_live & 3) * 2048;
+#pragma unroll
+                for (int i = 0; i < NMT; ++i) vc[i] -= (n_live & 3) * 2048;
+            }
+#pragma unroll 1
+            for (int it = n_live; it < n_iter; ++it) {          // the same loads, waits and barriers
+                begin_iteration();
+                const unsigned sa = slot_addr_of(it);
+                issue_k(sa, sk_int<0>{}); issue_k(sa, sk_int<1>{});
+                issue_v(sa, sk_int<0>{}); issue_v(sa, sk_int<1>{});
+                next_blocks();
             }
             SK_WAIT_VMCNT(0);                    // nothing is still on its way into the ring
             sk_lds_barrier();
-#pragma unroll
-            for (int i = 0; i < NKS; ++i) kc[i] -= (n_iter & 3) * 2048;
-#pragma unroll
-            for (int i = 0; i < NMT; ++i) vc[i] -= (n_iter & 3) * 2048;
         } else {
             // ---- eight waves in two groups of four that take turns.  Every wave alternates between
             // a matrix slot (P V of iteration j-1, then S of iteration j) and a vector slot (softmax

@@ -197,3 +197,31 @@ def test_shared_prefix_question_batch_head_dim_64(n, P, NQ, Sfx):
     if P:
         compare("prefix rows", op, lp, rop, rlp, shape.dtype)
     compare("suffix rows", os_, ls, ros.reshape(NQ * Sfx, shape.n_q_heads, -1), rls.reshape(NQ * Sfx, -1), shape.dtype)
+
+
+@pytest.mark.parametrize("n,P,NQ,Sfx", [(130, 20, 9, 8), (0, 16, 5, 16), (33, 0, 2, 32)])
+def test_infinite_value_of_one_question_stays_with_it_head_dim_64(n, P, NQ, Sfx):
+    """Questions packed into 256-row tiles: an infinite value of one question's suffix is met by no row of another question,
+    not even with a weight of 0."""
+    shape = synth.Shape("bf16", 32, 8, 64)
+    gen = synth.generator(5, stream=3100 + n + P)
+    pool = sk.Pool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, 16, n // 16 + 8, max_sessions=1)
+    sid = pool.sk_session_create()
+    if n:
+        _, k, v = synth.draw_qkv(gen, n, shape)
+        pool.sk_session_append(sid, None, dev(k), dev(v))
+    qp, kp, vp = (dev(x) if P else None for x in synth.draw_qkv(gen, P, shape))
+    r4 = lambda t: dev(t.reshape(NQ, Sfx, t.shape[1], shape.head_dim))
+    qs, ks, vs = (r4(x) for x in synth.draw_qkv(gen, NQ * Sfx, shape))
+    hit = NQ // 2
+    vs[hit, 0, :, 7] = 0.0
+    planted = vs.clone()
+    planted[hit, 0, :, 7] = float("inf")
+    a = pool.sk_session_query_shared_prefix(sid, qp, kp, vp, qs, ks, vs)
+    b = pool.sk_session_query_shared_prefix(sid, qp, kp, vp, qs, ks, planted)
+    assert pool.sk_pool_last_launch()["row_tiles"] == (1 if P else 0) + -(-NQ * Sfx * 4 // 256)       # packed
+    others = [j for j in range(NQ) if j != hit]
+    assert torch.equal(a[2][others], b[2][others]) and torch.equal(a[3], b[3])
+    assert not torch.isfinite(b[2][hit, :, :, 7]).any()
+    if P:
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])

@@ -725,3 +725,37 @@ def test_long_appends_in_a_row(shape):
     pr.check_cache(sid)
     q, k, v = synth.draw_qkv(gen, 5, shape)
     pr.query(sid, q, k, v)
+
+
+@pytest.mark.parametrize("n,T", [(0, 128), (70, 150), (40, 300)])
+def test_head_dim_64_infinite_value_of_a_later_token(n, T):
+    """256-row tiles of 128 tokens each (two query heads per KV head): the last token's value is infinite.  A wave computes
+    nothing for the 64 keys of an iteration that none of its rows sees, so the rows in front of the iteration that holds
+    the infinity give the bits they give with a zero in its place."""
+    shape = synth.Shape("bf16", 8, 4, 64)
+    gen = synth.generator(2, stream=1900 + T)
+    pr = Pair(shape, n_blocks=60, max_sessions=1, max_batch_tokens=1024)
+    sid = pr.create()
+    if n:
+        _, k, v = synth.draw_qkv(gen, n, shape)
+        pr.append(sid, None, k, v, check=False)
+    q, k, v = synth.draw_qkv(gen, T, shape)
+    v[-1, :, 5] = 0.0
+    planted = v.clone()
+    planted[-1, :, 5] = float("inf")
+    def append(v):
+        out, lse = pr.pool.sk_session_append(sid, dev(q), dev(k), dev(v))
+        variant = pr.pool.sk_pool_last_launch()["kernel_variant"]
+        pr.pool.sk_session_truncate(sid, n)
+        return out, lse, variant
+    def query(v):
+        out, lse = pr.pool.sk_session_query(sid, dev(q), dev(k), dev(v), n_splits=1)
+        return out, lse, pr.pool.sk_pool_last_launch()["kernel_variant"]
+    for call, first in ((append, (n + T - 1) // 64 * 64 - n), (query, (T - 1) // 64 * 64)):      # first token that shares the iteration
+        first = first // 16 * 16                                     # a wave holds 16 tokens
+        zero, inf = call(v), call(planted)
+        assert zero[2] == inf[2] and (call is append or zero[2] == 3)
+        assert 0 < first < T and torch.equal(zero[0][:first], inf[0][:first]), call.__name__
+        assert torch.equal(zero[1], inf[1]) and not torch.isfinite(inf[0][-1, :, 5]).any(), call.__name__
+        ref = pr.oracles[sid].query(synth.to_raw(q), synth.to_raw(k), synth.to_raw(v))
+        compare(call.__name__, zero[0], zero[1], *ref, shape.dtype)
