@@ -759,3 +759,23 @@ def test_head_dim_64_infinite_value_of_a_later_token(n, T):
         assert torch.equal(zero[1], inf[1]) and not torch.isfinite(inf[0][-1, :, 5]).any(), call.__name__
         ref = pr.oracles[sid].query(synth.to_raw(q), synth.to_raw(k), synth.to_raw(v))
         compare(call.__name__, zero[0], zero[1], *ref, shape.dtype)
+
+
+@pytest.mark.parametrize("hq,hkv,n,T", [(32, 8, 0, 64), (32, 8, 40, 70), (8, 4, 700, 200)])
+def test_head_dim_64_both_tile_heights_round_the_same_weights(hq, hkv, n, T):
+    """256- and 128-row tiles take a row's reference maximum from the same 64 keys, so the weights they round to 16 bits are the
+    same ones: results equal to fp32 summation error (a reference from 32 keys: 1e-3)."""
+    shape = synth.Shape("bf16", hq, hkv, 64)
+    gen = synth.generator(2, stream=2000 + T)
+    got = []
+    q, k, v = synth.draw_qkv(gen, T, shape)
+    _, kc, vc = synth.draw_qkv(gen, n, shape)
+    for env in (None, {"SK_NO_256": "1"}):
+        pr = Pair(shape, n_blocks=80, max_sessions=1, max_batch_tokens=1024, env=env)
+        sid = pr.create()
+        if n:
+            pr.append(sid, None, kc, vc, check=False)
+        got.append(pr.pool.sk_session_query(sid, dev(q), dev(k), dev(v), n_splits=1))
+        assert pr.pool.sk_pool_last_launch()["kernel_variant"] == (1 if env else 3)
+    (a, la), (b, lb) = got
+    assert float((a - b).norm() / b.norm()) <= 2e-6 and float((la - lb).abs().max()) <= 2e-5
