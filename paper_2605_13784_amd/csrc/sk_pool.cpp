@@ -751,8 +751,8 @@ int scatter_launch(sk_pool* p, const ScatterSlot& ss, const std::vector<sk_scatt
     if (!p->device) return SK_OK;
     int e = sk_launch_scatter(p->geom, k, v, (const sk_scatter*)ss.host, (int32_t)items.size(),
                               (int32_t*)(ws + p->L.off_tables), (unsigned char*)p->d.kv_mem, ws + p->L.off_eph, st);
+    ring_busy(p, ss.slot, st);         // whatever e is: an error that an earlier call left behind shows up here too, with the kernel on the stream
     if (e) { g_last_hip = e; return SK_E_HIP; }
-    ring_busy(p, ss.slot, st);
     p->stats.launches++;
     return SK_OK;
 }
