@@ -719,6 +719,8 @@ int64_t scatter_groups(int64_t dst_tok0, int64_t count)     // 16-token groups t
     return count <= 0 ? 0 : (dst_tok0 + count + 15) / 16 - dst_tok0 / 16;
 }
 
+constexpr size_t kListInPlaceMax = 4096;     // groups up to which the commit kernel reads its list in the pinned slot (scatter_launch)
+
 int scatter_reserve(sk_pool* p, int64_t n_items, ScatterSlot& ss)
 {
     ss = ScatterSlot();
@@ -743,15 +745,31 @@ int scatter_launch(sk_pool* p, const ScatterSlot& ss, const std::vector<sk_scatt
         p->stats.launches++;
         return SK_OK;
     }
-    // A longer one is read where it lies, in the pinned slot: each workgroup reads 32 bytes of it once, one round trip to
-    // the host where a copy in front is a launch of its own (2,600 tokens into an
-    // empty session and a question 97.1 -> 94.8 us).
+    // A longer one is read where it lies, in the pinned slot: every KV head's workgroup of a group reads its 32 bytes over the host
+    // link, one round trip where a copy in front is a launch of its own.  us per commit in a stream of them, and alone (a wait
+    // behind each); copied -> read in place:
+    //   heads       1,300 tokens             2,600                     10,400                  41,600                  131,072
+    //   1  d 128    10.1 ->  7.4/23 -> 23    10.8 ->  8.5/23 -> 26     23 -> 10/30 -> 33       29 ->  18/ 44 ->  68    46 ->  43/ 78 ->  78
+    //   2  d 64     10.3 ->  7.7/22 -> 26    10.7 ->  8.3/23 -> 26     23 -> 11/30 -> 31       29 ->  23/ 43 ->  74    48 ->  58/ 79 -> 103
+    //   8  d 128    10.2 ->  7.8/23 -> 26    11.1 ->  9.0/24 -> 30     34 -> 19/40 -> 44       78 ->  63/ 94 ->  84   214 -> 194/252 -> 236
+    //   32 d 128    13.2 -> 12.6/27 -> 31    19.4 -> 19.0/33 -> 40     82 -> 67/88 -> 81      276 -> 259/293 -> 285   -
+    // With its attention behind it an append gains 1 to 3 us up to 4,096 tokens, alone as well (2,600 tokens of 32/8 heads into an
+    // empty session and a question: 97.7 -> 96.2, alone 111.9 -> 110.9).  A commit that somebody waits for loses some, and of two
+    // heads of 64 dims 131,072 tokens lose in a stream too, where as many reads go over the link for a quarter of the bytes: so up
+    // to 4,096 groups, 65,536 tokens; longer lists are copied to the workspace.
     if (ss.host) memcpy(ss.host, items.data(), items.size() * sizeof(sk_scatter));
-    if (inject(p, SK_SITE_UPLOAD) || inject(p, SK_SITE_SCATTER)) return SK_E_HIP;
+    const sk_scatter* list = (const sk_scatter*)ss.host;
+    const bool in_place = items.size() <= kListInPlaceMax;
+    if (!in_place) {
+        int rc = ring_upload(p, ss.slot, items.size() * sizeof(sk_scatter), st);
+        if (rc) return rc;
+        list = (const sk_scatter*)(ws + p->L.off_meta);
+    } else if (inject(p, SK_SITE_UPLOAD)) return SK_E_HIP;
+    if (inject(p, SK_SITE_SCATTER)) return SK_E_HIP;
     if (!p->device) return SK_OK;
-    int e = sk_launch_scatter(p->geom, k, v, (const sk_scatter*)ss.host, (int32_t)items.size(),
+    int e = sk_launch_scatter(p->geom, k, v, list, (int32_t)items.size(),
                               (int32_t*)(ws + p->L.off_tables), (unsigned char*)p->d.kv_mem, ws + p->L.off_eph, st);
-    ring_busy(p, ss.slot, st);         // whatever e is: an error that an earlier call left behind shows up here too, with the kernel on the stream
+    if (in_place) ring_busy(p, ss.slot, st);         // whatever e is: an error that an earlier call left behind shows up here too, with the kernel on the stream
     if (e) { g_last_hip = e; return SK_E_HIP; }
     p->stats.launches++;
     return SK_OK;

@@ -50,7 +50,7 @@ int main()
 {
     sk_pool_desc d = {};
     d.dtype = SK_BF16; d.n_q_heads = d.n_kv_heads = 1; d.head_dim = 64; d.block_tokens = 16; d.max_sessions = 1;
-    d.n_blocks = 4096; d.max_batch_tokens = 1 << 15;
+    d.n_blocks = 8192; d.max_batch_tokens = 1 << 17;
     d.kv_bytes = sk_pool_kv_bytes(&d); d.workspace_bytes = sk_pool_workspace_bytes(&d);
     d.kv_mem = std::aligned_alloc(256, (d.kv_bytes + 255) / 256 * 256);
     d.workspace = std::aligned_alloc(256, (d.workspace_bytes + 255) / 256 * 256);
@@ -72,6 +72,17 @@ int main()
     for (int i = 1; i < slots; ++i) CHECK(append(1300) == SK_OK && recorded[i + 1] == 1);
     CHECK(waited[1] == 0);
     CHECK(append(1300) == SK_OK && waited[1] == 1);
+    // Up to 4,096 groups of 16 tokens the list is read where it lies, a longer one from the workspace, behind a copy.
+    for (int32_t groups : {81, 4096, 4097, 5000}) {
+        const int before = copies;
+        CHECK(append(16 * groups) == SK_OK && copies - before == (groups > 4096 ? 1 : 0));
+        const char* w = (const char*)d.workspace;
+        CHECK(((const char*)list_at >= w && (const char*)list_at < w + d.workspace_bytes) == (groups > 4096));
+        CHECK(((const sk_scatter*)list_at)[groups - 1].src_tok0 == 16 * (groups - 1) && ((const sk_scatter*)list_at)[groups - 1].count == 16);
+    }
+    int total = 0, busy = 0;
+    for (int i = 1; i <= slots; ++i) { total += recorded[i]; busy += waited[i]; }
+    CHECK(total == slots + 5 && busy == 5);         // every long append marked its slot once, whichever way its list went
     CHECK(sk_pool_destroy(p) == SK_OK);
     std::free(d.kv_mem); std::free(d.workspace);
     std::printf("fake device ok\n");
