@@ -719,7 +719,7 @@ int64_t scatter_groups(int64_t dst_tok0, int64_t count)     // 16-token groups t
     return count <= 0 ? 0 : (dst_tok0 + count + 15) / 16 - dst_tok0 / 16;
 }
 
-constexpr size_t kListInPlaceMax = 4096;     // groups up to which the commit kernel reads its list in the pinned slot (scatter_launch)
+constexpr size_t kListInPlaceMax = 8192;     // groups up to which the commit kernel reads its list in the pinned slot (scatter_launch)
 
 int scatter_reserve(sk_pool* p, int64_t n_items, ScatterSlot& ss)
 {
@@ -754,9 +754,9 @@ int scatter_launch(sk_pool* p, const ScatterSlot& ss, const std::vector<sk_scatt
     //   8  d 128    10.2 ->  7.8/23 -> 26    11.1 ->  9.0/24 -> 30     34 -> 19/40 -> 44       78 ->  63/ 94 ->  84   214 -> 194/252 -> 236
     //   32 d 128    13.2 -> 12.6/27 -> 31    19.4 -> 19.0/33 -> 40     82 -> 67/88 -> 81      276 -> 259/293 -> 285   -
     // With its attention behind it an append gains 1 to 3 us up to 4,096 tokens, alone as well (2,600 tokens of 32/8 heads into an
-    // empty session and a question: 97.7 -> 96.2, alone 111.9 -> 110.9).  A commit that somebody waits for loses some, and of two
-    // heads of 64 dims 131,072 tokens lose in a stream too, where as many reads go over the link for a quarter of the bytes: so up
-    // to 4,096 groups, 65,536 tokens; longer lists are copied to the workspace.
+    // empty session and a question: 97.7 -> 96.2, alone 111.9 -> 110.9).  A commit that somebody waits for loses some; in a stream
+    // only the longest of two heads of 64 dims does, which reads as much of the list for a quarter of the bytes.  Up to 8,192 groups,
+    // as far as it was measured; longer lists are copied to the workspace.
     if (ss.host) memcpy(ss.host, items.data(), items.size() * sizeof(sk_scatter));
     const sk_scatter* list = (const sk_scatter*)ss.host;
     const bool in_place = items.size() <= kListInPlaceMax;
@@ -1179,7 +1179,9 @@ int sk_pool_create(const sk_pool_desc* desc, sk_pool** out)
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
             p->n_cus = cus;
-        hipError_t e = hipHostMalloc((void**)&p->ring, p->L.meta_bytes * kRingSlots, hipHostMallocDefault);
+        // Kernels read lists in it (scatter_launch) that replace those an earlier kernel read in the same place: mapped, and coherent
+        // by name, as the default leaves that to HIP_HOST_COHERENT.
+        hipError_t e = hipHostMalloc((void**)&p->ring, p->L.meta_bytes * kRingSlots, hipHostMallocMapped | hipHostMallocCoherent);
         if (e != hipSuccess) { g_last_hip = (int)e; delete p; return SK_E_HIP; }
         for (int i = 0; i < kRingSlots; ++i) {
             e = hipEventCreateWithFlags(&p->ring_ev[i], hipEventDisableTiming);

@@ -13,6 +13,7 @@
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #c); std::exit(1); } } while (0)
 
 static int n_events, recorded[16], waited[16], copies, launch_error;
+static unsigned host_flags;
 static const void* list_at;
 
 extern "C" {
@@ -26,7 +27,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { ++recorded[(intptr_t)e]; 
 hipError_t hipEventSynchronize(hipEvent_t e) { ++waited[(intptr_t)e]; return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) { host_flags = flags; *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); ++copies; return hipSuccess; }
 hipError_t hipMemset(void* d, int x, size_t n) { std::memset(d, x, n); return hipSuccess; }
@@ -50,13 +51,14 @@ int main()
 {
     sk_pool_desc d = {};
     d.dtype = SK_BF16; d.n_q_heads = d.n_kv_heads = 1; d.head_dim = 64; d.block_tokens = 16; d.max_sessions = 1;
-    d.n_blocks = 8192; d.max_batch_tokens = 1 << 17;
+    d.n_blocks = 1 << 14; d.max_batch_tokens = 1 << 18;
     d.kv_bytes = sk_pool_kv_bytes(&d); d.workspace_bytes = sk_pool_workspace_bytes(&d);
     d.kv_mem = std::aligned_alloc(256, (d.kv_bytes + 255) / 256 * 256);
     d.workspace = std::aligned_alloc(256, (d.workspace_bytes + 255) / 256 * 256);
     sk_pool* p = nullptr;
     int32_t id = -1;
     CHECK(sk_pool_create(&d, &p) == SK_OK && sk_session_create(p, &id) == SK_OK);
+    CHECK((host_flags & hipHostMallocCoherent) && (host_flags & hipHostMallocMapped));       // kernels read lists there
     const int slots = n_events;                     // one event per slot of the pinned ring, numbered from 1
     CHECK(slots >= 2 && slots < 16);
     static __attribute__((aligned(16))) char kv[16];
@@ -72,12 +74,12 @@ int main()
     for (int i = 1; i < slots; ++i) CHECK(append(1300) == SK_OK && recorded[i + 1] == 1);
     CHECK(waited[1] == 0);
     CHECK(append(1300) == SK_OK && waited[1] == 1);
-    // Up to 4,096 groups of 16 tokens the list is read where it lies, a longer one from the workspace, behind a copy.
-    for (int32_t groups : {81, 4096, 4097, 5000}) {
+    // Up to 8,192 groups of 16 tokens the list is read where it lies, a longer one from the workspace, behind a copy.
+    for (int32_t groups : {81, 8192, 8193, 9000}) {
         const int before = copies;
-        CHECK(append(16 * groups) == SK_OK && copies - before == (groups > 4096 ? 1 : 0));
+        CHECK(append(16 * groups) == SK_OK && copies - before == (groups > 8192 ? 1 : 0));
         const char* w = (const char*)d.workspace;
-        CHECK(((const char*)list_at >= w && (const char*)list_at < w + d.workspace_bytes) == (groups > 4096));
+        CHECK(((const char*)list_at >= w && (const char*)list_at < w + d.workspace_bytes) == (groups > 8192));
         CHECK(((const sk_scatter*)list_at)[groups - 1].src_tok0 == 16 * (groups - 1) && ((const sk_scatter*)list_at)[groups - 1].count == 16);
     }
     int total = 0, busy = 0;
