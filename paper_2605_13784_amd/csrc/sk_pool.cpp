@@ -140,7 +140,7 @@ struct sk_pool {
     bool force_simple = false, no_small = false, no_256 = false, no_pack = false, no_interleave = false, no_stream_loads = false;
     int distrust = 0;                    // SK_SMALL_DISTRUST (tests)
     bool p128 = true;                    // SK_NO_P128=1: never the eight-wave 128-row instance
-    int64_t p128_min_tokens = 13312;     // SK_P128_MIN_TOKENS: cached tokens from which it is taken (break-even between 8,000 and 14,800: plan_regular)
+    int64_t p128_min_tokens = -1;        // SK_P128_MIN_TOKENS: cached tokens from which it is taken; -1: by the keys of a workgroup (kP128MinKeys)
     int64_t stream_min_tokens = 65536;   // SK_STREAM_MIN_TOKENS: cached tokens from which the 128-row instances load non-temporal
     bool fuse = false;                   // SK_FUSE=1: single-session calls merge their split partials inside the attention kernel
     bool fuse_list = false;              // batched calls too (the last workgroup of a unit merges alone)
@@ -266,6 +266,7 @@ struct Variant { int id; int rows_per_slot; int tok_per_tile; };
 //   14/2  d 64    11.8 ->  8.5/12.1 ->  8.6 13.6 ->  8.4/14.1 ->  9.7 20.3 -> 13.1/20.5 -> 13.7 24.0 -> 17.0 30.8 -> 24.6
 //   32/8  d 64    12.0 ->  8.3/12.3 ->  8.8 14.3 ->  8.5/14.5 ->  9.8 24.3 -> 17.0/24.3 -> 19.6 38.1 -> 26.5 -
 constexpr int64_t kSmallMaxBytes = int64_t(128) << 20;
+constexpr int64_t kP128MinKeys = 512;         // keys of a workgroup from which the 128-row tile takes eight waves (plan_regular)
 bool pick_variant(const sk_pool* p, int64_t n_tok, Variant& v, bool allow_256 = false, int64_t cached = -1)
 {
     const int G = p->L.G;
@@ -620,11 +621,17 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     const bool mfma = v.id != SK_KV_SIMPLE;
     // A 128-row call that gives every CU at most one workgroup takes the eight-wave instance: two key
     // phases per row group, so a wave has half the arithmetic per 64 keys and its SIMD a second wave
-    // to overlap it with.  Measured (us per query, four waves -> eight; 32 tokens unless said otherwise): 8,000 cached tokens
-    // 17.6 -> 18.8, 14,800 23.1 -> 22.6 (23 tokens with their own K/V 22.1 -> 21.4), 20,000 26.1 -> 25.6, 24,000 with 24 tokens
-    // 27.4 -> 25.7, 32,768 34.4 -> 32.6, 60,000 with 16 of 28/4 heads 32.6 -> 30.8: the eight waves pay off once the stream outweighs their longer start and
-    // their merge of the two phases.
-    if (p->p128 && v.id == SK_KV_MFMA128 && p->d.head_dim == 128 && R.wgs <= p->n_cus && kv_len >= p->p128_min_tokens) v.id = SK_KV_MFMA128P;
+    // to overlap it with.  They pay off once what a workgroup streams outweighs their longer start and their merge of the two phases.
+    // Measured (us per query, four waves -> eight, by the keys of a workgroup; cached tokens of the call in brackets):
+    //   heads, rows    256                         about 450                   about 510                  1,024 and more
+    //    8/1, 128      15.9 -> 17.0 [14,800]       -                           -                          -
+    //   14/2, 126      17.1 -> 18.4 [14,800]       22.9 -> 23.4 [45,000]       25.8 -> 25.6 [60,000]      -
+    //   28/4, 126      17.8 -> 18.8 [14,800]       22.0 -> 22.3 [28,000]       23.8 -> 23.3 [32,768]      33.3 -> 31.0 [60,000]
+    //   32/8, 128      17.3 -> 18.2 [7,000]        21.4 -> 21.5 [13,312]       23.1 -> 22.5 [14,800]      34.7 -> 32.2 [32,768]
+    //   64/16, 128     18.0 -> 19.4 [3,000]        21.8 -> 21.9 [7,000]        24.3 -> 23.9 [9,000]       35.0 -> 32.7 [17,000]
+    //   32/32, 128     -                           21.6 -> 21.9 [3,000]        27.2 -> 26.2 [5,000]       36.9 -> 33.9 [9,000]
+    const bool long_enough = p->p128_min_tokens >= 0 ? kv_len >= p->p128_min_tokens : chunk >= kP128MinKeys;
+    if (p->p128 && v.id == SK_KV_MFMA128 && p->d.head_dim == 128 && R.wgs <= p->n_cus && long_enough) v.id = SK_KV_MFMA128P;
     L.fuse = (p->fuse && mfma && parts > 1 && base_wgs <= p->L.sync_units && parts < 65536) ? 1 : 0;
     const int64_t resident = int64_t(p->n_cus) * ((v.id == SK_KV_MFMA256 || v.id == SK_KV_MFMA128P) ? 1 : 2);
     L.wait_polls = (L.fuse && R.wgs <= resident) ? p->wait_polls : 0;

@@ -43,7 +43,7 @@ def test_bf16_gqa_ragged_appends_and_queries(block_tokens, env):
     appends of ragged lengths (several row tiles, partial tiles, single tokens, block-straddling),
     then queries of several lengths in both modes with several split counts; once more with the
     eight-wave 128-row instance and the non-temporal loads that single-session calls of 65-128 rows
-    otherwise only take from 13,312 / 65,536 cached tokens on."""
+    otherwise only take from 512 keys a workgroup / 65,536 cached tokens on."""
     shape = synth.CFG2
     gen = synth.generator(2, stream=1)
     pr = Pair(shape, block_tokens=block_tokens, n_blocks=4096 // block_tokens + 8, kv_fill=0xFF, max_batch_tokens=1024, env=env)
@@ -779,3 +779,26 @@ def test_head_dim_64_both_tile_heights_round_the_same_weights(hq, hkv, n, T):
         assert pr.pool.sk_pool_last_launch()["kernel_variant"] == (1 if env else 3)
     (a, la), (b, lb) = got
     assert float((a - b).norm() / b.norm()) <= 2e-6 and float((la - lb).abs().max()) <= 2e-5
+
+
+@pytest.mark.parametrize("hq,hkv,n,T,eight", [(32, 8, 14336, 32, False), (32, 8, 14337, 17, True), (28, 4, 20000, 18, False), (12, 4, 29000, 22, True),
+                                              (8, 1, 45000, 16, False), (14, 2, 14800, 18, False), (32, 32, 3585, 66, True), (32, 32, 3584, 128, False)])
+def test_eight_waves_from_512_keys_a_workgroup(hq, hkv, n, T, eight):
+    """Calls of 65 to 128 rows take the eight-wave instance by the keys of a workgroup, which the number of KV heads decides as
+    much as the cached tokens: both sides of the line, single rows against attention in float64."""
+    shape = synth.Shape("bf16", hq, hkv, 128)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    draw = lambda T, H: torch.randn((T, H, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    pool = sk.Pool("bf16", hq, hkv, 128, 16, n // 16 + 8, max_sessions=1)
+    sid = pool.sk_session_create()
+    K, V = draw(n, hkv), draw(n, hkv)
+    for t in range(0, n, 4096):
+        pool.sk_session_append(sid, None, K[t:t + 4096], V[t:t + 4096])
+    q = draw(T, hq)
+    out, lse = pool.sk_session_query(sid, q)
+    geo = pool.sk_pool_last_launch()
+    assert geo["kernel_variant"] == (4 if eight else 1) and geo["workgroups"] <= 256, geo
+    for t, h in ((0, 0), (T - 1, hq - 1), (T // 2, hq // 2)):
+        s = (K[:, h // (hq // hkv)].double() @ q[t, h].double()) / 128 ** 0.5
+        ref = torch.softmax(s, 0) @ V[:, h // (hq // hkv)].double()
+        compare("row %d head %d" % (t, h), out[t, h], lse[t, h], ref.cpu().numpy(), torch.logsumexp(s, 0).cpu().numpy(), shape.dtype)
