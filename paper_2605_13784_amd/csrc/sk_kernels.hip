@@ -934,7 +934,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                              sk_u32x4 (&p_old)[2], sk_u32x4 (&p_new)[2], auto extra) __attribute__((always_inline)) {
                 constexpr int HALF = decltype(half_const)::value;
                 constexpr bool PV = decltype(pv_const)::value != 0;
-                mask_tile(tile, cur);
+                if (PV || HALF == 1) mask_tile(tile, cur);
                 const float neg_m = -m_ref;
                 float x[17], e[16], lx0 = 0.f, lx1 = 0.f;
                 auto pair = [&](const int i) __attribute__((always_inline)) {
@@ -1014,22 +1014,27 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             sk_lds_barrier();
             // K tile 0 lies in slot 7, tile 1 in slot 0 (a tile's K one slot below its number, its V one above)
             if (n_live > 0) {
-                sk_u32x4 k0[NKS], k1[NKS];
+                auto scores = [&](const int off) __attribute__((always_inline)) {
+                    sk_u32x4 k0[NKS];
 #pragma unroll
-                for (int i = 0; i < NKS; ++i) { k0[i] = *(sk_lds_u4ptr)(kc[i] + 7 * 1024); k1[i] = *(sk_lds_u4ptr)kc[i]; }
-                f32x16 s1 = zero;
-                sc[0] = zero;
+                    for (int i = 0; i < NKS; ++i) k0[i] = *(sk_lds_u4ptr)(kc[i] + off);
+                    f32x16 s0 = zero;
 #pragma unroll
-                for (int i = 0; i < NKS; ++i) {
-                    sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k0[i]), qreg[i], sc[0], 0, 0, 0);
-                    s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k1[i]), qreg[i], s1, 0, 0, 0);
-                }
+                    for (int i = 0; i < NKS; ++i) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k0[i]), qreg[i], s0, 0, 0, 0);
+                    return s0;
+                };
+                sc[0] = scores(7 * 1024);
+                mask_tile(0, sc[0]);                 // (the first stage does not again)
                 if (__any(m_ref == SK_NEG_INF)) {
-                    mask_tile(0, sc[0]);
-                    mask_tile(1, s1);
                     float mt_ = SK_NEG_INF;
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) mt_ = fmaxf(mt_, fmaxf(sc[0][v], s1[v]));
+                    for (int v = 0; v < 16; ++v) mt_ = fmaxf(mt_, sc[0][v]);
+                    if (first_0 + SK_TILE <= lim_wave_max) {
+                        f32x16 s1 = scores(0);
+                        mask_tile(1, s1);
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) mt_ = fmaxf(mt_, s1[v]);
+                    }
                     { const sk_halves h = sk_both_halves(mt_); mt_ = fmaxf(h.lo, h.hi) * c_scale; }
                     m_ref = m_ref == SK_NEG_INF ? mt_ : m_ref;
                 }
