@@ -444,7 +444,7 @@ uint32_t list_bucket(uint32_t len, uint32_t chunk) { return len == chunk ? 8 : u
 // rounds of the chip -> 2 pieces, one round).
 // The schedule is only played through where simple bounds of its end (the average load, the longest piece) do not
 // say already that the length is no better, and no further than to where it is known to be none.
-int64_t list_chunk(const sk_pool* p, const ListGroup& g, bool one_session = false, double* expected_end = nullptr)
+int64_t list_chunk(const sk_pool* p, const ListGroup& g)
 {
     int64_t longest = 0;
     for (const TileReq& t : g.tiles) longest = std::max<int64_t>(longest, t.kv_vis);
@@ -456,15 +456,15 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g, bool one_session = fals
     std::vector<double> lane;                              // when each lane is free: a heap, the first one on top
     std::vector<int32_t> rest(n_tiles), ordered(n_tiles);  // iterations of each tile's last piece; the same, longest eighths first
     std::vector<uint8_t> bucket(n_tiles);
-    for (int64_t k = 1; k <= 256; k += one_session && k < 64 ? 1 : std::max<int64_t>(1, k / 4)) {
+    for (int64_t k = 1; k <= 256; k += std::max<int64_t>(1, k / 4)) {
         const int64_t chunk = std::max<int64_t>(256, ((longest + k - 1) / k + 63) / 64 * 64);
-        if (chunk == last) { if (chunk == 256) break; continue; }
+        if (chunk == last) break;
         last = chunk;
-        int64_t whole = 0, parts = 0, split = 0, its_sum = 0, its_max = 0;
+        int64_t whole = 0, parts = 0, its_sum = 0, its_max = 0;
         size_t count[9] = {};
         for (size_t i = 0; i < n_tiles; ++i) {
             const uint32_t np = list_parts(g.tiles[i], (uint32_t)chunk), left = (uint32_t)g.tiles[i].kv_vis - (np - 1) * (uint32_t)chunk;
-            if (np > 1) { parts += np; ++split; }
+            if (np > 1) parts += np;
             whole += np - 1;
             rest[i] = int32_t((left + 63) / 64);
             bucket[i] = (uint8_t)list_bucket(left, (uint32_t)chunk);
@@ -473,16 +473,9 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g, bool one_session = fals
         }
         const int64_t n = whole + (int64_t)n_tiles;
         const bool sparse = big || n * Hkv <= p->n_cus;
-        const double it = big ? (wide ? 1.7 : 1.15) : one_session && !wide ? (sparse ? 0.8 : 1.15) : (sparse ? 1.4 : 2.7), ends = 6.0;
+        const double it = big ? (wide ? 1.7 : 1.15) : (sparse ? 1.4 : 2.7), ends = 6.0;
         const int64_t lanes = std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
-        // (one session: the combine launch 4, a partial of 128 rows 0.02, at head_dim 64 0.01.  Tiles of an append into an empty session
-        // are short and of all lengths, so that splitting them gains less than it seems: 7.5 for the launch and the split's own uneven
-        // end, 0.0004 for a row, 8 TB/s for the partials; fitted to us per call, whole - in two parts: 2,000 tokens of 32/8 heads
-        // 64.4 - 74.1, 1,500 50 - 53.8, 1,750 of 28/4 55.8 - 57.3)
-        const double partials = double(parts) * Hkv * g.v.rows_per_slot / 128.0;
-        const double merge = !one_session ? partials * 0.018 : split == 0 ? 0.0
-                             : g.tiles[0].pos0 > 0 ? 4.0 + partials * (wide ? 0.02 : 0.01)
-                             : 7.5 + 0.0004 * double(split) * Hkv * g.v.rows_per_slot + partials * (wide ? 0.008 : 0.004);
+        const double merge = double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0;
         // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
         const double c = double(chunk / 64) * it + ends, base = c * double(whole / lanes);
         const int64_t ahead = whole % lanes;               // lanes with one whole chunk more than the others
@@ -511,8 +504,98 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g, bool one_session = fals
         }
         best = end + merge; best_chunk = chunk;
     }
-    if (expected_end) *expected_end = best;
     return best_chunk;
+}
+
+// Expected time, in us, of the attention and combine launches of a single-session call whose row tiles are cut into pieces of
+// `chunk` keys, with `own` uncommitted tokens as one more piece of each tile.  The workgroups are played through in the order the
+// hardware takes them: workgroup b goes to XCD b % 8, where its shader engine is the next of four in turn, and waits there until
+// one of the engine's CUs is free, with all behind it on that XCD waiting too.  So an even share per CU is not enough: the
+// workgroups of splits that a tile does not have end at once but take their turn, and an engine that got more of the long pieces
+// holds up the others (700 tokens of 12/4 heads behind 2,600: 47 us in pieces of 384 keys, 35 in pieces of 576; a schedule over any free CU
+// expects 32 and 33).  Fitted to 39,000 timed launches of 3,330 calls (0 to 131,072 cached tokens, 9 to 3,300 new ones, 13 layer shapes).
+// Returns early with something not below `stop` where the end cannot be below it; *all_above: shorter pieces will not be either (their
+// load and merge are no less).
+struct RegCost {
+    double start;                    // of the launch, against that of the other instances of the head_dim
+    double it_alone, it_shared;      // an iteration of 64 keys with the chip empty, and what is added when all of it is busy
+    double ends;                     // start and end of a workgroup
+    double merge, part, row;         // combine launch; 1,000 rows of a partial written and read; 1,000 rows merged
+};
+constexpr RegCost kCost256 = {0.0, 1.1, 0.47, 8.0, 1.0, 0.05, 0.45}, kCost256d64 = {0.7, 0.9, 0.15, 2.7, 1.2, 0.08, 0.36},
+                  kCost128d64 = {0.0, 0.9, 0.25, 2.2, 1.3, 0.08, 0.34};
+double regular_end(const sk_pool* p, const Variant& v, int64_t n_tok, int32_t pos0, int64_t kv_len, int32_t own, int64_t chunk, double stop, bool* all_above)
+{
+    constexpr int kXcds = 8, kEngines = 4, kMaxLanes = 64;
+    const bool big = v.id == SK_KV_MFMA256;
+    const RegCost& c = p->d.head_dim == 128 ? kCost256 : big ? kCost256d64 : kCost128d64;
+    const int Hkv = p->d.n_kv_heads, per_cu = big ? 1 : 2;
+    const int64_t tiles = (n_tok + v.tok_per_tile - 1) / v.tok_per_tile, chunk_its = chunk / 64, own_its = (own + 63) / 64;
+    auto visible = [&](int64_t tile) { return pos0 < SK_NO_CAUSAL ? std::min(kv_len, pos0 + std::min(n_tok, (tile + 1) * v.tok_per_tile)) : kv_len; };
+    int64_t pieces = 0, parts = 0, split = 0, its = 0;
+    for (int64_t t = 0; t < tiles; ++t) {
+        const uint32_t kv = (uint32_t)visible(t), np = (kv + (uint32_t)chunk - 1) / (uint32_t)chunk + (own > 0 ? 1 : 0);
+        pieces += np; its += (kv + 63) / 64 + own_its;
+        if (np > 1) { parts += np; ++split; }
+    }
+    const double room = double(p->n_cus * per_cu), it = c.it_alone + c.it_shared * std::min(1.0, double(pieces * Hkv) / room);
+    const double stage = own > 0 && (tiles > 1 || own > SK_STAGE_TOKENS) ? 2.5 : 0.0;      // a launch in front writes the own tokens to the staging area
+    const double apart = c.start + stage + (split == 0 ? 0.0 : c.merge + double(Hkv * v.rows_per_slot) * 1e-3 * (c.part * double(parts) + c.row * double(split)));
+    const double load = (double(its) * it + double(pieces) * c.ends) * Hkv / room;
+    *all_above = apart + load >= stop;
+    if (*all_above) return apart + load;
+    const int64_t total = ((kv_len + chunk - 1) / chunk + (own > 0 ? 1 : 0)) * tiles * Hkv;
+    if (double(total) <= room)                                 // nobody waits
+        return apart + c.ends + it * double(std::max(std::min(chunk_its, (kv_len + 63) / 64), own_its));
+    if (double(total) > 64.0 * room)                           // the end of so long a launch is a small part of it
+        return apart + load + 0.5 * (c.ends + it * double(std::min(chunk_its, (kv_len + 63) / 64)));
+    const int lanes = std::min(kMaxLanes, std::max(1, p->n_cus * per_cu / (kXcds * kEngines)));
+    int stride = kXcds;                                        // XCDs that many apart get the same lengths
+    for (int h = Hkv; h != 0;) { const int r = stride % h; stride = h; h = r; }
+    double end = 0;
+    for (int x = 0; x < kXcds; x += stride) {
+        double free_at[kEngines][kMaxLanes];                   // heaps: the first CU to be free on top
+        for (int e = 0; e < kEngines; ++e) std::fill(free_at[e], free_at[e] + lanes, 0.0);
+        double turn = 0;
+        int engine = 0;
+        for (uint32_t b = (uint32_t)x; b < total; b += kXcds, engine = (engine + 1) % kEngines) {
+            const uint32_t rest = b / (uint32_t)Hkv, part = rest / (uint32_t)tiles;
+            const int64_t kv = visible(tiles - 1 - (rest - part * (uint32_t)tiles)), begin = part * chunk;
+            double* heap = free_at[engine];
+            turn = std::max(turn, heap[0]);
+            double t = turn + 0.3;                             // a split the tile does not have
+            const bool cached = begin < kv, last = own > 0 && !cached && begin - chunk < kv;
+            if (cached || last) {
+                t = turn + c.ends + it * double(last ? own_its : std::min(chunk_its, (kv - begin + 63) / 64));
+                end = std::max(end, t);
+                if (end + apart >= stop) return end + apart;
+            }
+            int hole = 0;                                      // t takes its place in the heap from the top
+            for (int kid = 1; kid < lanes; kid = 2 * hole + 1) {
+                if (kid + 1 < lanes && heap[kid + 1] < heap[kid]) ++kid;
+                if (!(heap[kid] < t)) break;
+                heap[hole] = heap[kid]; hole = kid;
+            }
+            heap[hole] = t;
+        }
+    }
+    return end + apart;
+}
+
+// Length of the pieces for which that time is least, if it is below `best`.
+int64_t regular_chunk(const sk_pool* p, const Variant& v, int64_t n_tok, int32_t pos0, int64_t kv_len, int32_t own, double& best)
+{
+    int64_t chosen = 0, last = 0;
+    for (int64_t k = 1; k <= 256; k += k < 64 ? 1 : k / 4) {
+        const int64_t chunk = std::max<int64_t>(256, ((kv_len + k - 1) / k + 63) / 64 * 64);
+        if (chunk == last) { if (chunk == 256) break; continue; }
+        last = chunk;
+        bool all_above = false;
+        const double stop = chosen ? 0.995 * best : best, end = regular_end(p, v, n_tok, pos0, kv_len, own, chunk, stop, &all_above);
+        if (all_above) break;
+        if (end < stop) { best = end; chosen = chunk; }
+    }
+    return chosen;
 }
 
 int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int64_t kv_len, int32_t eph_cnt, int32_t eph_pos0,
@@ -552,36 +635,25 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
         S = std::max<int64_t>(1, (target + base_wgs / 2) / base_wgs);
     }
     int64_t chunk = kv_len > 0 ? (kv_len + S - 1) / S : 64;
-    // The 256-row instance: by the expected end of the launch.  One workgroup to a CU makes the number of workgroups count: with
-    // the pieces cut for about 256 of them, 264 were two rounds of the chip.  Measured (us per append, before -> after; the model's
-    // times are in list_chunk): 9,001 cached and 129 tokens of 32/8 heads (24 tiles, 264 workgroups -> 240) 62.5 -> 40.5; 131,072
-    // and 183 575 -> 388; 32,512 and 377 of 64/8 530 -> 378; 330 of 28/4 into an empty session 27.0 -> 21.6; 1,160 of 32/8 54.4
-    // -> 38.9; 2,600 and 298 38.4 -> 35.0.  Over 150 calls of 0 to 131,072 cached and 31 to 3,376 tokens of six layer shapes 1.11 to 1.12
-    // times as fast in the mean, none more than 2 % slower.
-    if (n_splits_req <= 0 && !p->target_wgs_set && v.id == SK_KV_MFMA256 && kv_len > 256) {
-        ListGroup tiles;
-        tiles.v = v;
-        TileReq base = {};
-        base.pos0 = pos0; base.kv_vis = (int32_t)kv_len;
-        TileReq own = {};                                   // the own part of each row tile is a workgroup more
-        own.pos0 = SK_NO_CAUSAL; own.kv_vis = eph_cnt;
-        auto cut = [&](ListGroup& g) {
-            add_tiles(g, base, 0, (int32_t)n_tok);
-            if (has_eph) g.tiles.resize(2 * g.tiles.size(), own);
-        };
-        cut(tiles);
-        double end256 = 0;
-        chunk = list_chunk(p, tiles, true, &end256);
+    // The 256-row instance: by the expected end of the launches (regular_end).  One workgroup to a CU makes the number of
+    // workgroups count: with the pieces cut for about 256 of them, 264 were two rounds of the chip.
+    // us per append, pieces for about 256 workgroups -> by a schedule of longest pieces first over any free CU -> by the order of the launch:
+    //   32/8 d 128    1,500 tokens behind 1 cached 53.6 -> 58.3 -> 51.4, 1,750 behind 1 60.0 -> 68.6 -> 57.6, 1,500 behind 600 65.4 -> 76.7 -> 63.3,
+    //                 1,200 into an empty session 55.5 -> 39.8 -> 39.7, 700 behind 32,512 521 -> 351 -> 353
+    //   28/4 d 128    2,000 behind 1 63.0 -> 68.3 -> 60.7;  12/4 d 128  700 behind 2,600 37.4 -> 43.6 -> 34.0;  16/16 d 128  1,200 at 0 41.1 -> 43.1 -> 33.0
+    //   14/2 d 64     2,000 at 0 53.8 -> 43.7 -> 36.1;  32/8 d 64  2,000 behind 1 52.9 -> 58.1 -> 47.7
+    // Over 770 appends (0 to 32,512 cached, 200 to 3,376 tokens, seven layer shapes), against the first rule: 0.89 (128 dims) and 0.80 (64) of its time in the
+    // geometric mean, one of them more than 3 % slower (3.8); with the second 0.91 and 0.83, and 63 of them more than 3 % slower, up to 17.
+    if (n_splits_req <= 0 && !p->target_wgs_set && v.id == SK_KV_MFMA256 && kv_len > 0) {
+        double best = HUGE_VAL;
+        chunk = regular_chunk(p, v, n_tok, pos0, kv_len, eph_cnt, best);
         if (p->d.head_dim == 64) {
             // 128-row tiles of four waves, two workgroups to a CU, where they are expected to end earlier: less padding, or an evener
             // end
-            ListGroup low;
-            low.v = Variant{SK_KV_MFMA128, 128, 128 / p->L.G};
-            cut(low);
-            double end128 = 0;
-            const int64_t chunk128 = list_chunk(p, low, true, &end128);
-            if (end128 < end256) {
-                v = low.v; chunk = chunk128;
+            const Variant low = {SK_KV_MFMA128, 128, 128 / p->L.G};
+            const int64_t chunk128 = regular_chunk(p, low, n_tok, pos0, kv_len, eph_cnt, best);
+            if (chunk128 > 0) {
+                v = low; chunk = chunk128;
                 L.rows_per_slot = v.rows_per_slot; L.tok_per_tile = v.tok_per_tile;
                 L.n_tiles = int32_t((n_tok + v.tok_per_tile - 1) / v.tok_per_tile);
                 base_wgs = int64_t(L.n_tiles) * p->d.n_kv_heads;

@@ -234,7 +234,7 @@ def test_merge_inside_the_kernel_equals_the_separate_combine_bit_for_bit():
             for x, y in zip(results[0], r):
                 assert torch.equal(x, y), what
 
-    for L in (600, 256, 1, 2000, 77, 1300):
+    for L in (600, 256, 1, 2000, 77, 1300, 300):
         q, k, v = [dev(t) for t in synth.draw_qkv(gen, L, shape)]
         same([p.sk_session_append(s[0], q, k, v) for p, s in zip(pools, sids)], "append %d" % L)
     assert pools[0].sk_pool_last_launch()["fused_merge"] == 1 and pools[2].sk_pool_last_launch()["fused_merge"] == 0
