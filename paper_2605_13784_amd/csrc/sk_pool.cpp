@@ -410,6 +410,7 @@ struct ListGroup {          // tiles that share a kernel variant and the q/out/l
     Variant v = {SK_KV_SIMPLE, 16, 1};
     const void* q = nullptr; void* out = nullptr; float* lse = nullptr;
     std::vector<TileReq> tiles;
+    int64_t chunk = 0;      // length of the pieces its tiles are cut into, where that is chosen already
 };
 
 // Cuts T tokens (packed rows q_row0..) that share `base` into row tiles of the group's height.
@@ -444,53 +445,84 @@ uint32_t list_bucket(uint32_t len, uint32_t chunk) { return len == chunk ? 8 : u
 // rounds of the chip -> 2 pieces, one round).
 // The schedule is only played through where simple bounds of its end (the average load, the longest piece) do not
 // say already that the length is no better, and no further than to where it is known to be none.
-int64_t list_chunk(const sk_pool* p, const ListGroup& g)
+// head_dim 64 on the matrix pipe has times of its own (ListCost), with the uncommitted tokens of a tile and the upload of the lists:
+// beyond 16 KiB that copy takes 14 us longer.  `other_bytes`: what is uploaded beside this launch's lists; 0 is returned where no length
+// is expected to end before `bound`.
+// Fitted to 13,000 timed launches of 992 steps and question batches.
+struct ListCost {
+    double start, it_alone, it_shared, ends;     // as in RegCost
+    double segment;                              // start of a run of uncommitted tokens
+};
+constexpr ListCost kList256d64 = {2.0, 0.88, 0.16, 6.4, 1.05}, kList128d64 = {1.8, 0.87, 0.29, 5.2, 0.75}, kList64d64 = {3.8, 0.63, 0.0, 2.6, 0.75};
+constexpr size_t kUploadStep = 16384;
+constexpr double kUploadStepUs = 14.0;
+bool list_narrow(const sk_pool* p, const Variant& v) { return p->d.head_dim == 64 && p->L.elem == 2 && v.id != SK_KV_SIMPLE; }
+
+int64_t list_chunk(const sk_pool* p, const ListGroup& g, size_t other_bytes = 0, double* expected_us = nullptr, size_t* expected_bytes = nullptr,
+                   double bound = HUGE_VAL)
 {
     int64_t longest = 0;
     for (const TileReq& t : g.tiles) longest = std::max<int64_t>(longest, t.kv_vis);
-    if (longest == 0) return 256;
     const int Hkv = p->d.n_kv_heads;
-    const bool big = g.v.id == SK_KV_MFMA256, wide = p->d.head_dim == 128;
+    const bool big = g.v.id == SK_KV_MFMA256, narrow = list_narrow(p, g.v);
+    const ListCost& nc = big ? kList256d64 : g.v.id == SK_KV_MFMA128 ? kList128d64 : kList64d64;
     const size_t n_tiles = g.tiles.size();
+    if (n_tiles == 0 || (longest == 0 && !narrow)) return 256;
     double best = 0; int64_t best_chunk = 0, last = 0;
     std::vector<double> lane;                              // when each lane is free: a heap, the first one on top
-    std::vector<int32_t> rest(n_tiles), ordered(n_tiles);  // iterations of each tile's last piece; the same, longest eighths first
-    std::vector<uint8_t> bucket(n_tiles);
+    std::vector<int32_t> rest(n_tiles);                    // iterations of each tile's last piece
+    std::vector<double> ordered(n_tiles);                  // how long that piece takes, longest eighths first
+    std::vector<uint8_t> bucket(n_tiles), own_its(n_tiles), own_runs(n_tiles);
+    for (size_t i = 0; narrow && i < n_tiles; ++i) {
+        const TileReq& t = g.tiles[i];
+        const int32_t subs = t.tok_period > 0 ? (t.n_tok + t.tok_period - 1) / t.tok_period : 1;
+        int32_t its = 0, runs = 0;
+        for (int e = 0; e < 2; ++e)
+            if (t.eph_cnt[e] > 0) { const int32_t n = e == 1 ? subs : 1; its += n * ((t.eph_cnt[e] + 63) / 64); runs += n; }
+        own_its[i] = (uint8_t)std::min(its, 255); own_runs[i] = (uint8_t)std::min(runs, 255);
+    }
     for (int64_t k = 1; k <= 256; k += std::max<int64_t>(1, k / 4)) {
         const int64_t chunk = std::max<int64_t>(256, ((longest + k - 1) / k + 63) / 64 * 64);
         if (chunk == last) break;
         last = chunk;
-        int64_t whole = 0, parts = 0, its_sum = 0, its_max = 0;
+        int64_t whole = 0, parts = 0, split = 0, its_sum = 0, its_max = 0, runs = 0;
         size_t count[9] = {};
         for (size_t i = 0; i < n_tiles; ++i) {
             const uint32_t np = list_parts(g.tiles[i], (uint32_t)chunk), left = (uint32_t)g.tiles[i].kv_vis - (np - 1) * (uint32_t)chunk;
-            if (np > 1) parts += np;
+            if (np > 1) { parts += np; ++split; }
             whole += np - 1;
-            rest[i] = int32_t((left + 63) / 64);
+            rest[i] = int32_t((left + 63) / 64) + own_its[i];
+            runs += own_runs[i];
             bucket[i] = (uint8_t)list_bucket(left, (uint32_t)chunk);
             ++count[bucket[i]];
             its_sum += rest[i]; its_max = std::max<int64_t>(its_max, rest[i]);
         }
         const int64_t n = whole + (int64_t)n_tiles;
-        const bool sparse = big || n * Hkv <= p->n_cus;
-        const double it = big ? (wide ? 1.7 : 1.15) : (sparse ? 1.4 : 2.7), ends = 6.0;
+        const bool sparse = big || (!narrow && n * Hkv <= p->n_cus);
+        const double room = double(p->n_cus) * (big ? 1 : 2);
+        const double it = narrow ? nc.it_alone + nc.it_shared * std::min(1.0, double(n * Hkv) / room) : big ? 1.7 : sparse ? 1.4 : 2.7;
+        const double ends = narrow ? nc.ends : 6.0, segment = narrow ? nc.segment : 0.0;
         const int64_t lanes = std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
-        const double merge = double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0;
+        const size_t bytes = (size_t)(n * Hkv) * sizeof(sk_work) + (size_t)(split * Hkv) * sizeof(sk_comb);
+        const double step = narrow && other_bytes + bytes > kUploadStep ? kUploadStepUs : 0.0;
+        const double merge = step + (!narrow ? double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0
+                                     : split == 0 ? 0.0 : 4.0 + double(Hkv * g.v.rows_per_slot) * 1e-3 * (0.018 * double(parts) + 0.19 * double(split)));
         // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
         const double c = double(chunk / 64) * it + ends, base = c * double(whole / lanes);
         const int64_t ahead = whole % lanes;               // lanes with one whole chunk more than the others
-        auto no_better = [&](double end) { return best_chunk != 0 && !(end + merge < 0.995 * best); };
+        auto no_better = [&](double end) { return !(end + merge < (best_chunk != 0 ? 0.995 * best : bound)); };
         double end = std::max(ahead > 0 ? base + c : base, base + (double(its_max) * it + ends));
-        const double load = (double(whole) * c + double(its_sum) * it + double(n_tiles) * ends) / double(lanes);
+        const double load = (double(whole) * c + double(its_sum) * it + double(n_tiles) * ends + double(runs) * segment) / double(lanes);
+        if (narrow && no_better(load * (1 - 1e-9))) break;      // (neither the load nor the rest gets less with shorter pieces)
         if (no_better(std::max(end, load * (1 - 1e-9)))) continue;
         if ((int64_t)n_tiles > lanes - ahead) {            // (else each gets a lane that is free at `base`)
             size_t at[9], sum = 0;
             for (int b = 8; b >= 0; --b) { at[b] = sum; sum += count[b]; }
-            for (size_t i = 0; i < n_tiles; ++i) ordered[at[bucket[i]]++] = rest[i];
+            for (size_t i = 0; i < n_tiles; ++i) ordered[at[bucket[i]]++] = double(rest[i]) * it + double(own_runs[i]) * segment + ends;
             lane.assign((size_t)lanes, base + c);
             std::fill(lane.begin(), lane.begin() + (lanes - ahead), base);
             for (size_t i = 0; i < n_tiles && !no_better(end); ++i) {
-                const double x = lane[0] + (double(ordered[i]) * it + ends);
+                const double x = lane[0] + ordered[i];
                 end = std::max(end, x);
                 size_t hole = 0;                           // x takes its place in the heap from the top
                 for (size_t kid = 1; kid < (size_t)lanes; kid = 2 * hole + 1) {
@@ -502,9 +534,32 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g)
             }
             if (no_better(end)) continue;
         }
+        for (size_t i = 0; narrow && (int64_t)n_tiles <= lanes - ahead && i < n_tiles; ++i) end = std::max(end, base + (double(rest[i]) * it + double(own_runs[i]) * segment + ends));
+        if (no_better(end)) continue;
         best = end + merge; best_chunk = chunk;
+        if (expected_us) *expected_us = end + merge - step + nc.start + 2.0;       // (with the launch itself)
+        if (expected_bytes) *expected_bytes = bytes;
     }
     return best_chunk;
+}
+
+// Expected time of a call's launches (head_dim 64), or something not below `bound`: chooses the groups' pieces, and counts the upload's
+// step once.
+double list_cost(const sk_pool* p, ListGroup* const* groups, int n_groups, size_t scatter_bytes, double bound = HUGE_VAL)
+{
+    double us = 0;
+    size_t least = scatter_bytes, bytes = scatter_bytes;
+    for (int gi = 0; gi < n_groups; ++gi) least += groups[gi]->tiles.size() * p->d.n_kv_heads * sizeof(sk_work);
+    for (int gi = 0; gi < n_groups; ++gi) {
+        ListGroup& g = *groups[gi];
+        if (g.tiles.empty()) continue;
+        double end = 0;
+        size_t b = 0;
+        g.chunk = list_chunk(p, g, least - g.tiles.size() * p->d.n_kv_heads * sizeof(sk_work), &end, &b, bound - us);
+        if (g.chunk == 0) return bound;
+        us += end; bytes += b;
+    }
+    return us + (bytes > kUploadStep ? kUploadStepUs : 0.0);
 }
 
 // Expected time, in us, of the attention and combine launches of a single-session call whose row tiles are cut into pieces of
@@ -1009,7 +1064,9 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
         for (const TileReq& t : groups[gi].tiles) { P.kv_total += t.kv_vis; ++P.n_tiles; }
     if (P.n_tiles == 0) return SK_OK;
     int64_t chunk_g[kMaxGroups];
-    for (int gi = 0; gi < n_groups; ++gi) chunk_g[gi] = list_chunk(p, groups[gi]);
+    size_t scatter_bytes = 0;
+    for (int i = 0; i < n_sb; ++i) scatter_bytes += sb[i].items.size() * sizeof(sk_scatter);
+    for (int gi = 0; gi < n_groups; ++gi) chunk_g[gi] = groups[gi].chunk > 0 ? groups[gi].chunk : list_chunk(p, groups[gi], scatter_bytes);
     const int64_t cap_rows = p->L.part_slots * kPartSlotRows;
     size_t bytes = 0;
     for (;;) {
@@ -1505,6 +1562,8 @@ int sk_batch_step(sk_pool* p, int32_t n_items, const int32_t* session_id, const 
     sb.k = k; sb.v = v;
     ListGroup groups[3];
     const bool allow_256 = !p->no_256;
+    struct Item { TileReq base; int32_t row0, tokens; };
+    std::vector<Item> tall;                 // head_dim 64: the items in 256-row tiles
     int64_t eph_cursor = 0;
     std::vector<Undo> undo;
     int64_t appended = 0, queried = 0;
@@ -1549,6 +1608,27 @@ int sk_batch_step(sk_pool* p, int32_t n_items, const int32_t* session_id, const 
         ListGroup& g = groups[vv.id == SK_KV_MFMA64 ? 2 : vv.id == SK_KV_MFMA128 ? 1 : 0];
         g.v = vv; g.q = q; g.out = out; g.lse = lse;
         add_tiles(g, base, cu_tokens[i], T);
+        if (vv.id == SK_KV_MFMA256 && list_narrow(p, vv)) tall.push_back({base, cu_tokens[i], T});
+    }
+    if (list_narrow(p, groups[0].v) && !groups[0].tiles.empty()) {
+        // head_dim 64: the items above 128 rows in tiles of 128, together with those of 65 to 128, where that is expected to end
+        // earlier.  us per step in 256-row tiles and in 128: 12 sessions of 32/8 heads, 137 tokens at 888 cached each, 68 and 55; 48 of
+        // 14/2, 84 at 10,615, 307 and 256; 3 of 32/8, 363 at 304, 29 and 52 (its lists are then longer than 16 KiB); 4 of 12/4, 292 at
+        // 15,626, 112 and 166.  348 random steps against 128-row tiles always: with 256-row ones always 0.90 of the time in the
+        // geometric mean, 48 more than 3 % slower and up to 33; by expected end 0.81, the slowest 2 %.
+        ListGroup low = groups[1];
+        low.v = Variant{SK_KV_MFMA128, 128, 128 / p->L.G};
+        low.q = q; low.out = out; low.lse = lse;
+        for (const Item& it : tall) add_tiles(low, it.base, it.row0, it.tokens);
+        const size_t scatter = sb.items.size() * sizeof(sk_scatter);
+        ListGroup small = groups[2];
+        ListGroup* const as_low[2] = {&low, &small};
+        ListGroup* const as_tall[3] = {&groups[0], &groups[1], &groups[2]};
+        const double tall_us = list_cost(p, as_tall, 3, scatter);
+        if (list_cost(p, as_low, 2, scatter, tall_us) < tall_us) {
+            groups[0].tiles.clear();
+            groups[1] = std::move(low); groups[2].chunk = small.chunk;
+        }
     }
     ListPlan plan;
     int rc = plan_list(p, &sb, 1, groups, 3, plan);
@@ -1606,25 +1686,41 @@ int sk_session_query_shared_prefix(sk_pool* p, int32_t id, const void* qp, const
         // kernel (their rows see the same cache and prefix; each sees its own suffix), when a
         // question's rows are a multiple of a wave's 32 and divide 256.
         const int64_t rows_q = int64_t(Sfx) * p->L.G;
-        const bool pack = groups[1].v.id != SK_KV_SIMPLE && rows_q < 256 && rows_q % 32 == 0 &&
-                          256 % rows_q == 0 && NQ > 1 && !p->no_pack;
-        const int32_t per_tile = pack ? int32_t(256 / rows_q) : 1;
-        if (pack) groups[1].v = Variant{SK_KV_MFMA256, 256, 256 / p->L.G};
+        const bool can_pack = groups[1].v.id != SK_KV_SIMPLE && rows_q < 256 && rows_q % 32 == 0 &&
+                              256 % rows_q == 0 && NQ > 1 && !p->no_pack;
         for (int32_t j = 0; j < NQ; ++j)
             build_scatter(p, nullptr, id, 0, j * Sfx, Sfx, 0, true, pre_blocks + j * sfx_blocks, sb[1].items);
-        for (int32_t j = 0; j < NQ; j += per_tile) {
-            const int32_t nq_tile = std::min(per_tile, NQ - j);
-            TileReq base = {};
-            base.tbl_off = tbl_off; base.pos0 = int32_t(n + P); base.kv_vis = (int32_t)n;
-            base.hole_lo = (int32_t)s->frozen; base.hole_hi = (int32_t)s->win;
-            base.eph_blk[0] = 0; base.eph_cnt[0] = P; base.eph_pos0[0] = (int32_t)n;
-            base.eph_blk[1] = int32_t(pre_blocks + j * sfx_blocks); base.eph_cnt[1] = Sfx; base.eph_pos0[1] = int32_t(n + P);
-            if (pack) {
-                base.tok_period = Sfx; base.sub_blocks = (int32_t)sfx_blocks;
-                base.q_tok0 = j * Sfx; base.n_tok = nq_tile * Sfx;
-                groups[1].tiles.push_back(base);
-            } else add_tiles(groups[1], base, j * Sfx, Sfx);
-        }
+        auto cut = [&](ListGroup& g, bool pack) {
+            const int32_t per_tile = pack ? int32_t(256 / rows_q) : 1;
+            if (pack) g.v = Variant{SK_KV_MFMA256, 256, 256 / p->L.G};
+            for (int32_t j = 0; j < NQ; j += per_tile) {
+                const int32_t nq_tile = std::min(per_tile, NQ - j);
+                TileReq base = {};
+                base.tbl_off = tbl_off; base.pos0 = int32_t(n + P); base.kv_vis = (int32_t)n;
+                base.hole_lo = (int32_t)s->frozen; base.hole_hi = (int32_t)s->win;
+                base.eph_blk[0] = 0; base.eph_cnt[0] = P; base.eph_pos0[0] = (int32_t)n;
+                base.eph_blk[1] = int32_t(pre_blocks + j * sfx_blocks); base.eph_cnt[1] = Sfx; base.eph_pos0[1] = int32_t(n + P);
+                if (pack) {
+                    base.tok_period = Sfx; base.sub_blocks = (int32_t)sfx_blocks;
+                    base.q_tok0 = j * Sfx; base.n_tok = nq_tile * Sfx;
+                    g.tiles.push_back(base);
+                } else add_tiles(g, base, j * Sfx, Sfx);
+            }
+        };
+        // head_dim 64 packs where that is expected to end earlier: a tile walks the suffixes of all its questions, one after the
+        // other.  us per batch, one question a tile and packed: 8 questions of 32 tokens at 162 cached (8/8 heads) 31 and 48, 43 of 8 at
+        // 957 (32/8) 58 and 75; 5 of 8 behind a prefix of 16 at 1,550 51 and 47.  200 random batches against no packing: packed always
+        // 0.91 of the time, 50 more than 3 % slower and up to 56; by expected end 0.82, 4 more than 3 % slower, up to 14.
+        if (can_pack && list_narrow(p, groups[1].v)) {
+            ListGroup apart = groups[1], prefix = groups[0];
+            cut(apart, false);
+            cut(groups[1], true);
+            const size_t scatter = (sb[0].items.size() + sb[1].items.size()) * sizeof(sk_scatter);
+            ListGroup* const as_apart[2] = {&prefix, &apart};
+            ListGroup* const as_packed[2] = {&groups[0], &groups[1]};
+            const double packed_us = list_cost(p, as_packed, 2, scatter);
+            if (list_cost(p, as_apart, 2, scatter, packed_us) < packed_us) { groups[0].chunk = prefix.chunk; groups[1] = std::move(apart); }
+        } else cut(groups[1], can_pack);
     }
     ListPlan plan;
     rc = plan_list(p, sb, 2, groups, 2, plan);

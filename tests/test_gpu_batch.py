@@ -172,9 +172,10 @@ def test_shared_prefix_question_batch(n, P, NQ, Sfx):
     assert torch.equal(before, pool.kv_mem) and pool.sk_session_length(sid) == n
 
 
-@pytest.mark.parametrize("n,P,NQ,Sfx", [(700, 16, 6, 8), (0, 16, 9, 16), (330, 40, 3, 32), (65, 0, 5, 5)])
-def test_shared_prefix_question_batch_head_dim_64(n, P, NQ, Sfx):
-    """Questions of a head_dim 64 layer, packed into 256-row tiles where their rows allow it."""
+@pytest.mark.parametrize("n,P,NQ,Sfx,packed", [(700, 16, 6, 8, True), (0, 16, 9, 16, False), (330, 40, 3, 32, False), (65, 0, 5, 5, False),
+                                               (33, 16, 24, 16, True), (2000, 20, 9, 8, True)])
+def test_shared_prefix_question_batch_head_dim_64(n, P, NQ, Sfx, packed):
+    """Questions of a head_dim 64 layer, packed into 256-row tiles where their rows allow it and that is expected to end earlier."""
     shape = synth.Shape("bf16", 32, 8, 64)
     gen = synth.generator(5, stream=3000 + n + P)
     pool = sk.Pool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, 16, n // 16 + 8, max_sessions=1, kv_fill=0xFF)
@@ -190,6 +191,8 @@ def test_shared_prefix_question_batch_head_dim_64(n, P, NQ, Sfx):
     op, lp, os_, ls = pool.sk_session_query_shared_prefix(
         sid, dev(qp) if P else None, dev(kp) if P else None, dev(vp) if P else None,
         dev(r4(qs, shape.n_q_heads)), dev(r4(ks, shape.n_kv_heads)), dev(r4(vs, shape.n_kv_heads)))
+    tiles = -(-NQ * Sfx * 4 // 256) if packed else NQ * -(-Sfx * 4 // 128)
+    assert pool.sk_pool_last_launch()["row_tiles"] == tiles + -(-P * 4 // 128)
     rop, rlp, ros, rls = ref.query_shared_prefix(
         synth.to_raw(qp), synth.to_raw(kp), synth.to_raw(vp),
         synth.to_raw(qs).reshape(NQ, Sfx, shape.n_q_heads, -1), synth.to_raw(ks).reshape(NQ, Sfx, shape.n_kv_heads, -1),
@@ -199,7 +202,7 @@ def test_shared_prefix_question_batch_head_dim_64(n, P, NQ, Sfx):
     compare("suffix rows", os_, ls, ros.reshape(NQ * Sfx, shape.n_q_heads, -1), rls.reshape(NQ * Sfx, -1), shape.dtype)
 
 
-@pytest.mark.parametrize("n,P,NQ,Sfx", [(130, 20, 9, 8), (0, 16, 5, 16), (33, 0, 2, 32)])
+@pytest.mark.parametrize("n,P,NQ,Sfx", [(2000, 20, 9, 8), (2000, 16, 5, 16), (33, 16, 24, 16)])
 def test_infinite_value_of_one_question_stays_with_it_head_dim_64(n, P, NQ, Sfx):
     """Questions packed into 256-row tiles: an infinite value of one question's suffix is met by no row of another question,
     not even with a weight of 0."""
@@ -225,3 +228,27 @@ def test_infinite_value_of_one_question_stays_with_it_head_dim_64(n, P, NQ, Sfx)
     assert not torch.isfinite(b[2][hit, :, :, 7]).any()
     if P:
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("n,T,N,variant", [(304, 363, 3, 3), (888, 137, 12, 1), (90, 37, 12, 3)])
+def test_head_dim_64_steps_in_both_tile_heights(n, T, N, variant):
+    """A step's items of more than 128 rows go into tiles of 256 rows, or of 128 where the launches are expected to end earlier:
+    appends and both kinds of queries, beside an item of few rows."""
+    shape = synth.Shape("bf16", 32, 8, 64)
+    gen = synth.generator(4, stream=400 + T)
+    pool = sk.Pool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, 16, (N + 1) * ((n + T) // 16 + 2), max_sessions=N + 1,
+                   max_batch_tokens=2048, kv_fill=0xFF)
+    ref = oracle.OraclePool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim)
+    sids = [pool.sk_session_create() for _ in range(N + 1)]
+    for _ in sids:
+        ref.create()
+    _grow(pool, ref, sids, [n] * (N + 1), shape, gen)
+    ops = [(sk.SK_OP_APPEND, sk.SK_OP_QUERY_B, sk.SK_OP_QUERY_A)[i % 3] for i in range(N + 1)]
+    for counts in ([T] * N + [0], [T] * N + [5]):
+        cu = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+        q, k, v = synth.draw_qkv(gen, int(cu[-1]), shape)
+        out, lse = pool.sk_batch_step(sids, ops, cu, dev(q), dev(k), dev(v))
+        assert pool.sk_pool_last_launch()["kernel_variant"] == variant or counts[-1]
+        ro, rl = ref.batch_step(sids, ops, cu, synth.to_raw(q), synth.to_raw(k), synth.to_raw(v))
+        compare("step of %s" % counts, out, lse, ro, rl, shape.dtype)
+    _check_caches(pool, ref, sids)
