@@ -829,3 +829,31 @@ def test_one_cached_token_does_not_change_how_an_append_is_cut(hq, hkv, d, T):
         cut.append((geo["kernel_variant"], geo["row_tiles"], geo["n_splits"]))
         pool.sk_session_truncate(sid, 0)
     assert cut[0] == cut[1] == cut[2], cut
+
+
+@pytest.mark.parametrize("heads,n,splits", [(4096, 128, 2), (2048, 576, 9)])
+def test_combine_of_parts_beyond_32_bit_offsets(heads, n, splits):
+    """With thousands of KV heads the parts of a row lie so far apart that the combine kernel's round does not reach over eight, or
+    sixteen, of them within 32-bit offsets: it takes one part at a time, or two rounds of eight.  Against one part and, for some
+    heads, attention in float64."""
+    T, d = 130, 128
+    gen = torch.Generator(device="cuda").manual_seed(heads)
+    draw = lambda L: torch.randn((L, heads, d), generator=gen, device="cuda").to(torch.bfloat16)
+    pool = sk.Pool("bf16", heads, heads, d, 16, n // 16 + 8, max_sessions=1, max_batch_tokens=256 if splits == 2 else 1280)
+    sid = pool.sk_session_create()
+    k, v, q = draw(n), draw(n), draw(T)
+    for t in range(0, n, 256):
+        pool.sk_session_append(sid, None, k[t:t + 256], v[t:t + 256])
+    one = pool.sk_session_query(sid, q, n_splits=1)
+    assert pool.sk_pool_last_launch()["n_splits"] == 1
+    out, lse = pool.sk_session_query(sid, q, n_splits=splits)
+    geo = pool.sk_pool_last_launch()
+    assert geo["n_splits"] == splits, geo
+    step = heads * 256 * d * 4
+    assert geo["kernel_variant"] == 3 and (8 if splits == 2 else 16) * step >= 1 << 32
+    # two roundings of the weights to 16 bits, against other reference maxima: 2 x 2^-9 of the largest value's share of a row
+    assert float((out - one[0]).norm() / one[0].norm()) <= 2.0 ** -8 and float((lse - one[1]).abs().max()) <= 2e-5
+    for h in (0, heads // 2 + 1, heads - 1):
+        s = (q[:, h].double() @ k[:, h].double().t()) / d ** 0.5
+        ref = torch.softmax(s, 1) @ v[:, h].double()
+        compare("head %d" % h, out[:, h], lse[:, h], ref.cpu().numpy(), torch.logsumexp(s, 1).cpu().numpy(), "bf16")
