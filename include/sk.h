@@ -113,7 +113,8 @@ size_t sk_pool_workspace_bytes(const sk_pool_desc* desc);
  * device; zeroes nothing in kv_mem).  *out is NULL on error.
  * Tuning switches, read from the environment here and fixed for the life of the pool (none
  * changes a result beyond the rounding order of the split merge; they exist for sweeps):
- *   SK_TARGET_WGS=n    workgroups a single-session call is cut into (default: 256 or 512 by shape)
+ *   SK_TARGET_WGS=n    workgroups a single-session call is cut into (default: 256 or 512 by shape, calls in
+ *                      256-row tiles by the expected end of their launches)
  *   SK_FORCE_SIMPLE=1  bf16 pools: always the fp32-FMA attention kernel
  *   SK_NO_SMALL=1      never the kernel for calls of at most 32 query rows per KV head
  *   SK_SMALL_DISTRUST=n  tests: bit 0 set, in that kernel and the fp32 one the last workgroup of a row tile and KV

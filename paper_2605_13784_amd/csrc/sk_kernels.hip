@@ -206,7 +206,7 @@ __device__ __forceinline__ const unsigned char* sk_group_base(const sk_seg& g, i
 // others pstride rows apart):
 //   M = max_s m_s ; w_s = 2^(m_s - M) ; O = sum_s O_s w_s / sum_s l_s w_s ; LSE = (M + log2 sum_s lx_s w_s) ln 2
 // Lane s holds the statistics of splits s, s + 64, ..; every lane two output dimensions (one when
-// d = 64).  The splits are added in index order whoever does this (the combine kernel, sk_combine_row, or a
+// d = 64).  The splits are added in index order whoever does this (the combine kernel, or a
 // workgroup of the attention kernel, here), with explicit FMAs, so the result depends on the partials only.
 // Rows are read 16 splits at a time, the next ones requested before the current ones are used.  The partials were
 // written by other workgroups of the same launch (with write-through
@@ -294,7 +294,7 @@ __device__ __forceinline__ void sk_merge_row(const sk_launch& P, const size_t pr
 //
 // Keys move HBM -> LDS with direct-to-LDS loads (global_load_lds_dwordx4), never through
 // registers, into a ring of NSS iterations of two 32-key tiles (K 8 KiB + V^T 8 KiB each): 64 KiB
-// with two workgroups per CU, or 128 KiB with one.  One iteration consumes two tiles (64 keys:
+// with two workgroups per CU, or 128 KiB with one (half of each at head_dim 64).  One iteration consumes two tiles (64 keys:
 // both by every wave when NPH = 1, one per phase when NPH = 2) while the others are in flight,
 // which is what covers the HBM latency.  A direct-to-LDS load writes lane i's 16 bytes at
 // base + 16 i, so the bank swizzle is applied to the *source* address each lane picks:
@@ -465,9 +465,6 @@ __device__ __forceinline__ void sk_stage_own(const sk_launch& P, const sk_work& 
             make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
     }
     SK_WAIT_VMCNT(0);                                       // this wave's stores have completed (the barrier alone orders LDS)
-    // (with the wait one 64-byte line of instructions: the loops behind keep their places in the lines; four bytes off, a
-    // 50-token query of 32/8 heads of 64 dims at 60,000 cached takes 78.3 instead of 76.6 us)
-    asm volatile(".rept 15\n\ts_nop 0\n\t.endr");
     __syncthreads();                                        // so have the others'; LDS is free again
 }
 
@@ -849,10 +846,10 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // 1,200 cycles for 576 of matrix and 700 of vector instructions.  256 tokens of 32/8 heads at 32,512 cached, with the
             // combine and the commit kernel: 96.5 us with 128-row tiles of four waves that walk S, softmax and P V in turn, 88.4
             // with these; 512 at 130,560: 665 -> 618; the last ones of 2,600 into an empty session 63.4 -> 60.9.
-            constexpr int LPT = D / 64, LPW = 2 * LPT;      // direct-to-LDS loads per wave: of a tile's K (and V^T), per iteration
+            constexpr int LPW = 2;               // direct-to-LDS loads per wave and iteration: one of K, one of V^T
             constexpr int NP = 2 * NKS;          // matrix instructions of a stage
             constexpr int VP = 16 / NP;          // weights formed beside each
-            static_assert(NKS == 2 * NMT, "a stage has as many matrix instructions of either product");
+            static_assert(NKS == 4 && NMT == 2, "a stage has as many matrix instructions of either product; a tile is eight units, two loads of each of four waves");
             const int half = wave >> 2;
             const int n_iter = (g.end - g.begin + 2 * SK_TILE - 1) / (2 * SK_TILE);
             // Iterations that any row of this wave sees a key of.  In the others it loads its share of the tiles and computes
@@ -870,21 +867,14 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // block ids of the K tile loaded next and of the V tile, which is the K tile of the iteration before
             int t_k = g.begin + (half - 1) * SK_TILE;               // K tile -1 + half .. of "iteration -4"
             sk_tile_blocks kb = sk_lookup_tile<D>(g, t_k < g.begin ? g.begin : t_k, last_group, sub), vb = kb;
-            constexpr int LOG2_TOK_BYTES = D == 128 ? 8 : 7;
-            auto group_base = [&](const int t0, const sk_tile_blocks& tb, const int j) __attribute__((always_inline)) {
-                int tg = t0 + 16 * (D == 128 ? j : sub >> 1);
+            // a wave's load of the next K tile / V^T tile: unit `sub`, of group sub >> 1 (128 bytes per token for K and for V^T)
+            auto group_base = [&](const int t0, const sk_tile_blocks& tb) __attribute__((always_inline)) {
+                int tg = t0 + 16 * (sub >> 1);
                 tg = tg < last_group ? tg : last_group;
-                return g.base + ((uint64_t)tb.blk[j] << (g.log2B + LOG2_TOK_BYTES + 1)) + (((unsigned)tg & (unsigned)(g.B - 1)) << LOG2_TOK_BYTES);
+                return g.base + ((uint64_t)tb.blk[0] << (g.log2B + 8)) + (((unsigned)tg & (unsigned)(g.B - 1)) << 7);
             };
-            // load J of LPT of a wave for the next K tile / V^T tile
-            auto issue_k = [&](const unsigned slot_addr, auto j_const) __attribute__((always_inline)) {
-                constexpr int J = decltype(j_const)::value;
-                if (J < LPT) sk_dma16<J * 4 * US, false>(group_base(t_k, kb, J < LPT ? J : 0), koff, slot_addr);
-            };
-            auto issue_v = [&](const unsigned slot_addr, auto j_const) __attribute__((always_inline)) {
-                constexpr int J = decltype(j_const)::value;
-                if (J < LPT) sk_dma16<(NKS + J * 4) * US, false>(group_base(t_k - 2 * SK_TILE, vb, J < LPT ? J : 0), voff, slot_addr);
-            };
+            auto issue_k = [&](const unsigned slot_addr) __attribute__((always_inline)) { sk_dma16<0, false>(group_base(t_k, kb), koff, slot_addr); };
+            auto issue_v = [&](const unsigned slot_addr) __attribute__((always_inline)) { sk_dma16<NKS * US, false>(group_base(t_k - 2 * SK_TILE, vb), voff, slot_addr); };
             auto next_blocks = [&]() __attribute__((always_inline)) {
                 t_k += 2 * SK_TILE;
                 vb = kb;
@@ -892,15 +882,15 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             };
             auto slot_addr_of = [&](const int it) __attribute__((always_inline)) { return unit_base + (unsigned)((((it + 3) & 3) * 2 + half) * 1024); };
             // iterations -4 .. -1 (tiles in front of the segment are not loaded)
-            if (half == 1) { issue_k(slot_addr_of(-4), sk_int<0>{}); issue_k(slot_addr_of(-4), sk_int<1>{}); }
+            if (half == 1) issue_k(slot_addr_of(-4));
             next_blocks();
-            issue_k(slot_addr_of(-3), sk_int<0>{}); issue_k(slot_addr_of(-3), sk_int<1>{});
-            if (half == 1) { issue_v(slot_addr_of(-3), sk_int<0>{}); issue_v(slot_addr_of(-3), sk_int<1>{}); }
+            issue_k(slot_addr_of(-3));
+            if (half == 1) issue_v(slot_addr_of(-3));
 #pragma unroll
             for (int it = -2; it < 0; ++it) {
                 next_blocks();
-                issue_k(slot_addr_of(it), sk_int<0>{}); issue_k(slot_addr_of(it), sk_int<1>{});
-                issue_v(slot_addr_of(it), sk_int<0>{}); issue_v(slot_addr_of(it), sk_int<1>{});
+                issue_k(slot_addr_of(it));
+                issue_v(slot_addr_of(it));
             }
             next_blocks();
             await_query();
@@ -956,7 +946,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                     else {
                         const int t = p + 8 - NP, i = t >> 1;
                         if (HALF == 1) {
-                            if ((t & 1) == 0) { kc[i] += delta; if (i + 4 < NKS) kc[i + 4] += delta; }
+                            if ((t & 1) == 0) kc[i] += delta;
                             else if (i < NMT) vc[i] += delta;
                         }
                         op[p & 7] = ld_op(t, HALF == 0 ? 1024 : 0);
@@ -1009,8 +999,8 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // from.  The more keys it is taken from, the more often the row's largest weight is exactly 1 and not rounded: error
             // against 64 bits over the first tile alone and over two, 1,500 tokens of 32/8 heads into an empty session 1.30e-3 and
             // 1.27e-3, 300 behind 2,600 1.62e-3 and 1.60e-3, 256 behind 32,512 1.658e-3 and 1.656e-3.
-            if (half == 1) SK_WAIT_VMCNT(5 * LPT);
-            else SK_WAIT_VMCNT(4 * LPT);
+            if (half == 1) SK_WAIT_VMCNT(5);
+            else SK_WAIT_VMCNT(4);
             sk_lds_barrier();
             // K tile 0 lies in slot 7, tile 1 in slot 0 (a tile's K one slot below its number, its V one above)
             if (n_live > 0) {
@@ -1047,12 +1037,10 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 const unsigned sa = slot_addr_of(it);
                 const int delta = ((it + 1) & 3) == 0 ? -6 * 1024 : 2 * 1024;
                 stage(sk_int<0>{}, pv_const, 2 * it, delta, zero, sc[0], sc[1], pw[1], pw[0], [&](const int p) __attribute__((always_inline)) {
-                    if (p == 3) issue_k(sa, sk_int<0>{});
-                    if (p == NP - 5) issue_k(sa, sk_int<1>{});
+                    if (p == 3) issue_k(sa);
                 });
                 stage(sk_int<1>{}, sk_int<1>{}, 2 * it + 1, delta, zero, sc[1], sc[0], pw[0], pw[1], [&](const int p) __attribute__((always_inline)) {
-                    if (p == 3) issue_v(sa, sk_int<0>{});
-                    if (p == NP / 2) issue_v(sa, sk_int<1>{});
+                    if (p == 3) issue_v(sa);
                     if (p == NP - 3) next_blocks();
                 });
             };
@@ -1082,8 +1070,8 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             for (int it = n_live; it < n_iter; ++it) {          // the same loads, waits and barriers
                 begin_iteration();
                 const unsigned sa = slot_addr_of(it);
-                issue_k(sa, sk_int<0>{}); issue_k(sa, sk_int<1>{});
-                issue_v(sa, sk_int<0>{}); issue_v(sa, sk_int<1>{});
+                issue_k(sa);
+                issue_v(sa);
                 next_blocks();
             }
             SK_WAIT_VMCNT(0);                    // nothing is still on its way into the ring
@@ -1293,7 +1281,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     // A lane holds 4-float pieces of ONE row (its accumulators are O^T); written as they are, a store
     // instruction would touch 64 different 128-byte lines.  Each wave transposes its 32 x 128 tile in
     // 16 KiB of the (now idle) ring, XOR-swizzled by row so both directions are conflict-free (the
-    // ring holds one such tile per wave: 64 KiB for four waves, 128 KiB for eight).
+    // ring holds one such tile per wave: 64 KiB for four waves, 128 KiB for eight; half of that at head_dim 64).
     if (NPH == 1) __syncthreads();                    // every wave is done reading key tiles
     const bool direct = w.part < 0;
     if (NPH == 1 || ph == 0) {                        // with two key phases, phase 0 holds the merged rows
@@ -1407,7 +1395,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     }
 }
 
-// The kernels proper: head_dim 128 (all four instances) and head_dim 64 (the free-running ones).
+// The kernels proper: head_dim 128 (all four instances) and head_dim 64 (all but <4,2,2>).
 template <int NRG, int NPH, int NSS>
 __global__ __launch_bounds__(64 * NRG * NPH, NRG * NPH == 8 ? 1 : 2) void sk_attn_bf16_d128(const sk_launch P)
 {

@@ -253,8 +253,7 @@ bool prof_pair(sk_pool* p, int32_t call, int32_t kind, void** start, void** stop
 // Which attention kernel takes a tile of `max_rows` query rows per KV head.
 struct Variant { int id; int rows_per_slot; int tok_per_tile; };
 
-// `allow_256`: the caller can launch one workgroup per CU (single-session calls), which the
-// 256-row tile with its 128 KiB key ring needs.
+// `allow_256`: the caller can launch the 256-row tile, whose eight waves and key ring (128 KiB, 64 at head_dim 64) take a CU alone.
 // `cached` >= 0: a single-session call over so many cached tokens, which may take the kernel for at most 32 rows.  Up to
 // 128 MiB of cached K/V, where the ring kernel's stream gets close (us per cache-only query in a stream of them, ring and combine
 // kernel -> this one, one query token / 32 rows):
