@@ -116,8 +116,8 @@ def test_single_session_full_context(n, L, nq, n_rows, B):
 
 def test_head_dim_64_at_70000_cached_tokens():
     """A Llama-3.2-1B-shaped layer (32/8 heads, head_dim 64, bf16) at a length where the library takes
-    the launch configurations of the long caches (one workgroup per CU, the eight-wave 128-row instance,
-    non-temporal loads): a 256-token append, then 16-, 32- and 100-token queries on sampled rows."""
+    the launch configurations of the long caches (256-row tiles of eight waves, two workgroups per CU for the
+    smaller tiles, non-temporal loads): a 256-token append, then 16-, 32- and 100-token queries on sampled rows."""
     shape = synth.Shape("bf16", 32, 8, 64)
     n, L = 70000, 256
     gen = synth.generator(6, stream=21)
@@ -129,8 +129,8 @@ def test_head_dim_64_at_70000_cached_tokens():
     _build(pool, sid, ref, n - L, shape, gen)
     q, k, v = synth.draw_qkv(gen, L, shape)
     out, lse = pool.sk_session_append(sid, dev(q), dev(k), dev(v))
-    assert pool.sk_pool_last_launch()["kernel_variant"] != 0
-    rows = _sample_rows(rng, L, shape, extra=16, tile_rows=128)      # head_dim 64 has no 256-row tile
+    assert pool.sk_pool_last_launch()["kernel_variant"] == 3
+    rows = _sample_rows(rng, L, shape, extra=16)
     ro, rl = ref.append(synth.to_raw(q), synth.to_raw(k), synth.to_raw(v), rows=rows)
     _check_rows("append at %d" % (n - L), out, lse, rows, ro, rl, shape.dtype)
     for first in (0, n - 1024):
@@ -138,15 +138,17 @@ def test_head_dim_64_at_70000_cached_tokens():
         torch.cuda.synchronize()
         np.testing.assert_array_equal(synth.to_raw(kc.cpu()), ref.K[first:first + 1024])
         np.testing.assert_array_equal(synth.to_raw(vc.cpu()), ref.V[first:first + 1024])
-    for nq in (16, 32, 100):
+    for nq, variant in ((16, 2), (32, 1), (100, 3)):
         qq, kq, vq = synth.draw_qkv(gen, nq, shape)
-        rows = _sample_rows(rng, nq, shape, extra=4, tile_rows=min(128, _tile_rows(nq, shape)))
+        rows = _sample_rows(rng, nq, shape, extra=4)
         rows = [rows[i] for i in sorted(rng.choice(len(rows), size=min(16, len(rows)), replace=False))]
         out, lse = pool.sk_session_query(sid, dev(qq))
-        assert pool.sk_pool_last_launch()["workgroups"] >= 256
+        geo = pool.sk_pool_last_launch()
+        assert geo["workgroups"] >= (448 if variant != 3 else 192) and geo["kernel_variant"] == variant, geo
         ro, rl = ref.query(synth.to_raw(qq), rows=rows)
         _check_rows("query A, %d tokens" % nq, out, lse, rows, ro, rl, shape.dtype)
         out, lse = pool.sk_session_query(sid, dev(qq), dev(kq), dev(vq))
+        assert pool.sk_pool_last_launch()["kernel_variant"] == variant
         ro, rl = ref.query(synth.to_raw(qq), synth.to_raw(kq), synth.to_raw(vq), rows=rows)
         _check_rows("query B, %d tokens" % nq, out, lse, rows, ro, rl, shape.dtype)
 
