@@ -482,7 +482,7 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g, size_t other_bytes = 0,
     }
     for (int64_t k = 1; k <= 256; k += std::max<int64_t>(1, k / 4)) {
         const int64_t chunk = std::max<int64_t>(256, ((longest + k - 1) / k + 63) / 64 * 64);
-        if (chunk == last) break;
+        if (chunk == last) { if (chunk == 256) break; continue; }
         last = chunk;
         int64_t whole = 0, parts = 0, split = 0, its_sum = 0, its_max = 0, runs = 0;
         size_t count[9] = {};

@@ -230,6 +230,29 @@ def test_infinite_value_of_one_question_stays_with_it_head_dim_64(n, P, NQ, Sfx)
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
 
 
+def test_piece_lengths_behind_a_repeated_one_are_looked_at():
+    """The lengths a launch's tiles may be cut into are multiples of 64, at least 256: 3,143 keys in 10 pieces and in 12 are pieces of
+    320 keys both times, and the length chosen here, 256, comes behind them."""
+    shape = synth.Shape("bf16", 64, 8, 128)
+    n, P, NQ, Sfx = 3143, 16, 26, 16
+    gen = synth.generator(5, stream=3900)
+    pool = sk.Pool(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, 16, n // 16 + 8, max_sessions=1)
+    ref = oracle.OracleSession(shape.dtype, shape.n_q_heads, shape.n_kv_heads, shape.head_dim)
+    sid = pool.sk_session_create()
+    _, k, v = synth.draw_qkv(gen, n, shape)
+    pool.sk_session_append(sid, None, dev(k), dev(v))
+    ref.K, ref.V = synth.to_raw(k), synth.to_raw(v)
+    prefix = synth.draw_qkv(gen, P, shape)
+    suffix = [x.reshape(NQ, Sfx, x.shape[1], -1) for x in synth.draw_qkv(gen, NQ * Sfx, shape)]
+    op, lp, os_, ls = pool.sk_session_query_shared_prefix(sid, *(dev(x) for x in prefix), *(dev(x) for x in suffix))
+    geo = pool.sk_pool_last_launch()
+    assert geo["n_splits"] == -(-n // 256) and geo["workgroups"] == 8 * 3 * 13, geo
+    rop, rlp, ros, rls = ref.query_shared_prefix(*(synth.to_raw(x) for x in prefix), *(synth.to_raw(x) for x in suffix))
+    compare("prefix rows", op, lp, rop, rlp, shape.dtype)
+    compare("suffix rows", os_, ls, ros.reshape(NQ * Sfx, 64, -1), rls.reshape(NQ * Sfx, -1),
+            shape.dtype)
+
+
 @pytest.mark.parametrize("n,T,N,variant", [(304, 363, 3, 3), (888, 137, 12, 1), (90, 37, 12, 3)])
 def test_head_dim_64_steps_in_both_tile_heights(n, T, N, variant):
     """A step's items of more than 128 rows go into tiles of 256 rows, or of 128 where the launches are expected to end earlier:
