@@ -743,7 +743,7 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     // call).  Workgroups only wait for each other when the whole launch fits on the device at once (the
     // 256-row instance holds a CU alone, the others share it in pairs); otherwise the last workgroup of a
     // unit merges alone.  Not the default: a device-scope round trip (atomic, coherent load) measured about
-    // 3 us on this hardware and the scheme needs four in a row, against 6-7 us for the combine kernel.
+    // 3 us on this hardware and the scheme needs four in a row, against 4-7 us for the combine kernel.
     const bool mfma = v.id != SK_KV_SIMPLE;
     // A 128-row call that gives every CU at most one workgroup takes the eight-wave instance: two key
     // phases per row group, so a wave has half the arithmetic per 64 keys and its SIMD a second wave
