@@ -145,6 +145,7 @@ struct sk_launch {
     int32_t wait_polls;
     int32_t merge_fences;   // 1: full device-scope fences around the arrival (slow: an L2 walk each); 0: see the kernel
     sk_div by_heads, by_tiles, by_chunk;      // Hkv, n_tiles, chunk (regular mode)
+    sk_div by_step;         // interleaved splits: keys from one of a split's iterations to the next
     // single-session calls: the call's own tokens where the caller has them ([own_cnt][Hkv][d]).  sk_attn_bf16_small and
     // sk_attn_f32 attend to them there, as the last keys of the last part; the ring kernels stage them first, in the
     // workgroup of the own part (null: a launch in front has staged them).  Below, the small kernels' launch geometry.

@@ -92,9 +92,10 @@ __device__ __forceinline__ void sk_touch_arguments()
 // Work item of workgroup b.  Regular mode derives it from the launch parameters: consecutive
 // workgroups differ in KV head first (so with 8 KV heads a head stays on one XCD and its K/V
 // stay in that XCD's L2), then in row tile, then in split.
+template <bool MAY_BE_F32 = true>
 __device__ __forceinline__ int sk_tile_parts(const sk_launch& P, int tok0, int ntok, int* kv_vis_out)
 {
-    if (P.own_mode == SK_OWN_F32) {               // cached keys padded to whole 16-key tiles, then the call's own tokens
+    if (MAY_BE_F32 && P.own_mode == SK_OWN_F32) {               // cached keys padded to whole 16-key tiles, then the call's own tokens
         int own = P.own_cnt;
         if (P.pos0 < SK_NO_CAUSAL) own = tok0 + ntok < own ? tok0 + ntok : own;
         *kv_vis_out = ((P.kv_len + 15) & ~15) + own;
@@ -126,7 +127,7 @@ __device__ __forceinline__ bool sk_decode_work(const sk_launch& P, int b, sk_wor
     int tok0 = tile * P.tok_per_tile;
     int ntok = P.n_tok - tok0; ntok = ntok < P.tok_per_tile ? ntok : P.tok_per_tile;
     int kv_vis;
-    int np = sk_tile_parts(P, tok0, ntok, &kv_vis);
+    int np = sk_tile_parts<false>(P, tok0, ntok, &kv_vis);
     if (split >= np) return false;
     bool has_eph = (P.eph_cnt[0] > 0 || P.eph_cnt[1] > 0);
     bool eph_part = has_eph && (split == np - 1);
@@ -162,6 +163,7 @@ struct sk_seg {
     int32_t v_off, B, log2B;
     int32_t begin, end;          // token indices; begin is a multiple of 16
     int32_t step;                // iteration i covers the 64 keys from begin + i * step (64: one contiguous run)
+    int32_t iterations;
     int32_t pos_shift;           // absolute position = token index + pos_shift
     int32_t hole_lo, hole_n;     // tokens [hole_lo, hole_lo + hole_n) are evicted: streamed, never attended to
     int32_t once;                // 1: no other workgroup of the launch reads these keys (load them non-temporal)
@@ -178,6 +180,7 @@ __device__ __forceinline__ sk_seg sk_make_seg(const sk_launch& P, const sk_work&
         g.v_off = P.g.v_off; g.B = P.g.B; g.log2B = P.g.log2B;
         g.begin = w.kv_begin; g.end = w.kv_end; g.pos_shift = 0;
         g.step = w.kv_step > 0 ? w.kv_step : 64;
+        g.iterations = w.kv_step > 0 ? sk_divide(g.end - g.begin + w.kv_step - 1, P.by_step) : (g.end - g.begin + 63) >> 6;
         g.hole_lo = w.hole_lo; g.hole_n = w.hole_hi - w.hole_lo;
         g.once = P.kv_once;
     } else {
@@ -185,7 +188,7 @@ __device__ __forceinline__ sk_seg sk_make_seg(const sk_launch& P, const sk_work&
         g.table = P.g.eph_ident + (s == 1 ? w.eph_blk[0] : w.eph_blk[1] + (s - 2) * w.sub_blocks); g.blk_stride = P.g.eph_blk_stride;
         g.v_off = P.g.eph_v_off; g.B = 16; g.log2B = 4;
         g.begin = 0; g.end = (s == 1 ? w.eph_cnt[0] : w.eph_cnt[1]); g.pos_shift = (s == 1 ? w.eph_pos0[0] : w.eph_pos0[1]);
-        g.step = 64;
+        g.step = 64; g.iterations = (g.end + 63) >> 6;
         g.hole_lo = 0; g.hole_n = 0;
         g.once = 0;
     }
@@ -367,12 +370,12 @@ __device__ __forceinline__ void sk_dma16(const void* base, unsigned lane_off, un
 // 16-byte store that is written through to memory at once (cache policy "system coherent"), so that
 // the split partials never sit as dirty lines in one XCD's L2: the workgroups that merge them may run
 // on another XCD, and a release fence wide enough for that would have to walk the whole L2 for dirty
-// lines (measured: about 25 us per kernel).  Written as inline assembly (the compiler has no store
-// with these bits outside atomics), so the caller waits for it by hand (SK_WAIT_VMCNT(0)).
-__device__ __forceinline__ void sk_store16_through(float* p, const float4 v)
+// lines (measured: about 25 us per kernel).  Through a buffer resource, whose bounds drop what lies behind `bytes`: rows
+// that are not there need no branch.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t sk_bounded(float* base, const int bytes) { return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000); }
+__device__ __forceinline__ void sk_store16_through(const __amdgpu_buffer_rsrc_t to, const unsigned offset, const float4 v)
 {
-    const sk_f32x4 x = {v.x, v.y, v.z, v.w};
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" : : "v"(p), "v"(x) : "memory");
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sk_u32x4, v), to, offset, 0, 17);      // sc0 sc1
 }
 
 // Pool blocks holding the 16-key groups that wave `sub` loads of the tile that starts at key t0 (scalar loads): both, or with
@@ -390,6 +393,15 @@ __device__ __forceinline__ sk_tile_blocks sk_lookup_tile(const sk_seg& g, int t0
         b.blk[j] = (uint32_t)((const_i32_ptr)(uintptr_t)g.table)[(unsigned)tg >> g.log2B];
     }
     return b;
+}
+
+// Keeps a segment's first block ids together: looked up one by one, each in front of its loads, they are round trips one behind
+// the other (a table that this launch has not read yet: about 1 us each).
+template <int D>
+__device__ __forceinline__ void sk_together(const sk_tile_blocks& b)
+{
+#pragma unroll
+    for (int j = 0; j < D / 64; ++j) asm volatile("" : : "s"(b.blk[j]));
 }
 
 // Issues the four direct-to-LDS loads with which one of four waves contributes to one tile: a K
@@ -487,16 +499,17 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     constexpr int NLG = NW / 4;              // groups of four waves; each loads whole tiles
     static_assert(NW == 4 || ((LOCKSTEP || PIPELINED) && NSS == 4) || (NW == 8 && NPH == 2 && NSS == 2), "four waves, or eight as described");
     static_assert(NSS == 2 || NSS == 4, "ring depth in iterations: 64 KiB (two workgroups per CU) or 128 KiB (one)");
-    static_assert(NSS * TPI >= (NPH == 1 ? NW : NRG), "the epilogue transposes one 16 KiB tile per wave (per row group with two phases) in the ring");
     // The ring holds NSS iterations of TPI tiles.  Its 1 KiB units are interleaved: unit u of tile t
     // of ring slot s sits at (u * TPI * NSS + t * NSS + s) KiB, so that from a lane's per-unit base
     // address every tile of the ring is within reach of the 16-bit offset field of an LDS read.
     constexpr unsigned US = TPI * NSS * 1024;                 // bytes from unit u to unit u + 1
 #define SK_SLOT_OFF(s, t) (((t) * NSS + (s)) * 1024)          // tile t of ring slot s, relative to unit bases
-    // (with two key phases the merge of the phases needs 17 KiB per row group: 68 KiB for four row groups)
+    // The epilogue takes a 32 x D tile of floats per wave, which is more than the ring where two key phases share one; the
+    // phases' row statistics lie behind both.
     constexpr unsigned RING_BYTES = NSS * TPI * SK_TILE_BYTES * D / 128;
-    constexpr unsigned XCH_BYTES = NPH > 1 ? NRG * (4 * NMT + 1) * 64 * 16 : 0;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES];
+    constexpr unsigned XCH_BYTES = NW * 32 * D * 4;
+    constexpr unsigned STAT_BYTES = NPH > 1 ? NW * 32 * 16 : 0;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[(RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES) + STAT_BYTES];
 
     sk_touch_arguments<sizeof(sk_launch)>();
     sk_work w;
@@ -514,6 +527,72 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     const int lg = NLG == 1 ? 0 : (wave >> 2);                     // which tiles of an iteration this wave helps to load (free-running path)
     const int sub = wave & 3;
     const unsigned unit_base = lds_base + sub * US;                // LDS address of this wave's unit of ring slot 0, tile 0
+    const int half = PIPELINED ? (wave >> 2) : 0;
+
+    // The block ids a wave's first loads of a segment need, requested together: one by one, each in front of its loads, they
+    // are round trips one behind the other (about 1 us each where nobody has read the table yet).
+    constexpr int NPRE = PIPELINED ? 5 : LOCKSTEP ? 4 : NSS * (TPI / NLG);
+    sk_tile_blocks pre[NPRE];
+    auto look_up = [&](const sk_seg& g) __attribute__((always_inline)) {
+        const int last_group = g.end > 0 ? (g.end - 1) & ~15 : 0;
+#pragma unroll
+        for (int i = 0; i < NPRE; ++i) {
+            int t = PIPELINED ? g.begin + (half - 1 + 2 * i) * SK_TILE : LOCKSTEP ? g.begin + (1 - grp) * SK_TILE + i * g.step
+                              : g.begin + (i / (TPI / NLG)) * g.step + (NLG > 1 ? lg : i % TPI) * SK_TILE;
+            if (PIPELINED && i == 0) t = t > g.begin ? t : g.begin;
+            pre[i] = sk_lookup_tile<D>(g, t, last_group, sub);
+        }
+    };
+    // Lane-dependent parts of a wave's DMA source addresses in a segment
+    // (head_dim 64: lane -> (row rr of eight, chunk position of eight), source chunk (position ^ rr),
+    // the wave's rows and dims being those of unit sub & 1 of group sub >> 1).
+    const int krow = D == 128 ? sub * 4 + (lane >> 4) : (sub & 1) * 8 + (lane >> 3);
+    const unsigned koff = D == 128 ? (unsigned)(krow * 256 + (((lane & 15) ^ krow) << 4))
+                                   : (unsigned)(krow * 128 + (((lane & 7) ^ (krow & 7)) << 4));
+    const int vdd = (D == 128 ? sub : sub & 1) * 32 + (lane >> 1);
+    const unsigned voff0 = (unsigned)(vdd * 32 + ((((lane & 1) ^ ((vdd >> 3) & 1))) << 4));
+    // head_dim 64, 256-row tiles: a wave's load of the K tile / V^T tile at key t0: unit `sub`, of group sub >> 1 (128 bytes per token for
+    // K and for V^T), and the address of an iteration's ring slot
+    auto group_base = [&](const sk_seg& g, const int last_group, const int t0, const sk_tile_blocks& tb) __attribute__((always_inline)) {
+        int tg = t0 + 16 * (sub >> 1);
+        tg = tg < last_group ? tg : last_group;
+        return g.base + ((uint64_t)tb.blk[0] << (g.log2B + 8)) + (((unsigned)tg & (unsigned)(g.B - 1)) << 7);
+    };
+    auto slot_addr_of = [&](const int it) __attribute__((always_inline)) { return unit_base + (unsigned)((((it + 3) & 3) * 2 + half) * 1024); };
+    // A segment's first loads, those of the iterations in front of its loop (the loops say which): their block ids have arrived.
+    // The query operand has too: the compiler's wait for it, which does not know of these loads, would be one for all of
+    // them behind here, and drain the ring on every iteration inside a loop.
+    auto issue_first = [&](const sk_seg& g) __attribute__((always_inline)) {
+        const int last_group = (g.end - 1) & ~15;
+        const unsigned voff = (unsigned)g.v_off + voff0;
+        if constexpr (PIPELINED) {          // "iterations" -4 .. -1 (tiles in front of the segment are not loaded)
+#pragma unroll
+            for (int it = -4; it < 0; ++it) {
+                const int t_k = g.begin + (half + 2 * it + 7) * SK_TILE;
+                if (it > -4 || half == 1) sk_dma16<0, false>(group_base(g, last_group, t_k, pre[it + 4]), koff, slot_addr_of(it));
+                if (it > -3 || (it == -3 && half == 1)) sk_dma16<NKS * US, false>(group_base(g, last_group, t_k - 2 * SK_TILE, pre[it + 3]), voff, slot_addr_of(it));
+            }
+        } else if constexpr (LOCKSTEP) {    // iterations 0, 1 (group 1: and 2)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (i < 2 || grp == 1)
+                    sk_issue_tile<US, D, false>(g, g.begin + (1 - grp) * SK_TILE + i * g.step, last_group, pre[i], unit_base + SK_SLOT_OFF(i, 1 - grp), koff, voff, sub);
+        } else {                            // iterations 0 .. NSS - 2
+#pragma unroll
+            for (int a = 0; a < NSS - 1; ++a)
+                if (a < g.iterations) {
+#pragma unroll
+                    for (int p = 0; p < TPI; ++p) {
+                        if (NLG > 1 && (p % NLG) != lg) continue;
+                        sk_issue_tile<US, D, true>(g, g.begin + a * g.step + p * SK_TILE, last_group, pre[a * (TPI / NLG) + p / NLG], unit_base + SK_SLOT_OFF(a, p), koff, voff, sub);
+                    }
+                }
+        }
+    };
+    sk_seg g = sk_make_seg(P, w, 0);
+    look_up(g);
+    __builtin_amdgcn_sched_barrier(0);         // requested here, not behind the query operand's addresses
+
     const int r = lane & 31, kg = lane >> 5;
     // Row i of a tile is head i % G of token i / G (any group size up to 128; rows past the last
     // whole token of a tile are idle).  Rows are below 256, so the division is a multiplication by
@@ -525,6 +604,24 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     const int tok_local = div_g(row_in_tile);
     const int hq = w.kv_head * G + (row_in_tile - tok_local * G);
     const bool row_valid = tok_local < w.n_tok;
+
+    // Q^T operand: lane (row r, k-group kg) keeps Q[row][16*ks + 8*kg .. +7] for ks = 0..7.  It is on its way beside the block
+    // ids, and waited for with them, in front of the first loads into LDS: behind them the compiler's wait, which does not know of those,
+    // would be one for all of them.
+    bf16x8 qreg[NKS];
+    {
+        // Rows past the tile re-read its first token's head row; what they compute goes nowhere.
+        const uint4* qp = (const uint4*)((const unsigned char*)P.q +
+                          ((size_t)(w.q_tok0 + (row_valid ? tok_local : 0)) * P.g.Hq + hq) * (D * 2));
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[ks * 2 + kg]);
+    }
+#pragma unroll
+    for (int i = 0; i < NPRE; ++i) sk_together<D>(pre[i]);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) asm volatile("" : : "v"(qreg[ks]));
+    if (g.end > g.begin) issue_first(g);
+
     // positions of the first and last valid token of this wave (wave-uniform); with a group size that
     // does not divide 32 a token's rows can lie in two waves
     const int wave_tok_first = div_g(rg * 32);
@@ -536,23 +633,16 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     // the tile is token t % tok_period of sequence t / tok_period, all sequences start at pos0, and
     // each has its own second uncommitted segment.  A wave's rows belong to one sequence (the host
     // only packs when 32 rows divide a sequence's rows).
-    const unsigned period = w.tok_period > 0 ? (unsigned)w.tok_period : 0x7fffffffu;
-    const int n_sub = w.tok_period > 0 ? (w.n_tok + w.tok_period - 1) / w.tok_period : 1;
-    const int wave_sub = (int)((unsigned)wave_tok_first / period);
-    const int p_row = causal ? w.pos0 + (int)((unsigned)(row_valid ? tok_local : wave_tok_last) % period) : 0x7fffffff;
-    const int p_wave_min = causal ? w.pos0 + (int)((unsigned)wave_tok_first % period) : 0x7fffffff;
-    const int p_wave_max = causal ? w.pos0 + (int)((unsigned)wave_tok_last % period) : 0x7fffffff;
-
-    // Q^T operand: lane (row r, k-group kg) keeps Q[row][16*ks + 8*kg .. +7] for ks = 0..7
-    bf16x8 qreg[NKS];
-    {
-        // Rows past the tile re-read its first token's head row; what they compute goes nowhere.  Nothing here waits for
-        // the loads: the segment loop issues its own first.
-        const uint4* qp = (const uint4*)((const unsigned char*)P.q +
-                          ((size_t)(w.q_tok0 + (row_valid ? tok_local : 0)) * P.g.Hq + hq) * (D * 2));
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[ks * 2 + kg]);
+    int n_sub = 1, wave_sub = 0, t_row = row_valid ? tok_local : wave_tok_last, t_min = wave_tok_first, t_max = wave_tok_last;
+    if (w.tok_period > 0) {
+        const unsigned period = (unsigned)w.tok_period;
+        n_sub = (int)(((unsigned)w.n_tok + period - 1) / period);
+        wave_sub = (int)((unsigned)wave_tok_first / period);
+        t_row = (int)((unsigned)t_row % period); t_min = (int)((unsigned)t_min % period); t_max = (int)((unsigned)t_max % period);
     }
+    const int p_row = causal ? w.pos0 + t_row : 0x7fffffff;
+    const int p_wave_min = causal ? w.pos0 + t_min : 0x7fffffff;
+    const int p_wave_max = causal ? w.pos0 + t_max : 0x7fffffff;
 
     f32x16 oacc[NMT];
 #pragma unroll
@@ -584,9 +674,14 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
 
 #pragma unroll 1
     for (int s = 0; s < 2 + n_sub; ++s) {
-        sk_seg g = sk_make_seg(P, w, s);
+        if (s > 0) g = sk_make_seg(P, w, s);
         if (g.end <= g.begin) continue;
-        const int niter = (g.end - g.begin + g.step - 1) / g.step;      // iteration i: keys from g.begin + i * g.step
+        if (s > 0) {
+            sk_lds_barrier();                  // ring free (previous segment fully consumed)
+            look_up(g);
+            issue_first(g);
+        }
+        const int niter = g.iterations;          // iteration i: keys from g.begin + i * g.step
         const int last_group = (g.end - 1) & ~15;
         // last position of the segment this wave's rows may see; nothing of another sequence's segment
         const int seg_last_pos = (s >= 2 && s - 2 != wave_sub) ? (int)0x80000000 : g.end - 1 + g.pos_shift;
@@ -594,14 +689,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
         const int lim_wave_max = p_wave_max < seg_last_pos ? p_wave_max : seg_last_pos;
         const int lim_row = p_row < seg_last_pos ? p_row : seg_last_pos;
 
-        // lane-dependent parts of the DMA source addresses for this segment
-        // (head_dim 64: lane -> (row rr of eight, chunk position of eight), source chunk (position ^ rr),
-        // the wave's rows and dims being those of unit sub & 1 of group sub >> 1)
-        const int krow = D == 128 ? sub * 4 + (lane >> 4) : (sub & 1) * 8 + (lane >> 3);
-        const unsigned koff = D == 128 ? (unsigned)(krow * 256 + (((lane & 15) ^ krow) << 4))
-                                       : (unsigned)(krow * 128 + (((lane & 7) ^ (krow & 7)) << 4));
-        const int vdd = (D == 128 ? sub : sub & 1) * 32 + (lane >> 1);
-        const unsigned voff = (unsigned)(g.v_off + vdd * 32 + ((((lane & 1) ^ ((vdd >> 3) & 1))) << 4));
+        const unsigned voff = (unsigned)g.v_off + voff0;
 
         // ---- the three steps of one iteration (64 keys) for this wave; the ring slot is a
         // compile-time constant so that it folds into the offset field of the LDS instructions ----
@@ -752,39 +840,15 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                 }
         };
 
-        sk_lds_barrier();                      // ring free (previous segment fully consumed)
-        // The query operand must have arrived before the loop (a wait for it placed by the compiler inside
-        // the loop would drain the ring on every iteration), but the first tiles are requested before it is
-        // waited for.
-        auto await_query = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) asm volatile("" : : "v"(qreg[ks]));
-        };
-
         if constexpr (!LOCKSTEP && !PIPELINED) {
             // ---- free-running waves: every wave walks S, softmax, PV of an iteration in turn; overlap of
             // matrix and vector work comes from the other wave of the SIMD (the other workgroup on the
             // CU for the four-wave instances, the other key phase for the eight-wave one) ----
             constexpr int LPW = 4 * TPI / NLG;   // direct-to-LDS loads per wave per iteration (tile p is loaded by wave group p % NLG)
-            // prologue: iterations 0 .. NSS-2
-#pragma unroll
-            for (int a = 0; a < NSS - 1; ++a) {
-                if (a < niter) {
-#pragma unroll
-                    for (int p = 0; p < TPI; ++p) {
-                        if (NLG > 1 && (p % NLG) != lg) continue;
-                        const int t0 = g.begin + a * g.step + p * SK_TILE;
-                        const sk_tile_blocks tb = sk_lookup_tile<D>(g, t0, last_group, sub);
-                        sk_issue_tile<US, D, true>(g, t0, last_group, tb, unit_base + SK_SLOT_OFF(a, p), koff, voff, sub);
-                    }
-                }
-            }
-            await_query();
             // block ids of the next refill are looked up one iteration ahead of their use
             sk_tile_blocks nb[TPI];
 #pragma unroll
-            for (int p = 0; p < TPI; ++p)
-                nb[p] = sk_lookup_tile<D>(g, g.begin + (NSS - 1) * g.step + p * SK_TILE, last_group, sub);
+            for (int p = 0; p < TPI; ++p) nb[p] = pre[(NSS - 1) * (TPI / NLG) + p / NLG];
 
             // `slot` is the ring slot the iteration reads; the slot read by the previous iteration is
             // refilled with iteration it + NSS - 1.  With the two-slot ring the loop is unrolled over the
@@ -810,7 +874,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
                     if (it + NSS < niter) {
 #pragma unroll
                         for (int p = 0; p < TPI; ++p)
-                            nb[p] = sk_lookup_tile<D>(g, g.begin + (it + NSS) * g.step + p * SK_TILE, last_group, sub);
+                            nb[p] = sk_lookup_tile<D>(g, g.begin + (it + NSS) * g.step + (NLG > 1 ? lg : p) * SK_TILE, last_group, sub);
                     }
                 }
                 if (!is_active(it)) return;
@@ -850,8 +914,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             constexpr int NP = 2 * NKS;          // matrix instructions of a stage
             constexpr int VP = 16 / NP;          // weights formed beside each
             static_assert(NKS == 4 && NMT == 2, "a stage has as many matrix instructions of either product; a tile is eight units, two loads of each of four waves");
-            const int half = wave >> 2;
-            const int n_iter = (g.end - g.begin + 2 * SK_TILE - 1) / (2 * SK_TILE);
+            const int n_iter = niter;
             // Iterations that any row of this wave sees a key of.  In the others it loads its share of the tiles and computes
             // nothing: a weight of 0 times an infinite value would be NaN, and reach rows of questions and of tokens that lie in
             // front of that value (the 32 keys of one tile, and the two tiles of an iteration, are not told apart).
@@ -865,35 +928,15 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             sk_u32x4 op[8];
 
             // block ids of the K tile loaded next and of the V tile, which is the K tile of the iteration before
-            int t_k = g.begin + (half - 1) * SK_TILE;               // K tile -1 + half .. of "iteration -4"
-            sk_tile_blocks kb = sk_lookup_tile<D>(g, t_k < g.begin ? g.begin : t_k, last_group, sub), vb = kb;
-            // a wave's load of the next K tile / V^T tile: unit `sub`, of group sub >> 1 (128 bytes per token for K and for V^T)
-            auto group_base = [&](const int t0, const sk_tile_blocks& tb) __attribute__((always_inline)) {
-                int tg = t0 + 16 * (sub >> 1);
-                tg = tg < last_group ? tg : last_group;
-                return g.base + ((uint64_t)tb.blk[0] << (g.log2B + 8)) + (((unsigned)tg & (unsigned)(g.B - 1)) << 7);
-            };
-            auto issue_k = [&](const unsigned slot_addr) __attribute__((always_inline)) { sk_dma16<0, false>(group_base(t_k, kb), koff, slot_addr); };
-            auto issue_v = [&](const unsigned slot_addr) __attribute__((always_inline)) { sk_dma16<NKS * US, false>(group_base(t_k - 2 * SK_TILE, vb), voff, slot_addr); };
+            int t_k = g.begin + (half + 7) * SK_TILE;
+            sk_tile_blocks kb = pre[4], vb = pre[3];
+            auto issue_k = [&](const unsigned slot_addr) __attribute__((always_inline)) { sk_dma16<0, false>(group_base(g, last_group, t_k, kb), koff, slot_addr); };
+            auto issue_v = [&](const unsigned slot_addr) __attribute__((always_inline)) { sk_dma16<NKS * US, false>(group_base(g, last_group, t_k - 2 * SK_TILE, vb), voff, slot_addr); };
             auto next_blocks = [&]() __attribute__((always_inline)) {
                 t_k += 2 * SK_TILE;
                 vb = kb;
                 kb = sk_lookup_tile<D>(g, t_k, last_group, sub);
             };
-            auto slot_addr_of = [&](const int it) __attribute__((always_inline)) { return unit_base + (unsigned)((((it + 3) & 3) * 2 + half) * 1024); };
-            // iterations -4 .. -1 (tiles in front of the segment are not loaded)
-            if (half == 1) issue_k(slot_addr_of(-4));
-            next_blocks();
-            issue_k(slot_addr_of(-3));
-            if (half == 1) issue_v(slot_addr_of(-3));
-#pragma unroll
-            for (int it = -2; it < 0; ++it) {
-                next_blocks();
-                issue_k(slot_addr_of(it));
-                issue_v(slot_addr_of(it));
-            }
-            next_blocks();
-            await_query();
 
             // tiles that need a mask
             const int last_0 = g.begin + g.pos_shift + SK_TILE - 1;             // last position of tile 0
@@ -1101,20 +1144,16 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // 512 at 130,560 run at 1.18-1.22 where the bare matrix loop holds 1.85 and a library product of 8192^3 1.41.
             constexpr int LPW = 4;               // direct-to-LDS loads per wave per iteration (one tile)
             const int my_tile = 1 - grp;
-            const int ahead = 2 + grp;           // iterations loaded before the loop
+            const int ahead = 2 + grp;           // iterations loaded before the loop (issue_first)
             // Loads are issued for `ahead` iterations past the end too (they re-read the segment's last
             // group and nothing reads them), so that the number of loads in flight at each wait is a constant.
-            int t_next = g.begin + my_tile * SK_TILE;
-            sk_tile_blocks nb = sk_lookup_tile<D>(g, t_next, last_group, sub);
+            int t_next = g.begin + my_tile * SK_TILE + ahead * g.step;
+            sk_tile_blocks nb = grp == 1 ? pre[3] : pre[2];
             auto issue_next = [&](const int slot) __attribute__((always_inline)) {
                 sk_issue_tile<US, D, false>(g, t_next, last_group, nb, unit_base + SK_SLOT_OFF(slot, my_tile), koff, voff, sub);
                 t_next += g.step;
                 nb = sk_lookup_tile<D>(g, t_next, last_group, sub);
             };
-            issue_next(0);
-            issue_next(1);
-            if (grp == 1) issue_next(2);
-            await_query();
             SK_WAIT_VMCNT(LPW);                  // iteration 0 has landed (group 1: and iteration 1)
             if (grp == 1) sk_lds_barrier();      // group 1 stays one barrier behind
             // Matrix slot: eight groups of four matrix instructions, P V of the previous iteration
@@ -1240,89 +1279,89 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     float l_tot; { const sk_halves h = sk_both_halves(l_acc[0]); l_tot = h.lo + h.hi; }
     float lx_tot; { const sk_halves h = sk_both_halves(lx_run); lx_tot = h.lo + h.hi; }
 
-    if (NPH > 1) {
-        // merge the key phases of each row group through LDS: per row group 17 x 64 float4 (lane-major, so a
-        // wave's 16-byte accesses are conflict-free): entries 0..15 the accumulators, entry 16 = (m, l, lx, -)
-        __syncthreads();                                  // every wave is done reading key tiles
-        float4* xch = (float4*)lds + rg * ((4 * NMT + 1) * 64) + lane;
-        if (ph == 1) {
-#pragma unroll
-            for (int mt = 0; mt < NMT; ++mt)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    xch[(mt * 4 + q4) * 64] = make_float4(oacc[mt][q4 * 4 + 0], oacc[mt][q4 * 4 + 1], oacc[mt][q4 * 4 + 2], oacc[mt][q4 * 4 + 3]);
-            xch[4 * NMT * 64] = make_float4(m_ref, l_tot, lx_tot, 0.f);
-        }
-        __syncthreads();
-        if (ph == 0) {
-            const float4 s1 = xch[4 * NMT * 64];
-            const float m1 = s1.x, l1 = s1.y, lx1 = s1.z;
-            const float M = fmaxf(m_ref, m1);
-            const float a0 = (m_ref == SK_NEG_INF) ? 0.f : sk_exp2(m_ref - M);
-            const float a1 = (m1 == SK_NEG_INF) ? 0.f : sk_exp2(m1 - M);
-#pragma unroll
-            for (int mt = 0; mt < NMT; ++mt)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const float4 x = xch[(mt * 4 + q4) * 64];
-                    oacc[mt][q4 * 4 + 0] = oacc[mt][q4 * 4 + 0] * a0 + x.x * a1;
-                    oacc[mt][q4 * 4 + 1] = oacc[mt][q4 * 4 + 1] * a0 + x.y * a1;
-                    oacc[mt][q4 * 4 + 2] = oacc[mt][q4 * 4 + 2] * a0 + x.z * a1;
-                    oacc[mt][q4 * 4 + 3] = oacc[mt][q4 * 4 + 3] * a0 + x.w * a1;
-                }
-            l_tot = l_tot * a0 + l1 * a1;
-            lx_tot = lx_tot * a0 + lx1 * a1;
-            m_ref = M;
-        }
-        __syncthreads();                                  // the exchange area is read; the transposes reuse it
-    }
-
     // ---- epilogue: rows go out through LDS so that every store instruction writes whole rows ----
     // A lane holds 4-float pieces of ONE row (its accumulators are O^T); written as they are, a store
-    // instruction would touch 64 different 128-byte lines.  Each wave transposes its 32 x 128 tile in
-    // 16 KiB of the (now idle) ring, XOR-swizzled by row so both directions are conflict-free (the
-    // ring holds one such tile per wave: 64 KiB for four waves, 128 KiB for eight; half of that at head_dim 64).
-    if (NPH == 1) __syncthreads();                    // every wave is done reading key tiles
+    // instruction would touch 64 different 128-byte lines.  Each wave writes its 32 x D tile to LDS (the ring is
+    // idle by then), XOR-swizzled by row so both directions are conflict-free.  With two key phases the waves first tell each
+    // other their reference maxima, scale by them, and the rows of both are added on the way out: every wave stores half of
+    // its row group's rows.
+    // Bound: round trips of a wave to LDS.  The values of a batch of stores are read before the first of them goes out: the
+    // stores (volatile) keep their order, and with each read in front of its store that was 16 round trips, 1.8 us of a
+    // workgroup; the phases merged in registers by half of the waves, and only those storing, took another 1.8.
     const bool direct = w.part < 0;
-    if (NPH == 1 || ph == 0) {                        // with two key phases, phase 0 holds the merged rows
-        const float inv = direct ? 1.0f / l_tot : 1.0f;
-        float* tr = (float*)lds + (NPH == 1 ? wave : rg) * (32 * D);
+    const int nrows = w.n_tok * G;
+    float factor = 1.0f;
+    constexpr unsigned STATS = RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES;         // behind the ring: it may still be read
+    if (NPH > 1) {
+        float4* stat = (float4*)(lds + STATS) + (ph * NRG + rg) * 32 + r;
+        if (kg == 0) *stat = make_float4(m_ref, l_tot, lx_tot, 0.f);
+        __syncthreads();                              // every wave is done reading key tiles, and has written its statistics
+        const float4 other = *((const float4*)(lds + STATS) + ((ph ^ 1) * NRG + rg) * 32 + r);
+        const float M = fmaxf(m_ref, other.x);
+        const float a_own = (m_ref == SK_NEG_INF) ? 0.f : sk_exp2(m_ref - M);
+        const float a_other = (other.x == SK_NEG_INF) ? 0.f : sk_exp2(other.x - M);
+        factor = a_own;
+        l_tot = l_tot * a_own + other.y * a_other;
+        lx_tot = lx_tot * a_own + other.z * a_other;
+        m_ref = M;
+    } else __syncthreads();                           // every wave is done reading key tiles
+    if (direct) factor *= 1.0f / l_tot;
+    {
+        float* tr = (float*)lds + wave * (32 * D);
 #pragma unroll
         for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
                 const int c4 = mt * 8 + q4 * 2 + kg;
                 *(float4*)(tr + r * D + ((c4 ^ r) & (D / 4 - 1)) * 4) =
-                    make_float4(oacc[mt][q4 * 4 + 0] * inv, oacc[mt][q4 * 4 + 1] * inv, oacc[mt][q4 * 4 + 2] * inv, oacc[mt][q4 * 4 + 3] * inv);
+                    make_float4(oacc[mt][q4 * 4 + 0] * factor, oacc[mt][q4 * 4 + 1] * factor, oacc[mt][q4 * 4 + 2] * factor, oacc[mt][q4 * 4 + 3] * factor);
             }
         const size_t orow_lane = ((size_t)(w.q_tok0 + tok_local) * P.g.Hq + hq);
-        if (row_valid && kg == 0) {
+        if (row_valid && kg == 0 && ph == 0) {
             if (direct) { if (P.lse) P.lse[orow_lane] = (m_ref + sk_log2(lx_tot)) * SK_LN2; }
-            else sk_store16_through(P.part_ml + ((size_t)w.part * P.rows_per_slot + row_in_tile) * 4, make_float4(m_ref, l_tot, lx_tot, 0.f));
+            else sk_store16_through(sk_bounded(P.part_ml + (size_t)w.part * P.rows_per_slot * 4, nrows * 16), row_in_tile * 16, make_float4(m_ref, l_tot, lx_tot, 0.f));
         }
+    }
+    if (NPH > 1) __syncthreads();                     // the other phase's rows are there too
+    {
         // a row is D / 4 chunks of four floats: a store instruction writes two rows (four at head_dim 64)
-        constexpr int CPR = D / 4, RPI = 64 / CPR, NIT = 32 / RPI;
+        constexpr int CPR = D / 4, RPI = 64 / CPR, ROWS = 32 / NPH, NIT = ROWS / RPI, BATCH = NIT < 8 ? NIT : 8;
         const int c4 = lane & (CPR - 1);
+        const float* tr = (const float*)lds + rg * (32 * D);
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
+        for (int b0 = 0; b0 < NIT; b0 += BATCH) {
             // the row order is rotated by the workgroup index: workgroups that finish together (short
             // contexts) would otherwise all write the same offset of their partial slots, which lie a
             // power of two apart, at the same time, and crowd onto a few memory channels
-            const int row = ((it + blockIdx.x) & (NIT - 1)) * RPI + lane / CPR;
-            const float4 val = *(const float4*)(tr + row * D + ((c4 ^ row) & (D / 4 - 1)) * 4);
-            const int rit = rg * 32 + row;                 // row inside the tile
-            const int tok2 = div_g(rit);
-            if (tok2 >= w.n_tok) continue;
-            if (direct) {
+            auto row_of = [&](const int i) __attribute__((always_inline)) { return ph * ROWS + ((b0 + i + (int)blockIdx.x) & (NIT - 1)) * RPI + lane / CPR; };
+            float4 val[BATCH];
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int row = row_of(i), at = row * D + ((c4 ^ row) & (D / 4 - 1)) * 4;
+                val[i] = *(const float4*)(tr + at);
+                if (NPH > 1) {
+                    const float4 y = *(const float4*)(tr + NRG * 32 * D + at);
+                    val[i].x += y.x; val[i].y += y.y; val[i].z += y.z; val[i].w += y.w;
+                }
+            }
+            if (!direct) {
+                const __amdgpu_buffer_rsrc_t to = sk_bounded(P.part_o + (size_t)w.part * P.rows_per_slot * D, nrows * D * 4);
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) sk_store16_through(to, (unsigned)(rg * 32 + row_of(i)) * (D * 4) + c4 * 16, val[i]);
+                continue;
+            }
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int rit = rg * 32 + row_of(i);           // row inside the tile
+                if (rit >= nrows) continue;
+                const int tok2 = div_g(rit);
                 const size_t orow = ((size_t)(w.q_tok0 + tok2) * P.g.Hq + w.kv_head * G + (rit - tok2 * G));
-                if (P.out_dtype == 0) *(float4*)((float*)P.out + orow * D + c4 * 4) = val;
+                if (P.out_dtype == 0) *(float4*)((float*)P.out + orow * D + c4 * 4) = val[i];
                 else {
-                    const uint32_t lo = f32_to_bf16_bits(val.x) | ((uint32_t)f32_to_bf16_bits(val.y) << 16);
-                    const uint32_t hi = f32_to_bf16_bits(val.z) | ((uint32_t)f32_to_bf16_bits(val.w) << 16);
+                    const uint32_t lo = f32_to_bf16_bits(val[i].x) | ((uint32_t)f32_to_bf16_bits(val[i].y) << 16);
+                    const uint32_t hi = f32_to_bf16_bits(val[i].z) | ((uint32_t)f32_to_bf16_bits(val[i].w) << 16);
                     *(uint2*)((uint16_t*)P.out + orow * D + c4 * 4) = make_uint2(lo, hi);
                 }
-            } else {
-                sk_store16_through(P.part_o + ((size_t)w.part * P.rows_per_slot + rit) * D + c4 * 4, val);
             }
         }
     }
@@ -1373,7 +1412,6 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     __syncthreads();
     const int state = *flag;
     if (state != 0) {
-        const int nrows = w.n_tok * G;
         const int rps = (nrows + w.n_parts - 1) / w.n_parts;
         const int k_own = (w.part - w.part0) / P.g.Hkv;
         const int k_lo = state == 2 ? 0 : k_own, k_hi = state == 2 ? w.n_parts : k_own + 1;
@@ -2163,6 +2201,10 @@ __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
 // Cross-split combine: one wave per output row.
 //   M = max_s m_s ; L = sum_s l_s 2^(m_s - M) ; O = sum_s O_s 2^(m_s - M) / L
 //   LSE = (M + log2 sum_s lx_s 2^(m_s - M)) ln 2       (lx: the row sums before bf16 rounding)
+// A row tile and KV head's workgroups lie as many apart as there are of those, as the attention kernel's do: where that is a
+// multiple of 8 both run on one XCD.  On another, the lines of the parts stay behind in its L2, and the next call's stores to the same slots
+// wait for them to be taken back there (128 rows, 33 to 134 MB of keys loaded non-temporal, which do not push them out: 6 us
+// a call, 24.5 -> 18.1 at 14,800 cached tokens, 34.8 -> 28.4 at 32,768).
 // The parts of a round (R of them) are requested at once, beside the statistics: buffer loads return zeros behind the
 // last part, so no branch stands between the loads.  R is the smallest of 8, 16 and 32 that takes the launch's parts in one
 // round (kernels of few registers for launches of few parts: more rows in flight), 1 where a round would reach beyond
@@ -2178,9 +2220,8 @@ template <int D, int R>
 __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
 {
     sk_touch_arguments<sizeof(sk_launch)>();
-    const int groups_per_tile = P.rows_per_slot >> 2;
-    const int item = blockIdx.x / groups_per_tile;
-    const int row = (blockIdx.x % groups_per_tile) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int item = blockIdx.x;                  // row tile and KV head
+    const int row = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     sk_comb cb;
     if (P.mode == SK_MODE_LIST) cb = P.comb[item];
@@ -2465,7 +2506,7 @@ int sk_launch_combine(const sk_launch& L, int32_t n_row_tiles, int32_t max_parts
 {
     if (n_row_tiles <= 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid(n_row_tiles * (L.rows_per_slot >> 2)), block(256);
+    const dim3 grid(n_row_tiles, L.rows_per_slot >> 2), block(256);
     const int64_t step = part_stride * L.rows_per_slot * L.g.d * 4;
     int round = max_parts <= 8 ? 8 : max_parts <= 16 ? 16 : 32;
     while (round > 1 && round * step >= (int64_t(1) << 32)) round = round > 8 ? round / 2 : 1;

@@ -738,6 +738,7 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     // 2-3 % slower for the 128-row instance, which keeps contiguous chunks.  Larger blocks gain more
     // (16 tokens at 128K: 98 / 96 / 92 us with 16- / 64- / 256-token blocks).
     L.interleave = (!p->no_interleave && v.id == SK_KV_MFMA64 && S > 1 && kv_len <= (int64_t)pos0) ? 1 : 0;
+    L.by_step = sk_make_div((uint32_t)(S * 64));
     R.base_wgs = (int32_t)base_wgs; R.parts = (int32_t)parts; R.wgs = int32_t(base_wgs * parts); R.kv_len = kv_len;
     // On request (SK_FUSE=1) the ring kernels merge their split partials themselves (one launch per
     // call).  Workgroups only wait for each other when the whole launch fits on the device at once (the
