@@ -128,10 +128,10 @@ size_t sk_pool_workspace_bytes(const sk_pool_desc* desc);
  *   SK_P128_MIN_TOKENS=n  cached tokens from which a single-session call of 65-128 rows takes that
  *                      instance (default: where its workgroups have 512 keys and more; below, its
  *                      longer start outweighs the gain)
- *   SK_NO_STREAM_LOADS=1  calls with one row tile per KV head load the cache with the default cache
- *                      policy instead of non-temporal
- *   SK_STREAM_MIN_TOKENS=n  cached tokens from which the 128-row instances do so (default 65536;
- *                      the 64-row instance always does)
+ *   SK_NO_STREAM_LOADS=1  calls (and items of a batched step) with one row tile per KV head load the cache with the
+ *                      default cache policy instead of non-temporal
+ *   SK_STREAM_MIN_TOKENS=n  cached tokens from which the 128-row instances do so (default: where the call reads
+ *                      88 MiB of K/V and more; the 64-row instance always does)
  *   SK_FUSE=1          single-session calls of the ring kernels (more than 32 rows per KV head, or more than 128 MiB
  *                      of cached K/V) merge their split partials inside the attention kernel
  *                      instead of in a second kernel (one launch per call; measured slower on

@@ -60,7 +60,8 @@ struct sk_work {
     int32_t hole_hi;      // blocks are still streamed, the keys never attended to; empty when lo == hi
     int32_t tok_period;   // > 0: the tile packs sequences of tok_period tokens each, all starting at pos0;
     int32_t sub_blocks;   // sequence k's second uncommitted segment starts at staging block eph_blk[1] + k * sub_blocks
-    int32_t kv_step;      // keys from one 64-key iteration over [kv_begin, kv_end) to the next; 0 = 64 (contiguous)
+    uint32_t kv_step : 31;   // keys from one 64-key iteration over [kv_begin, kv_end) to the next; 0 = 64 (contiguous)
+    uint32_t once : 1;       // no other workgroup of the launch reads these cached keys (loaded non-temporal)
     // in-kernel merge of the split partials (part >= 0 and sk_launch::fuse): the workgroups of one
     // (row tile, KV head) are a unit; its partial slots are part0, part0 + Hkv, .. (n_parts of them)
     int32_t unit;         // index of the unit's pair of counters in sk_launch::sync
@@ -156,7 +157,7 @@ struct sk_launch {
     int32_t head_pad;       // workgroups from one part to the next of its unit (row tile x KV head): the units, padded to a multiple of 8 if merged
     sk_div by_pad;
     int32_t distrust;       // tests: bit 0, treat the parts as run on several XCDs (the last one computes them all); bit 1, leave the rows unwritten then
-    int32_t kv_once;        // 1: every key is read by exactly one workgroup of the launch (loaded non-temporal)
+    int32_t kv_once;        // regular mode: sk_work::once
 };
 
 // The commit of a small append, done by workgroups first_wg, first_wg + 1, .. of its attention launch.

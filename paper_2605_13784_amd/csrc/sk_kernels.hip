@@ -146,7 +146,7 @@ __device__ __forceinline__ bool sk_decode_work(const sk_launch& P, int b, sk_wor
     w.part = np == 1 ? -1 : (tile * P.n_splits + split) * Hkv + head;         // a tile of one part is written directly
     w.unit = tile * Hkv + head; w.part0 = tile * P.n_splits * Hkv + head; w.n_parts = np;
     w.hole_lo = P.hole_lo; w.hole_hi = P.hole_hi;
-    w.tok_period = 0; w.sub_blocks = 0;
+    w.tok_period = 0; w.sub_blocks = 0; w.once = P.kv_once;
     for (int i = 0; i < 2; ++i) {
         w.eph_blk[i] = P.eph_blk[i]; w.eph_cnt[i] = eph_part ? P.eph_cnt[i] : 0; w.eph_pos0[i] = P.eph_pos0[i];
     }
@@ -179,10 +179,10 @@ __device__ __forceinline__ sk_seg sk_make_seg(const sk_launch& P, const sk_work&
         g.table = P.g.tables + w.tbl_off; g.blk_stride = P.g.blk_stride;
         g.v_off = P.g.v_off; g.B = P.g.B; g.log2B = P.g.log2B;
         g.begin = w.kv_begin; g.end = w.kv_end; g.pos_shift = 0;
-        g.step = w.kv_step > 0 ? w.kv_step : 64;
-        g.iterations = w.kv_step > 0 ? sk_divide(g.end - g.begin + w.kv_step - 1, P.by_step) : (g.end - g.begin + 63) >> 6;
+        g.step = w.kv_step > 0 ? (int)w.kv_step : 64;
+        g.iterations = w.kv_step > 0 ? sk_divide(g.end - g.begin + g.step - 1, P.by_step) : (g.end - g.begin + 63) >> 6;
         g.hole_lo = w.hole_lo; g.hole_n = w.hole_hi - w.hole_lo;
-        g.once = P.kv_once;
+        g.once = w.once;
     } else {
         g.base = P.g.eph + (int64_t)w.kv_head * P.g.eph_head_stride;
         g.table = P.g.eph_ident + (s == 1 ? w.eph_blk[0] : w.eph_blk[1] + (s - 2) * w.sub_blocks); g.blk_stride = P.g.eph_blk_stride;
@@ -1905,7 +1905,7 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
         n_parts = sk_tile_parts(P, w.q_tok0, w.n_tok, &vis);
         if (part >= n_parts) return;
         w.tbl_off = P.tbl_off; w.pos0 = P.pos0 < SK_NO_CAUSAL ? P.pos0 + w.q_tok0 : P.pos0;
-        w.hole_lo = P.hole_lo; w.hole_hi = P.hole_hi; w.kv_step = 0; w.sub_blocks = 0;
+        w.hole_lo = P.hole_lo; w.hole_hi = P.hole_hi; w.kv_step = 0; w.sub_blocks = 0; w.once = 0;
         w.part0 = tile * P.n_splits * Hkv + w.kv_head;
         w.eph_cnt[0] = w.eph_cnt[1] = 0; w.eph_blk[0] = w.eph_blk[1] = 0; w.eph_pos0[0] = w.eph_pos0[1] = 0;
     }

@@ -141,7 +141,7 @@ struct sk_pool {
     int distrust = 0;                    // SK_SMALL_DISTRUST (tests)
     bool p128 = true;                    // SK_NO_P128=1: never the eight-wave 128-row instance
     int64_t p128_min_tokens = -1;        // SK_P128_MIN_TOKENS: cached tokens from which it is taken; -1: by the keys of a workgroup (kP128MinKeys)
-    int64_t stream_min_tokens = 65536;   // SK_STREAM_MIN_TOKENS: cached tokens from which the 128-row instances load non-temporal
+    int64_t stream_min_tokens = -1;      // SK_STREAM_MIN_TOKENS: cached tokens from which the 128-row instances load non-temporal; -1: by the bytes of K/V (streams_once)
     bool fuse = false;                   // SK_FUSE=1: single-session calls merge their split partials inside the attention kernel
     bool fuse_list = false;              // batched calls too (the last workgroup of a unit merges alone)
     bool merge_fences = false;           // SK_MERGE_FENCES=1: full fences around the arrival (for comparison)
@@ -397,6 +397,23 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
     return SK_OK;
 }
 
+// Whether the 128-row instances load keys that no other workgroup of the launch reads non-temporal: where so many are read that
+// of three sessions' (or layers') keys, read in turn, the last-level cache of 256 MiB holds none until its turn comes again.  The default
+// policy then costs the keys' way into the cache; below, a session that is read again at once is found there.  us per query of
+// 32 tokens of 32/8 heads (kernel alone), default -> non-temporal, reading one session again and again / three in turn / eight:
+//    8,000 cached   33 MB   12.4 -> 12.6 / 12.5 -> 13.2 / 14.4 -> 13.3
+//   14,800          61 MB   16.4 -> 18.1 / 16.5 -> 18.5 / 20.4 -> 18.5
+//   32,768         134 MB   25.7 -> 28.4 / 36.8 -> 29.1 / 36.8 -> 29.0
+//   48,000         197 MB   34.3 -> 38.8 / 48.9 -> 39.9 / 48.9 -> 39.8
+// The 64-row instance: 10.3 -> 10.5 / 10.9 -> 11.3 / 12.0 -> 11.8 at 8,000 (16 tokens), 23.8 -> 25.4 / 31.8 -> 26.3 / 31.8 -> 26.5 at 32,768.
+// The 256-row one: 38.0 -> 41.9 / 46.3 -> 44.5 / 46.5 -> 45.0 at 32,768 (64 tokens), 71.6 -> 72.1 / 72.8 -> 70.4 / 73.2 -> 71.9 at 65,536.
+constexpr int64_t kStreamMinBytes = int64_t(88) << 20;
+bool streams_once(const sk_pool* p, int64_t cached, int64_t longest)
+{
+    if (p->stream_min_tokens >= 0) return longest >= p->stream_min_tokens;
+    return cached * p->d.n_kv_heads * p->d.head_dim * 2 * p->L.elem >= kStreamMinBytes;
+}
+
 struct TileReq {            // one tile of query rows and the keys it may see
     int32_t tbl_off, q_tok0, n_tok;
     int32_t pos0;           // absolute position of its first token, or SK_NO_CAUSAL
@@ -404,6 +421,7 @@ struct TileReq {            // one tile of query rows and the keys it may see
     int32_t eph_blk[2], eph_cnt[2], eph_pos0[2];
     int32_t hole_lo, hole_hi;   // evicted cached tokens of the session
     int32_t tok_period, sub_blocks;   // > 0: the tile packs sequences of tok_period tokens (see sk_work)
+    int32_t alone;              // no other tile of the call reads the session's keys
 };
 struct ListGroup {          // tiles that share a kernel variant and the q/out/lse arrays
     Variant v = {SK_KV_SIMPLE, 16, 1};
@@ -419,6 +437,7 @@ void add_tiles(ListGroup& g, const TileReq& base, int32_t q_row0, int32_t T)
         TileReq r = base;
         r.q_tok0 = q_row0 + t0;
         r.n_tok = std::min(g.v.tok_per_tile, T - t0);
+        r.alone = base.alone && T <= g.v.tok_per_tile;
         if (base.pos0 < SK_NO_CAUSAL) {
             r.pos0 = base.pos0 + t0;
             r.kv_vis = std::min<int64_t>(base.kv_vis, int64_t(r.pos0) + r.n_tok);
@@ -763,15 +782,10 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     const int64_t resident = int64_t(p->n_cus) * ((v.id == SK_KV_MFMA256 || v.id == SK_KV_MFMA128P) ? 1 : 2);
     L.wait_polls = (L.fuse && R.wgs <= resident) ? p->wait_polls : 0;
     L.merge_fences = p->merge_fences ? 1 : 0;
-    // With one row tile per KV head no two workgroups read the same keys, and the kernel can load them
-    // non-temporal.  Measured (us per query in a stream of queries, default policy -> non-temporal):
-    //   rows per KV head   16K cached     32K            64K            128K
-    //   <= 64              26.2 -> 25.9   37.1 -> 35.5   57.1 -> 54.4    99.6 ->  94.6
-    //   65 - 128           29.5 -> 32.2   40.6 -> 41.9   64.8 -> 64.6   119.0 -> 111.9
-    //   129 - 256          37.8 -> 41.4   53.6 -> 56.8   90.7 -> 90.7   162.1 -> 162.0
-    // so the 64-row instance always does, the 128-row instances from 64K cached tokens on, the 256-row
-    // instance (and every call whose row tiles share their keys through the L2) never.
-    const bool once_pays = v.id == SK_KV_MFMA64 || ((v.id == SK_KV_MFMA128 || v.id == SK_KV_MFMA128P) && kv_len >= p->stream_min_tokens);
+    // With one row tile per KV head no two workgroups read the same keys, and the kernel can load them non-temporal: the 64-row
+    // instance always does, the 128-row ones by streams_once, the 256-row one (and every call whose row tiles share their keys
+    // through the L2) never.
+    const bool once_pays = v.id == SK_KV_MFMA64 || ((v.id == SK_KV_MFMA128 || v.id == SK_KV_MFMA128P) && streams_once(p, kv_len, kv_len));
     L.kv_once = (!p->no_stream_loads && L.n_tiles == 1 && once_pays) ? 1 : 0;
     return SK_OK;
 }
@@ -1060,8 +1074,14 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
     if (inject(p, SK_SITE_PLAN)) return SK_E_WORKSPACE;
     const int Hkv = p->d.n_kv_heads;
     P.kv_total = 0; P.n_tiles = 0;
+    int64_t cached = 0, longest = 0;         // the call's keys, each once
     for (int gi = 0; gi < n_groups; ++gi)
-        for (const TileReq& t : groups[gi].tiles) { P.kv_total += t.kv_vis; ++P.n_tiles; }
+        for (size_t i = 0; i < groups[gi].tiles.size(); ++i) {
+            const TileReq& t = groups[gi].tiles[i];
+            P.kv_total += t.kv_vis; ++P.n_tiles;
+            if (i + 1 == groups[gi].tiles.size() || groups[gi].tiles[i + 1].tbl_off != t.tbl_off) cached += t.kv_vis;      // an item's last tile sees all of them
+            longest = std::max<int64_t>(longest, t.kv_vis);
+        }
     if (P.n_tiles == 0) return SK_OK;
     int64_t chunk_g[kMaxGroups];
     size_t scatter_bytes = 0;
@@ -1079,6 +1099,7 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
             P.work[gi].clear(); P.comb[gi].clear();
             P.rows_base[gi] = rows_used;
             int64_t slot = 0;       // in units of this group's rows_per_slot, from rows_base
+            const bool once_pays = !p->no_stream_loads && (g.v.id == SK_KV_MFMA64 || (g.v.id == SK_KV_MFMA128 && streams_once(p, cached, longest)));
             struct Piece { int32_t tile, part, bucket; };
             std::vector<Piece> pieces, ordered;
             std::vector<int32_t> nparts(g.tiles.size()), slot0(g.tiles.size()), unit0(g.tiles.size());
@@ -1125,6 +1146,7 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
                 w.n_parts = np;
                 w.hole_lo = t.hole_lo; w.hole_hi = t.hole_hi;
                 w.tok_period = t.tok_period; w.sub_blocks = t.sub_blocks;
+                w.once = t.alone && once_pays ? 1 : 0;
                 if (part == np - 1)
                     for (int e = 0; e < 2; ++e) { w.eph_blk[e] = t.eph_blk[e]; w.eph_cnt[e] = t.eph_cnt[e]; w.eph_pos0[e] = t.eph_pos0[e]; }
                 for (int h = 0; h < Hkv; ++h) {
@@ -1581,6 +1603,7 @@ int sk_batch_step(sk_pool* p, int32_t n_items, const int32_t* session_id, const 
         TileReq base = {};
         base.tbl_off = tbl_off;
         base.hole_lo = (int32_t)s->frozen; base.hole_hi = (int32_t)s->win;
+        base.alone = 1;                 // (sessions are distinct)
         if (op[i] == SK_OP_APPEND) {
             Undo u;
             int64_t first_new = 0;

@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2605_13784_amd as sk
 from workloads import synth
-from gpu_common import compare, dev
+from gpu_common import Pair, compare, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -275,3 +275,30 @@ def test_head_dim_64_steps_in_both_tile_heights(n, T, N, variant):
         ro, rl = ref.batch_step(sids, ops, cu, synth.to_raw(q), synth.to_raw(k), synth.to_raw(v))
         compare("step of %s" % counts, out, lse, ro, rl, shape.dtype)
     _check_caches(pool, ref, sids)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (14, 2, 64)])
+def test_cache_policy_of_lone_tiles_in_batched_steps(hq, hkv, d):
+    """Items of one row tile load their keys non-temporal where a step reads enough of them (here: always, and never); several tiles of a
+    session never do.  The same bits either way, at both sides of the 64- and 128-row tiles and with evicted keys."""
+    shape = synth.Shape("bf16", hq, hkv, d)
+    gen = synth.generator(4, stream=4000 + d)
+    G = hq // hkv
+    counts = [1, 64 // G, 64 // G + 1, 128 // G, 128 // G + 1, 2 * (128 // G) + 3]
+    lengths = [1, 63, 700, 1025, 333, 64]
+    pools = [Pair(shape, block_tokens=16, n_blocks=400, max_sessions=len(counts), max_batch_tokens=2048, env=env).pool
+             for env in ({"SK_STREAM_MIN_TOKENS": "0"}, {"SK_NO_STREAM_LOADS": "1"}, None)]
+    sids = [[p.sk_session_create() for _ in counts] for p in pools]
+    for i, n in enumerate(lengths):
+        _, k, v = [dev(t) for t in synth.draw_qkv(gen, n, shape)]
+        for p, s in zip(pools, sids):
+            p.sk_session_append(s[i], None, k, v)
+            if n == 700:
+                p.sk_session_freeze(s[i], 5)
+                p.sk_session_evict_oldest(s[i], 100)
+    cu = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    for ops in ([sk.SK_OP_QUERY_B] * len(counts), [sk.SK_OP_QUERY_A] * len(counts), [sk.SK_OP_APPEND, sk.SK_OP_QUERY_B] * (len(counts) // 2)):
+        q, k, v = [dev(t) for t in synth.draw_qkv(gen, int(cu[-1]), shape)]
+        results = [p.sk_batch_step(s, ops, cu, q, k, v) for p, s in zip(pools, sids)]
+        for out, lse in results[1:]:
+            assert torch.equal(out, results[0][0]) and torch.equal(lse, results[0][1]), ops
