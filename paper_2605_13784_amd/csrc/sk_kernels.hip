@@ -2216,31 +2216,42 @@ __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(2))) unsigned sk_u32x2;
 
+// What the requests need comes in arguments of its own (sk_comb_args, in registers when a wave starts): where every tile has the same number of parts they
+// go out before the argument block, which nobody has read yet, has arrived (0.7 us).
 template <int D, int R>
-__global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
+__global__ __launch_bounds__(256) void sk_combine(const float* const part_ml, const float* const part_o, const uint32_t by_heads_mul, const int32_t by_heads_shift,
+                                                  const int32_t Hkv, const int32_t rows_per_slot, const int32_t n_splits, const int32_t parts_all,
+                                                  const int32_t tile_rows, const int32_t all_rows, const sk_launch P)
 {
-    sk_touch_arguments<sizeof(sk_launch)>();
     const int item = blockIdx.x;                  // row tile and KV head
     const int row = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    sk_comb cb;
-    if (P.mode == SK_MODE_LIST) cb = P.comb[item];
-    else {
-        const int Hkv = P.g.Hkv;
-        const int tile = sk_divide(item, P.by_heads), head = item - tile * Hkv;
-        int tok0 = tile * P.tok_per_tile;
-        int ntok = P.n_tok - tok0; ntok = ntok < P.tok_per_tile ? ntok : P.tok_per_tile;
-        int kv_vis;
-        cb.n_parts = P.own_mode == SK_OWN_SMALL ? P.n_splits : sk_tile_parts(P, tok0, ntok, &kv_vis);
-        if (cb.n_parts == 1) return;              // written by the attention kernel
-        cb.part0 = tile * P.n_splits * Hkv + head; cb.part_stride = Hkv;
-        cb.q_tok0 = tok0; cb.n_tok = ntok; cb.kv_head = head;
+    int n_parts = parts_all, part0, part_stride, q_tok0 = 0, kv_head;
+    if (parts_all > 0) {
+        const int tile = sk_divide(item, sk_div{by_heads_mul, by_heads_shift});
+        kv_head = item - tile * Hkv;
+        if (row >= tile_rows || row >= all_rows - tile * tile_rows) return;
+        part0 = tile * n_splits * Hkv + kv_head; part_stride = Hkv;
+        q_tok0 = tile;                            // (times the tile's tokens, below)
+    } else {
+        sk_touch_arguments<sizeof(sk_launch)>();
+        sk_comb cb;
+        if (P.mode == SK_MODE_LIST) cb = P.comb[item];
+        else {
+            const int tile = sk_divide(item, P.by_heads), head = item - tile * Hkv;
+            int tok0 = tile * P.tok_per_tile;
+            int ntok = P.n_tok - tok0; ntok = ntok < P.tok_per_tile ? ntok : P.tok_per_tile;
+            int kv_vis;
+            cb.n_parts = sk_tile_parts(P, tok0, ntok, &kv_vis);
+            if (cb.n_parts == 1) return;              // written by the attention kernel
+            cb.part0 = tile * P.n_splits * Hkv + head; cb.part_stride = Hkv;
+            cb.q_tok0 = tok0; cb.n_tok = ntok; cb.kv_head = head;
+        }
+        if (row >= cb.n_tok * P.g.G) return;
+        n_parts = cb.n_parts; part0 = cb.part0; part_stride = cb.part_stride; q_tok0 = cb.q_tok0; kv_head = cb.kv_head;
     }
-    const int G = P.g.G, n_parts = cb.n_parts;
-    if (row >= cb.n_tok * G) return;
-    const size_t orow = ((size_t)(cb.q_tok0 + row / G) * P.g.Hq + cb.kv_head * G + row % G);
-    const size_t prow0 = (size_t)cb.part0 * P.rows_per_slot + row, pstride = (size_t)cb.part_stride * P.rows_per_slot;
-    const float* ml = P.part_ml + prow0 * 4;
+    const size_t prow0 = (size_t)part0 * rows_per_slot + row, pstride = (size_t)part_stride * rows_per_slot;
+    const float* ml = part_ml + prow0 * 4;
     const unsigned step = R > 1 ? (unsigned)(pstride * D * 4) : 0;
     float M = SK_NEG_INF, L = 0.f, Lx = 0.f, a0 = 0.f, a1 = 0.f;
     if (n_parts > 64) {              // rare: the maximum needs its own pass
@@ -2253,7 +2264,7 @@ __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
         float x0[R], x1[R];
         auto request = [&](const int j0) __attribute__((always_inline)) {
             const int left = cnt - j0 < R ? cnt - j0 : R;
-            const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(P.part_o + (prow0 + (size_t)(base + j0) * pstride) * D, 0,
+            const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(part_o) + (prow0 + (size_t)(base + j0) * pstride) * D, 0,
                                                                                   (int)((unsigned)(left - 1) * step + D * 4), 0x00020000);
 #pragma unroll
             for (int j = 0; j < R; ++j) {
@@ -2266,6 +2277,7 @@ __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
             }
         };
         request(0);
+        if (parts_all > 0 && base == 0) sk_touch_arguments<sizeof(sk_launch)>();
         const float m_s = lane < cnt ? t.x : SK_NEG_INF;
         if (n_parts <= 64) M = sk_wave_max(m_s);
         const float wgt = (m_s == SK_NEG_INF) ? 0.f : sk_exp2(m_s - M);
@@ -2281,6 +2293,9 @@ __global__ __launch_bounds__(256) void sk_combine(const sk_launch P)
     }
     L = sk_wave_sum(L); Lx = sk_wave_sum(Lx);
     const float inv = 1.0f / L;
+    if (parts_all > 0) q_tok0 *= P.tok_per_tile;
+    const int tok = (int)(((unsigned)row * P.g.g_magic) >> 16);        // rows of a tile: below 256 (see sk_attn_bf16_body)
+    const size_t orow = (size_t)(q_tok0 + tok) * P.g.Hq + kv_head * P.g.G + (row - tok * P.g.G);
     if (D == 128) {
         if (P.out_dtype == 0) *(float2*)((float*)P.out + orow * D + 2 * lane) = make_float2(a0 * inv, a1 * inv);
         else *(uint32_t*)((uint16_t*)P.out + orow * D + 2 * lane) = f32_to_bf16_bits(a0 * inv) | ((uint32_t)f32_to_bf16_bits(a1 * inv) << 16);
@@ -2510,16 +2525,35 @@ int sk_launch_combine(const sk_launch& L, int32_t n_row_tiles, int32_t max_parts
     const int64_t step = part_stride * L.rows_per_slot * L.g.d * 4;
     int round = max_parts <= 8 ? 8 : max_parts <= 16 ? 16 : 32;
     while (round > 1 && round * step >= (int64_t(1) << 32)) round = round > 8 ? round / 2 : 1;
+    // Whether every tile has the same number of parts: by what the first tile and the last one see.
+    int parts_all = 0;
+    if (L.mode == SK_MODE_REGULAR && L.own_mode == SK_OWN_SMALL) parts_all = L.n_splits;
+    else if (L.mode == SK_MODE_REGULAR && L.own_mode == SK_OWN_NONE) {
+        const int first = L.n_tok < L.tok_per_tile ? L.n_tok : L.tok_per_tile;
+        const int vis = L.pos0 < SK_NO_CAUSAL && L.pos0 + first < L.kv_len ? L.pos0 + first : L.kv_len;
+        const int own = L.eph_cnt[0] > 0 || L.eph_cnt[1] > 0 ? 1 : 0;
+        if ((vis + L.chunk - 1) / L.chunk + own == L.n_splits && L.n_splits > 1) parts_all = L.n_splits;
+    }
+    const sk_div by_heads = L.by_heads;
+    const int32_t tile_rows = L.tok_per_tile * L.g.G, all_rows = L.n_tok * L.g.G;
+#define SK_LAUNCH_COMBINE_R(D, R)                                                                                   \
+    do {                                                                                                            \
+        if (ev_start) hipExtLaunchKernelGGL((sk_combine<D, R>), grid, block, 0, st, (hipEvent_t)ev_start, (hipEvent_t)ev_stop, 0, L.part_ml, L.part_o, \
+                                            by_heads.mul, by_heads.shift, L.g.Hkv, L.rows_per_slot, L.n_splits, parts_all, tile_rows, all_rows, L); \
+        else hipLaunchKernelGGL((sk_combine<D, R>), grid, block, 0, st, L.part_ml, L.part_o,                        \
+                                by_heads.mul, by_heads.shift, L.g.Hkv, L.rows_per_slot, L.n_splits, parts_all, tile_rows, all_rows, L); \
+    } while (0)
 #define SK_LAUNCH_COMBINE(D)                                                                                        \
     do {                                                                                                            \
-        if (round == 32) SK_LAUNCH((sk_combine<D, 32>), grid, block);                                               \
-        else if (round == 16) SK_LAUNCH((sk_combine<D, 16>), grid, block);                                          \
-        else if (round == 8) SK_LAUNCH((sk_combine<D, 8>), grid, block);                                            \
-        else SK_LAUNCH((sk_combine<D, 1>), grid, block);                                                            \
+        if (round == 32) SK_LAUNCH_COMBINE_R(D, 32);                                                                \
+        else if (round == 16) SK_LAUNCH_COMBINE_R(D, 16);                                                           \
+        else if (round == 8) SK_LAUNCH_COMBINE_R(D, 8);                                                             \
+        else SK_LAUNCH_COMBINE_R(D, 1);                                                                             \
     } while (0)
     if (L.g.d == 128) SK_LAUNCH_COMBINE(128);
     else SK_LAUNCH_COMBINE(64);
 #undef SK_LAUNCH_COMBINE
+#undef SK_LAUNCH_COMBINE_R
     return (int)hipGetLastError();
 }
 #undef SK_LAUNCH
