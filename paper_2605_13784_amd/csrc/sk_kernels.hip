@@ -89,6 +89,17 @@ __device__ __forceinline__ void sk_touch_arguments()
     for (unsigned i = 0; i < LINES; ++i) asm volatile("" : : "s"(x[i]));
 }
 
+// An argument at byte OFFSET of the block, read from here on and not earlier: left to itself the compiler reads what a loop
+// uses in front of it, and the wait for that is one for every scalar load in flight, the first block ids among them.
+template <class T, unsigned OFFSET>
+__device__ __forceinline__ T sk_late_argument()
+{
+    typedef const __attribute__((address_space(4))) unsigned char* args_ptr;
+    args_ptr a = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr() + OFFSET;
+    asm volatile("" : "+s"(a));
+    return *(const T*)a;
+}
+
 // Work item of workgroup b.  Regular mode derives it from the launch parameters: consecutive
 // workgroups differ in KV head first (so with 8 KV heads a head stays on one XCD and its K/V
 // stay in that XCD's L2), then in row tile, then in split.
@@ -1478,8 +1489,8 @@ template <int D>
 __device__ __forceinline__ void sk_commit_group(const sk_geom& g, const void* k, const void* v, const sk_scatter& it, const int head,
                                                 int32_t* tables_rw, unsigned char* kv_rw, uint16_t* vt);
 
-// What a workgroup of the kernels below does once its four waves have scaled their accumulators to the common row
-// maxima and laid them side by side in LDS (tr[wave][row][16-byte chunk ^ row], stat[wave][row] = (m, l, lx, -)): adds
+// What a workgroup of the kernels below does once its four waves have laid their accumulators side by side in LDS
+// (tr[wave][row][16-byte chunk ^ row], stat[wave][row] = (m, l, lx, -)): brings them to the common row maxima, adds
 // the four up, writes the rows out (n_parts == 1) or to the slot of `part` (slot0 + part * Hkv), and, with P.fuse,
 // arrives at `unit` and merges the unit's parts if it is the last one there.  False: the parts did not run on
 // one XCD and this workgroup has to compute them all, part 0 first (`alone` from then on).  `orow_of`: row of the
@@ -1490,7 +1501,7 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
                                         const OutRow orow_of)
 {
     const bool whole = n_parts == 1;
-    constexpr int CPR = D / 4, SUBS = 256 / ROWS;
+    constexpr int CPR = D / 4;
     auto put_row = [&](const int row, const int c4, const float4 x, const float inv, const float lse) __attribute__((always_inline)) {
         const size_t orow = orow_of(row);
         if (P.out_dtype == 0) *(float4*)((float*)P.out + orow * D + c4 * 4) = make_float4(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
@@ -1505,13 +1516,16 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
     const size_t prow = (size_t)(slot0 + part * P.g.Hkv) * P.rows_per_slot;
     for (int i = tid; i < nrows * CPR; i += 256) {
         const int row = i / CPR, c4 = i % CPR;
-        float4 x = tr[0][row][(c4 ^ row) & (CPR - 1)];
-        float m = stat[0][row].x, l = stat[0][row].y, lx = stat[0][row].z;
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f), st[4];
+        float m = SK_NEG_INF, l = 0.f, lx = 0.f;
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
+        for (int w = 0; w < 4; ++w) { st[w] = stat[w][row]; m = fmaxf(m, st[w].x); }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
             const float4 y = tr[w][row][(c4 ^ row) & (CPR - 1)];
-            x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
-            m = fmaxf(m, stat[w][row].x); l += stat[w][row].y; lx += stat[w][row].z;
+            const float a = st[w].x == SK_NEG_INF ? 0.f : sk_exp2(st[w].x - m);
+            x.x = fmaf(y.x, a, x.x); x.y = fmaf(y.y, a, x.y); x.z = fmaf(y.z, a, x.z); x.w = fmaf(y.w, a, x.w);
+            l = fmaf(st[w].y, a, l); lx = fmaf(st[w].z, a, lx);
         }
         if (whole) put_row(row, c4, x, 1.0f / l, (m + sk_log2(lx)) * SK_LN2);
         else {
@@ -1545,90 +1559,103 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
         if (d == 0) return true;
         if (d == 2) return false;
     }
-    // All statistics in one round of loads, the weights of all parts to LDS, then every thread sums its 16-byte
-    // pieces of output rows over the parts, in part order, eight loads in flight (a short loop: code that
-    // runs once per launch costs its instruction fetches, so 32 unrolled loads took 1 us longer).
-    float4* ml = &tr[0][0][0];                        // [part][ROWS]: at most D parts
-    float4* tot = &stat[0][0];                        // [ROWS]
+    // The CPR lanes that merge a row (a 16-byte piece each) find its weights by themselves: lane c holds the statistics of parts c, c + CPR, ..,
+    // maxima and sums go over the lanes without LDS, the weights through a corner of LDS that only this wave uses.  Nobody waits for another
+    // wave, and the first parts' rows are requested beside the statistics: two round trips to the L2 for up to 16 parts, one more for every
+    // 16 further ones.  (Against statistics loaded by all, two barriers and rounds of eight, a decoded token at 2,600 cached, 21 parts: from the
+    // decision to the rows 3.2 us -> SK_T1.)  The rounds are short loops: code that runs once per launch costs its instruction fetches.
+    constexpr int STAT = 64 / CPR > 0 ? 64 / CPR : 1, ROUND = 16;      // at most 64 parts (can_merge)
     const size_t pstep = (size_t)P.g.Hkv * P.rows_per_slot;
     const unsigned row0 = (unsigned)(slot0 * P.rows_per_slot);
-    {
-        const int r = tid % ROWS;
-        for (int p = tid / ROWS; p < n_parts; p += SUBS)
-            if (r < nrows) ml[p * ROWS + r] = *((const float4*)P.part_ml + p * pstep + (row0 + (unsigned)r));
-    }
-    __syncthreads();
-    {
-        const int row = tid / SUBS, sub = tid % SUBS;
-        float M2 = SK_NEG_INF, L = 0.f, Lx = 0.f;
-        if (row < nrows) for (int p = sub; p < n_parts; p += SUBS) M2 = fmaxf(M2, ml[p * ROWS + row].x);
-        // (over the 8 or 16 neighbouring lanes of a row, without LDS: a decoded token at 2,600 cached 7.50 -> 7.28 us against shuffles.
-        // Requesting the first 16 parts' rows beside the statistics: 7.85.)
-        static_assert(SUBS == 8 || SUBS == 16, "lanes of a row");
-        M2 = fmaxf(M2, sk_dpp<0xB1>(M2)); M2 = fmaxf(M2, sk_dpp<0x4E>(M2)); M2 = fmaxf(M2, sk_dpp<0x141>(M2));
-        if (SUBS == 16) M2 = fmaxf(M2, sk_dpp<0x140>(M2));
-        if (row < nrows)
-#pragma unroll 1
-            for (int p = sub; p < n_parts; p += SUBS) {
-                const float4 t = ml[p * ROWS + row];
-                const float wgt = t.x == SK_NEG_INF ? 0.f : sk_exp2(t.x - M2);
-                ml[p * ROWS + row].x = wgt;
-                L = fmaf(t.y, wgt, L); Lx = fmaf(t.z, wgt, Lx);
-            }
-        L += sk_dpp<0xB1>(L); L += sk_dpp<0x4E>(L); L += sk_dpp<0x141>(L);
-        Lx += sk_dpp<0xB1>(Lx); Lx += sk_dpp<0x4E>(Lx); Lx += sk_dpp<0x141>(Lx);
-        if (SUBS == 16) { L += sk_dpp<0x140>(L); Lx += sk_dpp<0x140>(Lx); }
-        if (row < nrows && sub == 0) tot[row] = make_float4(M2, L, Lx, 0.f);
-    }
-    __syncthreads();
-    // (buffer loads return zeros behind the unit's last part, so that the last round needs no branch around its loads)
     const unsigned step = (unsigned)(pstep * D * 4);                   // bytes from part to part
+    // (buffer loads return zeros behind the unit's last part, so that no round needs a branch around its loads)
     const __amdgpu_buffer_rsrc_t parts = __builtin_amdgcn_make_buffer_rsrc(P.part_o + (size_t)row0 * D, 0, (int)((unsigned)n_parts * step), 0x00020000);
+    const __amdgpu_buffer_rsrc_t stats = __builtin_amdgcn_make_buffer_rsrc(P.part_ml + (size_t)row0 * 4, 0, (int)((unsigned)n_parts * (unsigned)(pstep * 16)), 0x00020000);
+    const int c = tid & (CPR - 1);
+    float* const wgt = (float*)&tr[0][0][0] + (tid / CPR) * 64;        // [lane group][part]
 #pragma unroll 1
     for (int i = tid; i < nrows * CPR; i += 256) {
         const int row = i / CPR;
+        float4 ml[STAT], x[ROUND];
+#pragma unroll
+        for (int j = 0; j < STAT; ++j)
+            ml[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(stats, (unsigned)(c + j * CPR) * (unsigned)(pstep * 16) + (unsigned)row * 16, 0, 0));
+#pragma unroll
+        for (int j = 0; j < ROUND; ++j) x[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(parts, (unsigned)j * step + (unsigned)i * 16, 0, 0));
+        float M = SK_NEG_INF, L = 0.f, Lx = 0.f;
+#pragma unroll
+        for (int j = 0; j < STAT; ++j) M = fmaxf(M, c + j * CPR < n_parts ? ml[j].x : SK_NEG_INF);
+        M = fmaxf(M, sk_dpp<0xB1>(M)); M = fmaxf(M, sk_dpp<0x4E>(M)); M = fmaxf(M, sk_dpp<0x141>(M)); M = fmaxf(M, sk_dpp<0x140>(M));
+        if (CPR == 32) { const sk_halves h = sk_row_pairs(M); M = fmaxf(h.lo, h.hi); }
+#pragma unroll
+        for (int j = 0; j < STAT; ++j) {
+            const float a = c + j * CPR >= n_parts || ml[j].x == SK_NEG_INF ? 0.f : sk_exp2(ml[j].x - M);
+            wgt[c + j * CPR] = a;
+            L = fmaf(ml[j].y, a, L); Lx = fmaf(ml[j].z, a, Lx);
+        }
+        L += sk_dpp<0xB1>(L); L += sk_dpp<0x4E>(L); L += sk_dpp<0x141>(L); L += sk_dpp<0x140>(L);
+        Lx += sk_dpp<0xB1>(Lx); Lx += sk_dpp<0x4E>(Lx); Lx += sk_dpp<0x141>(Lx); Lx += sk_dpp<0x140>(Lx);
+        if (CPR == 32) {
+            { const sk_halves h = sk_row_pairs(L); L = h.lo + h.hi; }
+            { const sk_halves h = sk_row_pairs(Lx); Lx = h.lo + h.hi; }
+        }
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 1
-        for (int p0 = 0; p0 < n_parts; p0 += 8) {
-            float4 x[8];
-            float wgt[8];
+        for (int p0 = 0;;) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                x[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(parts, (unsigned)(p0 + j) * step + (unsigned)i * 16, 0, 0));
-                wgt[j] = ml[(p0 + j < n_parts ? p0 + j : n_parts - 1) * ROWS + row].x;
-            }
+            for (int j = 0; j < ROUND; j += 4) {
+                const float4 w4 = *(const float4*)(wgt + p0 + j);
+                const float w[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                acc.x = fmaf(x[j].x, wgt[j], acc.x); acc.y = fmaf(x[j].y, wgt[j], acc.y);
-                acc.z = fmaf(x[j].z, wgt[j], acc.z); acc.w = fmaf(x[j].w, wgt[j], acc.w);
+                for (int k = 0; k < 4; ++k) {
+                    acc.x = fmaf(x[j + k].x, w[k], acc.x); acc.y = fmaf(x[j + k].y, w[k], acc.y);
+                    acc.z = fmaf(x[j + k].z, w[k], acc.z); acc.w = fmaf(x[j + k].w, w[k], acc.w);
+                }
             }
+            p0 += ROUND;
+            if (p0 >= n_parts) break;
+#pragma unroll
+            for (int j = 0; j < ROUND; ++j) x[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(parts, (unsigned)(p0 + j) * step + (unsigned)i * 16, 0, 0));
         }
-        const float4 t = tot[row];
-        put_row(row, i % CPR, acc, 1.0f / t.y, (t.x + sk_log2(t.z)) * SK_LN2);
+        put_row(row, c, acc, 1.0f / L, (M + sk_log2(Lx)) * SK_LN2);
     }
     return true;
 }
 
+// The kernel's arguments, as they lie in memory.
+struct sk_small_args {
+    const int32_t* table; const unsigned char *q, *kv;
+    uint32_t head_pages; int32_t Hkv; uint32_t shape, pad_mul, g_magic; int32_t n_parts, chunk, kv_len;
+    sk_launch P;
+    sk_commit C;
+};
+// The first arguments are in registers when a wave starts: what the first loads need (`table`: of the session; `shape`: see
+// sk_launch_attention_small), which go out before the argument block, that nobody has read yet, has arrived.
 template <int D>
-__global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, const sk_commit C)
+__global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const int32_t* const table, const unsigned char* const q, const unsigned char* const kv,
+                                                             const uint32_t head_pages, const int32_t Hkv, const uint32_t shape, const uint32_t pad_mul,
+                                                             const uint32_t g_magic, const int32_t n_parts, const int32_t chunk, const int32_t kv_len,
+                                                             const sk_launch, const sk_commit)
 {
     constexpr int NKS = D / 16, NMT = D / 32, NWV = 4, CPR = D / 4;      // CPR: float4 chunks of an output row
     constexpr int ROWB = D * 2, LOG2_TOK_BYTES = D == 128 ? 8 : 7;
     __shared__ float4 tr[NWV][32][CPR];
     __shared__ float4 stat[NWV][32];
     __shared__ int decision;
-    sk_touch_arguments<sizeof(sk_launch) + offsetof(sk_commit, item)>();
-    const int Hkv = P.g.Hkv;
-    if (__builtin_expect((int)blockIdx.x >= C.first_wg, 0)) {                  // the commit of an append
+    const int G = shape & 255, log2B = (shape >> 8) & 15, n_tok = (shape >> 18) & 63, own_cnt = shape >> 24 & 63;
+    // workgroup -> (part, KV head); the heads of a part are padded to a multiple of the XCD count
+    const int head_pad = (shape >> 17) & 1 ? (Hkv + 7) & ~7 : Hkv;
+    int part = sk_divide(blockIdx.x, sk_div{pad_mul, (int)(shape >> 12) & 31});
+    const int head = blockIdx.x - part * head_pad;
+    if (__builtin_expect(part >= n_parts, 0)) {                                // the commit of an append
+        const sk_launch P = sk_late_argument<sk_launch, offsetof(sk_small_args, P)>();
+        typedef const __attribute__((address_space(4))) unsigned char* args_ptr;
+        const sk_commit& C = *(const sk_commit*)((args_ptr)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(sk_small_args, C));
         const int i = blockIdx.x - C.first_wg, item = sk_divide(i, P.by_heads);
         sk_commit_group<D>(P.g, P.own_k, P.own_v, C.item[item], i - item * Hkv, C.tables_rw, C.kv_rw, (uint16_t*)&tr[0][0][0]);
         return;
     }
-    // workgroup -> (part, KV head); the heads of a part are padded to a multiple of the XCD count
-    int part = sk_divide(blockIdx.x, P.by_pad);
-    const int head = blockIdx.x - part * P.head_pad;
     if (head >= Hkv) return;
-    const int n_parts = P.n_splits;
     bool alone = false;                                   // the parts ran on several XCDs: this workgroup computes them all
     for (;;) {
         // (opaque, or everything below that depends on the lane only is computed before the first load is
@@ -1637,43 +1664,33 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
         asm volatile("" : "+v"(tid));
         const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int r = lane & 31, kg = lane >> 5;
-        const int G = P.g.G, nrows = P.n_tok * G;
-        const unsigned g_magic = P.g.g_magic;
+        const int nrows = n_tok * G;
         auto div_g = [&](const int row) __attribute__((always_inline)) { return (int)(((unsigned)row * g_magic) >> 16); };
         const int tok = div_g(r < nrows ? r : 0), hq = head * G + (r < nrows ? r - tok * G : 0);
-        const float c_scale = P.g.scale_log2e;
         const int tau = (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);      // key of S^T row r (bits 2 and 3 swapped)
-        bf16x8 qreg[NKS];
-        {
-            const sk_u32x4* qp = (const sk_u32x4*)((const unsigned char*)P.q + ((size_t)tok * P.g.Hq + hq) * ROWB);
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[ks * 2 + kg]);
-        }
 
-        int k_begin = 0, k_end = P.kv_len;
+        int k_begin = 0, k_end = kv_len;
         if (n_parts > 1) {
-            k_begin = part * P.chunk;
-            k_end = k_begin + P.chunk < k_end ? k_begin + P.chunk : k_end;
+            k_begin = part * chunk;
+            k_end = k_begin + chunk < k_end ? k_begin + chunk : k_end;
         }
         const int n_cached = k_end > k_begin ? (k_end - k_begin + 31) >> 5 : 0;
-        const int last_group = (k_end - 1) & ~15;
+        const int last_group = k_end > 0 ? (k_end - 1) & ~15 : 0;
 
-        f32x16 oacc[NMT];
-#pragma unroll
-        for (int mt = 0; mt < NMT; ++mt)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) oacc[mt][v] = 0.f;
-        float m_ref = SK_NEG_INF, l_run = 0.f, lx_run = 0.f;
+        bf16x8 qreg[NKS];
         sk_u32x4 ka[NKS], va[2][NMT];
-
-        // the two 16-key groups of cached tile t: base of each group's K (its V^T lies v_off further)
-        auto group_base = [&](const int t, const int j) __attribute__((always_inline)) -> const unsigned char* {
+        // the two 16-key groups of cached tile t: their block ids, requested at once, and the base of each group's K (its V^T lies v_off further)
+        auto group_at = [&](const int t, const int j) __attribute__((always_inline)) {
+            const int tg = k_begin + t * 32 + 16 * j;
+            return tg < last_group ? tg : last_group;
+        };
+        auto group_id = [&](const int t, const int j) __attribute__((always_inline)) {
             typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-            int tg = k_begin + t * 32 + 16 * j;
-            tg = tg < last_group ? tg : last_group;
-            const uint32_t blk = (uint32_t)((const_i32_ptr)(uintptr_t)P.g.tables)[(unsigned)P.tbl_off + ((unsigned)tg >> P.g.log2B)];
-            return P.g.kv + (int64_t)head * P.g.head_stride + ((uint64_t)blk << (P.g.log2B + LOG2_TOK_BYTES + 1)) +
-                   (((unsigned)tg & (unsigned)(P.g.B - 1)) << LOG2_TOK_BYTES);
+            return (uint32_t)((const_i32_ptr)(uintptr_t)table)[(unsigned)group_at(t, j) >> log2B];
+        };
+        auto group_base = [&](const int t, const int j, const uint32_t blk) __attribute__((always_inline)) -> const unsigned char* {
+            return kv + (int64_t)head * ((int64_t)head_pages << 12) + ((uint64_t)blk << (log2B + LOG2_TOK_BYTES + 1)) +
+                   (((unsigned)group_at(t, j) & ((1u << log2B) - 1)) << LOG2_TOK_BYTES);
         };
         auto load_k = [&](const unsigned char* b0, const unsigned char* b1) __attribute__((always_inline)) {
             const unsigned char* p = ((r & 16) ? b1 : b0) + (tau & 15) * ROWB + kg * 16;
@@ -1681,13 +1698,32 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
             for (int ks = 0; ks < NKS; ++ks) ka[ks] = *(const sk_u32x4*)(p + ks * 32);
         };
         auto load_v = [&](const unsigned char* b0, const unsigned char* b1) __attribute__((always_inline)) {
-            const unsigned voff = (unsigned)(P.g.v_off + r * 32 + kg * 16);
+            const unsigned voff = ((unsigned)ROWB << log2B) + (unsigned)(r * 32 + kg * 16);
 #pragma unroll
             for (int mt = 0; mt < NMT; ++mt) {
                 va[0][mt] = *(const sk_u32x4*)(b0 + voff + mt * 1024);
                 va[1][mt] = *(const sk_u32x4*)(b1 + voff + mt * 1024);
             }
         };
+        uint32_t id0 = group_id(wave, 0), id1 = group_id(wave, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        {
+            const sk_u32x4* qp = (const sk_u32x4*)(q + ((size_t)tok * (Hkv * G) + hq) * ROWB);
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) qreg[ks] = __builtin_bit_cast(bf16x8, qp[ks * 2 + kg]);
+        }
+        const unsigned char *b0 = group_base(wave, 0, id0), *b1 = group_base(wave, 1, id1);
+        if (wave < n_cached) { load_k(b0, b1); load_v(b0, b1); }
+        sk_touch_arguments<offsetof(sk_small_args, C)>();
+        const sk_launch P = sk_late_argument<sk_launch, offsetof(sk_small_args, P)>();
+        const float c_scale = P.g.scale_log2e;
+
+        f32x16 oacc[NMT];
+#pragma unroll
+        for (int mt = 0; mt < NMT; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) oacc[mt][v] = 0.f;
+        float m_ref = SK_NEG_INF, l_run = 0.f, lx_run = 0.f;
         f32x16 sacc;
         bf16x8 pb[2];
         auto scores = [&]() __attribute__((always_inline)) {
@@ -1761,26 +1797,25 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
                     oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va[q][mt]), pb[q], oacc[mt], 0, 0, 0);
         };
 
-        if (wave < n_cached) {
-            const unsigned char *b0 = group_base(wave, 0), *b1 = group_base(wave, 1);
-            load_k(b0, b1); load_v(b0, b1);
 #pragma unroll 1
-            for (int t = wave; t < n_cached; t += NWV) {
-                const bool more = t + NWV < n_cached;
-                if (more) { b0 = group_base(t + NWV, 0); b1 = group_base(t + NWV, 1); }
-                scores();
-                if (more) load_k(b0, b1);
-                const int k0 = k_begin + t * 32;          // keys past the end of the part and evicted keys do not count
-                if (k0 + 32 > k_end || (k0 < P.hole_hi && k0 + 32 > P.hole_lo)) mask(k0, k_end - 1, P.hole_lo, P.hole_hi - P.hole_lo);
-                softmax();
-                if (k0 + 32 > k_end) drop_values(k_end - k0);
-                values();
-                if (more) load_v(b0, b1);
+        for (int t = wave; t < n_cached; t += NWV) {
+            const bool more = t + NWV < n_cached;
+            if (more) {
+                id0 = group_id(t + NWV, 0); id1 = group_id(t + NWV, 1);
+                b0 = group_base(t + NWV, 0, id0); b1 = group_base(t + NWV, 1, id1);
             }
+            scores();
+            if (more) load_k(b0, b1);
+            const int k0 = k_begin + t * 32;          // keys past the end of the part and evicted keys do not count
+            if (k0 + 32 > k_end || (k0 < P.hole_hi && k0 + 32 > P.hole_lo)) mask(k0, k_end - 1, P.hole_lo, P.hole_hi - P.hole_lo);
+            softmax();
+            if (k0 + 32 > k_end) drop_values(k_end - k0);
+            values();
+            if (more) load_v(b0, b1);
         }
         // The call's own tokens: one tile, for a wave that has no cached one when the launch is cut into parts.
-        if (part == n_parts - 1 && P.own_cnt > 0 && wave == (n_cached & (NWV - 1))) {
-            const int key = tau < P.own_cnt ? tau : P.own_cnt - 1;
+        if (part == n_parts - 1 && own_cnt > 0 && wave == (n_cached & (NWV - 1))) {
+            const int key = tau < own_cnt ? tau : own_cnt - 1;
             const unsigned char* p = (const unsigned char*)P.own_k + ((size_t)key * Hkv + head) * ROWB + kg * 16;
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) ka[ks] = *(const sk_u32x4*)(p + ks * 32);
@@ -1791,11 +1826,11 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
             for (int i = 0; i < 32 * ROWB / 16 / 64; ++i) {
                 const int c = i * 64 + lane, vkey = c / (ROWB / 16), cc = c % (ROWB / 16);
                 uint4 x = make_uint4(0, 0, 0, 0);
-                if (vkey < P.own_cnt) x = *(const uint4*)((const unsigned char*)P.own_v + ((size_t)vkey * Hkv + head) * ROWB + cc * 16);
+                if (vkey < own_cnt) x = *(const uint4*)((const unsigned char*)P.own_v + ((size_t)vkey * Hkv + head) * ROWB + cc * 16);
                 rows[c] = x;
             }
             scores();
-            mask(0, P.pos0 < SK_NO_CAUSAL ? tok : P.own_cnt - 1, 0, 0);
+            mask(0, P.pos0 < SK_NO_CAUSAL ? tok : own_cnt - 1, 0, 0);
             softmax();
             const uint16_t* vt = (const uint16_t*)rows + 8 * kg * D + r;
 #pragma unroll
@@ -1809,26 +1844,19 @@ __global__ __launch_bounds__(256, 2) void sk_attn_bf16_small(const sk_launch P, 
             values();
         }
 
-        // ---- the four waves meet: common maximum, scaled accumulators side by side in LDS, sum ----
+        // ---- the four waves meet: accumulators and row statistics side by side in LDS ----
         float l_tot, lx_tot;
         { const sk_halves h = sk_both_halves(l_run); l_tot = h.lo + h.hi; }
         { const sk_halves h = sk_both_halves(lx_run); lx_tot = h.lo + h.hi; }
-        if (r < nrows && kg == 0) stat[wave][r].x = m_ref;
-        __syncthreads();
-        float M = SK_NEG_INF;
-#pragma unroll
-        for (int w = 0; w < NWV; ++w) M = fmaxf(M, stat[w][r].x);
-        const float a = m_ref == SK_NEG_INF ? 0.f : sk_exp2(m_ref - M);
         if (r < nrows) {
 #pragma unroll
             for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
                     const int c4 = mt * 8 + q4 * 2 + kg;
-                    tr[wave][r][(c4 ^ r) & (CPR - 1)] = make_float4(oacc[mt][q4 * 4 + 0] * a, oacc[mt][q4 * 4 + 1] * a,
-                                                                    oacc[mt][q4 * 4 + 2] * a, oacc[mt][q4 * 4 + 3] * a);
+                    tr[wave][r][(c4 ^ r) & (CPR - 1)] = make_float4(oacc[mt][q4 * 4 + 0], oacc[mt][q4 * 4 + 1], oacc[mt][q4 * 4 + 2], oacc[mt][q4 * 4 + 3]);
                 }
-            if (kg == 0) { stat[wave][r].y = l_tot * a; stat[wave][r].z = lx_tot * a; }
+            if (kg == 0) stat[wave][r] = make_float4(m_ref, l_tot, lx_tot, 0.f);
         }
         if (sk_meet<D, 32>(P, tr, stat, &decision, tid, nrows, part, alone, head, n_parts, head,
                            [&](const int row) __attribute__((always_inline)) {
@@ -2050,19 +2078,13 @@ __global__ __launch_bounds__(256, 2) void sk_attn_f32(const sk_launch P, const s
         }
 
         const float l_tot = sk_sum_over_groups(l_run);
-        if (c < nrows && g4 == 0) stat[wave][c].x = m_ref;
-        __syncthreads();
-        float M = SK_NEG_INF;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) M = fmaxf(M, stat[v][c].x);
-        const float a = m_ref == SK_NEG_INF ? 0.f : sk_exp2(m_ref - M);
         if (c < nrows) {
 #pragma unroll
             for (int h = 0; h < NH; ++h)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    tr[wave][c][((h * 16 + g4 + i) ^ c) & (CPR - 1)] = make_float4(o[h][0][i] * a, o[h][1][i] * a, o[h][2][i] * a, o[h][3][i] * a);
-            if (g4 == 0) { stat[wave][c].y = l_tot * a; stat[wave][c].z = l_tot * a; }
+                    tr[wave][c][((h * 16 + g4 + i) ^ c) & (CPR - 1)] = make_float4(o[h][0][i], o[h][1][i], o[h][2][i], o[h][3][i]);
+            if (g4 == 0) stat[wave][c] = make_float4(m_ref, l_tot, l_tot, 0.f);
         }
         if (sk_meet<D, 16>(P, tr, stat, &decision, tid, nrows, part, alone, slot0, n_parts, unit,
                            [&](const int row) __attribute__((always_inline)) {
@@ -2216,7 +2238,7 @@ __global__ __launch_bounds__(256) void sk_attn_simple(const sk_launch P)
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(2))) unsigned sk_u32x2;
 
-// What the requests need comes in arguments of its own (sk_comb_args, in registers when a wave starts): where every tile has the same number of parts they
+// What the requests need comes in arguments of their own (the first 14 words of a kernel's arguments are in registers when a wave starts): where every tile has the same number of parts they
 // go out before the argument block, which nobody has read yet, has arrived (0.7 us).
 template <int D, int R>
 __global__ __launch_bounds__(256) void sk_combine(const float* const part_ml, const float* const part_o, const uint32_t by_heads_mul, const int32_t by_heads_shift,
@@ -2498,20 +2520,29 @@ int sk_launch_attention_small(const sk_launch& L, const sk_commit& C, int32_t n_
 {
     if (n_workgroups <= 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-#define SK_LAUNCH_SMALL(kernel)                                                                                     \
+#define SK_LAUNCH_SMALL(kernel, ...)                                                                                \
     do {                                                                                                            \
-        if (ev_start) hipExtLaunchKernelGGL(kernel, dim3(n_workgroups), dim3(256), 0, st, (hipEvent_t)ev_start, (hipEvent_t)ev_stop, 0, L, C); \
-        else hipLaunchKernelGGL(kernel, dim3(n_workgroups), dim3(256), 0, st, L, C);                                \
+        if (ev_start) hipExtLaunchKernelGGL(kernel, dim3(n_workgroups), dim3(256), 0, st, (hipEvent_t)ev_start, (hipEvent_t)ev_stop, 0, __VA_ARGS__); \
+        else hipLaunchKernelGGL(kernel, dim3(n_workgroups), dim3(256), 0, st, __VA_ARGS__);                         \
     } while (0)
     if (L.g.elem == 4) {
-        if (L.g.d == 128) SK_LAUNCH_SMALL(sk_attn_f32<128>);
-        else if (L.g.d == 64) SK_LAUNCH_SMALL(sk_attn_f32<64>);
+        if (L.g.d == 128) SK_LAUNCH_SMALL(sk_attn_f32<128>, L, C);
+        else if (L.g.d == 64) SK_LAUNCH_SMALL(sk_attn_f32<64>, L, C);
         else return (int)hipErrorInvalidValue;
-    } else if (L.g.d == 128) {
-        SK_LAUNCH_SMALL(sk_attn_bf16_small<128>);
-    } else if (L.g.d == 64) {
-        SK_LAUNCH_SMALL(sk_attn_bf16_small<64>);
-    } else return (int)hipErrorInvalidValue;
+        return (int)hipGetLastError();
+    }
+    // G | log2B << 8 | shift of by_pad << 12 | padded << 17 | tokens << 18 | own tokens << 24 (at most 32 rows per KV head); a head's blocks
+    // lie whole 4 KiB pages apart (a block holds K and V of at least 16 tokens of 64 dims)
+    const uint32_t shape = (uint32_t)L.g.G | (uint32_t)L.g.log2B << 8 | (uint32_t)L.by_pad.shift << 12 | (L.head_pad != L.g.Hkv ? 1u : 0u) << 17 |
+                           (uint32_t)L.n_tok << 18 | (uint32_t)L.own_cnt << 24;
+    const int32_t* table = L.g.tables + L.tbl_off;
+    const unsigned char* q = (const unsigned char*)L.q;
+    const uint32_t pages = (uint32_t)(L.g.head_stride >> 12);
+#define SK_SMALL_ARGS table, q, L.g.kv, pages, L.g.Hkv, shape, L.by_pad.mul, L.g.g_magic, L.n_splits, L.chunk, L.kv_len, L, C
+    if (L.g.d == 128) SK_LAUNCH_SMALL(sk_attn_bf16_small<128>, SK_SMALL_ARGS);
+    else if (L.g.d == 64) SK_LAUNCH_SMALL(sk_attn_bf16_small<64>, SK_SMALL_ARGS);
+    else return (int)hipErrorInvalidValue;
+#undef SK_SMALL_ARGS
 #undef SK_LAUNCH_SMALL
     return (int)hipGetLastError();
 }

@@ -312,12 +312,12 @@ struct RegPlan {
 };
 
 // Whether the last workgroup of a unit can merge its parts: few enough for one workgroup to read, and within reach of
-// 32-bit offsets in the rounds of eight it reads them in.
+// 32-bit offsets in the rounds of sixteen it reads them in (at most 64 parts: four rounds of one row tile's pieces, or fewer parts of more).
 bool can_merge(const sk_pool* p, const Variant& v, int64_t tile_rows, int64_t parts)
 {
     const int64_t rounds = (tile_rows * p->d.head_dim + 1023) / 1024 * ((parts + 7) / 8);
     const int64_t step = int64_t(p->d.n_kv_heads) * v.rows_per_slot * p->d.head_dim * 4;
-    return parts > 1 && parts <= p->d.head_dim && rounds <= 8 && (parts + 7) * step < (int64_t(1) << 32);
+    return parts > 1 && parts <= p->d.head_dim && rounds <= 8 && (parts + 15) * step < (int64_t(1) << 32);
 }
 
 // The kernel for at most 32 rows per KV head: cached tokens in parts of whole 32-key tiles, four waves to a
