@@ -82,10 +82,15 @@ struct sk_scatter {
     int32_t src_tok0;     // first packed token row in k/v
     int32_t count;        // tokens (1..16), all inside one 16-token group of the block
     int32_t dst_slot0;    // slot of the first token inside the destination block
-    int32_t to_eph;       // 0: pool (block size B), 1: staging (block size 16)
+    int32_t to_eph;       // 0: pool (block size B), 1: staging (block size 16); SK_COPY_LIST: see there
     int32_t tbl_index;    // >= 0: also write tables[tbl_index] = block_id
     int32_t block_id;
 };
+
+// sk_scatter::to_eph of an item that copies, instead, a stretch of the lists of a batched call's other launches from pinned memory to the
+// workspace: `count` 16-byte pieces (at most 256 for each KV head: a workgroup copies 4 KiB), from piece src_tok0 behind the start of
+// the item list to dst_off bytes behind the staging area's start (the lists lie in front of it: negative).
+#define SK_COPY_LIST 2
 
 // A short scatter list that travels in the kernel arguments.
 #define SK_SCATTER_ARGS_MAX 80

@@ -1562,8 +1562,8 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
     // The CPR lanes that merge a row (a 16-byte piece each) find its weights by themselves: lane c holds the statistics of parts c, c + CPR, ..,
     // maxima and sums go over the lanes without LDS, the weights through a corner of LDS that only this wave uses.  Nobody waits for another
     // wave, and the first parts' rows are requested beside the statistics: two round trips to the L2 for up to 16 parts, one more for every
-    // 16 further ones.  (Against statistics loaded by all, two barriers and rounds of eight, a decoded token at 2,600 cached, 21 parts: from the
-    // decision to the rows 3.2 us -> SK_T1.)  The rounds are short loops: code that runs once per launch costs its instruction fetches.
+    // 16 further ones.  (Against statistics loaded by all, two barriers and rounds of eight, a decoded token at 2,600 cached, 21 parts:
+    // 8.31 -> 6.61 us.)  The rounds are short loops: code that runs once per launch costs its instruction fetches.
     constexpr int STAT = 64 / CPR > 0 ? 64 / CPR : 1, ROUND = 16;      // at most 64 parts (can_merge)
     const size_t pstep = (size_t)P.g.Hkv * P.rows_per_slot;
     const unsigned row0 = (unsigned)(slot0 * P.rows_per_slot);
@@ -2400,14 +2400,21 @@ __device__ __forceinline__ void sk_scatter_item(const sk_geom& g, const void* k,
     sk_commit_group_f32(g, k, v, it, head, tables_rw, it.to_eph ? eph_rw : kv_rw);
 }
 
-// Items read from a list in the workspace (batched steps) or in pinned host memory (long single-session appends) ...
+// Items read from a list in pinned host memory or in the workspace.  A batched call's list has items of another kind behind the others, which
+// copy the lists that its other launches read from pinned memory to the workspace.
+// Bound of those: the host link's latency, beside the commit.
 __global__ __launch_bounds__(256) void sk_scatter_kernel(const sk_geom g, const sk_div by_heads, const void* k, const void* v,
                                                          const sk_scatter* items, int32_t* tables_rw,
                                                          unsigned char* kv_rw, unsigned char* eph_rw)
 {
-    const int i = sk_divide(blockIdx.x, by_heads);
+    const int i = sk_divide(blockIdx.x, by_heads), head = blockIdx.x - i * g.Hkv;
     const sk_scatter it = items[i];                          // at once: the list may lie in host memory
-    sk_scatter_item(g, k, v, it, blockIdx.x - i * g.Hkv, tables_rw, kv_rw, eph_rw);
+    if (it.to_eph == SK_COPY_LIST) {
+        const int at = head * 256 + threadIdx.x;
+        if (at < it.count) ((uint4*)(eph_rw + it.dst_off))[at] = ((const uint4*)items)[it.src_tok0 + at];
+        return;
+    }
+    sk_scatter_item(g, k, v, it, head, tables_rw, kv_rw, eph_rw);
 }
 // ... or carried in the kernel arguments (single-session calls: no host-to-device copy in front)
 __global__ __launch_bounds__(256) void sk_scatter_kernel_args(const sk_geom g, const sk_div by_heads, const void* k, const void* v,

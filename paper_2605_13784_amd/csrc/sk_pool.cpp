@@ -463,8 +463,9 @@ uint32_t list_bucket(uint32_t len, uint32_t chunk) { return len == chunk ? 8 : u
 // rounds of the chip -> 2 pieces, one round).
 // The schedule is only played through where simple bounds of its end (the average load, the longest piece) do not
 // say already that the length is no better, and no further than to where it is known to be none.
-// head_dim 64 on the matrix pipe has times of its own (ListCost), with the uncommitted tokens of a tile and the upload of the lists:
-// beyond 16 KiB that copy takes 14 us longer.  `other_bytes`: what is uploaded beside this launch's lists; 0 is returned where no length
+// head_dim 64 on the matrix pipe has times of its own (ListCost), with the uncommitted tokens of a tile and the way of the lists:
+// beyond 16 KiB a copy of them took 14 us longer. The scatter launch now carries those (launch_list), which takes about 2 us longer; the choices between
+// row tiles are still those fitted and checked with the former.  `other_bytes`: what is uploaded beside this launch's lists; 0 is returned where no length
 // is expected to end before `bound`.
 // Fitted to 13,000 timed launches of 992 steps and question batches.
 struct ListCost {
@@ -1189,33 +1190,66 @@ int launch_list(sk_pool* p, ListPlan& P, const ScatterBatch* sb, int n_sb, ListG
 {
     if (P.n_tiles == 0) return SK_OK;
     const int Hkv = p->d.n_kv_heads;
-    // one upload: scatter lists, work lists, combine lists
+    // The lists, in the pinned slot as in the workspace: scatter lists, work lists, combine lists.  Up to 16 KiB one copy in front takes them there (2.5 us;
+    // 16 beyond).  Beyond, the scatter lists are read where they lie, in the pinned slot, and items behind those of the first
+    // copy the others (a launch of such items alone where there is nothing to scatter).  us per call, a copy in front -> by the
+    // scatter launch: 3 sessions of 32/8 heads (24 KiB and more) 93.5 -> 77.0, 20 sessions 700 -> 685, 48 4,033 -> 4,009; 16 questions 92.7 ->
+    // 80.8, of 64 dims 62.5 -> 50.3; below 16 KiB 4 questions 60.9 -> 62.6, of 64 dims 43.4 -> 45.0.  More groups than kListInPlaceMax
+    // are copied too, as in scatter_launch.
     unsigned char* ws = (unsigned char*)p->d.workspace;
     unsigned char* dev_meta = p->device ? ws + p->L.off_meta : nullptr;
+    size_t lists_bytes = 0, n_items = 0;
+    int carrier = n_sb - 1;                     // the scatter list that carries the others
+    for (int i = n_sb - 1; i >= 0; --i) { n_items += sb[i].items.size(); if (!sb[i].items.empty()) carrier = i; }
+    for (int gi = 0; gi < n_groups; ++gi)
+        lists_bytes += align_up(P.work[gi].size() * sizeof(sk_work), 256) + align_up(P.comb[gi].size() * sizeof(sk_comb), 256);
+    const size_t stretch = size_t(Hkv) * 256, pieces = lists_bytes / 16, n_copies = (pieces + stretch - 1) / stretch;
     size_t off = 0, off_sb[2] = {0, 0}, off_work[kMaxGroups] = {}, off_comb[kMaxGroups] = {};
-    for (int i = 0; i < n_sb; ++i) {
-        off_sb[i] = off;
-        if (P.host) memcpy(P.host + off, sb[i].items.data(), sb[i].items.size() * sizeof(sk_scatter));
-        off += align_up(sb[i].items.size() * sizeof(sk_scatter), 256);
+    bool in_place = lists_bytes + n_items * sizeof(sk_scatter) > kUploadStep && n_items <= kListInPlaceMax;
+    auto place = [&]() {
+        off = 0;
+        for (int i = 0; i < n_sb; ++i) {
+            off_sb[i] = off;
+            off += align_up((sb[i].items.size() + (in_place && i == carrier ? n_copies : 0)) * sizeof(sk_scatter), 256);
+        }
+        for (int gi = 0; gi < n_groups; ++gi) {
+            off_work[gi] = off; off += align_up(P.work[gi].size() * sizeof(sk_work), 256);
+            off_comb[gi] = off; off += align_up(P.comb[gi].size() * sizeof(sk_comb), 256);
+        }
+    };
+    place();
+    if (off > p->L.meta_bytes) { in_place = false; place(); }          // (what plan_list has checked has no room for the copies' items)
+    for (int i = 0; i < n_sb && P.host; ++i) {
+        memcpy(P.host + off_sb[i], sb[i].items.data(), sb[i].items.size() * sizeof(sk_scatter));
+        if (!in_place || i != carrier) continue;
+        sk_scatter* more = (sk_scatter*)(P.host + off_sb[i]) + sb[i].items.size();
+        for (size_t c = 0; c < n_copies; ++c) {
+            sk_scatter it = {};
+            it.to_eph = SK_COPY_LIST;
+            it.src_tok0 = int32_t((off_work[0] - off_sb[i]) / 16 + c * stretch);
+            it.count = int32_t(std::min(stretch, pieces - c * stretch));
+            it.dst_off = int64_t(p->L.off_meta + off_work[0] + c * stretch * 16) - int64_t(p->L.off_eph);
+            it.tbl_index = -1;
+            more[c] = it;
+        }
     }
-    for (int gi = 0; gi < n_groups; ++gi) {
-        off_work[gi] = off;
-        if (P.host) memcpy(P.host + off, P.work[gi].data(), P.work[gi].size() * sizeof(sk_work));
-        off += align_up(P.work[gi].size() * sizeof(sk_work), 256);
-        off_comb[gi] = off;
-        if (P.host) memcpy(P.host + off, P.comb[gi].data(), P.comb[gi].size() * sizeof(sk_comb));
-        off += align_up(P.comb[gi].size() * sizeof(sk_comb), 256);
+    for (int gi = 0; gi < n_groups && P.host; ++gi) {
+        memcpy(P.host + off_work[gi], P.work[gi].data(), P.work[gi].size() * sizeof(sk_work));
+        memcpy(P.host + off_comb[gi], P.comb[gi].data(), P.comb[gi].size() * sizeof(sk_comb));
     }
-    int rc = ring_upload(p, P.slot, off, st);
-    if (rc) return rc;
+    if (!in_place) { int rc = ring_upload(p, P.slot, off, st); if (rc) return rc; }
+    else if (inject(p, SK_SITE_UPLOAD)) return SK_E_HIP;
+    const unsigned char* scatter_lists = in_place ? P.host : dev_meta;
     for (int i = 0; i < n_sb; ++i) {
-        if (sb[i].items.empty()) continue;
-        if (inject(p, SK_SITE_SCATTER)) return SK_E_HIP;
+        const size_t n = sb[i].items.size() + (in_place && i == carrier ? n_copies : 0);
+        if (n == 0) continue;
+        if (!sb[i].items.empty() && inject(p, SK_SITE_SCATTER)) return SK_E_HIP;
         if (!p->device) continue;
-        int e = sk_launch_scatter(p->geom, sb[i].k, sb[i].v, (const sk_scatter*)(dev_meta + off_sb[i]), (int32_t)sb[i].items.size(),
+        int e = sk_launch_scatter(p->geom, sb[i].k, sb[i].v, (const sk_scatter*)(scatter_lists + off_sb[i]), (int32_t)n,
                                   (int32_t*)(ws + p->L.off_tables), (unsigned char*)p->d.kv_mem, ws + p->L.off_eph, st);
+        if (in_place) ring_busy(p, P.slot, st);            // whatever e is (see scatter_launch)
         if (e) { g_last_hip = e; return SK_E_HIP; }
-        P.scatter_enqueued = true;
+        if (!sb[i].items.empty()) P.scatter_enqueued = true;
         p->stats.launches++;
     }
     if (inject(p, SK_SITE_ATTENTION)) return SK_E_HIP;
@@ -1636,7 +1670,7 @@ int sk_batch_step(sk_pool* p, int32_t n_items, const int32_t* session_id, const 
     if (list_narrow(p, groups[0].v) && !groups[0].tiles.empty()) {
         // head_dim 64: the items above 128 rows in tiles of 128, together with those of 65 to 128, where that is expected to end
         // earlier.  us per step in 256-row tiles and in 128: 12 sessions of 32/8 heads, 137 tokens at 888 cached each, 68 and 55; 48 of
-        // 14/2, 84 at 10,615, 307 and 256; 3 of 32/8, 363 at 304, 29 and 52 (its lists are then longer than 16 KiB); 4 of 12/4, 292 at
+        // 14/2, 84 at 10,615, 307 and 256; 4 of 12/4, 292 at
         // 15,626, 112 and 166.  348 random steps against 128-row tiles always: with 256-row ones always 0.90 of the time in the
         // geometric mean, 48 more than 3 % slower and up to 33; by expected end 0.81, the slowest 2 %.
         ListGroup low = groups[1];

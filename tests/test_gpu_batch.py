@@ -302,3 +302,36 @@ def test_cache_policy_of_lone_tiles_in_batched_steps(hq, hkv, d):
         results = [p.sk_batch_step(s, ops, cu, q, k, v) for p, s in zip(pools, sids)]
         for out, lse in results[1:]:
             assert torch.equal(out, results[0][0]) and torch.equal(lse, results[0][1]), ops
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(32, 8, 128, "bf16"), (16, 2, 64, "bf16"), (4, 4, 64, "f32")])
+def test_lists_that_the_scatter_launch_carries(hq, hkv, d, dtype):
+    """Lists beyond 16 KiB are copied to the workspace by items of the scatter launch, 4 KiB a workgroup: steps with something to scatter and
+    without, few KV heads (several such items) and more, then questions without a prefix (whose own scatter list is empty)."""
+    shape = synth.Shape(dtype, hq, hkv, d)
+    gen = synth.generator(4, stream=5000 + hq + d)
+    n_sessions, T = {8: (14, 40), 4: (24, 40), 2: (48, 80)}[hkv]
+    pr = Pair(shape, block_tokens=16, n_blocks=n_sessions * 60, max_sessions=n_sessions, max_batch_tokens=4096)
+    sids = [pr.create() for _ in range(n_sessions)]
+    for i, s in enumerate(sids):
+        _, k, v = synth.draw_qkv(gen, 500 + 7 * i, shape)
+        pr.pool.sk_session_append(s, None, dev(k), dev(v))
+        pr.oracles[s].K, pr.oracles[s].V = synth.to_raw(k), synth.to_raw(v)
+    cu = np.arange(n_sessions + 1, dtype=np.int32) * T
+    for op in (sk.SK_OP_QUERY_A, sk.SK_OP_QUERY_B):
+        q, k, v = synth.draw_qkv(gen, n_sessions * T, shape)
+        own = (dev(k), dev(v)) if op == sk.SK_OP_QUERY_B else (None, None)
+        out, lse = pr.pool.sk_batch_step(sids, [op] * n_sessions, cu, dev(q), *own)
+        assert pr.pool.sk_pool_last_launch()["workgroups"] * 88 > 16384
+        for i in (0, n_sessions // 2, n_sessions - 1):
+            a, b = cu[i], cu[i + 1]
+            ro, rl = pr.oracles[sids[i]].query(synth.to_raw(q[a:b]), *((synth.to_raw(k[a:b]), synth.to_raw(v[a:b])) if own[0] is not None else ()))
+            compare("op %d session %d" % (op, i), out[a:b], lse[a:b], ro, rl, dtype)
+    NQ, Sfx = (40 if hkv > 2 else 120), 8
+    qs, ks, vs = synth.draw_qkv(gen, NQ * Sfx, shape)
+    r4 = lambda t: t.reshape(NQ, Sfx, t.shape[1], d)
+    _, _, os_, ls = pr.pool.sk_session_query_shared_prefix(sids[-1], None, None, None, dev(r4(qs)), dev(r4(ks)), dev(r4(vs)))
+    for j in (0, NQ - 1):
+        a, b = j * Sfx, (j + 1) * Sfx
+        ro, rl = pr.oracles[sids[-1]].query(*[synth.to_raw(t[a:b]) for t in (qs, ks, vs)])
+        compare("question %d" % j, os_[j], ls[j], ro, rl, dtype)
