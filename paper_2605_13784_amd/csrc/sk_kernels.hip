@@ -406,8 +406,7 @@ __device__ __forceinline__ sk_tile_blocks sk_lookup_tile(const sk_seg& g, int t0
     return b;
 }
 
-// Keeps a segment's first block ids together: looked up one by one, each in front of its loads, they are round trips one behind
-// the other (a table that this launch has not read yet: about 1 us each).
+// Keeps a segment's first block ids together.
 template <int D>
 __device__ __forceinline__ void sk_together(const sk_tile_blocks& b)
 {
@@ -540,8 +539,10 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     const unsigned unit_base = lds_base + sub * US;                // LDS address of this wave's unit of ring slot 0, tile 0
     const int half = PIPELINED ? (wave >> 2) : 0;
 
-    // The block ids a wave's first loads of a segment need, requested together: one by one, each in front of its loads, they
-    // are round trips one behind the other (about 1 us each where nobody has read the table yet).
+    // The block ids a wave's first loads of a segment need, requested together and as the first thing: one by one, each in front of
+    // its loads, they are round trips one behind the other.  With the query operand beside them, the first loads right behind and no
+    // division on the way the 64-row instance takes 9.2 instead of 10.2 us at 2,600 cached tokens (with the epilogue below) and 80.9
+    // instead of 84.4 at 131,072.
     constexpr int NPRE = PIPELINED ? 5 : LOCKSTEP ? 4 : NSS * (TPI / NLG);
     sk_tile_blocks pre[NPRE];
     auto look_up = [&](const sk_seg& g) __attribute__((always_inline)) {
@@ -864,9 +865,9 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             // `slot` is the ring slot the iteration reads; the slot read by the previous iteration is
             // refilled with iteration it + NSS - 1.  With the two-slot ring the loop is unrolled over the
             // slots (the slot offsets fold into the LDS instructions); a four-slot ring takes the slot at
-            // run time (one copy of the loop body).  The four-wave instances in use have two slots: with
-            // four (three iterations in flight, 128 KiB, one workgroup per CU) a query measured slower
-            // (32 tokens at 32K: 38 against 33 us; 16 tokens at 128K: 103 against 98 us).
+            // run time (one copy of the loop body).  The instances in use have two slots: with
+            // four (three iterations in flight, 128 KiB, one workgroup per CU) a query is slower, as its first tile comes behind three times
+            // the bytes of all CUs (kernel, us: 16 tokens at 131,072 cached 80.9 -> 94.0, 32 at 32,768 29.0 -> 30.1, 23 at 14,800 16.4 -> 18.8).
             auto iteration = [&](const int it, const int slot) __attribute__((always_inline)) {
                 // this wave's loads of iteration `it` have landed: everything but the loads of the
                 // (at most NSS - 2) later iterations already issued
