@@ -131,7 +131,8 @@ size_t sk_pool_workspace_bytes(const sk_pool_desc* desc);
  *   SK_NO_STREAM_LOADS=1  calls (and items of a batched step) with one row tile per KV head load the cache with the
  *                      default cache policy instead of non-temporal
  *   SK_STREAM_MIN_TOKENS=n  cached tokens from which the 128-row instances do so (default: where the call reads
- *                      88 MiB of K/V and more; the 64-row instance always does)
+ *                      88 MiB of K/V and more, 256 of a session that shares blocks with forks; the 64-row
+ *                      instance always does, but for items of a step that share blocks)
  *   SK_FUSE=1          single-session calls of the ring kernels (more than 32 rows per KV head, or more than 128 MiB
  *                      of cached K/V) merge their split partials inside the attention kernel
  *                      instead of in a second kernel (one launch per call; measured slower on

@@ -36,6 +36,7 @@ struct Session {
     int64_t len = 0;
     int64_t frozen = 0, win = 0;
     std::vector<int32_t> blocks;
+    mutable bool may_share = false;      // forked, or a fork: other sessions may hold some of its blocks too (holds_shared)
     int64_t retained() const { return frozen + (len - win); }
 };
 
@@ -178,6 +179,18 @@ int64_t blocks_needed(const sk_pool* p, int64_t len, int64_t add)
 {
     const int64_t B = p->d.block_tokens;
     return (len + add + B - 1) / B - (len + B - 1) / B;
+}
+
+// Whether another session holds one of the session's blocks too (forks share those of their prefix, and evictions
+// and truncations on either side can leave any of them shared).  Blocks come to be shared by a fork alone, so that a session found to
+// hold none is not looked at again before the next.
+bool holds_shared(const sk_pool* p, const Session& s)
+{
+    if (!s.may_share) return false;
+    for (int32_t b : s.blocks)
+        if (p->refcnt[(size_t)b] > 1) return true;
+    s.may_share = false;
+    return false;
 }
 
 // Test hook: true when a failure was ordered for this site and its countdown has run out.  The sites
@@ -407,11 +420,13 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
 //   48,000         197 MB   34.3 -> 38.8 / 48.9 -> 39.9 / 48.9 -> 39.8
 // The 64-row instance: 10.3 -> 10.5 / 10.9 -> 11.3 / 12.0 -> 11.8 at 8,000 (16 tokens), 23.8 -> 25.4 / 31.8 -> 26.3 / 31.8 -> 26.5 at 32,768.
 // The 256-row one: 38.0 -> 41.9 / 46.3 -> 44.5 / 46.5 -> 45.0 at 32,768 (64 tokens), 71.6 -> 72.1 / 72.8 -> 70.4 / 73.2 -> 71.9 at 65,536.
-constexpr int64_t kStreamMinBytes = int64_t(88) << 20;
-bool streams_once(const sk_pool* p, int64_t cached, int64_t longest)
+// Forks of one prefix read the same bytes, so what one of them left in the cache is there for the next: their calls do so only where the
+// keys are more than it holds (eight forks of 32,768 tokens queried in turn, 32 tokens each, 33.1 -> 36.8 us a query from 88 MiB on).
+constexpr int64_t kStreamMinBytes = int64_t(88) << 20, kLastLevelBytes = int64_t(256) << 20;
+bool streams_once(const sk_pool* p, int64_t cached, int64_t longest, bool shared)
 {
     if (p->stream_min_tokens >= 0) return longest >= p->stream_min_tokens;
-    return cached * p->d.n_kv_heads * p->d.head_dim * 2 * p->L.elem >= kStreamMinBytes;
+    return cached * p->d.n_kv_heads * p->d.head_dim * 2 * p->L.elem >= (shared ? kLastLevelBytes : kStreamMinBytes);
 }
 
 struct TileReq {            // one tile of query rows and the keys it may see
@@ -422,6 +437,7 @@ struct TileReq {            // one tile of query rows and the keys it may see
     int32_t hole_lo, hole_hi;   // evicted cached tokens of the session
     int32_t tok_period, sub_blocks;   // > 0: the tile packs sequences of tok_period tokens (see sk_work)
     int32_t alone;              // no other tile of the call reads the session's keys
+    int32_t shared;             // the session holds blocks that other sessions hold too: other items of the call may read them
 };
 struct ListGroup {          // tiles that share a kernel variant and the q/out/lse arrays
     Variant v = {SK_KV_SIMPLE, 16, 1};
@@ -437,7 +453,7 @@ void add_tiles(ListGroup& g, const TileReq& base, int32_t q_row0, int32_t T)
         TileReq r = base;
         r.q_tok0 = q_row0 + t0;
         r.n_tok = std::min(g.v.tok_per_tile, T - t0);
-        r.alone = base.alone && T <= g.v.tok_per_tile;
+        r.alone = base.alone && !base.shared && T <= g.v.tok_per_tile;
         if (base.pos0 < SK_NO_CAUSAL) {
             r.pos0 = base.pos0 + t0;
             r.kv_vis = std::min<int64_t>(base.kv_vis, int64_t(r.pos0) + r.n_tok);
@@ -786,7 +802,7 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     // With one row tile per KV head no two workgroups read the same keys, and the kernel can load them non-temporal: the 64-row
     // instance always does, the 128-row ones by streams_once, the 256-row one (and every call whose row tiles share their keys
     // through the L2) never.
-    const bool once_pays = v.id == SK_KV_MFMA64 || ((v.id == SK_KV_MFMA128 || v.id == SK_KV_MFMA128P) && streams_once(p, kv_len, kv_len));
+    const bool once_pays = v.id == SK_KV_MFMA64 || ((v.id == SK_KV_MFMA128 || v.id == SK_KV_MFMA128P) && streams_once(p, kv_len, kv_len, holds_shared(p, p->sessions[id])));
     L.kv_once = (!p->no_stream_loads && L.n_tiles == 1 && once_pays) ? 1 : 0;
     return SK_OK;
 }
@@ -1075,12 +1091,12 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
     if (inject(p, SK_SITE_PLAN)) return SK_E_WORKSPACE;
     const int Hkv = p->d.n_kv_heads;
     P.kv_total = 0; P.n_tiles = 0;
-    int64_t cached = 0, longest = 0;         // the call's keys, each once
+    int64_t cached = 0, longest = 0;         // the call's keys that no two of its items read
     for (int gi = 0; gi < n_groups; ++gi)
         for (size_t i = 0; i < groups[gi].tiles.size(); ++i) {
             const TileReq& t = groups[gi].tiles[i];
             P.kv_total += t.kv_vis; ++P.n_tiles;
-            if (i + 1 == groups[gi].tiles.size() || groups[gi].tiles[i + 1].tbl_off != t.tbl_off) cached += t.kv_vis;      // an item's last tile sees all of them
+            if (!t.shared && (i + 1 == groups[gi].tiles.size() || groups[gi].tiles[i + 1].tbl_off != t.tbl_off)) cached += t.kv_vis;      // an item's last tile sees all of them
             longest = std::max<int64_t>(longest, t.kv_vis);
         }
     if (P.n_tiles == 0) return SK_OK;
@@ -1100,7 +1116,7 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
             P.work[gi].clear(); P.comb[gi].clear();
             P.rows_base[gi] = rows_used;
             int64_t slot = 0;       // in units of this group's rows_per_slot, from rows_base
-            const bool once_pays = !p->no_stream_loads && (g.v.id == SK_KV_MFMA64 || (g.v.id == SK_KV_MFMA128 && streams_once(p, cached, longest)));
+            const bool once_pays = !p->no_stream_loads && (g.v.id == SK_KV_MFMA64 || (g.v.id == SK_KV_MFMA128 && streams_once(p, cached, longest, false)));
             struct Piece { int32_t tile, part, bucket; };
             std::vector<Piece> pieces, ordered;
             std::vector<int32_t> nparts(g.tiles.size()), slot0(g.tiles.size()), unit0(g.tiles.size());
@@ -1433,7 +1449,7 @@ int sk_session_create(sk_pool* p, int32_t* out_id)
     int32_t id = p->free_ids.back();
     p->free_ids.pop_back();
     Session& s = p->sessions[id];
-    s.live = true; s.len = 0; s.frozen = 0; s.win = 0; s.blocks.clear();
+    s.live = true; s.len = 0; s.frozen = 0; s.win = 0; s.blocks.clear(); s.may_share = false;
     *out_id = id;
     return SK_OK;
 }
@@ -1579,6 +1595,7 @@ int sk_batch_step(sk_pool* p, int32_t n_items, const int32_t* session_id, const 
     std::vector<char> seen((size_t)p->d.max_sessions, 0);
     int64_t need_blocks = 0;
     bool any_kv = false;
+    std::vector<char> shared((size_t)n_items, 0);               // as it is before an append takes its own copy of a shared tail
     for (int i = 0; i < n_items; ++i) {
         const Session* s = get_session(p, session_id[i]);
         if (!s) return SK_E_BADSESSION;
@@ -1588,6 +1605,7 @@ int sk_batch_step(sk_pool* p, int32_t n_items, const int32_t* session_id, const 
         if (T < 0) return SK_E_INVAL;
         if (op[i] != SK_OP_APPEND && op[i] != SK_OP_QUERY_A && op[i] != SK_OP_QUERY_B) return SK_E_INVAL;
         if (T == 0) continue;
+        shared[(size_t)i] = holds_shared(p, *s);
         if (op[i] == SK_OP_APPEND) {
             if (s->len + T > p->L.max_session_tokens) return SK_E_NOMEM;
             need_blocks += blocks_needed(p, s->len, T) + (tail_shared(p, s) ? 1 : 0);
@@ -1637,7 +1655,7 @@ int sk_batch_step(sk_pool* p, int32_t n_items, const int32_t* session_id, const 
         TileReq base = {};
         base.tbl_off = tbl_off;
         base.hole_lo = (int32_t)s->frozen; base.hole_hi = (int32_t)s->win;
-        base.alone = 1;                 // (sessions are distinct)
+        base.alone = 1; base.shared = shared[(size_t)i];        // (sessions are distinct, but forks share the blocks of a prefix)
         if (op[i] == SK_OP_APPEND) {
             Undo u;
             int64_t first_new = 0;
@@ -1925,6 +1943,7 @@ int sk_session_fork(sk_pool* p, int32_t src_id, int64_t n_prefix, int32_t* out_i
     p->free_ids.pop_back();
     Session& d = p->sessions[id];
     d.live = true; d.frozen = frozen; d.win = win; d.len = len;
+    src->may_share = d.may_share = true;
     d.blocks.swap(blocks);
     for (int64_t i = 0; i < n_blk - (tail_partial ? 1 : 0); ++i) p->refcnt[(size_t)d.blocks[(size_t)i]]++;
     if (tail_partial) {

@@ -1,11 +1,12 @@
 // The library's host code against a device that is not there: the HIP calls and the kernel launchers are replaced by functions
 // that count, so that what a call asks the runtime for can be checked where no GPU is.  Built and run by
-// tests/test_host_fake_device.py; exits non-zero on a mismatch.
+// tests/test_host_fake_device.py, a check of those in main at a time; exits non-zero on a mismatch.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <vector>
 
 #include "../include/sk.h"
 #include "../paper_2605_13784_amd/csrc/sk_internal.h"
@@ -15,6 +16,8 @@
 static int n_events, recorded[16], waited[16], copies, launch_error;
 static unsigned host_flags;
 static const void* list_at;
+static std::vector<sk_work> work;            // of the last batched call's attention launches, and their other arguments
+static std::vector<sk_launch> launches;
 
 extern "C" {
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
@@ -33,21 +36,40 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
 hipError_t hipMemset(void* d, int x, size_t n) { std::memset(d, x, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 }
-int sk_launch_scatter(const sk_geom&, const void*, const void*, const sk_scatter* items, int32_t, int32_t*, unsigned char*, unsigned char*, void*)
+int sk_launch_scatter(const sk_geom&, const void*, const void*, const sk_scatter* items, int32_t n, int32_t*, unsigned char*, unsigned char* eph, void*)
 {
     list_at = items;
+    for (int32_t i = 0; i < n; ++i)          // what the kernel does with such an item
+        if (items[i].to_eph == SK_COPY_LIST) std::memcpy(eph + items[i].dst_off, (const char*)items + 16 * (size_t)items[i].src_tok0, 16 * (size_t)items[i].count);
     const int e = launch_error;
     launch_error = 0;
     return e;
 }
 int sk_launch_scatter_args(const sk_geom&, const void*, const void*, const sk_scatter_list&, int32_t, int32_t*, unsigned char*, unsigned char*, void*) { return 0; }
-int sk_launch_attention(const sk_launch&, int, int32_t, void*, void*, void*) { return 0; }
+int sk_launch_attention(const sk_launch& L, int, int32_t n, void*, void*, void*)
+{
+    launches.push_back(L);
+    if (L.mode == SK_MODE_LIST) work.insert(work.end(), L.work, L.work + n);
+    return 0;
+}
 int sk_launch_attention_small(const sk_launch&, const sk_commit&, int32_t, void*, void*, void*) { return 0; }
 int sk_launch_combine(const sk_launch&, int32_t, int32_t, int64_t, void*, void*, void*) { return 0; }
 int sk_launch_gather(const sk_geom&, int32_t, int64_t, int64_t, void*, void*, void*) { return 0; }
 int sk_launch_copy_block(const sk_geom&, unsigned char*, int32_t, int32_t, void*) { return 0; }
 
-int main()
+static sk_pool* make_pool(sk_pool_desc& d)
+{
+    d.dtype = SK_BF16; d.block_tokens = 16;
+    d.kv_bytes = sk_pool_kv_bytes(&d); d.workspace_bytes = sk_pool_workspace_bytes(&d);
+    d.kv_mem = std::aligned_alloc(256, (d.kv_bytes + 255) / 256 * 256);
+    d.workspace = std::aligned_alloc(256, (d.workspace_bytes + 255) / 256 * 256);
+    sk_pool* p = nullptr;
+    CHECK(sk_pool_create(&d, &p) == SK_OK);
+    return p;
+}
+static void drop_pool(sk_pool* p, sk_pool_desc& d) { CHECK(sk_pool_destroy(p) == SK_OK); std::free(d.kv_mem); std::free(d.workspace); }
+
+static void check_ring()
 {
     sk_pool_desc d = {};
     d.dtype = SK_BF16; d.n_q_heads = d.n_kv_heads = 1; d.head_dim = 64; d.block_tokens = 16; d.max_sessions = 1;
@@ -87,6 +109,78 @@ int main()
     CHECK(total == slots + 5 && busy == 5);         // every long append marked its slot once, whichever way its list went
     CHECK(sk_pool_destroy(p) == SK_OK);
     std::free(d.kv_mem); std::free(d.workspace);
+}
+
+// Keys that other sessions hold too are not marked as read by one workgroup alone, and do not count as such: sessions of 32/8 heads of 128 dims,
+// 4 KiB a token.
+static void check_forks()
+{
+    sk_pool_desc d = {};
+    d.n_q_heads = 32; d.n_kv_heads = 8; d.head_dim = 128; d.max_sessions = 16; d.n_blocks = 1 << 13; d.max_batch_tokens = 1 << 15;
+    sk_pool* p = make_pool(d);
+    static __attribute__((aligned(16))) char x[16];
+    auto grown = [&](int32_t tokens) {
+        int32_t id = -1;
+        CHECK(sk_session_create(p, &id) == SK_OK && sk_session_append(p, id, nullptr, x, x, tokens, nullptr, SK_F32, nullptr, nullptr) == SK_OK);
+        return id;
+    };
+    auto fork_of = [&](int32_t id, int64_t n) { int32_t f = -1; CHECK(sk_session_fork(p, id, n, &f, nullptr) == SK_OK); return f; };
+    auto query_once = [&](int32_t id) {                     // 128 rows per KV head
+        launches.clear();
+        CHECK(sk_session_query(p, id, x, nullptr, nullptr, 32, x, SK_F32, nullptr, 0, nullptr) == SK_OK);
+        CHECK(launches.size() == 1 && launches[0].mode == SK_MODE_REGULAR);
+        return launches[0].kv_once;
+    };
+    auto step_once = [&](const std::vector<int32_t>& ids, int32_t tokens) {      // per item, of a step that queries all of them
+        std::vector<int32_t> op(ids.size(), SK_OP_QUERY_A), cu(1, 0), once(ids.size(), -1);
+        for (size_t i = 0; i < ids.size(); ++i) cu.push_back(cu.back() + tokens);
+        launches.clear(); work.clear();
+        CHECK(sk_batch_step(p, (int32_t)ids.size(), ids.data(), op.data(), cu.data(), x, nullptr, nullptr, x, SK_F32, nullptr, nullptr) == SK_OK);
+        for (const sk_work& w : work) {
+            const size_t i = size_t(w.q_tok0 / tokens);
+            CHECK(i < ids.size() && (once[i] < 0 || once[i] == (int32_t)w.once));
+            once[i] = (int32_t)w.once;
+        }
+        return once;
+    };
+    using flags = std::vector<int32_t>;
+    const int32_t a = grown(25000), c = grown(500);
+    CHECK(query_once(a) == 1);
+    const int32_t b = fork_of(a, 25000);
+    CHECK(query_once(a) == 0 && query_once(b) == 0);
+    CHECK(step_once({a, b, c}, 16) == (flags{0, 0, 1}));
+    // of blocks that go on being shared whatever is evicted and cut off on either side
+    CHECK(sk_session_evict_oldest(p, a, 20000, nullptr) == SK_OK);
+    CHECK(step_once({a, b, c}, 16) == (flags{0, 0, 1}));
+    CHECK(sk_session_truncate(p, b, 20000) == SK_OK);       // b: tokens 0 .. 19,999; a: 20,000 ..
+    CHECK(step_once({a, b, c}, 16) == (flags{1, 1, 1}));
+    CHECK(sk_session_destroy(p, a) == SK_OK && sk_session_destroy(p, b) == SK_OK);
+    // 128-row items, 33 MB each: four sessions of their own are more than 88 MiB, one and three forks of another are not
+    std::vector<int32_t> own, forks;
+    for (int i = 0; i < 4; ++i) own.push_back(grown(8000));
+    CHECK(step_once(own, 32) == (flags{1, 1, 1, 1}));
+    for (int i = 0; i < 3; ++i) forks.push_back(fork_of(own[0], 8000));
+    CHECK(step_once({forks[0], forks[1], forks[2], own[1]}, 32) == (flags{0, 0, 0, 0}));
+    CHECK(step_once({own[1], own[2], own[3], forks[0]}, 32) == (flags{1, 1, 1, 0}));
+    for (int32_t f : forks) CHECK(sk_session_destroy(p, f) == SK_OK);
+    CHECK(step_once(own, 32) == (flags{1, 1, 1, 1}));
+    // an append that is taken back leaves the sessions sharing their last block, which alone they share, as before
+    const int32_t e = grown(40), g = fork_of(e, 32);
+    CHECK(sk_session_evict_oldest(p, e, 16, nullptr) == SK_OK && sk_session_truncate(p, e, 8) == SK_OK);       // e: the second block, half of it
+    CHECK(step_once({e, g}, 16) == (flags{0, 0}));
+    const int32_t ids[2] = {e, g}, op[2] = {SK_OP_APPEND, SK_OP_QUERY_A}, cu[3] = {0, 16, 32};
+    CHECK(sk_pool_inject_failure(p, SK_SITE_PLAN, 1) == SK_OK);
+    CHECK(sk_batch_step(p, 2, ids, op, cu, x, x, x, x, SK_F32, nullptr, nullptr) == SK_E_WORKSPACE);
+    CHECK(step_once({e, g}, 16) == (flags{0, 0}));
+    drop_pool(p, d);
+}
+
+int main(int argc, char** argv)
+{
+    const char* what = argc > 1 ? argv[1] : "ring";
+    if (!std::strcmp(what, "ring")) check_ring();
+    else if (!std::strcmp(what, "forks")) check_forks();
+    else return 1;
     std::printf("fake device ok\n");
     return 0;
 }

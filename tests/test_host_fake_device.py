@@ -7,9 +7,17 @@ from paper_2605_13784_amd import _build
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-def test_pinned_ring_slots_and_the_kernels_that_read_them(tmp_path):
+def _run(tmp_path, check):
     exe = str(tmp_path / "fake_device")
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-o", exe,
                     os.path.join(HERE, "host_fake_device_driver.cpp"), os.path.join(_build.CSRC, "sk_pool.cpp")], check=True, capture_output=True)
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    r = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "fake device ok" in r.stdout, r.stdout + r.stderr
+
+
+def test_pinned_ring_slots_and_the_kernels_that_read_them(tmp_path):
+    _run(tmp_path, "ring")
+
+
+def test_keys_that_forks_share_are_not_read_once(tmp_path):
+    _run(tmp_path, "forks")
