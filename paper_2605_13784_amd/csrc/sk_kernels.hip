@@ -1630,6 +1630,15 @@ struct sk_small_args {
     sk_launch P;
     sk_commit C;
 };
+// Byte offset at which argument N of a kernel lies in its argument block: each behind the one in front, aligned as its type.
+template <int N, class... A>
+constexpr size_t sk_argument_offset(void (*)(A...))
+{
+    constexpr size_t size[] = {sizeof(A)...}, align[] = {alignof(A)...};
+    size_t at = 0;
+    for (int i = 0; i < N; ++i) at = (at + align[i] - 1) / align[i] * align[i] + size[i];
+    return (at + align[N] - 1) / align[N] * align[N];
+}
 // The first arguments are in registers when a wave starts: what the first loads need (`table`: of the session; `shape`: see
 // sk_launch_attention_small), which go out before the argument block, that nobody has read yet, has arrived.
 template <int D>
@@ -2541,11 +2550,18 @@ int sk_launch_attention_small(const sk_launch& L, const sk_commit& C, int32_t n_
     }
     // G | log2B << 8 | shift of by_pad << 12 | padded << 17 | tokens << 18 | own tokens << 24 (at most 32 rows per KV head); a head's blocks
     // lie whole 4 KiB pages apart (a block holds K and V of at least 16 tokens of 64 dims)
+    if (L.g.G < 1 || L.g.G > 255 || L.g.log2B > 15 || L.by_pad.shift > 31 || L.n_tok < 1 || L.n_tok * L.g.G > 32 || L.own_cnt < 0 || L.own_cnt > 32 ||
+        (L.g.head_stride & 4095) || (L.g.head_stride >> 44) || (L.head_pad != L.g.Hkv && L.head_pad != ((L.g.Hkv + 7) & ~7)))
+        return (int)hipErrorInvalidValue;          // would not fit its field, or the kernel's LDS
     const uint32_t shape = (uint32_t)L.g.G | (uint32_t)L.g.log2B << 8 | (uint32_t)L.by_pad.shift << 12 | (L.head_pad != L.g.Hkv ? 1u : 0u) << 17 |
                            (uint32_t)L.n_tok << 18 | (uint32_t)L.own_cnt << 24;
     const int32_t* table = L.g.tables + L.tbl_off;
     const unsigned char* q = (const unsigned char*)L.q;
     const uint32_t pages = (uint32_t)(L.g.head_stride >> 12);
+    constexpr void (*kernel)(const int32_t*, const unsigned char*, const unsigned char*, uint32_t, int32_t, uint32_t, uint32_t, uint32_t, int32_t, int32_t,
+                             int32_t, sk_launch, sk_commit) = sk_attn_bf16_small<128>;         // (a changed parameter list does not convert)
+    static_assert(sk_argument_offset<11>(kernel) == offsetof(sk_small_args, P) && sk_argument_offset<12>(kernel) == offsetof(sk_small_args, C) &&
+                  sk_argument_offset<6>(kernel) == offsetof(sk_small_args, pad_mul), "the kernel reads its arguments through sk_small_args");
 #define SK_SMALL_ARGS table, q, L.g.kv, pages, L.g.Hkv, shape, L.by_pad.mul, L.g.g_magic, L.n_splits, L.chunk, L.kv_len, L, C
     if (L.g.d == 128) SK_LAUNCH_SMALL(sk_attn_bf16_small<128>, SK_SMALL_ARGS);
     else if (L.g.d == 64) SK_LAUNCH_SMALL(sk_attn_bf16_small<64>, SK_SMALL_ARGS);

@@ -9,7 +9,10 @@
 #include <map>
 #include <vector>
 
+#include <hip/hip_runtime_api.h>
+
 #include "../include/sk.h"
+#include "../paper_2605_13784_amd/csrc/sk_internal.h"
 
 static uint64_t rng_state = 0x5EED0009ull;
 static uint32_t rnd(uint32_t n) { rng_state = rng_state * 6364136223846793005ull + 1442695040888963407ull; return (uint32_t)(rng_state >> 33) % n; }
@@ -129,6 +132,24 @@ int main(int argc, char** argv)
         CHECK(sk_pool_create(&d, &p) == SK_OK && sk_session_create(p, &id) == SK_OK);
         for (int i = 0; i < 104; ++i) CHECK(sk_session_append(p, id, nullptr, nullptr, nullptr, 1, nullptr, SK_F32, nullptr, nullptr) == SK_OK);
         CHECK(sk_pool_destroy(p) == SK_OK);
+    }
+    {   // A short call that would not fit the fields its launch packs, or the kernel's LDS, is refused in front of the launch.
+        auto refused = [](auto&& change) {
+            static sk_launch L;
+            static sk_commit C;
+            L = sk_launch{};
+            L.g.elem = 2; L.g.d = 128; L.g.G = 4; L.g.Hkv = 8; L.g.log2B = 4; L.g.head_stride = 8192; L.n_tok = 8; L.head_pad = 8; L.n_splits = 1;
+            change(L);
+            return sk_launch_attention_small(L, C, 8, nullptr, nullptr, nullptr) == (int)hipErrorInvalidValue;
+        };
+        CHECK(refused([](sk_launch& L) { L.n_tok = 9; }));                  // 36 rows
+        CHECK(refused([](sk_launch& L) { L.n_tok = 64; L.g.G = 1; L.g.Hkv = 32; L.head_pad = 32; }));
+        CHECK(refused([](sk_launch& L) { L.own_cnt = 33; }));
+        CHECK(refused([](sk_launch& L) { L.g.G = 256; }));
+        CHECK(refused([](sk_launch& L) { L.g.log2B = 16; }));
+        CHECK(refused([](sk_launch& L) { L.g.head_stride = 8192 + 2048; }));
+        CHECK(refused([](sk_launch& L) { L.g.head_stride = int64_t(1) << 44; }));
+        CHECK(refused([](sk_launch& L) { L.head_pad = 24; }));
     }
     std::printf("host walk ok\n");
     return 0;
