@@ -1297,9 +1297,8 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     // idle by then), XOR-swizzled by row so both directions are conflict-free.  With two key phases the waves first tell each
     // other their reference maxima, scale by them, and the rows of both are added on the way out: every wave stores half of
     // its row group's rows.
-    // Bound: round trips of a wave to LDS.  The values of a batch of stores are read before the first of them goes out: the
-    // stores (volatile) keep their order, and with each read in front of its store that was 16 round trips, 1.8 us of a
-    // workgroup; the phases merged in registers by half of the waves, and only those storing, took another 1.8.
+    // Bound: round trips of a wave to LDS.  The values of a batch of stores are read before the first of them goes out: with
+    // each read in front of its store that was 16 round trips, 1.8 us of a workgroup; the phases merged in registers by half of the waves, and only those storing, took another 1.8.
     const bool direct = w.part < 0;
     const int nrows = w.n_tok * G;
     float factor = 1.0f;
@@ -1377,7 +1376,8 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
             }
         }
     }
-    SK_WAIT_VMCNT(0);                                 // the partial's stores (inline assembly) have completed
+    asm volatile("" : : : "memory");                  // the partial's stores are issued in front of the wait,
+    SK_WAIT_VMCNT(0);                                 // and behind it they have completed
     if (direct || !P.fuse) return;
 
     // ---- in-kernel merge of the split partials ----
