@@ -1600,6 +1600,7 @@ __device__ __forceinline__ bool sk_meet(const sk_launch& P, float4 (*tr)[ROWS][D
             { const sk_halves h = sk_row_pairs(L); L = h.lo + h.hi; }
             { const sk_halves h = sk_row_pairs(Lx); Lx = h.lo + h.hi; }
         }
+        __builtin_amdgcn_wave_barrier();                  // the weights of a row come from the lanes of this wave: no read is moved in front of them
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 1
         for (int p0 = 0;;) {

@@ -54,3 +54,15 @@ def test_partials_are_in_memory_before_the_workgroup_arrives(assembly):
         assert waits and any(lines[i].startswith("s_barrier") for i in range(waits[0], arrival)), name
         found += 1
     assert found == 7
+
+
+def test_weights_of_the_merge_are_written_before_the_lanes_read_them(assembly):
+    """The lanes of a row exchange the weights of its parts through LDS without a barrier instruction, as they are lanes of one
+    wave: the compiler is told where the writes end, and the reads of the rounds stand behind it."""
+    found = 0
+    for name, lines in _kernels(assembly, "sk_attn_bf16_small|sk_attn_f32"):
+        at = [i for i, x in enumerate(lines) if x.startswith("; wave barrier")]
+        assert len(at) == 1, name
+        assert any(x.startswith("ds_write") for x in lines[at[0] - 60:at[0]]) and any(x.startswith("ds_read_b128") for x in lines[at[0]:at[0] + 60]), name
+        found += 1
+    assert found == 4
