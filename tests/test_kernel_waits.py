@@ -32,7 +32,7 @@ def test_staged_keys_are_in_memory_before_the_barrier_that_announces_them(assemb
     """The workgroup of the own part stores a query's own K/V and then loads them into LDS, each wave tiles that others
     stored: between its last store and the next barrier every wave has to wait for its stores (vmcnt(0))."""
     found = 0
-    for name, lines in _kernels(assembly):
+    for name, lines in _kernels(assembly, RING):
         tiles = next(i for i, x in enumerate(lines) if x.startswith("global_load_lds"))
         stores = [i for i in range(tiles) if lines[i].startswith("global_store_dwordx4")]
         assert len(stores) == 2, "%s: staging stores one K and one V piece" % name
@@ -46,7 +46,7 @@ def test_partials_are_in_memory_before_the_workgroup_arrives(assembly):
     """A workgroup whose partial another one may merge in the same launch announces it by an atomic: each wave waits for its
     write-through stores (vmcnt(0)) behind the last of them, in front of the barrier and of that arrival."""
     found = 0
-    for name, lines in _kernels(assembly):
+    for name, lines in _kernels(assembly, RING):
         arrival = next(i for i, x in enumerate(lines) if x.startswith("global_atomic_add"))
         stores = [i for i, x in enumerate(lines) if x.startswith("buffer_store_dwordx4")]
         assert stores and stores[-1] < arrival and all(lines[i].endswith("sc0 sc1") for i in stores), name
