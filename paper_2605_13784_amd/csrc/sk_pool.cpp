@@ -443,7 +443,6 @@ struct ListGroup {          // tiles that share a kernel variant and the q/out/l
     Variant v = {SK_KV_SIMPLE, 16, 1};
     const void* q = nullptr; void* out = nullptr; float* lse = nullptr;
     std::vector<TileReq> tiles;
-    int64_t chunk = 0;      // length of the pieces its tiles are cut into, where that is chosen already
 };
 
 // Cuts T tokens (packed rows q_row0..) that share `base` into row tiles of the group's height.
@@ -479,22 +478,22 @@ uint32_t list_bucket(uint32_t len, uint32_t chunk) { return len == chunk ? 8 : u
 // rounds of the chip -> 2 pieces, one round).
 // The schedule is only played through where simple bounds of its end (the average load, the longest piece) do not
 // say already that the length is no better, and no further than to where it is known to be none.
-// head_dim 64 on the matrix pipe has times of its own (ListCost), with the uncommitted tokens of a tile and the way of the lists:
-// beyond 16 KiB a copy of them took 14 us longer. The scatter launch now carries those (launch_list), which takes about 2 us longer; the choices between
-// row tiles are still those fitted and checked with the former.  `other_bytes`: what is uploaded beside this launch's lists; 0 is returned where no length
-// is expected to end before `bound`.
-// Fitted to 13,000 timed launches of 992 steps and question batches.
+// head_dim 64 on the matrix pipe has times of its own (ListCost), with the uncommitted tokens of a tile.  0 is returned where no length
+// is expected to end before `bound`.  Fitted to 13,000 timed launches of 992 steps and question batches.
+// `step`: what lists beyond 16 KiB count, with `other_bytes` beside this launch's.  The length of the pieces is chosen with nothing, as
+// the scatter launch carries such lists (launch_list) for less than the times err: with the 14 us of the copy that they once needed,
+// plans stayed under 16 KiB (of 850 random steps and 650 question batches 146 and 234 are cut otherwise, at 0.85 and 0.93 of their time in
+// the geometric mean, six steps and three batches more than 3 % slower, up to 8).
 struct ListCost {
     double start, it_alone, it_shared, ends;     // as in RegCost
     double segment;                              // start of a run of uncommitted tokens
 };
 constexpr ListCost kList256d64 = {2.0, 0.88, 0.16, 6.4, 1.05}, kList128d64 = {1.8, 0.87, 0.29, 5.2, 0.75}, kList64d64 = {3.8, 0.63, 0.0, 2.6, 0.75};
-constexpr size_t kUploadStep = 16384;
-constexpr double kUploadStepUs = 14.0;
+constexpr size_t kUploadStep = 16384;        // bytes of lists beyond which a copy of them takes 14 us longer (launch_list)
 bool list_narrow(const sk_pool* p, const Variant& v) { return p->d.head_dim == 64 && p->L.elem == 2 && v.id != SK_KV_SIMPLE; }
 
-int64_t list_chunk(const sk_pool* p, const ListGroup& g, size_t other_bytes = 0, double* expected_us = nullptr, size_t* expected_bytes = nullptr,
-                   double bound = HUGE_VAL)
+int64_t list_chunk(const sk_pool* p, const ListGroup& g, double step = 0.0, size_t other_bytes = 0, double* expected_us = nullptr,
+                   size_t* expected_bytes = nullptr, double bound = HUGE_VAL)
 {
     int64_t longest = 0;
     for (const TileReq& t : g.tiles) longest = std::max<int64_t>(longest, t.kv_vis);
@@ -539,8 +538,8 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g, size_t other_bytes = 0,
         const double ends = narrow ? nc.ends : 6.0, segment = narrow ? nc.segment : 0.0;
         const int64_t lanes = std::max<int64_t>(1, int64_t(p->n_cus) * (sparse ? 1 : 2) / Hkv);
         const size_t bytes = (size_t)(n * Hkv) * sizeof(sk_work) + (size_t)(split * Hkv) * sizeof(sk_comb);
-        const double step = narrow && other_bytes + bytes > kUploadStep ? kUploadStepUs : 0.0;
-        const double merge = step + (!narrow ? double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0
+        const double carried = narrow && other_bytes + bytes > kUploadStep ? step : 0.0;
+        const double merge = carried + (!narrow ? double(parts) * Hkv * 0.018 * g.v.rows_per_slot / 128.0
                                      : split == 0 ? 0.0 : 4.0 + double(Hkv * g.v.rows_per_slot) * 1e-3 * (0.018 * double(parts) + 0.19 * double(split)));
         // whole chunks fill the lanes evenly; the rest goes to whichever lane is free first
         const double c = double(chunk / 64) * it + ends, base = c * double(whole / lanes);
@@ -572,29 +571,27 @@ int64_t list_chunk(const sk_pool* p, const ListGroup& g, size_t other_bytes = 0,
         for (size_t i = 0; narrow && (int64_t)n_tiles <= lanes - ahead && i < n_tiles; ++i) end = std::max(end, base + (double(rest[i]) * it + double(own_runs[i]) * segment + ends));
         if (no_better(end)) continue;
         best = end + merge; best_chunk = chunk;
-        if (expected_us) *expected_us = end + merge - step + nc.start + 2.0;       // (with the launch itself)
+        if (expected_us) *expected_us = end + merge - carried + nc.start + 2.0;       // (with the launch itself)
         if (expected_bytes) *expected_bytes = bytes;
     }
     return best_chunk;
 }
 
-// Expected time of a call's launches (head_dim 64), or something not below `bound`: chooses the groups' pieces, and counts the upload's
-// step once.
-double list_cost(const sk_pool* p, ListGroup* const* groups, int n_groups, size_t scatter_bytes, double bound = HUGE_VAL)
+// Expected time of a call's launches (head_dim 64), or something not below `bound`; `step` as in list_chunk, counted once.
+double list_cost(const sk_pool* p, const ListGroup* const* groups, int n_groups, size_t scatter_bytes, double step, double bound = HUGE_VAL)
 {
     double us = 0;
     size_t least = scatter_bytes, bytes = scatter_bytes;
     for (int gi = 0; gi < n_groups; ++gi) least += groups[gi]->tiles.size() * p->d.n_kv_heads * sizeof(sk_work);
     for (int gi = 0; gi < n_groups; ++gi) {
-        ListGroup& g = *groups[gi];
+        const ListGroup& g = *groups[gi];
         if (g.tiles.empty()) continue;
         double end = 0;
         size_t b = 0;
-        g.chunk = list_chunk(p, g, least - g.tiles.size() * p->d.n_kv_heads * sizeof(sk_work), &end, &b, bound - us);
-        if (g.chunk == 0) return bound;
+        if (list_chunk(p, g, step, least - g.tiles.size() * p->d.n_kv_heads * sizeof(sk_work), &end, &b, bound - us) == 0) return bound;
         us += end; bytes += b;
     }
-    return us + (bytes > kUploadStep ? kUploadStepUs : 0.0);
+    return us + (bytes > kUploadStep ? step : 0.0);
 }
 
 // Expected time, in us, of the attention and combine launches of a single-session call whose row tiles are cut into pieces of
@@ -1101,9 +1098,7 @@ int plan_list(sk_pool* p, const ScatterBatch* sb, int n_sb, ListGroup* groups, i
         }
     if (P.n_tiles == 0) return SK_OK;
     int64_t chunk_g[kMaxGroups];
-    size_t scatter_bytes = 0;
-    for (int i = 0; i < n_sb; ++i) scatter_bytes += sb[i].items.size() * sizeof(sk_scatter);
-    for (int gi = 0; gi < n_groups; ++gi) chunk_g[gi] = groups[gi].chunk > 0 ? groups[gi].chunk : list_chunk(p, groups[gi], scatter_bytes);
+    for (int gi = 0; gi < n_groups; ++gi) chunk_g[gi] = list_chunk(p, groups[gi]);
     const int64_t cap_rows = p->L.part_slots * kPartSlotRows;
     size_t bytes = 0;
     for (;;) {
@@ -1690,19 +1685,21 @@ int sk_batch_step(sk_pool* p, int32_t n_items, const int32_t* session_id, const 
         // earlier.  us per step in 256-row tiles and in 128: 12 sessions of 32/8 heads, 137 tokens at 888 cached each, 68 and 55; 48 of
         // 14/2, 84 at 10,615, 307 and 256; 4 of 12/4, 292 at
         // 15,626, 112 and 166.  348 random steps against 128-row tiles always: with 256-row ones always 0.90 of the time in the
-        // geometric mean, 48 more than 3 % slower and up to 33; by expected end 0.81, the slowest 2 %.
+        // geometric mean, 48 more than 3 % slower and up to 33; by expected end 0.81, the slowest 2 %.  Lists beyond 16 KiB count the
+        // 2 us that they take longer: 400 of the steps in list_chunk's comment then take 0.887 of their former time, with 14 here 0.902, with
+        // nothing 0.874 and one of them 1.4 times as long.
+        constexpr double kCarriedUs = 2.0;
         ListGroup low = groups[1];
         low.v = Variant{SK_KV_MFMA128, 128, 128 / p->L.G};
         low.q = q; low.out = out; low.lse = lse;
         for (const Item& it : tall) add_tiles(low, it.base, it.row0, it.tokens);
         const size_t scatter = sb.items.size() * sizeof(sk_scatter);
-        ListGroup small = groups[2];
-        ListGroup* const as_low[2] = {&low, &small};
-        ListGroup* const as_tall[3] = {&groups[0], &groups[1], &groups[2]};
-        const double tall_us = list_cost(p, as_tall, 3, scatter);
-        if (list_cost(p, as_low, 2, scatter, tall_us) < tall_us) {
+        const ListGroup* const as_low[2] = {&low, &groups[2]};
+        const ListGroup* const as_tall[3] = {&groups[0], &groups[1], &groups[2]};
+        const double tall_us = list_cost(p, as_tall, 3, scatter, kCarriedUs);
+        if (list_cost(p, as_low, 2, scatter, kCarriedUs, tall_us) < tall_us) {
             groups[0].tiles.clear();
-            groups[1] = std::move(low); groups[2].chunk = small.chunk;
+            groups[1] = std::move(low);
         }
     }
     ListPlan plan;
@@ -1785,16 +1782,19 @@ int sk_session_query_shared_prefix(sk_pool* p, int32_t id, const void* qp, const
         // head_dim 64 packs where that is expected to end earlier: a tile walks the suffixes of all its questions, one after the
         // other.  us per batch, one question a tile and packed: 8 questions of 32 tokens at 162 cached (8/8 heads) 31 and 48, 43 of 8 at
         // 957 (32/8) 58 and 75; 5 of 8 behind a prefix of 16 at 1,550 51 and 47.  200 random batches against no packing: packed always
-        // 0.91 of the time, 50 more than 3 % slower and up to 56; by expected end 0.82, 4 more than 3 % slower, up to 14.
+        // 0.91 of the time, 50 more than 3 % slower and up to 56; by expected end 0.82, 4 more than 3 % slower, up to 14.  That was with
+        // 14 us for lists beyond 16 KiB, and is kept for this choice: it leaves to the packed tiles what they save in lists and launches
+        // (300 random batches without it: 1.2 % less time in the geometric mean, two more than 3 % slower).
+        constexpr double kListsUs = 14.0;
         if (can_pack && list_narrow(p, groups[1].v)) {
-            ListGroup apart = groups[1], prefix = groups[0];
+            ListGroup apart = groups[1];
             cut(apart, false);
             cut(groups[1], true);
             const size_t scatter = (sb[0].items.size() + sb[1].items.size()) * sizeof(sk_scatter);
-            ListGroup* const as_apart[2] = {&prefix, &apart};
-            ListGroup* const as_packed[2] = {&groups[0], &groups[1]};
-            const double packed_us = list_cost(p, as_packed, 2, scatter);
-            if (list_cost(p, as_apart, 2, scatter, packed_us) < packed_us) { groups[0].chunk = prefix.chunk; groups[1] = std::move(apart); }
+            const ListGroup* const as_apart[2] = {&groups[0], &apart};
+            const ListGroup* const as_packed[2] = {&groups[0], &groups[1]};
+            const double packed_us = list_cost(p, as_packed, 2, scatter, kListsUs);
+            if (list_cost(p, as_apart, 2, scatter, kListsUs, packed_us) < packed_us) groups[1] = std::move(apart);
         } else cut(groups[1], can_pack);
     }
     ListPlan plan;

@@ -175,11 +175,35 @@ static void check_forks()
     drop_pool(p, d);
 }
 
+// Pieces of head_dim 64 plans are not kept long for the sake of lists below 16 KiB, which need no copy beyond it either: a step of four
+// sessions of 32/8 heads, 83 tokens each behind 1,950, and 17 questions of 16 tokens behind 2,701.
+static void check_pieces()
+{
+    sk_pool_desc d = {};
+    d.n_q_heads = 32; d.n_kv_heads = 8; d.head_dim = 64; d.max_sessions = 4; d.n_blocks = 800;
+    sk_pool* p = make_pool(d);
+    static __attribute__((aligned(16))) char x[16];
+    int32_t ids[4], op[4], cu[5] = {0, 83, 166, 249, 332};
+    for (int i = 0; i < 4; ++i) {
+        op[i] = SK_OP_APPEND;
+        CHECK(sk_session_create(p, &ids[i]) == SK_OK && sk_session_append(p, ids[i], nullptr, x, x, i ? 1950 : 2701, nullptr, SK_F32, nullptr, nullptr) == SK_OK);
+    }
+    work.clear();
+    CHECK(sk_session_query_shared_prefix(p, ids[0], nullptr, nullptr, nullptr, 0, x, x, x, 17, 16, nullptr, x, SK_F32, nullptr, nullptr, nullptr) == SK_OK);
+    CHECK(work.size() * sizeof(sk_work) > 16384);
+    CHECK(sk_session_truncate(p, ids[0], 1950) == SK_OK);
+    work.clear();
+    CHECK(sk_batch_step(p, 4, ids, op, cu, x, x, x, x, SK_F32, nullptr, nullptr) == SK_OK);
+    CHECK(work.size() * sizeof(sk_work) > 16384);
+    drop_pool(p, d);
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "ring";
     if (!std::strcmp(what, "ring")) check_ring();
     else if (!std::strcmp(what, "forks")) check_forks();
+    else if (!std::strcmp(what, "pieces")) check_pieces();
     else return 1;
     std::printf("fake device ok\n");
     return 0;

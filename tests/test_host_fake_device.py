@@ -21,3 +21,7 @@ def test_pinned_ring_slots_and_the_kernels_that_read_them(tmp_path):
 
 def test_keys_that_forks_share_are_not_read_once(tmp_path):
     _run(tmp_path, "forks")
+
+
+def test_pieces_of_head_dim_64_plans_whose_lists_need_no_copy(tmp_path):
+    _run(tmp_path, "pieces")
