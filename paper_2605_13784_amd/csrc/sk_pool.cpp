@@ -324,13 +324,28 @@ struct RegPlan {
     bool enqueued = false;                             // set by launch_regular once the attention kernel is on the stream
 };
 
-// Whether the last workgroup of a unit can merge its parts: few enough for one workgroup to read, and within reach of
-// 32-bit offsets in the rounds of sixteen it reads them in (at most 64 parts: four rounds of one row tile's pieces, or fewer parts of more).
-bool can_merge(const sk_pool* p, const Variant& v, int64_t tile_rows, int64_t parts)
+// Whether the last workgroup of a unit merges its parts, `rows` rows each, instead of the combine kernel in a second launch.  Its lanes
+// take a turn for every 1,024 floats of the rows, one behind the other: two round trips to the L2 for up to 16 parts, one more for every 16
+// further ones.  The combine kernel does all of them at once, behind a launch of about 1 us of the device's time.  us per query, combine
+// kernel -> merged in the launch, in a stream of queries / alone (a wait behind each), 32/8 heads:
+//   rows (turns) d 128   5 parts [600 cached]         16 [2,048]                   21 [2,600]                   32 [32,768]
+//    8  (1)              7.9 -> 6.0/19.4 -> 18.7      7.6 -> 5.9/19.5 -> 18.7      7.5 -> 6.3/19.9 -> 19.0      24.4 -> 23.4/36.4 -> 35.5
+//   12  (2)              8.0 -> 6.9/19.7 -> 19.6      7.7 -> 6.9/19.7 -> 19.6      8.0 -> 8.0/20.2 -> 20.3      24.9 -> 25.3/37.0 -> 37.6
+//   16  (2)              7.9 -> 7.2/19.8 -> 20.1      7.8 -> 7.3/20.0 -> 20.1      8.1 -> 8.6/20.4 -> 20.9      25.2 -> 25.9/37.2 -> 38.2
+//   20  (3)              7.8 -> 8.1/20.1 -> 20.9      8.1 -> 8.4/20.2 -> 20.9      8.4 -> 9.8/20.7 -> 22.1      25.4 -> 27.3/37.6 -> 39.7
+//   32  (4)              8.0 -> 9.5/20.7 -> 22.2      8.3 -> 9.9/20.8 -> 22.6      8.7 -> 11.8/21.3 -> 24.2     26.1 -> 30.0/38.2 -> 42.3
+// Up to four parts are merged whatever the rows: 1.0 us more of the device's time at 32 rows for 1.8 less of the host's (6.2 of 8.0 a call).
+// Two turns of 64 dims are merged up to 32 parts where the host's second launch is what a stream waits for (20 rows,
+// combine -> merged: 2,600 cached 8.1 -> 7.4/19.6 -> 20.2, 5,000 8.3 -> 7.8/20.3 -> 20.6, 6,500 7.8 -> 7.8/19.4 -> 20.3, 9,001 7.8 -> 8.4, 14,800 9.0 -> 10.1); fp32,
+// whose workgroups end further apart, one turn up to 48 (4/4 heads, 8 rows: 2,048 cached, 33 parts 8.4 -> 8.0; 16 rows: 32 parts 8.5 ->
+// 8.1, 4,096, 64 parts 9.0 -> 10.0), or 64 where a single wave has all of it (4 rows: 9.0 -> 8.7).
+// Offsets of the rounds of sixteen it reads the parts in are 32-bit; at most 64 parts (their weights' place in LDS).
+bool can_merge(const sk_pool* p, const Variant& v, int64_t rows, int64_t parts, int64_t kv_len)
 {
-    const int64_t rounds = (tile_rows * p->d.head_dim + 1023) / 1024 * ((parts + 7) / 8);
+    const int64_t floats = rows * p->d.head_dim, turns = (floats + 1023) / 1024;
+    const int64_t most = turns == 1 ? (p->L.elem == 2 || floats <= 256 ? 64 : 48) : turns == 2 ? (p->d.head_dim == 64 && kv_len <= 6144 ? 32 : 16) : 4;
     const int64_t step = int64_t(p->d.n_kv_heads) * v.rows_per_slot * p->d.head_dim * 4;
-    return parts > 1 && parts <= p->d.head_dim && rounds <= 8 && (parts + 15) * step < (int64_t(1) << 32);
+    return parts > 1 && parts <= most && (parts + 15) * step < (int64_t(1) << 32);
 }
 
 // The kernel for at most 32 rows per KV head: cached tokens in parts of whole 32-key tiles, four waves to a
@@ -354,15 +369,14 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
         }
     };
     // The last workgroup to finish merges the parts of a KV head (they lie a multiple of 8 workgroups apart, hence on
-    // one XCD) if they are few enough for one workgroup to read.
-    // Measured (parts x rows, us per query, merged by the last workgroup against the combine kernel): 21 x 4 rows 8.6
-    // against 12.0, 21 x 16 9.4 against 12.4, 20 x 20 12.8 against 12.5, 21 x 32 13.7 against 13.3.  It reads eight parts
-    // of 2,048 / head_dim output rows in one round.
+    // one XCD) if they are few enough for one workgroup to read (can_merge).
     // A head then has the CUs of one XCD.  Where the heads are no multiple of 8, others have less to do or nothing: up to
     // 4 MiB of K/V for the busiest XCD the launch saved is worth more than that (us per query of one token, merged in the
-    // launch against by the combine kernel: 8 heads on 1, 5,000 cached tokens 9.4 against 11.9, 6,500 10.0 - 12.0, 9,001
-    // 12.0 - 12.8, 13,000 14.5 - 13.7, 32,768 21.7 - 16.4; 12 on 4, 6,500 9.9 - 11.9, 13,000 15.5 - 13.1, 65,536 42.8 - 29.6; 24
-    // on 12, 3,500 9.2 - 11.9, 5,000 13.8 - 11.9, 13,000 22.5 - 18.5), and the parts are cut for its CUs alone.
+    // launch against by the combine kernel: 8 heads on 1, 5,000 cached tokens 7.5 against 8.8, 8,100 8.0 - 9.2, 9,001 9.3
+    // - 9.9, 13,000 11.0 - 10.0, 32,768 18.4 - 12.0; 12 on 4, 6,500 7.1 - 8.4, 9,001 9.1 - 9.1, 13,000 12.1 - 9.4; 24 on
+    // 12, 4,096 7.1 - 7.7, 5,000 9.6 - 8.4; 14 on 2 of 64 dims, 14,800 7.5 - 7.8, 18,000 8.8 - 8.1), and the parts are cut for its
+    // CUs alone, also where their rows are more than one workgroup merges (12 on 4, 27 rows at 6,500 in 26 parts 10.2, in 51
+    // 10.8; at 8,100 in 32 10.3, in 64 10.9).
     // For the combine kernel, which reads the statistics of 64 parts at once, no more than 64 of up to 1,024 keys (8
     // heads on 1: 32,768 tokens in 256 parts 27.9, 128 19.9, 64 16.4, 32 18.3; 65,536 28.9 - 21.3 - 20.7 - 26.9).
     constexpr int64_t kXcds = 8, kOneXcdBytes = int64_t(4) << 20;
@@ -371,9 +385,9 @@ int plan_small(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_spli
     const bool even = Hkv % kXcds == 0;
     if (even || kv_len * heads_per_xcd * p->d.head_dim * 4 <= kOneXcdBytes) {
         cut(n_splits_req > 0 ? n_splits_req : even ? wanted : std::min(wanted, std::max<int64_t>(1, p->n_cus / kXcds / heads_per_xcd)));
-        L.fuse = (can_merge(p, R.v, int64_t(L.n_tok) * p->L.G, parts) && Hkv * 16 <= p->L.sync_units) ? 1 : 0;
+        L.fuse = (can_merge(p, R.v, int64_t(L.n_tok) * p->L.G, parts, kv_len) && Hkv * 16 <= p->L.sync_units) ? 1 : 0;
     }
-    if (!L.fuse) cut(n_splits_req > 0 ? n_splits_req : std::min(wanted, std::max<int64_t>(64, kv_len / 1024)));
+    else cut(n_splits_req > 0 ? n_splits_req : std::min(wanted, std::max<int64_t>(64, kv_len / 1024)));
     L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts;
     L.own_cnt = own_cnt; L.own_mode = SK_OWN_SMALL;
     L.head_pad = L.fuse ? (int32_t)((Hkv + 7) / 8 * 8) : (int32_t)Hkv;
@@ -398,10 +412,10 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
     }
     L.chunk = (int32_t)chunk; L.n_splits = (int32_t)parts; L.by_chunk = sk_make_div((uint32_t)chunk);
     L.own_cnt = own_cnt; L.own_mode = SK_OWN_F32;
-    // Merged by the last workgroup of a unit while that is a few rounds of loads (see plan_small).  Few units leave XCDs idle here
+    // Merged by the last workgroup of a unit while that is a few rounds of loads (can_merge).  Few units leave XCDs idle here
     // too, but such calls stay short: 1/1, 16/1, 10/2, 4/4 and 8/2 heads with 1 to 1,024 tokens at 128 to 32,768 cached are 1.4
     // to 17 times as fast as with the fp32-FMA kernel and its combine, none slower.
-    L.fuse = (can_merge(p, R.v, int64_t(R.v.tok_per_tile) * p->L.G, parts) && units * 16 <= p->L.sync_units) ? 1 : 0;
+    L.fuse = (can_merge(p, R.v, std::min<int64_t>(L.n_tok, R.v.tok_per_tile) * p->L.G, parts, kv_len) && units * 16 <= p->L.sync_units) ? 1 : 0;
     const int64_t pad = L.fuse ? (units + 7) / 8 * 8 : units;
     if (pad * parts > (int64_t(1) << 30)) return SK_E_WORKSPACE;
     L.head_pad = (int32_t)pad; L.by_pad = sk_make_div((uint32_t)pad); L.by_tiles = sk_make_div((uint32_t)L.n_tiles);

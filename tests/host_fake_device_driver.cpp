@@ -52,14 +52,14 @@ int sk_launch_attention(const sk_launch& L, int, int32_t n, void*, void*, void*)
     if (L.mode == SK_MODE_LIST) work.insert(work.end(), L.work, L.work + n);
     return 0;
 }
-int sk_launch_attention_small(const sk_launch&, const sk_commit&, int32_t, void*, void*, void*) { return 0; }
+int sk_launch_attention_small(const sk_launch& L, const sk_commit&, int32_t n, void*, void*, void*) { return sk_launch_attention(L, 0, n, nullptr, nullptr, nullptr); }
 int sk_launch_combine(const sk_launch&, int32_t, int32_t, int64_t, void*, void*, void*) { return 0; }
 int sk_launch_gather(const sk_geom&, int32_t, int64_t, int64_t, void*, void*, void*) { return 0; }
 int sk_launch_copy_block(const sk_geom&, unsigned char*, int32_t, int32_t, void*) { return 0; }
 
-static sk_pool* make_pool(sk_pool_desc& d)
+static sk_pool* make_pool(sk_pool_desc& d, int dtype = SK_BF16)
 {
-    d.dtype = SK_BF16; d.block_tokens = 16;
+    d.dtype = dtype; d.block_tokens = 16;
     d.kv_bytes = sk_pool_kv_bytes(&d); d.workspace_bytes = sk_pool_workspace_bytes(&d);
     d.kv_mem = std::aligned_alloc(256, (d.kv_bytes + 255) / 256 * 256);
     d.workspace = std::aligned_alloc(256, (d.workspace_bytes + 255) / 256 * 256);
@@ -198,12 +198,42 @@ static void check_pieces()
     drop_pool(p, d);
 }
 
+// Which short calls merge their parts in the attention launch: by the turns of 1,024 floats that their rows are, and by the parts.
+static void check_merges()
+{
+    static __attribute__((aligned(16))) char x[16];
+    auto merged = [&](int dtype, int hq, int hkv, int dim, int32_t n, int32_t tokens, int parts, int32_t splits = 0) {
+        sk_pool_desc d = {};
+        d.n_q_heads = hq; d.n_kv_heads = hkv; d.head_dim = dim; d.max_sessions = 1; d.n_blocks = n / 16 + 8; d.max_batch_tokens = 16384;
+        sk_pool* p = make_pool(d, dtype);
+        int32_t id;
+        CHECK(sk_session_create(p, &id) == SK_OK && sk_session_append(p, id, nullptr, x, x, n, nullptr, SK_F32, nullptr, nullptr) == SK_OK);
+        launches.clear();
+        CHECK(sk_session_query(p, id, x, nullptr, nullptr, tokens, x, SK_F32, nullptr, splits, nullptr) == SK_OK);
+        CHECK(launches.size() == 1 && launches[0].n_splits == parts);
+        const int fuse = launches[0].fuse;
+        drop_pool(p, d);
+        return fuse;
+    };
+    CHECK(merged(SK_BF16, 32, 8, 128, 14800, 1, 29) && merged(SK_BF16, 32, 8, 128, 4096, 2, 32));        // one turn
+    CHECK(merged(SK_BF16, 32, 8, 128, 4096, 2, 64, 64) && !merged(SK_BF16, 32, 8, 128, 4160, 2, 65, 65));
+    CHECK(merged(SK_BF16, 32, 8, 128, 2048, 4, 16) && !merged(SK_BF16, 32, 8, 128, 2049, 4, 17));        // two
+    CHECK(merged(SK_BF16, 8, 8, 128, 2048, 9, 16) && !merged(SK_BF16, 8, 8, 128, 2600, 9, 21));
+    CHECK(!merged(SK_BF16, 32, 8, 128, 600, 5, 5) && !merged(SK_BF16, 32, 8, 128, 2048, 8, 16));         // three and four
+    CHECK(merged(SK_BF16, 32, 8, 128, 512, 8, 4) && !merged(SK_BF16, 32, 8, 128, 513, 8, 5) && merged(SK_BF16, 32, 1, 128, 300, 1, 3));
+    CHECK(merged(SK_BF16, 32, 8, 64, 6144, 8, 24) && !merged(SK_BF16, 32, 8, 64, 6145, 8, 25) && merged(SK_BF16, 32, 8, 64, 14800, 4, 29));
+    CHECK(!merged(SK_BF16, 12, 4, 128, 6500, 9, 26) && !merged(SK_BF16, 12, 4, 128, 9001, 1, 36));        // KV heads that are no multiple of 8
+    CHECK(merged(SK_F32, 4, 4, 64, 3072, 16, 48) && !merged(SK_F32, 4, 4, 64, 3088, 16, 49) && merged(SK_F32, 4, 4, 64, 4096, 4, 64));
+    CHECK(merged(SK_F32, 8, 2, 128, 1024, 4, 16) && !merged(SK_F32, 8, 2, 128, 2048, 4, 32) && merged(SK_F32, 8, 2, 128, 2048, 1, 32));
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "ring";
     if (!std::strcmp(what, "ring")) check_ring();
     else if (!std::strcmp(what, "forks")) check_forks();
     else if (!std::strcmp(what, "pieces")) check_pieces();
+    else if (!std::strcmp(what, "merges")) check_merges();
     else return 1;
     std::printf("fake device ok\n");
     return 0;

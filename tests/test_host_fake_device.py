@@ -25,3 +25,7 @@ def test_keys_that_forks_share_are_not_read_once(tmp_path):
 
 def test_pieces_of_head_dim_64_plans_whose_lists_need_no_copy(tmp_path):
     _run(tmp_path, "pieces")
+
+
+def test_short_calls_merged_in_their_launch(tmp_path):
+    _run(tmp_path, "merges")
