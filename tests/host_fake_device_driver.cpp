@@ -8,8 +8,7 @@
 #include <cstring>
 #include <vector>
 
-#include "../include/sk.h"
-#include "../paper_2605_13784_amd/csrc/sk_internal.h"
+#include "../paper_2605_13784_amd/csrc/sk_pool.cpp"
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed at line %d: %s\n", __LINE__, #c); std::exit(1); } } while (0)
 
@@ -18,6 +17,7 @@ static unsigned host_flags;
 static const void* list_at;
 static std::vector<sk_work> work;            // of the last batched call's attention launches, and their other arguments
 static std::vector<sk_launch> launches;
+static std::vector<sk_comb> merges;
 
 extern "C" {
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
@@ -53,7 +53,11 @@ int sk_launch_attention(const sk_launch& L, int, int32_t n, void*, void*, void*)
     return 0;
 }
 int sk_launch_attention_small(const sk_launch& L, const sk_commit&, int32_t n, void*, void*, void*) { return sk_launch_attention(L, 0, n, nullptr, nullptr, nullptr); }
-int sk_launch_combine(const sk_launch&, int32_t, int32_t, int64_t, void*, void*, void*) { return 0; }
+int sk_launch_combine(const sk_launch& L, int32_t n, int32_t, int64_t, void*, void*, void*)
+{
+    if (L.mode == SK_MODE_LIST) merges.insert(merges.end(), L.comb, L.comb + n);
+    return 0;
+}
 int sk_launch_gather(const sk_geom&, int32_t, int64_t, int64_t, void*, void*, void*) { return 0; }
 int sk_launch_copy_block(const sk_geom&, unsigned char*, int32_t, int32_t, void*) { return 0; }
 
@@ -227,6 +231,94 @@ static void check_merges()
     CHECK(merged(SK_F32, 8, 2, 128, 1024, 4, 16) && !merged(SK_F32, 8, 2, 128, 2048, 4, 32) && merged(SK_F32, 8, 2, 128, 2048, 1, 32));
 }
 
+// The lists of batched calls: where they are read, that they arrive as they were built, and that a slot of the ring is not
+// written again before the kernels that read it are done.
+static void check_lists()
+{
+    static __attribute__((aligned(16))) char x[16];
+    sk_pool_desc d = {};
+    d.n_q_heads = 4; d.n_kv_heads = 2; d.head_dim = 128; d.max_sessions = 64; d.n_blocks = 1 << 13; d.max_batch_tokens = 1 << 13;
+    n_events = 0; std::memset(recorded, 0, sizeof recorded); std::memset(waited, 0, sizeof waited);
+    sk_pool* p = make_pool(d);
+    const int slots = n_events;
+    const char *ws = (const char*)d.workspace, *ring = (const char*)p->ring;
+    std::vector<int32_t> ids;
+    for (int i = 0; i < 64; ++i) {
+        int32_t id;
+        CHECK(sk_session_create(p, &id) == SK_OK && sk_session_append(p, id, nullptr, x, x, 1000 + 8 * i, nullptr, SK_F32, nullptr, nullptr) == SK_OK);
+        ids.push_back(id);
+    }
+    std::memset(recorded, 0, sizeof recorded); std::memset(waited, 0, sizeof waited); p->ring_next = 0; std::memset(p->ring_used, 0, sizeof p->ring_used);
+    int calls = 0;
+    // a step that queries the first n sessions, 40 tokens each; its lists' bytes
+    auto step = [&](int n, int kind, bool copied) {
+        std::vector<int32_t> op((size_t)n, kind), cu(1, 0);
+        for (int i = 0; i < n; ++i) cu.push_back(cu.back() + 40);
+        const int before = copies;
+        work.clear(); merges.clear(); launches.clear(); list_at = nullptr;
+        std::memset((char*)d.workspace + p->L.off_meta, 0xee, p->L.meta_bytes);
+        CHECK(sk_batch_step(p, n, ids.data(), op.data(), cu.data(), x, x, x, x, SK_F32, nullptr, nullptr) == SK_OK);
+        ++calls;
+        CHECK(copies - before == (copied ? 1 : 0));
+        const bool scattered = kind == SK_OP_QUERY_B, in_place = !copied;
+        if (scattered || in_place) {
+            const char* at = (const char*)list_at;
+            if (in_place) CHECK(at >= ring && at < ring + slots * p->L.meta_bytes);
+            else CHECK(at >= ws + p->L.off_meta && at < ws + p->L.off_meta + p->L.meta_bytes);
+        }
+        // every session's cached keys once for each KV head, parts as the combine kernel is told
+        std::vector<int64_t> keys((size_t)n, 0);
+        std::vector<int32_t> parts((size_t)n, 0), told((size_t)n, 1);
+        for (const sk_work& w : work) {
+            const size_t i = size_t(w.q_tok0 / 40);
+            CHECK(i < (size_t)n && w.n_tok == 40 && w.tbl_off == ids[i] * (int32_t)p->L.max_blocks_per_session && w.kv_begin <= w.kv_end);
+            if (w.kv_head == 0) { keys[i] += w.kv_end - w.kv_begin; ++parts[i]; }
+        }
+        for (const sk_comb& c : merges) told[size_t(c.q_tok0 / 40)] = c.n_parts;
+        for (int i = 0; i < n; ++i) CHECK(keys[(size_t)i] == 1000 + 8 * i && parts[(size_t)i] == told[(size_t)i]);
+        return align_up(work.size() * sizeof(sk_work), 256) + align_up(merges.size() * sizeof(sk_comb), 256) +
+               (scattered ? align_up((size_t)n * 3 * sizeof(sk_scatter), 256) : 0);
+    };
+    CHECK(step(4, SK_OP_QUERY_B, true) <= 16384 && step(4, SK_OP_QUERY_A, true) <= 16384);
+    CHECK(step(64, SK_OP_QUERY_A, false) > 16384);                  // nothing to scatter: a launch of copies alone
+    const size_t bytes = step(64, SK_OP_QUERY_B, false);
+    int total = 0, busy = 0;
+    for (int i = 1; i <= slots; ++i) { total += recorded[i]; busy += waited[i]; }
+    CHECK(total == calls && busy == std::max(0, calls - slots));
+    step(64, SK_OP_QUERY_B, false);
+    CHECK(waited[(calls - 1) % slots + 1] == (calls > slots ? 1 : 0));
+    // a list region that holds the lists, but not the copies' items beside them: one copy
+    const size_t meta = p->L.meta_bytes;
+    p->L.meta_bytes = bytes;
+    CHECK(step(64, SK_OP_QUERY_B, true) == bytes);
+    p->L.meta_bytes = meta;
+    // a launch that reports an error is on the stream all the same: its slot stays busy, no session is changed
+    launch_error = (int)hipErrorInvalidValue;
+    const int slot = p->ring_next, marks = recorded[slot + 1];
+    std::vector<int32_t> op(64, SK_OP_QUERY_B), cu(1, 0);
+    for (int i = 0; i < 64; ++i) cu.push_back(cu.back() + 40);
+    CHECK(sk_batch_step(p, 64, ids.data(), op.data(), cu.data(), x, x, x, x, SK_F32, nullptr, nullptr) == SK_E_HIP && recorded[slot + 1] == marks + 1);
+    drop_pool(p, d);
+
+    // up to 8,192 groups of 16 tokens a batched call's scatter list is read where it lies, a longer one behind a copy of all lists
+    sk_pool_desc e = {};
+    e.n_q_heads = e.n_kv_heads = 1; e.head_dim = 64; e.max_sessions = 1; e.n_blocks = 1 << 14; e.max_batch_tokens = 1 << 18;
+    p = make_pool(e);
+    int32_t id;
+    CHECK(sk_session_create(p, &id) == SK_OK);
+    for (int32_t groups : {8192, 8193}) {
+        const int32_t what = SK_OP_APPEND, ends[2] = {0, 16 * groups};
+        const int before = copies;
+        work.clear();
+        CHECK(sk_batch_step(p, 1, &id, &what, ends, x, x, x, x, SK_F32, nullptr, nullptr) == SK_OK && copies - before == (groups > 8192 ? 1 : 0));
+        CHECK(((const sk_scatter*)list_at)[groups - 1].src_tok0 == 16 * (groups - 1));
+        int64_t rows = 0;
+        for (const sk_work& w : work) if (w.kv_begin == 0) rows += w.n_tok;
+        CHECK(rows == 16 * groups && sk_session_truncate(p, id, 0) == SK_OK);
+    }
+    drop_pool(p, e);
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "ring";
@@ -234,6 +326,7 @@ int main(int argc, char** argv)
     else if (!std::strcmp(what, "forks")) check_forks();
     else if (!std::strcmp(what, "pieces")) check_pieces();
     else if (!std::strcmp(what, "merges")) check_merges();
+    else if (!std::strcmp(what, "lists")) check_lists();
     else return 1;
     std::printf("fake device ok\n");
     return 0;

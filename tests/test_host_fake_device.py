@@ -2,15 +2,13 @@
 import os
 import subprocess
 
-from paper_2605_13784_amd import _build
-
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 def _run(tmp_path, check):
     exe = str(tmp_path / "fake_device")
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-o", exe,
-                    os.path.join(HERE, "host_fake_device_driver.cpp"), os.path.join(_build.CSRC, "sk_pool.cpp")], check=True, capture_output=True)
+                    os.path.join(HERE, "host_fake_device_driver.cpp")], check=True, capture_output=True)
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "fake device ok" in r.stdout, r.stdout + r.stderr
 
@@ -29,3 +27,7 @@ def test_pieces_of_head_dim_64_plans_whose_lists_need_no_copy(tmp_path):
 
 def test_short_calls_merged_in_their_launch(tmp_path):
     _run(tmp_path, "merges")
+
+
+def test_lists_of_batched_calls(tmp_path):
+    _run(tmp_path, "lists")
