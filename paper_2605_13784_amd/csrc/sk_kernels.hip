@@ -542,7 +542,7 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
     // The block ids a wave's first loads of a segment need, requested together and as the first thing: one by one, each in front of
     // its loads, they are round trips one behind the other.  With the query operand beside them, the first loads right behind and no
     // division on the way the 64-row instance takes 9.2 instead of 10.2 us at 2,600 cached tokens (with the epilogue below) and 80.9
-    // instead of 84.4 at 131,072.
+    // instead of 84.4 at 131,072 (right behind an append to the same session; in a stream of queries 85.8 instead of 86.7).
     constexpr int NPRE = PIPELINED ? 5 : LOCKSTEP ? 4 : NSS * (TPI / NLG);
     sk_tile_blocks pre[NPRE];
     auto look_up = [&](const sk_seg& g) __attribute__((always_inline)) {
@@ -619,7 +619,8 @@ __device__ __forceinline__ void sk_attn_bf16_body(const sk_launch P)
 
     // Q^T operand: lane (row r, k-group kg) keeps Q[row][16*ks + 8*kg .. +7] for ks = 0..7.  It is on its way beside the block
     // ids, and waited for with them, in front of the first loads into LDS: behind them the compiler's wait, which does not know of those,
-    // would be one for all of them.
+    // would be one for all of them (the 256-row kernel, 64 tokens of 32/8 heads at 2,600 cached: 13.5 -> 13.8 us from its first workgroup's
+    // start to its last one's end).
     bf16x8 qreg[NKS];
     {
         // Rows past the tile re-read its first token's head row; what they compute goes nowhere.
@@ -1479,10 +1480,10 @@ __global__ __launch_bounds__(64 * NRG * NPH, 2) void sk_attn_bf16_d64(const sk_l
 // merges those (the slots get the bytes they hold already): the result is the same to the last bit wherever the
 // parts ran.  Nobody waits for anybody.
 //
-// Bound: round trips.  One query token with its own K/V at 2,600 cached tokens: one launch of 8.1 us where a staging,
-// an attention and a combine kernel took 17.3 back to back.  By time stamps (taken before the merge
-// read through bounded buffer loads, 0.3 us slower): 1.0 us from a workgroup's start to its first loads (arguments, block
-// table), 2.2 to the end of its keys, 1.1 for the meeting in LDS, 0.4 for the arrival and 2.2 for the merge (three round trips).  10.7 MB of cache at the rate of a plain read would be 1.7 us.
+// Bound: round trips.  One query token with its own K/V at 2,600 cached tokens: one launch of 6.6 us where a staging,
+// an attention and a combine kernel took 17.3 back to back.  By time stamps: 0.6 us from a workgroup's start to its block ids, 1.9 to the
+// end of its keys, 1.2 for the meeting in LDS, 0.6 for the arrival and 1.4 for the merge (two round trips, a third behind 16 parts).
+// 10.7 MB of cache at the rate of a plain read would be 1.7 us.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ unsigned sk_xcd_id() { return (unsigned)__builtin_amdgcn_s_getreg((3 << 11) | 20); }    // HW_REG_XCC_ID, bits 3:0
 

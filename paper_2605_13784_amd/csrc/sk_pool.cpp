@@ -270,13 +270,14 @@ struct Variant { int id; int rows_per_slot; int tok_per_tile; };
 // `cached` >= 0: a single-session call over so many cached tokens, which may take the kernel for at most 32 rows.  Up to
 // 128 MiB of cached K/V, where the ring kernel's stream gets close (us per cache-only query in a stream of them, ring and combine
 // kernel -> this one, one query token / 32 rows):
-//   heads         2,600 cached              9,001                     32,768                    65,536       131,072
-//   32/8  d 128   13.6 ->  8.5/14.6 -> 12.8 17.9 -> 11.9/18.0 -> 15.0 32.8 -> 26.6/33.1 -> 28.8 -            (90.2 -> 96.8)
-//   28/4  d 128   13.6 ->  8.5/14.5 -> 11.9 16.6 -> 12.8/17.1 -> 14.4 24.3 -> 21.1/24.8 -> 22.1 34.6 -> 29.4 -
-//    8/1  d 128   13.5 ->  8.7/14.5 -> 11.5 15.4 -> 12.6/16.2 -> 13.6 22.7 -> 16.4/23.2 -> 17.5 33.1 -> 21.0 38.6 -> 28.0
-//   24/12 d 128   13.9 ->  8.9/14.8 -> 11.9 19.9 -> 15.3/20.2 -> 16.9 -                         -            -
-//   14/2  d 64    11.8 ->  8.5/12.1 ->  8.6 13.6 ->  8.4/14.1 ->  9.7 20.3 -> 13.1/20.5 -> 13.7 24.0 -> 17.0 30.8 -> 24.6
-//   32/8  d 64    12.0 ->  8.3/12.3 ->  8.8 14.3 ->  8.5/14.5 ->  9.8 24.3 -> 17.0/24.3 -> 19.6 38.1 -> 26.5 -
+//   heads         2,600 cached              9,001                     32,768                    65,536                    131,072
+//   32/8  d 128   11.9 ->  6.3/12.0 ->  9.7 15.2 ->  9.4/15.2 -> 12.5 29.3 -> 23.0/29.4 -> 25.4 -                         -
+//   28/4  d 128   11.7 ->  6.8/11.8 ->  9.3 13.9 ->  9.9/13.8 -> 11.4 20.0 -> 15.5/19.9 -> 16.9 29.7 -> 25.4/29.7 -> 26.7 -
+//    8/1  d 128   11.4 ->  6.8/11.7 ->  9.2 13.2 -> 10.0/13.5 -> 11.3 16.2 -> 12.1/16.4 -> 13.8 21.4 -> 17.2/22.2 -> 19.2 27.0 -> 20.6/27.2 -> 22.3
+//   24/12 d 128   11.6 ->  6.7/12.1 ->  9.9 17.5 -> 12.7/17.7 -> 14.9 -                         -                         -
+//   14/2  d 64     9.2 ->  5.5/ 9.5 ->  7.9 10.4 ->  6.5/10.8 ->  9.0 13.1 ->  9.6/13.5 -> 10.2 18.3 -> 12.7/18.3 -> 13.3 22.9 -> 16.5/23.3 -> 17.4
+//   32/8  d 64     9.4 ->  5.2/ 9.5 ->  8.1 11.1 ->  6.4/11.2 ->  9.0 17.2 -> 13.8/17.4 -> 15.1 26.6 -> 22.9/27.1 -> 24.3 -
+// (beyond, before short queries' first loads and merge were what they are: 32/8 of 128 dims at 131,072 90.2 -> 96.8)
 constexpr int64_t kSmallMaxBytes = int64_t(128) << 20;
 constexpr int64_t kP128MinKeys = 512;         // keys of a workgroup from which the 128-row tile takes eight waves (plan_regular)
 bool pick_variant(const sk_pool* p, int64_t n_tok, Variant& v, bool allow_256 = false, int64_t cached = -1)
@@ -424,14 +425,21 @@ int plan_f32(const sk_pool* p, int64_t kv_len, int32_t own_cnt, int32_t n_splits
     return SK_OK;
 }
 
-// Whether the 128-row instances load keys that no other workgroup of the launch reads non-temporal: where so many are read that
-// of three sessions' (or layers') keys, read in turn, the last-level cache of 256 MiB holds none until its turn comes again.  The default
-// policy then costs the keys' way into the cache; below, a session that is read again at once is found there.  us per query of
-// 32 tokens of 32/8 heads (kernel alone), default -> non-temporal, reading one session again and again / three in turn / eight:
-//    8,000 cached   33 MB   12.4 -> 12.6 / 12.5 -> 13.2 / 14.4 -> 13.3
-//   14,800          61 MB   16.4 -> 18.1 / 16.5 -> 18.5 / 20.4 -> 18.5
-//   32,768         134 MB   25.7 -> 28.4 / 36.8 -> 29.1 / 36.8 -> 29.0
-//   48,000         197 MB   34.3 -> 38.8 / 48.9 -> 39.9 / 48.9 -> 39.8
+// Whether the 128-row instances load keys that no other workgroup of the launch reads non-temporal.  The default policy costs the keys'
+// way into the last-level cache of 256 MiB and pays if they are still there when they are read again, which depends on what the
+// program reads in between (a model reads each layer's pool in turn; nobody tells the library) and not on this call.  The line
+// is a compromise: where the keys of three sessions or layers, read in turn, push one another out.  Of more in turn, shorter ones
+// would gain too; one session read again and again loses above it.  us per query of 32 tokens of 32/8 heads, default -> non-temporal:
+//                           one again and again   two in turn      three            eight
+//   14,800 cached   61 MB   23.4 -> 23.3          22.2 -> 23.2     22.2 -> 23.2     25.6 -> 23.4
+//   18,000          74 MB   24.5 -> 25.5          24.1 -> 25.3     24.4 -> 25.5     28.7 -> 25.4
+//   20,000          82 MB   25.7 -> 26.8          25.1 -> 26.6     27.6 -> 26.7     30.3 -> 26.7
+//   22,528          92 MB   28.0 -> 29.0          26.4 -> 28.0     30.7 -> 27.9     33.7 -> 28.0
+//   25,000         102 MB   28.8 -> 30.6          27.8 -> 30.6     33.1 -> 30.4     36.7 -> 30.3
+//   32,768         134 MB   34.0 -> 34.5          35.3 -> 34.9     40.8 -> 34.6     41.1 -> 34.6
+//   48,000         197 MB   43.9 -> 47.8          54.3 -> 47.4     54.1 -> 47.6     54.4 -> 47.7
+// (kernel alone: 8,000 cached, 33 MB, 12.4 -> 12.6 again and again, 12.5 -> 13.2 of three, 14.4 -> 13.3 of eight in turn; 32,768 25.7 -> 28.4,
+// 36.8 -> 29.1, 36.8 -> 29.0)
 // The 64-row instance: 10.3 -> 10.5 / 10.9 -> 11.3 / 12.0 -> 11.8 at 8,000 (16 tokens), 23.8 -> 25.4 / 31.8 -> 26.3 / 31.8 -> 26.5 at 32,768.
 // The 256-row one: 38.0 -> 41.9 / 46.3 -> 44.5 / 46.5 -> 45.0 at 32,768 (64 tokens), 71.6 -> 72.1 / 72.8 -> 70.4 / 73.2 -> 71.9 at 65,536.
 // Forks of one prefix read the same bytes, so what one of them left in the cache is there for the next: their calls do so only where the
@@ -485,7 +493,8 @@ uint32_t list_bucket(uint32_t len, uint32_t chunk) { return len == chunk ? 8 : u
 // the CUs), so the end is that of a list schedule; more pieces end more evenly, but each costs its start and
 // end and a partial that the combine kernel reads back.  Times in us, measured: an iteration of 64 keys in the
 // 256-row kernel 1.7 (one workgroup per CU); in the smaller ones 1.4 with one workgroup per CU and 2.7 with
-// two (the stream from HBM); start and end of a workgroup 6; a partial of 128 rows 0.018.
+// two (the stream from HBM); start and end of a workgroup 6; a partial of 128 rows 0.018 (with the present start, end and combine launch,
+// 31 random steps that they decide: ends of 4 choose 0.3 % slower pieces, of 7 0.4 % faster ones, 0.012 3.5 % slower ones).
 // Measured against pieces of one length for about 2,048 workgroups, in session order: 48-session step 4.58 ->
 // 4.05 ms (append launch 4.25 -> 3.76: no 19,648-key pieces that end in a ragged last round, tiles whole and
 // longest first; combine kernels 0.16 -> 0.02); 64 questions at 64K 1.13 -> 1.04 ms (7 pieces per tile, 3.5
@@ -623,6 +632,9 @@ struct RegCost {
     double ends;                     // start and end of a workgroup
     double merge, part, row;         // combine launch; 1,000 rows of a partial written and read; 1,000 rows merged
 };
+// (Start, end and combine launch have become about 1 us shorter each since: tried again on 83 random appends of 128 dims and 214 of 64 that
+// they decide, ends of 6 and 7, merge of 0.3, row of 0.3 and part of 0.04 choose 0.0 to 0.4 % slower pieces, and the first rule 8 to 11 %;
+// the best piece among those of seven such settings is 1.4 to 1.7 % faster than the chosen one.)
 constexpr RegCost kCost256 = {0.0, 1.1, 0.47, 8.0, 1.0, 0.05, 0.45}, kCost256d64 = {0.7, 0.9, 0.15, 2.7, 1.2, 0.08, 0.36},
                   kCost128d64 = {0.0, 0.9, 0.25, 2.2, 1.3, 0.08, 0.34};
 double regular_end(const sk_pool* p, const Variant& v, int64_t n_tok, int32_t pos0, int64_t kv_len, int32_t own, int64_t chunk, double stop, bool* all_above)
@@ -796,14 +808,15 @@ int plan_regular(const sk_pool* p, int32_t id, int64_t n_tok, int32_t pos0, int6
     // A 128-row call that gives every CU at most one workgroup takes the eight-wave instance: two key
     // phases per row group, so a wave has half the arithmetic per 64 keys and its SIMD a second wave
     // to overlap it with.  They pay off once what a workgroup streams outweighs their longer start and their merge of the two phases.
-    // Measured (us per query, four waves -> eight, by the keys of a workgroup; cached tokens of the call in brackets):
-    //   heads, rows    256                         about 450                   about 510                  1,024 and more
-    //    8/1, 128      15.9 -> 17.0 [14,800]       -                           -                          -
-    //   14/2, 126      17.1 -> 18.4 [14,800]       22.9 -> 23.4 [45,000]       25.8 -> 25.6 [60,000]      -
-    //   28/4, 126      17.8 -> 18.8 [14,800]       22.0 -> 22.3 [28,000]       23.8 -> 23.3 [32,768]      33.3 -> 31.0 [60,000]
-    //   32/8, 128      17.3 -> 18.2 [7,000]        21.4 -> 21.5 [13,312]       23.1 -> 22.5 [14,800]      34.7 -> 32.2 [32,768]
-    //   64/16, 128     18.0 -> 19.4 [3,000]        21.8 -> 21.9 [7,000]        24.3 -> 23.9 [9,000]       35.0 -> 32.7 [17,000]
-    //   32/32, 128     -                           21.6 -> 21.9 [3,000]        27.2 -> 26.2 [5,000]       36.9 -> 33.9 [9,000]
+    // Measured (us per query, four waves -> eight, by the keys of a workgroup, 256 workgroups; three sessions in turn):
+    //   heads, rows    256               384               448               512               1,024
+    //    8/1, 128      24.7 -> 25.3      27.6 -> 27.5      29.1 -> 28.8      30.2 -> 30.0      -
+    //   14/2, 126      20.0 -> 20.7      23.0 -> 23.0      24.5 -> 24.2      25.7 -> 25.3      38.8 -> 38.4
+    //   28/4, 126      17.9 -> 18.5      20.9 -> 20.9      22.1 -> 21.9      23.4 -> 22.9      36.9 -> 35.9
+    //   32/8, 128      17.7 -> 18.3      20.6 -> 20.6      21.9 -> 21.7      23.2 -> 22.7      36.1 -> 35.1
+    //   64/16, 128     17.4 -> 18.0      20.1 -> 20.3      21.6 -> 21.4      22.9 -> 22.5      35.2 -> 34.4
+    //   32/32, 128     17.6 -> 18.2      20.5 -> 20.5      21.8 -> 21.6      23.1 -> 22.7      35.4 -> 34.5
+    // (break-even lies at 384 to 448 keys since the phases' merge got shorter; what 448 would gain on 512 is 1 %)
     const bool long_enough = p->p128_min_tokens >= 0 ? kv_len >= p->p128_min_tokens : chunk >= kP128MinKeys;
     if (p->p128 && v.id == SK_KV_MFMA128 && p->d.head_dim == 128 && R.wgs <= p->n_cus && long_enough) v.id = SK_KV_MFMA128P;
     L.fuse = (p->fuse && mfma && parts > 1 && base_wgs <= p->L.sync_units && parts < 65536) ? 1 : 0;

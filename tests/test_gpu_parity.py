@@ -242,8 +242,8 @@ def test_calls_of_at_most_32_rows(hq, hkv, d, env):
 @pytest.mark.parametrize("shape", [synth.Shape("bf16", 32, 8, 128), synth.Shape("bf16", 14, 2, 64), synth.Shape("f32", 8, 2, 128)])
 def test_one_launch_calls_with_larger_blocks_and_many_parts(shape, block):
     """The kernels that read a call's own tokens in place, with blocks of several 16-token groups: commits that start
-    inside a group, at a block's end and across it, evicted tokens, and as many parts as one workgroup merges (59: eight
-    rounds of eight; in fp32, where a round takes half as many, 30)."""
+    inside a group, at a block's end and across it, evicted tokens, and parts for one round of the merge and for more,
+    up to those that one workgroup still merges (64; in fp32, with these rows, 48: the 59 of n_splits = 60 are merged in bf16 alone)."""
     gen = synth.generator(2, stream=1300 + block + shape.head_dim)
     pr = Pair(shape, block_tokens=block, n_blocks=4200 // block + 6, max_sessions=1, max_batch_tokens=4096, kv_fill=0xFF)
     sid = pr.create()
@@ -552,8 +552,8 @@ def test_results_over_the_calls_own_keys_and_values(shape, tokens, n):
 @pytest.mark.parametrize("shape,n,parts", [(synth.Shape("bf16", 32, 8, 128), 2592, 21), (synth.Shape("bf16", 14, 2, 64), 1184, 10),
                                            (synth.Shape("f32", 4, 2, 64), 80, 2)])
 def test_infinite_value_in_the_last_part_of_a_merged_call(shape, n, parts):
-    """The workgroup that merges reads eight parts at a time: an infinite value of the last part reaches the output
-    dimension it stands in and is not met by a weight of 0 where the eight are not full."""
+    """The workgroup that merges reads sixteen parts at a time: an infinite value of the last part reaches the output
+    dimension it stands in and is not met by a weight of 0 where the sixteen are not full."""
     gen = synth.generator(2, stream=60 + n)
     inf = float("inf")
     pr = Pair(shape, n_blocks=n // 16 + 8, max_sessions=1)
